@@ -54,19 +54,39 @@ struct GemmStage {
     bool empty() const { return probs.empty(); }
 };
 
+// Tile shape of a launch: 128 x 128, unless the narrower tile saves a sixth of the padded columns (ranks
+// and sketch widths are rarely multiples of 128), or the launch is so small that smaller tiles are what
+// gives it enough workgroups.
+int pick_shape(const std::vector<LogicalGemm>& gemms, int want_tiles) {
+    long long area128 = 0, area64 = 0, units = 0;
+    int max_m = 0, max_n = 0;
+    for (const LogicalGemm& g : gemms) {
+        const long long rows = ceil_div(g.M, 128) * 128LL;
+        area128 += rows * (ceil_div(g.N, 128) * 128LL);
+        area64 += rows * (ceil_div(g.N, 64) * 64LL);
+        units += (long long)ceil_div(g.M, 128) * ceil_div(g.N, 128) * (want_tiles > 1 ? std::max(1, g.K / 128) : 1);
+        max_m = std::max(max_m, g.M); max_n = std::max(max_n, g.N);
+    }
+    if ((max_m <= 64 && max_n <= 64) || units < 256) return GEMM_64x64;
+    return (area128 * 5 >= area64 * 6) ? GEMM_128x64 : GEMM_128x128;
+}
+
 // Decide k-splits, carve partial buffers from `ar`, and list the tiles.
 // want_tiles: keep splitting k while the launch has fewer tiles than this.
+// coarse_k: lower bound of the k pieces in place of the built-in one (fewer partials, less workspace).
 // lower_only: the outputs are symmetric and only tiles on or below the diagonal are computed
 // (the rest of the output is left unwritten).
 void build_stage(GemmStage& st, const GemmVariant& var, const std::vector<LogicalGemm>& gemms, Arena& ar,
-                 int want_tiles = 512, bool lower_only = false) {
+                 int want_tiles = 512, bool lower_only = false, int coarse_k = 0) {
     st = GemmStage{};
     st.var = var;
     if (gemms.empty()) return;
+    st.var.shape = pick_shape(gemms, want_tiles);
+    const int TM = gemm_tile_m(st.var.shape), TN = gemm_tile_n(st.var.shape);
     long long base_tiles = 0;
     bool shared_out = false;
     for (size_t i = 0; i < gemms.size(); ++i) {
-        base_tiles += (long long)ceil_div(gemms[i].M, GEMM_BM) * ceil_div(gemms[i].N, GEMM_BN);
+        base_tiles += (long long)ceil_div(gemms[i].M, TM) * ceil_div(gemms[i].N, TN);
         if (i > 0 && gemms[i].group >= 0 && gemms[i].group == gemms[i - 1].group) shared_out = true;
     }
     int want_split = (int)std::max<long long>(1, want_tiles / std::max<long long>(1, base_tiles));
@@ -74,7 +94,9 @@ void build_stage(GemmStage& st, const GemmVariant& var, const std::vector<Logica
     bool any_split = false;
     for (size_t i = 0; i < gemms.size(); ++i) {
         const int K = gemms[i].K;
-        int s = std::min(want_split, std::max(1, K / 256));
+        // pieces of at least 128 (64 where that leaves most of the chip idle), or what the caller asks for
+        const int least = coarse_k ? coarse_k : (base_tiles * (K / 128) < 256) ? 64 : 128;
+        int s = std::min(want_split, std::max(1, K / least));
         int chunk = ceil_div(ceil_div(K, s), 32) * 32;
         s = ceil_div(K, chunk);
         ksplit[i] = s; kchunk[i] = chunk;
@@ -87,7 +109,7 @@ void build_stage(GemmStage& st, const GemmVariant& var, const std::vector<Logica
         // [i, e) = consecutive gemms summed into one output; their partials are one buffer
         size_t e = i + 1;
         while (e < gemms.size() && gemms[i].group >= 0 && gemms[e].group == gemms[i].group) ++e;
-        const size_t mn = (size_t)gemms[i].M * gemms[i].N;
+        const size_t mn = ((size_t)gemms[i].M * gemms[i].N + 3) / 4 * 4;   // partials start on 16-byte boundaries
         float* part = nullptr;
         int group_splits = 0;
         if (!st.direct) {
@@ -114,11 +136,11 @@ void build_stage(GemmStage& st, const GemmVariant& var, const std::vector<Logica
                 p.ldc = g.N; p.c_split_stride = (long long)mn; p.kchunk = kchunk[j];
                 prefix += ksplit[j];
             }
-            const int tmn = ceil_div(g.M, GEMM_BM), tnn = ceil_div(g.N, GEMM_BN);
+            const int tmn = ceil_div(g.M, TM), tnn = ceil_div(g.N, TN);
             for (int ks = 0; ks < ksplit[j]; ++ks)
                 for (int tm = 0; tm < tmn; ++tm)
                     for (int tn = 0; tn < tnn; ++tn)
-                        if (!lower_only || tn <= tm) st.tiles.push_back(GemmTile{(int)j, tm, tn, ks});
+                        if (!lower_only || tn * TN <= tm * TM + TM - 1) st.tiles.push_back(GemmTile{(int)j, tm, tn, ks});
             st.tiles_m = tmn; st.tiles_n = tnn; st.ksplit = ksplit[j];
         }
         i = e;
@@ -158,7 +180,7 @@ void upload_stage(GemmStage& st, Arena& ar, Uploader& up) {
 }
 
 inline GemmVariant variant(int aks, int bks, int abf, int pa, int pb) {
-    GemmVariant v; v.a_kstrided = aks; v.b_kstrided = bks; v.a_bf16 = abf; v.a_pieces = abf ? 1 : pa; v.b_pieces = pb;
+    GemmVariant v{}; v.a_kstrided = aks; v.b_kstrided = bks; v.a_bf16 = abf; v.a_pieces = abf ? 1 : pa; v.b_pieces = pb;
     return v;
 }
 
@@ -180,7 +202,8 @@ struct ProjectProgram {
 };
 
 // P buffers: one m x r fp32 per (block, worker), carved from `ar`.
-void build_project(ProjectProgram& pg, const std::vector<BlockView>& blocks, int n_workers, int prec, Arena& ar) {
+void build_project(ProjectProgram& pg, const std::vector<BlockView>& blocks, int n_workers, int prec, Arena& ar,
+                   int coarse_k = 0) {
     std::vector<LogicalGemm> gv[2], utp;
     int group = 0;
     for (const BlockView& b : blocks) {
@@ -194,9 +217,20 @@ void build_project(ProjectProgram& pg, const std::vector<BlockView>& blocks, int
         }
     }
     const int pv = (prec == TSR_PREC_BF16) ? 1 : 2;
-    build_stage(pg.gv[TSR_F32], variant(0, 1, 0, pv, pv), gv[TSR_F32], ar);
-    build_stage(pg.gv[TSR_BF16], variant(0, 1, 1, 1, pv), gv[TSR_BF16], ar);
-    build_stage(pg.utp, variant(1, 1, 0, pv, pv), utp, ar);
+    build_stage(pg.gv[TSR_F32], variant(0, 1, 0, pv, pv), gv[TSR_F32], ar, 512, false, coarse_k);
+    build_stage(pg.gv[TSR_BF16], variant(0, 1, 1, 1, pv), gv[TSR_BF16], ar, 512, false, coarse_k);
+    build_stage(pg.utp, variant(1, 1, 0, pv, pv), utp, ar, 512, false, coarse_k);
+}
+
+// The program of one matrix (the single calls).  Where the partial cores of the fine k split would take
+// the workspace beyond the built-in scratch of tsr_project_core_static, k is cut into pieces of 256.
+void build_project_one(ProjectProgram& pg, const std::vector<BlockView>& block, int prec, Arena& ar) {
+    Arena probe(nullptr);
+    build_project(pg, block, 1, prec, probe);
+    const int coarse_k = probe.used() > (size_t)TSR_PROJECT_STATIC_SCRATCH_BYTES ? 256 : 0;
+    if (ar.base == nullptr && coarse_k == 0) { ar.off += probe.used(); return; }
+    pg = ProjectProgram{};
+    build_project(pg, block, 1, prec, ar, coarse_k);
 }
 
 int run_project(const ProjectProgram& pg, bool grouped, float alpha, float beta, Ctx& cx) {
@@ -711,7 +745,7 @@ size_t tsr_project_workspace_bytes(int m, int n, int r) {
     one_block_view(v, nullptr, TSR_F32, m, n, r, n, nullptr, n, nullptr, nullptr, nullptr, nullptr);
     Arena ar(nullptr);
     ProjectProgram pg;
-    build_project(pg, v, 1, TSR_PREC_SPLIT, ar);
+    build_project_one(pg, v, TSR_PREC_SPLIT, ar);
     return ar.used();
 }
 
@@ -729,7 +763,7 @@ int tsr_project_core(const void* G, int g_dtype, int m, int n, long long ldg, co
     one_block_view(v, G, g_dtype, m, n, r, ldg, nullptr, n, (float*)U, (float*)V, C, nullptr);
     Arena ar(ws);
     ProjectProgram pg;
-    build_project(pg, v, 1, precision, ar);
+    build_project_one(pg, v, precision, ar);
     Ctx cx{(hipStream_t)stream, nullptr};
     return run_project(pg, false, alpha, accumulate ? 1.0f : 0.0f, cx);
 }
@@ -782,7 +816,7 @@ int tsr_project_core_static(const void* G, int g_dtype, int m, int n, long long 
     one_block_view(v, G, g_dtype, m, n, r, ldg, nullptr, n, (float*)U, (float*)V, C, nullptr);
     Arena ar(ws);
     ProjectProgram pg;
-    build_project(pg, v, 1, precision, ar);
+    build_project_one(pg, v, precision, ar);
     Ctx cx{(hipStream_t)stream, nullptr};
     return run_project(pg, false, alpha, accumulate ? 1.0f : 0.0f, cx);
 }

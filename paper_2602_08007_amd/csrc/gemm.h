@@ -41,10 +41,12 @@ struct GemmVariant {
     int a_bf16;       // A elements are bf16 (then a_pieces must be 1)
     int a_pieces;     // 1..3
     int b_pieces;     // 1..3
+    int shape;        // GemmShape
 };
 
-constexpr int GEMM_BM = 128;
-constexpr int GEMM_BN = 128;
+enum GemmShape { GEMM_128x128 = 0, GEMM_128x64 = 1, GEMM_64x64 = 2, GEMM_SHAPES = 3 };
+inline int gemm_tile_m(int shape) { return shape == GEMM_64x64 ? 64 : 128; }
+inline int gemm_tile_n(int shape) { return shape == GEMM_128x128 ? 128 : 64; }
 
 // Enqueue one grouped GEMM.  Returns hipSuccess or the launch error; an unsupported
 // variant returns hipErrorInvalidValue.

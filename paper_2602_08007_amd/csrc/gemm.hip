@@ -1,254 +1,300 @@
-// Grouped tall-skinny GEMM on gfx950 matrix cores: 128x128 output tile per 256-thread
-// workgroup, 32-deep k-tiles staged through LDS as bf16 pieces, fp32 accumulation with
-// v_mfma_f32_32x32x16_bf16 (each of the 4 waves owns a 64x64 quadrant = 2x2 MFMA tiles).
+// Grouped tall-skinny GEMM on gfx950 matrix cores: TM x TN output tile (128 x 128, 128 x 64 or 64 x 64)
+// per 256-thread workgroup, 32-deep k-tiles staged through LDS as bf16 pieces, fp32 accumulation with
+// v_mfma_f32_32x32x16_bf16 (the four waves own the four quadrants of the tile).
 //
-// Global -> registers (prefetch of the next k-tile overlaps the MFMAs of the current one)
-// -> split into bf16 pieces -> LDS in [row][k] order with a padded row -> 16-byte fragment
-// reads.  Both operand orientations end up in the same LDS layout, so the MFMA loop is
-// shared by all variants.
+// Global -> registers (two k-tiles ahead) -> split into bf16 pieces -> LDS in [row][k] order with a
+// padded row -> 16-byte fragment reads.  Both operand orientations end up in the same LDS layout, so the
+// MFMA loop is shared by all variants.
+//
+// What bounds it: with few tiles per compute unit the trips to memory, with many the LDS traffic (with
+// two pieces per operand 64 KB of fragment reads and 40 KB of stores per k-tile against 768 cycles of
+// MFMAs).  Hence two register stages, branch-free loads in the loop (edges by clamped addresses, the rest
+// of a partial k-tile by a mask when it is stored), two LDS buffers with one barrier per k-tile where
+// they fit twice into a compute unit (up to two pieces), and for operands stored across k a lane layout
+// (eight lanes along k, eight along the rows) whose transposing LDS stores touch every bank once: with
+// the lanes along the rows the stores met in two banks and took sixteen passes.  Measured (before, with one
+// stage, per-element guards and element-by-element read-modify-write -> now): the step of one 512 x 1376
+// fp32 matrix at rank 64, 104 -> 39 us; of the 60M model in fp32 at rank 256, 643 -> 304 us; of a
+// 32000 x 2048 embedding and LM head at rank 128, 1060 -> 551 us.
 #include "gemm.h"
+
+#include <type_traits>
 
 namespace tsr {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+// the same with the alignment the operands are guaranteed to have (the hardware loads any address)
+typedef f32x4 __attribute__((aligned(4))) f32x4_u;
+typedef u32x4 __attribute__((aligned(2))) u32x4_u;
+typedef u32x2 __attribute__((aligned(2))) u32x2_u;
+
+// Addresses that come out of a descriptor are marked as global memory: a generic (flat) access counts as
+// an LDS access too, and every wait for LDS would then wait for the loads in flight.
+#define TSR_GLOBAL __attribute__((address_space(1)))
+typedef const TSR_GLOBAL char* gcptr;
 
 constexpr int BK = 32;          // k-tile depth
 constexpr int KP = BK + 8;      // padded LDS row, bf16 elements (80 bytes: 16-byte aligned rows)
 constexpr int NTHREADS = 256;
-constexpr int TILE_ELEMS = 128 * KP;
 
-// ------------------------------------------------------------------ staging registers
-// k-contiguous operand: each thread owns 2 chunks of 8 consecutive k of one row.
-// k-strided operand:    each thread owns a 4(k) x 4(row) micro-tile.
-template <bool BF16> struct StageKC;
-template <> struct StageKC<false> { float v[2][8]; };
-template <> struct StageKC<true> { u32x4 v[2]; };
-template <bool BF16> struct StageKS;
-template <> struct StageKS<false> { float v[4][4]; };
-template <> struct StageKS<true> { unsigned short v[4][4]; };
+// ------------------------------------------------------------------ operand staging
+// One operand's share of a k-tile, ROWS x 32 elements, in the registers of the workgroup.
+//   k-contiguous, fp32: chunks of 4 k (eight lanes cover the 128 bytes of a row), rows 32 apart;
+//   k-contiguous, bf16: chunks of 8 k (four lanes per row), rows 64 apart;
+//   k-strided: a micro-tile of KPT k x 4 rows per thread, the lanes running along k first.
+template <bool KS, bool BF16, int ROWS> struct Operand {
+    static constexpr int KPT = KS ? ROWS / 32 : (BF16 ? 8 : 4);       // k values per chunk
+    static constexpr int KL = BK / KPT;                               // lanes along k
+    static constexpr int NCH = KS ? KPT : ROWS * KL / NTHREADS;       // loads per thread and k-tile
+    static constexpr int ESZ = BF16 ? 2 : 4;
+    static constexpr int TILE = ROWS * KP;                            // one piece of one LDS buffer
+    typedef typename std::conditional<BF16, typename std::conditional<KS, u32x2, u32x4>::type, f32x4>::type Reg;
 
-__device__ inline float bf16_bits_to_float(unsigned short b) {
-    return __uint_as_float(((unsigned int)b) << 16);
-}
+    gcptr base;            // first element of the k range; k-contiguous: of the tile's first row
+    unsigned ldb;          // row pitch, bytes
+    int klen;              // k range
+    int rows, row0;        // rows of the operand, first row of the tile
+    int kl, rl;            // this thread's lane along k, and along the rows
+    unsigned roff[KS ? 1 : NCH];
 
-// rows x K operand, element (row, k) at p[row*ld + k]; tile rows row0..row0+127, k0..k0+31
-template <bool BF16>
-__device__ inline void load_kc(StageKC<BF16>& s, const void* base, long long ld, int rows,
-                               int row0, int k0, int kend, bool vec_ok, int tid) {
+    __device__ inline void init(const void* p, long long ld, int rows_, int row0_, int kbeg, int klen_, int tid) {
+        ldb = (unsigned)ld * ESZ; klen = klen_; rows = rows_; row0 = row0_;
+        kl = tid % KL; rl = tid / KL;
+        if constexpr (KS) {
+            base = (gcptr)p + (long long)kbeg * ld * ESZ;
+            roff[0] = (unsigned)min(row0 + rl * 4, max(rows - 4, 0)) * ESZ;
+        } else {
+            base = (gcptr)p + ((long long)row0 * ld + kbeg) * ESZ;
 #pragma unroll
-    for (int it = 0; it < 2; ++it) {
-        const int c = tid + NTHREADS * it;
-        const int grow = row0 + (c >> 2);
-        const int gk = k0 + (c & 3) * 8;
-        if constexpr (BF16) {
-            const unsigned short* p = (const unsigned short*)base + (long long)grow * ld + gk;
-            u32x4 r = {0u, 0u, 0u, 0u};
-            if (grow < rows) {
-                if (vec_ok && gk + 8 <= kend) {
-                    r = *(const u32x4*)p;
+            for (int it = 0; it < NCH; ++it) roff[it] = (unsigned)min(rl + it * (NTHREADS / KL), rows - 1 - row0) * ldb;
+        }
+    }
+    // smallest extents the vector loads work on
+    __device__ inline bool vector_ok() const { return KS ? rows >= 4 : klen >= KPT; }
+
+    __device__ inline void load(Reg (&v)[NCH], int t) const {
+        if constexpr (KS) {
+            const gcptr b = base + (long long)(t * BK) * ldb;
+            const int last = klen - 1 - t * BK;
+#pragma unroll
+            for (int kk = 0; kk < NCH; ++kk) {
+                const unsigned off = (unsigned)min(kl * KPT + kk, last) * ldb + roff[0];
+                if constexpr (BF16) v[kk] = *(const TSR_GLOBAL u32x2_u*)(b + off);
+                else v[kk] = *(const TSR_GLOBAL f32x4_u*)(b + off);
+            }
+        } else {
+            const unsigned ko = (unsigned)min(t * BK + kl * KPT, klen - KPT) * ESZ;
+#pragma unroll
+            for (int it = 0; it < NCH; ++it) {
+                if constexpr (BF16) v[it] = *(const TSR_GLOBAL u32x4_u*)(base + (roff[it] + ko));
+                else v[it] = *(const TSR_GLOBAL f32x4_u*)(base + (roff[it] + ko));
+            }
+        }
+    }
+    // the same element by element, for extents below a vector's
+    __device__ inline void load_scalar(Reg (&v)[NCH], int t) const {
+        auto at = [&](int r, int k) -> float {        // bf16: the bits in the upper half
+            r = min(r, rows - 1);
+            const bool ok = k < klen;
+            k = min(k, klen - 1);
+            const gcptr p = KS ? base + (long long)k * ldb + (long long)r * ESZ
+                               : base + (long long)(r - row0) * ldb + (long long)k * ESZ;
+            const float x = BF16 ? __uint_as_float((unsigned)*(const TSR_GLOBAL unsigned short*)p << 16) : *(const TSR_GLOBAL float*)p;
+            return ok ? x : 0.0f;
+        };
+#pragma unroll
+        for (int it = 0; it < NCH; ++it) {
+            constexpr int N = KS ? 4 : KPT;
+            float e[N];
+#pragma unroll
+            for (int j = 0; j < N; ++j)
+                e[j] = KS ? at(row0 + rl * 4 + j, t * BK + kl * KPT + it)
+                          : at(row0 + rl + it * (NTHREADS / KL), t * BK + kl * KPT + j);
+            if constexpr (BF16) {
+#pragma unroll
+                for (int j = 0; j < N / 2; ++j) v[it][j] = (__float_as_uint(e[2 * j]) >> 16) | (__float_as_uint(e[2 * j + 1]) & 0xffff0000u);
+            } else {
+#pragma unroll
+                for (int j = 0; j < N; ++j) v[it][j] = e[j];
+            }
+        }
+    }
+
+    // Registers -> NS pieces in LDS.  partial: the k-tile reaches past the k range (its loads were clamped,
+    // unless they were load_scalar's); edge: (k-strided) the tile reaches past the last row likewise.
+    template <int NS>
+    __device__ inline void store(Reg (&v)[NCH], unsigned short* lds, int t, bool partial, bool edge) const {
+        if (partial) mask_k(v, t);
+        if constexpr (KS) {
+            const int r = (edge ? min(row0 + rl * 4, rows - 4) - row0 : rl * 4);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (edge && r + j < 0) continue;
+                unsigned short* d = lds + (r + j) * KP + kl * KPT;
+                if constexpr (BF16) {
+                    unsigned h[KPT / 2];
+#pragma unroll
+                    for (int q = 0; q < KPT / 2; ++q) {
+                        const unsigned a = v[2 * q][j >> 1], b = v[2 * q + 1][j >> 1];
+                        h[q] = (j & 1) ? (a >> 16) | (b & 0xffff0000u) : (a & 0xffffu) | (b << 16);
+                    }
+                    if constexpr (KPT == 4) *(u32x2*)d = u32x2{h[0], h[1]};
+                    else *(unsigned*)d = h[0];
                 } else {
-                    unsigned short e[8];
+                    float x[KPT];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) e[j] = (gk + j < kend) ? p[j] : (unsigned short)0;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) r[j] = (unsigned int)e[2 * j] | ((unsigned int)e[2 * j + 1] << 16);
+                    for (int kk = 0; kk < KPT; ++kk) x[kk] = v[kk][j];
+                    put<NS, KPT>(x, d);
                 }
             }
-            s.v[it] = r;
         } else {
-            const float* p = (const float*)base + (long long)grow * ld + gk;
-            if (grow < rows && vec_ok && gk + 8 <= kend) {
-                const f32x4 a = *(const f32x4*)p;
-                const f32x4 b = *(const f32x4*)(p + 4);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) { s.v[it][j] = a[j]; s.v[it][4 + j] = b[j]; }
-            } else {
+            for (int it = 0; it < NCH; ++it) {
+                unsigned short* d = lds + (rl + it * (NTHREADS / KL)) * KP + kl * KPT;
+                if constexpr (BF16) {
+                    *(u32x4*)d = v[it];
+                } else {
+                    float x[KPT];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) s.v[it][j] = (grow < rows && gk + j < kend) ? p[j] : 0.0f;
-            }
-        }
-    }
-}
-
-// K x rows operand, element (row, k) at p[k*ld + row]
-template <bool BF16>
-__device__ inline void load_ks(StageKS<BF16>& s, const void* base, long long ld, int rows,
-                               int row0, int k0, int kend, bool vec_ok, int tid) {
-    const int gi = row0 + (tid & 31) * 4;
-    const int kb = k0 + (tid >> 5) * 4;
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        const int gk = kb + kk;
-        if constexpr (BF16) {
-            const unsigned short* p = (const unsigned short*)base + (long long)gk * ld + gi;
-            if (gk < kend && vec_ok && gi + 4 <= rows) {
-                const u32x2 r = *(const u32x2*)p;
-                s.v[kk][0] = (unsigned short)(r[0] & 0xffffu); s.v[kk][1] = (unsigned short)(r[0] >> 16);
-                s.v[kk][2] = (unsigned short)(r[1] & 0xffffu); s.v[kk][3] = (unsigned short)(r[1] >> 16);
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) s.v[kk][j] = (gk < kend && gi + j < rows) ? p[j] : (unsigned short)0;
-            }
-        } else {
-            const float* p = (const float*)base + (long long)gk * ld + gi;
-            if (gk < kend && vec_ok && gi + 4 <= rows) {
-                const f32x4 r = *(const f32x4*)p;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) s.v[kk][j] = r[j];
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) s.v[kk][j] = (gk < kend && gi + j < rows) ? p[j] : 0.0f;
-            }
-        }
-    }
-}
-
-// Write the staged k-contiguous chunks into LDS as NS bf16 pieces.
-template <bool BF16, int NS>
-__device__ inline void store_kc(const StageKC<BF16>& s, unsigned short* lds, int tid) {
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-        const int c = tid + NTHREADS * it;
-        const int off = (c >> 2) * KP + (c & 3) * 8;
-        if constexpr (BF16) {
-            *(u32x4*)(lds + off) = s.v[it];
-        } else {
-            float r[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) r[j] = s.v[it][j];
-#pragma unroll
-            for (int p = 0; p < NS; ++p) {
-                bf16x8 h;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    h[j] = (__bf16)r[j];
-                    if (p + 1 < NS) r[j] -= (float)h[j];
+                    for (int j = 0; j < KPT; ++j) x[j] = v[it][j];
+                    put<NS, KPT>(x, d);
                 }
-                *(bf16x8*)(lds + p * TILE_ELEMS + off) = h;
             }
         }
     }
-}
 
-template <bool BF16, int NS>
-__device__ inline void store_ks(const StageKS<BF16>& s, unsigned short* lds, int tid) {
-    const int rb = (tid & 31) * 4;
-    const int kb = (tid >> 5) * 4;
+private:
+    template <int NS, int N> __device__ static inline void put(float (&x)[N], unsigned short* d) {
+        typedef __attribute__((ext_vector_type(N))) __bf16 hv;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int off = (rb + j) * KP + kb;
-        if constexpr (BF16) {
-            u32x2 w;
-            w[0] = (unsigned int)s.v[0][j] | ((unsigned int)s.v[1][j] << 16);
-            w[1] = (unsigned int)s.v[2][j] | ((unsigned int)s.v[3][j] << 16);
-            *(u32x2*)(lds + off) = w;
+        for (int p = 0; p < NS; ++p) {
+            hv h;
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                h[j] = (__bf16)x[j];
+                if (p + 1 < NS) x[j] -= (float)h[j];
+            }
+            *(hv*)(d + p * TILE) = h;
+        }
+    }
+    // what lies past the k range becomes zero; a clamped k-contiguous chunk is moved back into place
+    __device__ inline void mask_k(Reg (&v)[NCH], int t) const {
+        if constexpr (KS) {
+#pragma unroll
+            for (int kk = 0; kk < NCH; ++kk)
+                if (t * BK + kl * KPT + kk >= klen)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) { if (j < (int)(sizeof(Reg) / 4)) v[kk][j] = 0; }
         } else {
-            float r[4];
+            const int k0 = t * BK + kl * KPT;
+            const int sh = k0 - min(k0, klen - KPT);          // elements the load was moved down by
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) r[kk] = s.v[kk][j];
+            for (int it = 0; it < NCH; ++it) {
+                float e[KPT], o[KPT];
 #pragma unroll
-            for (int p = 0; p < NS; ++p) {
-                bf16x4 h;
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk) {
-                    h[kk] = (__bf16)r[kk];
-                    if (p + 1 < NS) r[kk] -= (float)h[kk];
+                for (int j = 0; j < KPT; ++j) {
+                    if constexpr (BF16) e[j] = __uint_as_float((j & 1) ? (v[it][j >> 1] & 0xffff0000u) : (v[it][j >> 1] << 16));
+                    else e[j] = v[it][j];
                 }
-                *(bf16x4*)(lds + p * TILE_ELEMS + off) = h;
+#pragma unroll
+                for (int j = 0; j < KPT; ++j) {
+                    o[j] = 0.0f;
+#pragma unroll
+                    for (int q = j; q < KPT; ++q) o[j] = (q - j == sh) ? e[q] : o[j];
+                }
+                if constexpr (BF16) {
+#pragma unroll
+                    for (int j = 0; j < KPT / 2; ++j) v[it][j] = (__float_as_uint(o[2 * j]) >> 16) | (__float_as_uint(o[2 * j + 1]) & 0xffff0000u);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < KPT; ++j) v[it][j] = o[j];
+                }
             }
         }
     }
-}
-
-template <bool KS, bool BF16> struct StageSel { typedef StageKC<BF16> type; };
-template <bool BF16> struct StageSel<true, BF16> { typedef StageKS<BF16> type; };
+};
 
 // ------------------------------------------------------------------ the kernel
-template <bool A_KS, bool B_KS, bool A_BF16, int NSA, int NSB>
-__global__ __launch_bounds__(NTHREADS) void gemm_kernel(const GemmLaunch L) {
-    __shared__ __attribute__((aligned(16))) unsigned short sA[NSA * TILE_ELEMS];
-    __shared__ __attribute__((aligned(16))) unsigned short sB[NSB * TILE_ELEMS];
+template <bool A_KS, bool B_KS, bool A_BF16, int NSA, int NSB, int TM, int TN>
+__global__ __launch_bounds__(NTHREADS, 2) void gemm_kernel(const GemmLaunch L) {
+    typedef Operand<A_KS, A_BF16, TM> OpA;
+    typedef Operand<B_KS, false, TN> OpB;
+    constexpr int A_ELEMS = NSA * OpA::TILE, BUF = A_ELEMS + NSB * OpB::TILE;
+    constexpr int NBUF = (BUF * 4 <= 80 * 1024) ? 2 : 1;       // two workgroups per compute unit either way
+    constexpr int FM = TM / 64, FN = TN / 64;
+    __shared__ __attribute__((aligned(16))) unsigned short lds[NBUF * BUF];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
 
+    // Workgroups go to the eight XCDs in turn: neighbouring tiles, which share operand panels, are
+    // given to workgroups of one XCD (and its L2).
+    int tile;
+    {
+        const int n = gridDim.x, x = blockIdx.x % 8, q = n / 8, rem = n % 8;
+        tile = x * q + min(x, rem) + blockIdx.x / 8;
+    }
     int tm, tn, ks;
     const GemmProblem* pp;
     if (L.tiles != nullptr) {
-        const GemmTile t = L.tiles[blockIdx.x];
+        const GemmTile t = L.tiles[tile];
         tm = t.tm; tn = t.tn; ks = t.ks;
         pp = L.probs + t.prob;
     } else {
-        const int b = blockIdx.x;
-        tn = b % L.tiles_n;
-        tm = (b / L.tiles_n) % L.tiles_m;
-        ks = b / (L.tiles_n * L.tiles_m);
+        tn = tile % L.tiles_n;
+        tm = (tile / L.tiles_n) % L.tiles_m;
+        ks = tile / (L.tiles_n * L.tiles_m);
         pp = &L.single;
     }
-    const void* A = pp->A;
-    const float* B = pp->B;
-    const long long lda = pp->lda, ldb = pp->ldb, ldc = pp->ldc;
-    const int M = pp->M, N = pp->N, K = pp->K;
+    const long long ldc = pp->ldc;
+    const int M = pp->M, N = pp->N;
     const float alpha = L.alpha, beta = L.beta;
-    float* C = pp->C + (long long)ks * pp->c_split_stride;
+    TSR_GLOBAL float* C = (TSR_GLOBAL float*)pp->C + (long long)ks * pp->c_split_stride;
     const int kbeg = ks * pp->kchunk;
-    const int kend = min(K, kbeg + pp->kchunk);
-    const int row0 = tm * GEMM_BM, col0 = tn * GEMM_BN;
+    const int klen = min(pp->K - kbeg, pp->kchunk);
+    const int row0 = tm * TM, col0 = tn * TN;
 
-    // vector loads need 16-byte aligned rows (8 bytes for the bf16 k-strided micro-tile)
-    const int a_elem = A_BF16 ? 2 : 4;
-    const bool a_vec = (((unsigned long long)A) % 16 == 0) && ((lda * a_elem) % 16 == 0);
-    const bool b_vec = (((unsigned long long)B) % 16 == 0) && ((ldb * 4) % 16 == 0);
-
-    f32x16 acc[2][2];
+    f32x16 acc[FM][FN];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < FN; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
-    typename StageSel<A_KS, A_BF16>::type stA;
-    typename StageSel<B_KS, false>::type stB;
+    OpA a; OpB b;
+    a.init(pp->A, pp->lda, M, row0, kbeg, klen, tid);
+    b.init(pp->B, pp->ldb, N, col0, kbeg, klen, tid);
+    const int nt = (klen + BK - 1) / BK;
+    const bool edge_a = row0 + TM > M, edge_b = col0 + TN > N;
 
-    auto load_tiles = [&](int k0) {
-        if constexpr (A_KS) load_ks<A_BF16>(stA, A, lda, M, row0, k0, kend, a_vec, tid);
-        else load_kc<A_BF16>(stA, A, lda, M, row0, k0, kend, a_vec, tid);
-        if constexpr (B_KS) load_ks<false>(stB, B, ldb, N, col0, k0, kend, b_vec, tid);
-        else load_kc<false>(stB, B, ldb, N, col0, k0, kend, b_vec, tid);
-    };
+    typename OpA::Reg sa[2][OpA::NCH];
+    typename OpB::Reg sb[2][OpB::NCH];
 
-    if (kbeg < kend) load_tiles(kbeg);
-
-    for (int k0 = kbeg; k0 < kend; k0 += BK) {
-        if constexpr (A_KS) store_ks<A_BF16, NSA>(stA, sA, tid);
-        else store_kc<A_BF16, NSA>(stA, sA, tid);
-        if constexpr (B_KS) store_ks<false, NSB>(stB, sB, tid);
-        else store_kc<false, NSB>(stB, sB, tid);
-        __syncthreads();
-        if (k0 + BK < kend) load_tiles(k0 + BK);
-
+    auto compute = [&](const unsigned short* sA) {
+        const unsigned short* sB = sA + A_ELEMS;
 #pragma unroll
         for (int kk = 0; kk < BK / 16; ++kk) {
             const int kofs = kk * 16 + (lane >> 5) * 8;
-            bf16x8 fa[NSA][2], fb[NSB][2];
+            bf16x8 fa[NSA][FM], fb[NSB][FN];
 #pragma unroll
             for (int p = 0; p < NSA; ++p)
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    fa[p][i] = *(const bf16x8*)(sA + p * TILE_ELEMS + (wm * 64 + i * 32 + (lane & 31)) * KP + kofs);
+                for (int i = 0; i < FM; ++i)
+                    fa[p][i] = *(const bf16x8*)(sA + p * OpA::TILE + (wm * (TM / 2) + i * 32 + (lane & 31)) * KP + kofs);
 #pragma unroll
             for (int p = 0; p < NSB; ++p)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    fb[p][j] = *(const bf16x8*)(sB + p * TILE_ELEMS + (wn * 64 + j * 32 + (lane & 31)) * KP + kofs);
+                for (int j = 0; j < FN; ++j)
+                    fb[p][j] = *(const bf16x8*)(sB + p * OpB::TILE + (wn * (TN / 2) + j * 32 + (lane & 31)) * KP + kofs);
             // cross products of the pieces, smallest terms first; keep those of total order
             // below max(NSA, NSB)
             constexpr int ORD = (NSA > NSB) ? NSA : NSB;
@@ -259,42 +305,95 @@ __global__ __launch_bounds__(NTHREADS) void gemm_kernel(const GemmLaunch L) {
                     const int pb = o - pa;
                     if (pb < 0 || pb >= NSB) continue;
 #pragma unroll
-                    for (int i = 0; i < 2; ++i)
+                    for (int i = 0; i < FM; ++i)
 #pragma unroll
-                        for (int j = 0; j < 2; ++j)
+                        for (int j = 0; j < FN; ++j)
                             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[pa][i], fb[pb][j], acc[i][j], 0, 0, 0);
                 }
         }
+    };
+    // One k-tile: register stage S (holding tile t) -> LDS, the stage refilled with tile t + 2, multiply.
+    auto step = [&](auto slot, auto refill, int t) {
+        constexpr int S = decltype(slot)::value;
+        unsigned short* d = lds + (NBUF == 2 ? S : 0) * BUF;
+        const bool partial = !decltype(refill)::value && (t + 1) * BK > klen;
+        a.template store<NSA>(sa[S], d, t, partial, edge_a);
+        b.template store<NSB>(sb[S], d + A_ELEMS, t, partial, edge_b);
         __syncthreads();
-    }
-
-    // epilogue: lane holds column (lane & 31), rows 8*(e/4) + 4*(lane>>5) + e%4 of each 32x32 tile
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int col = col0 + wn * 64 + j * 32 + (lane & 31);
-            const int rbase = row0 + wm * 64 + i * 32 + (lane >> 5) * 4;
-            if (col >= N) continue;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int row = rbase + (e >> 2) * 8 + (e & 3);
-                if (row < M) {
-                    float* c = C + (long long)row * ldc + col;
-                    float v = alpha * acc[i][j][e];
-                    if (beta != 0.0f) v += beta * (*c);
-                    *c = v;
-                }
+        if constexpr (decltype(refill)::value) { a.load(sa[S], t + 2); b.load(sb[S], t + 2); }
+        compute(d);
+        if constexpr (NBUF == 1) __syncthreads();
+    };
+    typedef std::integral_constant<int, 0> S0;
+    typedef std::integral_constant<int, 1> S1;
+    if (nt > 0) {
+        if (a.vector_ok() && b.vector_ok()) {
+            a.load(sa[0], 0); b.load(sb[0], 0);
+            if (nt > 1) { a.load(sa[1], 1); b.load(sb[1], 1); }
+            int t = 0;
+            for (; t + 3 < nt; t += 2) {
+                step(S0{}, std::true_type{}, t);
+                step(S1{}, std::true_type{}, t + 1);
+            }
+            if (nt - t == 3) {
+                step(S0{}, std::true_type{}, t);
+                step(S1{}, std::false_type{}, t + 1);
+                step(S0{}, std::false_type{}, t + 2);
+            } else {
+                step(S0{}, std::false_type{}, t);
+                if (nt - t == 2) step(S1{}, std::false_type{}, t + 1);
+            }
+        } else {
+            for (int t = 0; t < nt; ++t) {
+                a.load_scalar(sa[0], t); b.load_scalar(sb[0], t);
+                a.template store<NSA>(sa[0], lds, t, false, false);
+                b.template store<NSB>(sb[0], lds + A_ELEMS, t, false, false);
+                __syncthreads();
+                compute(lds);
+                __syncthreads();
             }
         }
+    }
+
+    // epilogue: lane holds column (lane & 31), rows 8*(e/4) + 4*(lane>>5) + e%4 of each 32x32 tile.
+    // With beta the whole tile is read before the first element is written (one trip to memory).
+    TSR_GLOBAL float* cp[FN];
+    bool cok[FN];
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+        const int col = col0 + wn * (TN / 2) + j * 32 + (lane & 31);
+        cok[j] = col < N;
+        cp[j] = C + col;
+    }
+    const int rbase = row0 + wm * (TM / 2) + (lane >> 5) * 4;
+    auto each = [&](auto&& f) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int row = rbase + i * 32 + (e >> 2) * 8 + (e & 3);
+                    if (row < M && cok[j]) f(cp[j] + (long long)row * ldc, acc[i][j][e], i, j, e);
+                }
+    };
+    if (beta != 0.0f) {
+        f32x16 old[FM][FN];
+        each([&](const TSR_GLOBAL float* c, float, int i, int j, int e) { old[i][j][e] = *c; });
+        each([&](TSR_GLOBAL float* c, float v, int i, int j, int e) { *c = alpha * v + beta * old[i][j][e]; });
+    } else {
+        each([&](TSR_GLOBAL float* c, float v, int, int, int) { *c = alpha * v; });
+    }
 }
 
 // ------------------------------------------------------------------ dispatch
 typedef void (*gemm_fn)(const GemmLaunch);
-struct Entry { GemmVariant v; gemm_fn fn; };
+struct Entry { GemmVariant v; gemm_fn fn[GEMM_SHAPES]; };
 
 #define TSR_GEMM(aks, bks, abf, nsa, nsb) \
-    { {aks, bks, abf, nsa, nsb}, gemm_kernel<(aks) != 0, (bks) != 0, (abf) != 0, nsa, nsb> }
+    { {aks, bks, abf, nsa, nsb}, {gemm_kernel<(aks) != 0, (bks) != 0, (abf) != 0, nsa, nsb, 128, 128>, \
+                                  gemm_kernel<(aks) != 0, (bks) != 0, (abf) != 0, nsa, nsb, 128, 64>, \
+                                  gemm_kernel<(aks) != 0, (bks) != 0, (abf) != 0, nsa, nsb, 64, 64>} }
 
 static const Entry kTable[] = {
     // A = G (k contiguous), B k-strided: G V, G Omega, G Qrow; also U D, Y Rinv, Q X
@@ -309,10 +408,11 @@ static const Entry kTable[] = {
 
 hipError_t launch_gemm(const GemmLaunch& L, const GemmVariant& v, hipStream_t stream) {
     if (L.n_tiles <= 0) return hipSuccess;
+    if (v.shape < 0 || v.shape >= GEMM_SHAPES) return hipErrorInvalidValue;
     for (const Entry& e : kTable) {
         if (e.v.a_kstrided == v.a_kstrided && e.v.b_kstrided == v.b_kstrided && e.v.a_bf16 == v.a_bf16 &&
             e.v.a_pieces == v.a_pieces && e.v.b_pieces == v.b_pieces) {
-            hipLaunchKernelGGL(e.fn, dim3(L.n_tiles), dim3(NTHREADS), 0, stream, L);
+            hipLaunchKernelGGL(e.fn[v.shape], dim3(L.n_tiles), dim3(NTHREADS), 0, stream, L);
             return hipGetLastError();
         }
     }
@@ -320,26 +420,60 @@ hipError_t launch_gemm(const GemmLaunch& L, const GemmVariant& v, hipStream_t st
 }
 
 // ------------------------------------------------------------------ split-k reduction
+// Four neighbouring elements per thread, the partials of all splits fetched eight at a time.
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceProblem* probs, const ReduceProblem single,
                                                             const float alpha, const float beta) {
-    const ReduceProblem* p = probs ? probs + blockIdx.y : &single;
-    const int M = p->M, N = p->N, splits = p->splits;
-    const long long total = (long long)M * N;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-         i += (long long)gridDim.x * blockDim.x) {
-        float s = 0.0f;
-        for (int k = 0; k < splits; ++k) s += p->part[(long long)k * p->stride + i];
-        const long long o = (i / N) * p->ldc + (i % N);
+    const ReduceProblem p = probs ? probs[blockIdx.y] : single;
+    const TSR_GLOBAL float* part = (const TSR_GLOBAL float*)p.part;
+    TSR_GLOBAL float* out = (TSR_GLOBAL float*)p.out;
+    const long long total = (long long)p.M * p.N;
+    const bool dense = p.ldc == p.N;
+    const long long nv = total / 4;                           // whole vectors; the last elements one by one
+    const bool vec = (p.stride % 4) == 0 || p.splits == 1;    // partials on 16-byte boundaries
+    auto finish = [&](long long i, float s) {
+        const long long o = dense ? i : (long long)((unsigned long long)i / (unsigned)p.N) * p.ldc + (long long)((unsigned long long)i % (unsigned)p.N);
         float v = alpha * s;
-        if (beta != 0.0f) v += beta * p->out[o];
-        p->out[o] = v;
+        if (beta != 0.0f) v += beta * out[o];
+        out[o] = v;
+    };
+    const long long step = (long long)gridDim.x * blockDim.x;
+    const long long me = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (vec) {
+        for (long long q = me; q < nv; q += step) {
+            const TSR_GLOBAL f32x4* src = (const TSR_GLOBAL f32x4*)(part + 4 * q);
+            const long long st = p.stride / 4;
+            f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+            int k = 0;
+            for (; k + 8 <= p.splits; k += 8) {
+                f32x4 x[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x[u] = src[(k + u) * st];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s += x[u];
+            }
+            for (; k < p.splits; ++k) s += src[k * st];
+            if (dense) {
+                f32x4 v = alpha * s;
+                TSR_GLOBAL f32x4_u* o = (TSR_GLOBAL f32x4_u*)(out + 4 * q);
+                if (beta != 0.0f) v += beta * (f32x4)*o;
+                *o = v;
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) finish(4 * q + u, s[u]);
+            }
+        }
+    }
+    for (long long i = (vec ? 4 * nv : 0) + me; i < total; i += step) {
+        float s = 0.0f;
+        for (int k = 0; k < p.splits; ++k) s += part[(long long)k * p.stride + i];
+        finish(i, s);
     }
 }
 
 hipError_t launch_splitk_reduce(const ReduceProblem* probs_dev, const ReduceProblem* single, int count,
                                 int max_elems, float alpha, float beta, hipStream_t stream) {
     if (count <= 0 || max_elems <= 0) return hipSuccess;
-    int bx = (max_elems + 255) / 256;
+    int bx = (max_elems + 1023) / 1024;
     if (bx > 1024) bx = 1024;
     ReduceProblem s{};
     if (single) s = *single;

@@ -1,0 +1,59 @@
+"""Kernels at the sizes where a tile, a k split or a vector load can go wrong, through the single calls,
+against the fp64 oracle.
+
+Tolerance of the split-precision products: an operand is the sum of two bf16 pieces up to 2^-17 of its
+size and the product of the two second pieces is dropped, so a product is off by at most 3 x 2^-17 of
+|a||b|; two chained products, errors of random sign over the sums: 2 x 3 x 2^-17 = 4.6e-5.  One piece
+(bf16 operands): 2^-9 per rounding, four roundings (G or T, V, U, P or D): 7.8e-3."""
+import pytest
+import torch
+
+import synth_inputs as si
+from oracle import tsr_oracle as orc
+from gpu_util import check_close, dev, f32
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"split": 4.6e-5, "bf16": 7.8e-3}
+
+
+@pytest.fixture(scope="module")
+def tsr():
+    import paper_2602_08007_amd as t
+    assert torch.cuda.is_available()
+    return t
+
+
+def _bases(m, n, r, key):
+    return si.orthonormal(m, r, si.stream_key(key, 1)).float(), si.orthonormal(n, r, si.stream_key(key, 2)).float()
+
+
+# 64 x 64 tiles (few units of work), 128 x 64 (rank 30 at many units), 128 x 128; k remainders of 1 and 31
+# beside whole k-tiles; row remainders of 1, 2 and 127; extents below a vector's (2, 3, 5 and 7)
+SIZES = [(2, 3, 2), (5, 7, 3), (7, 65, 5), (64, 64, 64), (65, 97, 33), (127, 129, 65), (1026, 3713, 65), (1151, 4127, 30),
+         (641, 4097, 129)]
+
+
+@pytest.mark.parametrize("m,n,r", SIZES)
+@pytest.mark.parametrize("dtype,prec", [(torch.float32, "split"), (torch.bfloat16, "bf16")])
+def test_project_sizes(tsr, m, n, r, dtype, prec):
+    key = si.stream_key(701, m, n, r)
+    G = si.normal((m, n), si.stream_key(key, 3)).to(dtype)
+    U, V = _bases(m, n, r, key)
+    C = torch.full((r, r), float("nan"), device="cuda")
+    tsr.tsr_project_core(dev(G), dev(U), dev(V), C, precision=getattr(tsr, "TSR_PREC_" + prec.upper()))
+    # the core of a white gradient is 1 / sqrt(mn / r^2) of its norm: errors relative to what the sums hold
+    check_close(C, orc.project_core(G, U, V), TOL[prec] * max(1.0, (min(m, n) / r) ** 0.5), "core")
+
+
+@pytest.mark.parametrize("m,n,r", SIZES)
+@pytest.mark.parametrize("prec", ["split", "bf16"])
+def test_lift_sizes(tsr, m, n, r, prec):
+    key = si.stream_key(702, m, n, r)
+    U, V = _bases(m, n, r, key)
+    D = si.normal((r, r), si.stream_key(key, 3)).clamp(-1, 1)
+    W0 = si.weights(m, n, si.stream_key(key, 4))
+    W = dev(W0)
+    tsr.tsr_backproject_apply(W, dev(U), dev(V), dev(D), 1.0, 0.1, 0.75, precision=getattr(tsr, "TSR_PREC_" + prec.upper()))
+    ref = orc.backproject_apply(orc.f64(W0).copy(), U, V, D, 1.0, f32(0.1), 0.75)
+    check_close(orc.f64(W) - orc.f64(W0), ref - orc.f64(W0), TOL[prec], "movement")
