@@ -602,11 +602,306 @@ __global__ __launch_bounds__(256) void chol_output_kernel(const CholBlock* table
     }
 }
 
+// Variant for k <= 272, one launch: factor and inverse of one matrix in the registers of one workgroup.
+// The lower triangle is cut into 16 x 16 tiles, each owned by a wave in the fp64 MFMA accumulator layout
+// (v_mfma_f64_16x16x4: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16], receives
+// D[4 v + l / 16][l % 16]).  At step J the row and column through the diagonal tile J are finished
+//     L_IJ = A_IJ Li_J^T (I > J)          X_Jc = Li_J E_Jc (c < J),   Li_J = L_JJ^-1
+// and shared through LDS; then every tile below row J takes its update
+//     A_IK -= L_IJ L_KJ^T (K > J)         E_Ic -= L_IJ X_Jc (c <= J)
+// where the tile of column c, done as part of L after step c, holds E, the part of the inverse under way,
+// from then on.  So nothing but the input and the results touches memory, and the inverse costs no
+// launches of its own.  What bounds it is the serial chain of the diagonal tiles (sixteen dependent
+// reciprocal square roots each): the last wave owns the diagonal tiles, takes the next one first and
+// factors it while the other waves work on the rest.
+// Per call, one matrix per compute unit, the three launches of the blocked variant -> this: k = 72 68 -> 28 us,
+// k = 136 130 -> 62 us, k = 264 315 -> 160 us (there the fp64 products of the early steps take over: about
+// 150 tiles of four products each, at two waves per SIMD).  272 is where the tiles fill the registers; larger
+// matrices take the blocked variant.
+constexpr int CT = 16;
+constexpr int CT_P = CT + 2;                   // LDS row: 144 bytes, operand reads free of bank conflicts
+constexpr int CT_MAXK = 272;
+
+// Workgroup barrier that orders LDS only: the results on their way to global memory are not waited for.
+__device__ inline void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <int NT, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlock* table, const CholBlock single,
+                                                                    const double tol, const double shift_rel) {
+    constexpr int OFF = (NT * (NT - 1) / 2 + WAVES - 2) / (WAVES - 1);     // off-diagonal tiles per wave
+    constexpr int SLOTS = OFF > NT ? OFF : NT;
+    typedef double d4_t __attribute__((ext_vector_type(4)));
+    typedef double tile_t[CT][CT_P];
+    extern __shared__ double smem[];
+    // two buffers of NT tiles; slot x: L_xJ (x > J), X_Jx (x < J), Li_J (x = J)
+    tile_t& dg = ((tile_t*)smem)[2 * NT];                      // the diagonal tile being factored
+    float* s_diag = (float*)(smem + (2 * NT + 1) * CT * CT_P);  // diagonal of S
+
+    CholBlock cb = single;
+    if (table) cb = table[blockIdx.x];
+    const int k = cb.k;
+    const int nt = (k + CT - 1) / CT;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, lk = lane >> 4;
+    const bool diag_wave = wave == WAVES - 1;
+    typedef const float __attribute__((address_space(1))) gfloat;
+    gfloat* S = (gfloat*)cb.S;
+    float __attribute__((address_space(1)))* Rinv = (float __attribute__((address_space(1)))*)cb.Rinv;
+    double __attribute__((address_space(1)))* Rtot = (double __attribute__((address_space(1)))*)cb.Rtot;
+
+    // ---- tiles of this wave: the diagonal ones, or number wave + (WAVES - 1) s of the row-major strict triangle
+    int tI[SLOTS], tK[SLOTS];
+    d4_t acc[SLOTS];
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+        const int t = s * (WAVES - 1) + wave;
+        int I = (int)((sqrtf(8.0f * (float)t + 1.0f) + 1.0f) * 0.5f);
+        while (I * (I + 1) / 2 <= t) ++I;
+        while (I * (I - 1) / 2 > t) --I;
+        tI[s] = diag_wave ? s : __builtin_amdgcn_readfirstlane(I);
+        tK[s] = diag_wave ? s : __builtin_amdgcn_readfirstlane(t - I * (I - 1) / 2);
+    }
+    double mx = 0.0;
+    for (int j = tid; j < nt * CT; j += 64 * WAVES) {
+        const float d = (j < k) ? S[(size_t)j * k + j] : 1.0f;
+        s_diag[j] = d;
+        if (j < k) mx = fmax(mx, (double)d);
+    }
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+        if (tI[s] >= nt) continue;                             // uniform
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int i = tI[s] * CT + 4 * v + lk, c = tK[s] * CT + li;
+            const bool in = i < k && c < k;
+            const int lo = min(min(i, c), k - 1), hi = min(max(i, c), k - 1);    // the lower triangle of S is read
+            const float x = S[(size_t)hi * k + lo];
+            acc[s][v] = in ? (double)x : (i == c ? 1.0 : 0.0);
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
+    if (lane == 0) smem[wave] = mx;
+    __syncthreads();
+    mx = smem[0];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) mx = fmax(mx, smem[w]);
+    const double shift = shift_rel * mx;
+    __syncthreads();
+    if (diag_wave) {
+#pragma unroll
+        for (int s = 0; s < NT; ++s)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (4 * v + lk == li && s * CT + li < k) acc[s][v] += shift;
+    }
+    // below the block diagonal both results are zero
+    for (int a = CT + wave; a < k; a += WAVES)
+        for (int b = lane; b < a / CT * CT; b += 64) {
+            Rinv[(size_t)a * k + b] = 0.0f;
+            if (Rtot) Rtot[(size_t)a * k + b] = 0.0;
+        }
+
+    // A slot's tile coordinates, opaque to the compiler: it would otherwise keep the LDS addresses of every
+    // slot in vector registers across the loop (and spill).
+    auto coords = [&](int s, int& I, int& K) {
+        I = tI[s]; K = tK[s];
+        asm volatile("" : "+s"(I), "+s"(K));
+    };
+    auto put = [&](tile_t& d, const d4_t& x) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) d[4 * v + lk][li] = x[v];
+    };
+    // Factor the tile in dg and invert the factor, both by the same updates: lane l < 16 holds row l of the
+    // tile, lane 16 + l column l of the inverse (which starts as the identity).  A dropped pivot leaves a
+    // zero column in L and a zero row and column in the inverse.  (Above the diagonal a lane's values are
+    // meaningless and never read by another lane.)
+    auto factor = [&](int J, tile_t& out) {
+        double a[CT];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) a[c] = (lk == 0) ? dg[li][c] : ((c == li) ? 1.0 : 0.0);
+        const double thr = tol * (double)s_diag[J * CT + li];
+        // 1 / sqrt(pivot), zero for a dropped one: the hardware's first digits and one third-order step
+        double piv = readlane_f64(a[0], 0), t0 = readlane_f64(thr, 0);
+        double r0 = __builtin_amdgcn_rsq(piv);
+        double e = fma(-(piv * r0), r0, 1.0);
+        double invd = (piv > 0.0 && piv > t0) ? fma(r0 * e, fma(0.375, e, 0.5), r0) : 0.0;
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+            const double aj = a[j] * invd;
+            a[j] = aj;
+            if (j + 1 < CT) {
+                // the next pivot's column first; its reciprocal root is under way while the other columns follow
+                a[j + 1] -= aj * readlane_f64(aj, j + 1);
+                double l[CT];
+#pragma unroll
+                for (int c = j + 2; c < CT; ++c) l[c] = readlane_f64(aj, c);
+                piv = readlane_f64(a[j + 1], j + 1);
+                t0 = readlane_f64(thr, j + 1);
+                r0 = __builtin_amdgcn_rsq(piv);
+                const double m = piv * r0;
+                constexpr int N = CT;
+                auto part = [&](int q) {                       // a quarter of the remaining columns
+#pragma unroll
+                    for (int c = 0; c < N; ++c)
+                        if (c >= j + 2 && (c - j - 2) % 4 == q) a[c] -= aj * l[c];
+                };
+                part(0);
+                e = fma(-m, r0, 1.0);
+                part(1);
+                const double s2 = fma(0.375, e, 0.5), re = r0 * e;
+                part(2);
+                invd = (piv > 0.0 && piv > t0) ? fma(re, s2, r0) : 0.0;
+                part(3);
+            }
+        }
+        // outputs of the diagonal tile: Rtot = L^T (lane = its column), Rinv = X^T (lane = its row)
+        const int g = J * CT + li;
+        if (lk == 0) {
+            if (Rtot)
+#pragma unroll
+                for (int j = 0; j < CT; ++j)
+                    if (J * CT + j < k && g < k) Rtot[(size_t)(J * CT + j) * k + g] = (j <= li) ? a[j] : 0.0;
+        } else if (lk == 1) {
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                out[c][li] = a[c];
+                if (J * CT + c < k && g < k) Rinv[(size_t)g * k + J * CT + c] = (float)a[c];
+            }
+        }
+    };
+
+    for (int J = -1; J < nt; ++J) {
+        tile_t* cur = (tile_t*)smem + ((J & 1) ? NT : 0);
+        tile_t* nxt = (tile_t*)smem + ((J & 1) ? 0 : NT);
+        if (J >= 0) {
+            // ---- finish column J of L and row J of the inverse, the tiles dealt to all waves
+            tile_t& Li = cur[J];
+            for (int x = wave; x < nt; x += WAVES) {
+                if (x != J) {
+                    // row of the left factor and column of the right one of this lane, four k apart per element
+                    const double *pa, *pb;
+                    int sb;
+                    if (x > J) { pa = &cur[x][li][lk]; pb = &Li[li][lk]; sb = 4; }
+                    else { pa = &Li[li][lk]; pb = &cur[x][lk][li]; sb = 4 * CT_P; }
+                    double a[4], b[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) { a[q] = pa[4 * q]; b[q] = pb[sb * q]; }
+                    __builtin_amdgcn_sched_barrier(0);         // all operands on their way before the first product
+                    d4_t p = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) p = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], p, 0, 0, 0);
+                    put(cur[x], p);
+                }
+            }
+            lds_barrier();
+            // ---- results of step J to memory, transposed: L_xJ -> Rtot, X_Jx -> Rinv
+            if (!diag_wave) {
+                for (int x = wave; x < nt; x += WAVES - 1) {
+                    if (x == J) continue;
+                    double o[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) o[v] = cur[x][li][4 * v + lk];
+                    const int r = (x > J ? J : x) * CT + lk, c = (x > J ? x : J) * CT + li;
+                    const size_t at = (size_t)r * k + c;
+                    if (c < k) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            if (r + 4 * v < k) {
+                                if (x < J) Rinv[at + (size_t)(4 * v) * k] = (float)o[v];
+                                else if (Rtot) Rtot[at + (size_t)(4 * v) * k] = o[v];
+                            }
+                    }
+                }
+            }
+        }
+        if (J + 1 >= nt) break;
+        // ---- update of tile (I, K) with step J (a finished tile, I <= J, may take one too: it is dead)
+        auto fetch = [&](int I, int K, double (&a)[4], double (&b)[4]) {
+            const double* pa = &cur[I][li][lk];
+            const double* pb = (K > J) ? &cur[K][li][lk] : &cur[K][lk][li];
+            const int sb = (K > J) ? 4 : 4 * CT_P;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) { a[q] = -pa[4 * q]; b[q] = pb[sb * q]; }
+        };
+        if (diag_wave) {
+#pragma unroll
+            for (int s = 0; s < NT; ++s)
+                if (tI[s] == J + 1) {
+                    if (J >= 0) {
+                        double a[4], b[4];
+                        fetch(J + 1, J + 1, a, b);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) acc[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], acc[s], 0, 0, 0);
+                    }
+                    put(dg, acc[s]);
+                }
+            __builtin_amdgcn_s_setprio(3);
+            factor(J + 1, nxt[J + 1]);
+            __builtin_amdgcn_s_setprio(0);
+        }
+        // two tiles at a time, their products interleaved
+        if (J >= 0) {
+#pragma unroll
+            for (int s = 0; s < SLOTS; s += 2) {
+                constexpr int LAST = SLOTS - 1;
+                const int s1 = s < LAST ? s + 1 : s;
+                int I0, K0, I1, K1;
+                coords(s, I0, K0);
+                coords(s1, I1, K1);
+                if (I1 <= J || I0 >= nt) continue;             // a wave's tiles come in row order
+                double a[2][4], b[2][4];
+                fetch(I0, K0, a[0], b[0]);
+                if (s < LAST) fetch(I1, K1, a[1], b[1]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    acc[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0][q], b[0][q], acc[s], 0, 0, 0);
+                    if (s < LAST) acc[s1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1][q], b[1][q], acc[s1], 0, 0, 0);
+                }
+            }
+        }
+        // the raw values of the tiles that the next step finishes go to LDS; a tile of column J + 1 starts
+        // from zero as a tile of E
+        if (!diag_wave) {
+#pragma unroll
+            for (int s = 0; s < OFF; ++s) {
+                int I, K;
+                coords(s, I, K);
+                if (I >= nt || I <= J || (K != J + 1 && I != J + 1)) continue;
+                put(nxt[K == J + 1 ? I : K], acc[s]);
+                if (K == J + 1) acc[s] = d4_t{0.0, 0.0, 0.0, 0.0};
+            }
+        }
+        lds_barrier();
+    }
+}
+
+template <int NT, int WAVES>
+static hipError_t launch_chol_tiles(const CholBlock* table_dev, const CholBlock& single, int blocks, double tol, double shift_rel,
+                                    hipStream_t stream) {
+    constexpr int lds = (2 * NT + 1) * CT * CT_P * 8 + NT * CT * 4;
+    static thread_local bool configured = false;
+    if (!configured && lds > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute((const void*)chol_tiles_kernel<NT, WAVES>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+    }
+    configured = true;
+    hipLaunchKernelGGL((chol_tiles_kernel<NT, WAVES>), dim3(blocks), dim3(64 * WAVES), lds, stream, table_dev, single, tol, shift_rel);
+    return hipGetLastError();
+}
+
 hipError_t launch_chol_inv(const CholBlock* table_dev, const CholBlock* single, int blocks, int max_k, double tol,
                            double shift_rel, hipStream_t stream) {
     if (blocks <= 0) return hipSuccess;
     CholBlock sb{};
     if (single) sb = *single;
+    if (max_k <= 5 * CT) return launch_chol_tiles<5, 4>(table_dev, sb, blocks, tol, shift_rel, stream);
+    if (max_k <= 9 * CT) return launch_chol_tiles<9, 4>(table_dev, sb, blocks, tol, shift_rel, stream);
+    if (max_k <= CT_MAXK) return launch_chol_tiles<17, 8>(table_dev, sb, blocks, tol, shift_rel, stream);
     if (max_k <= CHB_MAXK) {
         // panel rows below the first diagonal block; in the inverse phase one block column of X
         const int pn_rows = ((max_k + CHB - 1) / CHB) * CHB;

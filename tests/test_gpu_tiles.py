@@ -57,3 +57,30 @@ def test_lift_sizes(tsr, m, n, r, prec):
     tsr.tsr_backproject_apply(W, dev(U), dev(V), dev(D), 1.0, 0.1, 0.75, precision=getattr(tsr, "TSR_PREC_" + prec.upper()))
     ref = orc.backproject_apply(orc.f64(W0).copy(), U, V, D, 1.0, f32(0.1), 0.75)
     check_close(orc.f64(W) - orc.f64(W0), ref - orc.f64(W0), TOL[prec], "movement")
+
+
+# the orthonormalisation and the small SVD around their tile sizes: 16-wide Cholesky tiles (5, 9 and 17 of
+# them per kernel), the blocked variant above 272
+@pytest.mark.parametrize("k", [5, 15, 16, 17, 33, 64, 80, 81, 144, 145, 264, 272, 273])
+def test_refresh_full_sketch_sizes(tsr, k):
+    """A sketch as wide as the matrix is high spans everything: the singular values and the leading
+    subspaces are those of the matrix, up to the orthonormality the last pass leaves (Gram matrix of three
+    bf16 pieces, 2^-24 per entry over k columns) and fp32 storage."""
+    p = min(4, k - 1)
+    r, m, n = k - p, k, k + 9
+    key = si.stream_key(703, k)
+    G = si.normal((m, n), si.stream_key(key, 1))
+    G[:, :3] *= 4.0
+    U = torch.full((m, r), float("nan"), device="cuda")
+    V = torch.full((n, r), float("nan"), device="cuda")
+    sigma = torch.full((k,), float("nan"), device="cuda")
+    tsr.tsr_refresh_rsvd(dev(G), dev(si.omega(n, k, si.stream_key(key, 2))), r, p, 1, U, V, sigma)
+    s = torch.linalg.svdvals(G.double())
+    # an fp32 sum of k products is off by at most k x 2^-24 of the sum of their sizes; four such sums in a
+    # row lead from the matrix to the triangular factor (apply, Gram, apply, product with Q)
+    assert float((sigma.cpu().double() - s).abs().max() / s[0]) < (k + 4) * 2.0 ** -22
+    U64, V64, eye = U.cpu().double(), V.cpu().double(), torch.eye(r, dtype=torch.float64)
+    for X in (U64, V64):
+        assert float(torch.linalg.norm(X.T @ X - eye)) < 2.0 ** -20 * k
+    core = U64.T @ G.double() @ V64
+    assert float(torch.linalg.norm(core - torch.diag(s[:r])) / torch.linalg.norm(s)) < 2e-5
