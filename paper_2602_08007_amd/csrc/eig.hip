@@ -2,7 +2,7 @@
 // Algorithm 1's refresh step) as a chain of launches, for k <= EIG_MAXK:
 //   1. T = R R^T                        fp64 MFMA GEMM, 64 x 64 tiles over the whole chip
 //   2. per matrix, one workgroup:       Householder tridiagonalization of T (reflectors parked in
-//      the rows of T they cleared); then eigenvalues by Sturm-count multisection (chip-wide),
+//      the rows of T they cleared), the last 288 columns in registers; then eigenvalues by Sturm-count multisection (chip-wide),
 //      eigenvectors of the tridiagonal matrix by inverse iteration (one per thread, pivoted LU
 //      of T - lambda I), Gram-Schmidt inside groups of numerically equal eigenvalues
 //   3. E = H_0 H_1 ... Z                reflectors applied to 64 eigenvectors per workgroup, the
@@ -20,8 +20,6 @@ namespace {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 constexpr int EIG_THREADS = 1024;
-constexpr int EIG_PARTS = 4;          // full-matrix pass of the tridiagonalization: pieces of a column sum
-constexpr int EIG_HALF_MIN_K = 384;   // from this size on the pass moves the lower triangle only
 constexpr double EIG_EPS = 2.220446049250313e-16;
 // Solves per eigenvector.  With an eigenvalue good to a few ulps of the spectral radius one solve
 // from a random start already carries the vector to the accuracy the gap allows (its component
@@ -147,12 +145,28 @@ __device__ inline double eig_start_value(unsigned i, unsigned j) {
     return (double)h * (1.0 / 4294967296.0) - 0.5 + 1.0 / 8589934592.0;
 }
 
+// Householder tridiagonalization of matrices too large for registers (k > EIG_TILES_K), down to a trailing
+// matrix of EIG_TILES_K columns that eig_tridiag_tiles_kernel takes on.  Reflector t, H_t = I - beta v v^T
+// on indices t+1..k-1, clears column t below the sub-diagonal; v goes to row t of T (columns t+1..), beta to
+// T[t][t].  The rank-two update of reflector t-1,  T -= v w^T + w v^T, is still pending when reflector t is
+// formed: column t is corrected on the fly, and one pass over the lower triangle of the trailing matrix then
+// applies the pending update and multiplies the updated matrix with the new v.  The pass runs at the rate
+// one CU moves data to and from L2.  The rows are dealt to the waves in turn, a wave sweeps its row up to the
+// diagonal in strips of 64 columns, and an entry (c, i) below the diagonal adds to two sums of p = T v, p_i
+// (kept per lane and strip over all rows of the wave, summed over the waves through LDS at the end) and p_c
+// (summed over the lanes once per row); the upper triangle is dead storage but for the reflectors.
+// (v, w) are indexed from t for the pending pair and from t+1 for the new one.
+constexpr int EIG_TILES_K = 288;
 __global__ __launch_bounds__(EIG_THREADS) void eig_tridiag_kernel(const JacobiBlock* table, const JacobiBlock single) {
     JacobiBlock jb = single;
     if (table) jb = table[blockIdx.x];
     const JacobiBlock* blk = &jb;
     const int k = blk->k;
-    double* T = blk->tmp;                       // symmetric, full storage; afterwards the reflectors
+    const int stop = k - EIG_TILES_K;           // columns reduced here
+    if (stop <= 0) return;
+    // (marked as global memory: a generic access would count as one to LDS, too)
+    typedef double __attribute__((address_space(1))) gdouble;
+    gdouble* T = (gdouble*)blk->tmp;            // symmetric; afterwards the reflectors
     const int tid = threadIdx.x, nt = blockDim.x;
     const int lane = tid & 63, wave = tid >> 6, nw = nt >> 6;
     __shared__ double s_d[EIG_MAXK];            // diagonal
@@ -175,38 +189,18 @@ __global__ __launch_bounds__(EIG_THREADS) void eig_tridiag_kernel(const JacobiBl
         return t;
     };
 
-    // ---- Householder tridiagonalization.  Reflector t, H_t = I - beta v v^T on indices
-    // t+1..k-1, clears column t below the sub-diagonal; v goes to row t of T (columns t+1..),
-    // beta to T[t][t].  The rank-two update of reflector t-1,  T -= v w^T + w v^T, is still
-    // pending when reflector t is formed: column t is corrected on the fly, and one pass over
-    // the trailing matrix then applies the pending update and multiplies the updated matrix
-    // with the new v.  The pass runs at the rate one CU moves data to and from L2.  Small
-    // matrices (k < EIG_HALF_MIN_K) keep the full symmetric matrix up to date: a thread owns a
-    // piece of a column, whose sum has one target.  Larger ones keep and move the lower
-    // triangle only (half the matrix, half the time; for small ones the short rows make that
-    // form the slower one): the rows are dealt to the waves in turn, a wave sweeps its row up to the
-    // diagonal in strips of 64 columns, and an entry (c, i) below the diagonal adds to two sums
-    // of p = T v, p_i (kept per lane and strip over all rows of the wave, summed over the waves
-    // through LDS at the end) and p_c (summed over the lanes once per row); the upper triangle
-    // is then dead storage from the first pass on.  Either way row t receives reflector t.
-    // (v, w) are indexed from t for the pending pair and from t+1 for the new one.
     constexpr int STRIPS = (EIG_MAXK + 63) / 64;
-    const bool half = k >= EIG_HALF_MIN_K;
-    const int parts = EIG_PARTS;
-    const int tpp = nt / parts;
-    const int part = tid / tpp, li = tid % tpp;
     for (int i = tid; i < k; i += nt) { s_v[i] = 0.0; s_w[i] = 0.0; }
     __syncthreads();
     double* pv_ = s_v; double* pw_ = s_w;      // pending pair
     double* nv_ = s_vn; double* nw_ = s_wn;    // pair being formed
-    for (int t = 0; t + 2 < k; ++t) {
+    for (int t = 0; t < stop; ++t) {
         const int n1 = k - t - 1;
         const double v0 = pv_[0], w0 = pw_[0];
-        // column t below the diagonal; with the full matrix kept, read along row t (coalesced)
+        // column t below the diagonal
         double psum = 0.0;
         for (int i = tid; i < n1; i += nt) {
-            const double tc = half ? T[(size_t)(t + 1 + i) * k + t] : T[(size_t)t * k + t + 1 + i];
-            const double x = tc - v0 * pw_[1 + i] - w0 * pv_[1 + i];
+            const double x = T[(size_t)(t + 1 + i) * k + t] - v0 * pw_[1 + i] - w0 * pv_[1 + i];
             nv_[i] = x;
             psum += x * x;
         }
@@ -225,103 +219,65 @@ __global__ __launch_bounds__(EIG_THREADS) void eig_tridiag_kernel(const JacobiBl
         __syncthreads();
         if (!skip) { for (int i = tid; i < n1; i += nt) T[(size_t)t * k + t + 1 + i] = nv_[i]; }
         double pv = 0.0;
-        if (half) {
-            // entry (c, i), i <= c, of the trailing matrix: pending update, then its terms of p = T v
-            double colacc[STRIPS];
+        // entry (c, i), i <= c, of the trailing matrix: pending update, then its terms of p = T v
+        double colacc[STRIPS];
 #pragma unroll
-            for (int q = 0; q < STRIPS; ++q) colacc[q] = 0.0;
-            // (the next row of a wave is fetched while the current one is worked on)
-            auto fetch = [&](int c, double* x) {
-                const double* row = T + (size_t)(t + 1 + c) * k + (t + 1);
+        for (int q = 0; q < STRIPS; ++q) colacc[q] = 0.0;
+        // (the next row of a wave is fetched while the current one is worked on)
+        auto fetch = [&](int c, double* x) {
+            const gdouble* row = T + (size_t)(t + 1 + c) * k + (t + 1);
 #pragma unroll
-                for (int q = 0; q < STRIPS; ++q) {
-                    const int i = 64 * q + lane;
-                    x[q] = (c < n1 && i <= c) ? row[i] : 0.0;
-                }
-            };
-            double xa[STRIPS], xb[STRIPS];
-            fetch(wave, xa);
-            auto work = [&](int c, const double* x) {
-                const double vc = pv_[1 + c], wc = pw_[1 + c], nc = nv_[c];
-                double* row = T + (size_t)(t + 1 + c) * k + (t + 1);
-                double rowacc = 0.0;
+            for (int q = 0; q < STRIPS; ++q) {
+                const int i = 64 * q + lane;
+                x[q] = (c < n1 && i <= c) ? row[i] : 0.0;
+            }
+        };
+        double xa[STRIPS], xb[STRIPS];
+        fetch(wave, xa);
+        auto work = [&](int c, const double* x) {
+            const double vc = pv_[1 + c], wc = pw_[1 + c], nc = nv_[c];
+            gdouble* row = T + (size_t)(t + 1 + c) * k + (t + 1);
+            double rowacc = 0.0;
 #pragma unroll
-                for (int q = 0; q < STRIPS; ++q) {
-                    const int i = 64 * q + lane;
-                    if (i <= c) {
-                        const double xi = x[q] - (vc * pw_[1 + i] + wc * pv_[1 + i]);
-                        row[i] = xi;
-                        colacc[q] += xi * nc;
-                        if (i < c) rowacc += xi * nv_[i];
-                    }
-                }
-                rowacc = eig_wave_sum(rowacc);
-                if (lane == 0) s_prow[c] = rowacc;
-            };
-            for (int c = wave; c < n1; c += 2 * nw) {
-                fetch(c + nw, xb);
-                work(c, xa);
-                if (c + nw < n1) {
-                    fetch(c + 2 * nw, xa);
-                    work(c + nw, xb);
+            for (int q = 0; q < STRIPS; ++q) {
+                const int i = 64 * q + lane;
+                if (i <= c) {
+                    const double xi = x[q] - (vc * pw_[1 + i] + wc * pv_[1 + i]);
+                    row[i] = xi;
+                    colacc[q] += xi * nc;
+                    if (i < c) rowacc += xi * nv_[i];
                 }
             }
-            // column sums of the waves: the first half of the waves store theirs, the second half add to them
-            if (wave < nw / 2) {
+            rowacc = eig_wave_sum(rowacc);
+            if (lane == 0) s_prow[c] = rowacc;
+        };
+        for (int c = wave; c < n1; c += 2 * nw) {
+            fetch(c + nw, xb);
+            work(c, xa);
+            if (c + nw < n1) {
+                fetch(c + 2 * nw, xa);
+                work(c + nw, xb);
+            }
+        }
+        // column sums of the waves: the first half of the waves store theirs, the second half add to them
+        if (wave < nw / 2) {
 #pragma unroll
-                for (int q = 0; q < STRIPS; ++q)
-                    if (64 * q + lane < n1) s_part[wave * EIG_MAXK + 64 * q + lane] = colacc[q];
-            }
-            __syncthreads();
-            if (wave >= nw / 2) {
+            for (int q = 0; q < STRIPS; ++q)
+                if (64 * q + lane < n1) s_part[wave * EIG_MAXK + 64 * q + lane] = colacc[q];
+        }
+        __syncthreads();
+        if (wave >= nw / 2) {
 #pragma unroll
-                for (int q = 0; q < STRIPS; ++q)
-                    if (64 * q + lane < n1) s_part[(wave - nw / 2) * EIG_MAXK + 64 * q + lane] += colacc[q];
-            }
-            __syncthreads();
-            for (int i = tid; i < n1; i += nt) {
-                double a = s_prow[i];
-                for (int q = 0; q < nw / 2; ++q) a += s_part[q * EIG_MAXK + i];
-                a *= beta;
-                nw_[i] = a;
-                pv += a * nv_[i];
-            }
-        } else {
-            const int seg = (n1 + parts - 1) / parts;
-            const int c_lo = min(n1, part * seg), c_hi = min(n1, c_lo + seg);
-            // entry (c, i) of the trailing matrix, c in this thread's piece: pending update, then its
-            // term of p = T v (rows read as columns, coalesced over the output index i)
-            for (int i = li; i < n1; i += tpp) {
-                const double vi = pv_[1 + i], wi = pw_[1 + i];
-                double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-                double* col = T + (size_t)(t + 1) * k + (t + 1 + i);
-                int c = c_lo;
-                for (; c + 8 <= c_hi; c += 8) {
-                    double x[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) x[u] = col[(size_t)(c + u) * k];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        x[u] -= pv_[1 + c + u] * wi + pw_[1 + c + u] * vi;
-                        col[(size_t)(c + u) * k] = x[u];
-                        acc[u] += x[u] * nv_[c + u];
-                    }
-                }
-                for (; c < c_hi; ++c) {
-                    const double x = col[(size_t)c * k] - (pv_[1 + c] * wi + pw_[1 + c] * vi);
-                    col[(size_t)c * k] = x;
-                    acc[0] += x * nv_[c];
-                }
-                s_part[part * EIG_MAXK + i] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
-            }
-            __syncthreads();
-            for (int i = tid; i < n1; i += nt) {
-                double a = 0.0;
-                for (int q = 0; q < parts; ++q) a += s_part[q * EIG_MAXK + i];
-                a *= beta;
-                nw_[i] = a;
-                pv += a * nv_[i];
-            }
+            for (int q = 0; q < STRIPS; ++q)
+                if (64 * q + lane < n1) s_part[(wave - nw / 2) * EIG_MAXK + 64 * q + lane] += colacc[q];
+        }
+        __syncthreads();
+        for (int i = tid; i < n1; i += nt) {
+            double a = s_prow[i];
+            for (int q = 0; q < nw / 2; ++q) a += s_part[q * EIG_MAXK + i];
+            a *= beta;
+            nw_[i] = a;
+            pv += a * nv_[i];
         }
         const double kk2 = 0.5 * beta * block_sum(pv);
         for (int i = tid; i < n1; i += nt) nw_[i] -= kk2 * nv_[i];           // w = p - (beta/2)(p.v) v
@@ -330,21 +286,287 @@ __global__ __launch_bounds__(EIG_THREADS) void eig_tridiag_kernel(const JacobiBl
         sw = pv_; pv_ = nv_; nv_ = sw;
         sw = pw_; pw_ = nw_; nw_ = sw;
     }
-    // the last pending update touches the trailing 2 x 2 block only
-    if (tid == 0) {
-        if (k >= 2) {
-            s_d[k - 2] = T[(size_t)(k - 2) * k + k - 2] - 2.0 * pv_[0] * pw_[0];
-            s_e[k - 2] = T[(size_t)(k - 1) * k + k - 2] - pv_[1] * pw_[0] - pw_[1] * pv_[0];
-            s_d[k - 1] = T[(size_t)(k - 1) * k + k - 1] - 2.0 * pv_[1] * pw_[1];
-        } else {
-            s_d[0] = T[0];
+    // the last pending update
+    for (int c = wave; c < EIG_TILES_K; c += nw) {
+        const double vc = pv_[c], wc = pw_[c];
+        gdouble* row = T + (size_t)(stop + c) * k + stop;
+        for (int i = lane; i <= c; i += 64) row[i] -= vc * pw_[i] + wc * pv_[i];
+    }
+    // the tridiagonal matrix travels to the next launches behind the LU scratch
+    double* DE = blk->scratch + (size_t)3 * k * k;
+    for (int i = tid; i < stop; i += nt) { DE[i] = s_d[i]; DE[k + i] = s_e[i]; }
+}
+
+// ---- Tridiagonalization with the matrix in registers, for the trailing part of at most 288 columns.
+// Cross-lane sums without LDS: data-parallel moves inside the 16-lane rows, row and half swaps beyond.
+template <int CTRL> __device__ inline double eig_dpp(double x) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_MIRROR8 = 0x141, DPP_MIRROR16 = 0x140, DPP_ROR8 = 0x128;
+// (a, b) -> (a of the lower 32 lanes, b of the lower 32 lanes) + (a of the upper, b of the upper): the sum of
+// a over the halves in lanes 0-31, that of b in lanes 32-63
+__device__ inline double eig_sum32(double a, double b) {
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+// likewise over the two 16-lane rows of a half: a's sum in the even rows, b's in the odd ones
+__device__ inline double eig_sum16(double a, double b) {
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ inline double eig_wave_sum_dpp(double x) {         // result in every lane
+    x += eig_dpp<DPP_XOR1>(x);
+    x += eig_dpp<DPP_XOR2>(x);
+    x += eig_dpp<DPP_MIRROR8>(x);
+    x += eig_dpp<DPP_MIRROR16>(x);
+    x = eig_sum16(x, x);
+    return eig_sum32(x, x);
+}
+// Barrier that orders LDS only (the reflectors on their way to memory are not waited for).
+__device__ inline void eig_lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The lower triangle in 32 x 32 tiles (diagonal tiles whole), dealt to the waves in turn; lane 8 a + b of a
+// wave holds the 4 x 4 patch of a tile at row 4 a, column 4 b.  Per reflector v of column t:
+//   every wave: norm of the column (in LDS), the reflector's scalars; row sums (A v) and column sums (A^T v)
+//     of its tiles, reduced over the lanes; v^T A v                                       -> LDS, barrier
+//   p = beta A v, an entry per thread, the sums of its tiles added                         -> LDS, barrier
+//   every wave: w = p - (beta/2)(p.v) v, A -= v w^T + w v^T in registers; column t + 1     -> LDS, barrier
+// so a reflector costs three barriers and no memory traffic but its own entries: it is bound by the latency
+// of these steps.  The 4 x 4 patches keep that short: eight vector entries read from LDS, two reductions and
+// a branch serve sixteen entries (16 x 16 tiles with four entries per lane took 1.8 times as long at k = 264).
+// One matrix per compute unit, the pass over the matrix in L2 -> this: k = 72 304 -> 123 us, k = 136 725 -> 315 us,
+// k = 264 2.65 -> 0.97 ms.  288 is what the registers hold (45 tiles over eight waves, 192 registers a lane).
+constexpr int TT = 32;
+template <int NB, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 1) void eig_tridiag_tiles_kernel(const JacobiBlock* table, const JacobiBlock single) {
+    constexpr int SLOTS = (NB * (NB + 1) / 2 + WAVES - 1) / WAVES;
+    constexpr int N = NB * TT;
+    typedef double d2_t __attribute__((ext_vector_type(2)));
+    JacobiBlock jb = single;
+    if (table) jb = table[blockIdx.x];
+    const int kfull = jb.k;
+    const int first = kfull > N ? kfull - N : 0;               // the columns before it are reduced already
+    const int k = kfull - first;
+    typedef double __attribute__((address_space(1))) gdouble;
+    gdouble* T = (gdouble*)jb.tmp + (size_t)first * kfull + first;
+    const int nb = (k + TT - 1) / TT;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int la = lane >> 3, lb = lane & 7;
+    __shared__ __attribute__((aligned(16))) double s_x[2][N];           // column being reduced / the next one
+    __shared__ __attribute__((aligned(16))) double s_p[N];
+    __shared__ double s_part[NB][NB][TT];       // [block][other block of the tile]: the tile's sums for the block
+    __shared__ double s_q[WAVES];               // v^T A v
+    __shared__ double s_d[N], s_e[N];
+
+    int tI[SLOTS], tK[SLOTS];
+    double a[SLOTS][4][4];
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+        const int t = s * WAVES + wave;
+        int I = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+        while ((I + 1) * (I + 2) / 2 <= t) ++I;
+        while (I * (I + 1) / 2 > t) --I;
+        tI[s] = __builtin_amdgcn_readfirstlane(I);
+        tK[s] = __builtin_amdgcn_readfirstlane(t - I * (I + 1) / 2);
+    }
+    auto coords = [&](int s, int& I, int& K) {   // opaque: keeps LDS addresses of all slots out of the registers
+        I = tI[s]; K = tK[s];
+        asm volatile("" : "+s"(I), "+s"(K));
+    };
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+        if (tI[s] >= nb) continue;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int i = tI[s] * TT + 4 * la + r, j = tK[s] * TT + 4 * lb + c;
+                const double x = T[(size_t)min(max(i, j), k - 1) * kfull + min(min(i, j), k - 1)];
+                a[s][r][c] = (i < k && j < k) ? x : 0.0;
+            }
+    }
+    // column c of the matrix below the diagonal -> LDS, zeros up to the diagonal; the diagonal entry -> s_d
+    auto put_column = [&](int c, double* dst) {
+        const int Kc = c / TT, bc = (c % TT) / 4, cc = c % 4;
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            int I, K;
+            coords(s, I, K);
+            if (K != Kc || I >= nb) continue;
+            if (lb == bc) {
+                double y[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    // (selected by value: an array indexed by a variable would have to live in memory)
+                    const double y0 = a[s][r][0], y1 = a[s][r][1], y2 = a[s][r][2], y3 = a[s][r][3];
+                    y[r] = cc == 0 ? y0 : cc == 1 ? y1 : cc == 2 ? y2 : y3;
+                }
+                if (I == Kc) {
+                    const int i = I * TT + 4 * la;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (i + r == c) s_d[c] = y[r];
+                        y[r] = (i + r > c) ? y[r] : 0.0;
+                    }
+                }
+                d2_t* d = (d2_t*)(dst + I * TT + 4 * la);
+                d[0] = d2_t{y[0], y[1]};
+                d[1] = d2_t{y[2], y[3]};
+            }
         }
+    };
+    put_column(0, s_x[0]);
+    __syncthreads();                            // (every wave has its tiles: the reflectors overwrite parts of T)
+
+    for (int t = 0; t + 2 < k; ++t) {
+        const double* x = s_x[t & 1];
+        const int T0 = (t + 1) / TT;
+        // ---- norm of the column below the diagonal, scalars of the reflector (every wave the same)
+        double psum = 0.0;
+#pragma unroll
+        for (int q = 0; q < (N + 63) / 64; ++q) {
+            const int i = 64 * q + lane;
+            const double xi = (i >= T0 * TT && i < nb * TT) ? x[min(i, N - 1)] : 0.0;
+            psum = fma(xi, xi, psum);
+        }
+        const double x0 = x[t + 1];
+        const double xnorm2 = eig_wave_sum_dpp(psum);
+        const bool skip = !(xnorm2 - x0 * x0 > 0.0);           // already tridiagonal here
+        // alpha = -sign(x0) |x|, beta = 2 / |x - alpha e1|^2 = 1 / (|x|^2 + |x0| |x|)
+        double rs = __builtin_amdgcn_rsq(xnorm2);
+        {
+            const double e = fma(-(xnorm2 * rs), rs, 1.0);
+            rs = fma(rs * e, fma(0.375, e, 0.5), rs);
+        }
+        const double xn = xnorm2 * rs;
+        const double alpha = skip ? x0 : (x0 >= 0.0 ? -xn : xn);
+        const double beta = skip ? 0.0 : eig_rcp(fma(fabs(x0), xn, xnorm2));
+        const double v0 = x0 - alpha;
+        if (wave == WAVES - 1 && lane == 0) {
+            s_e[t] = alpha;
+            T[(size_t)t * kfull + t] = beta;
+        }
+        if (!skip)
+            for (int i = t + 1 + tid; i < k; i += 64 * WAVES) T[(size_t)t * kfull + i] = (i == t + 1) ? v0 : x[i];
+
+        // four entries from 4 g on within block B; in a vector v, entry t + 1 has to be put right afterwards
+        auto load4 = [&](double (&v)[4], const double* src, int B, int g) {
+            const d2_t* p = (const d2_t*)(src + B * TT + 4 * g);
+            const d2_t u0 = p[0], u1 = p[1];
+            v[0] = u0[0]; v[1] = u0[1]; v[2] = u1[0]; v[3] = u1[1];
+        };
+        auto fix = [&](double (&v)[4], int B, int g) {
+            if (B == T0) {
+                const int i = t + 1 - (B * TT + 4 * g);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = (i == r) ? v0 : v[r];
+            }
+        };
+
+        // ---- sums of the tiles
+        double q1 = 0.0;
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            int I, K;
+            coords(s, I, K);
+            if (I >= nb || K < T0 || skip) continue;           // uniform
+            double vI[4], vK[4], R[4];
+            load4(vK, x, K, lb);
+            load4(vI, x, I, la);
+            __builtin_amdgcn_sched_barrier(0);
+            fix(vK, K, lb);
+            fix(vI, I, la);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                R[r] = a[s][r][0] * vK[0];
+#pragma unroll
+                for (int c = 1; c < 4; ++c) R[r] = fma(a[s][r][c], vK[c], R[r]);
+                q1 = fma(R[r], vI[r], q1);
+            }
+            {   // over the eight lanes of a patch row: lane b ends up with row b / 2
+                const bool hi = lb >= 4, up = (lb & 2) != 0;
+                double k0 = (hi ? R[2] : R[0]) + eig_dpp<DPP_MIRROR8>(hi ? R[0] : R[2]);
+                double k1 = (hi ? R[3] : R[1]) + eig_dpp<DPP_MIRROR8>(hi ? R[1] : R[3]);
+                double y = (up ? k1 : k0) + eig_dpp<DPP_XOR2>(up ? k0 : k1);
+                y += eig_dpp<DPP_XOR1>(y);
+                if ((lb & 1) == 0) s_part[I][K][4 * la + (lb >> 1)] = y;
+            }
+            if (I != K) {
+                double C[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    C[c] = a[s][0][c] * vI[0];
+#pragma unroll
+                    for (int r = 1; r < 4; ++r) C[c] = fma(a[s][r][c], vI[r], C[c]);
+                    q1 = fma(C[c], vK[c], q1);
+                }
+                // over the eight patches of a column: rows of lanes 0, 1, 2, 3 end up with columns 0, 2, 1, 3
+                double y = eig_sum16(eig_sum32(C[0], C[1]), eig_sum32(C[2], C[3]));
+                y += eig_dpp<DPP_ROR8>(y);
+                const int c = ((lane >> 4) & 1) * 2 + (lane >> 5);
+                if ((lane & 8) == 0) s_part[K][I][4 * lb + c] = y;
+            }
+        }
+        q1 = eig_wave_sum_dpp(q1);
+        if (lane == 0) s_q[wave] = q1;
+        eig_lds_barrier();
+
+        // ---- p, an entry per thread
+        for (int i = T0 * TT + tid; i < nb * TT; i += 64 * WAVES) {
+            double y[NB], p = 0.0;
+#pragma unroll
+            for (int X = 0; X < NB; ++X) y[X] = s_part[i / TT][X][i % TT];
+#pragma unroll
+            for (int X = 0; X < NB; ++X) p += (X >= T0 && X < nb) ? y[X] : 0.0;
+            s_p[i] = (i > t && !skip) ? beta * p : 0.0;
+        }
+        eig_lds_barrier();
+
+        // ---- w and the rank-two update
+        double pv = 0.0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) pv += s_q[w];
+        const double kk2 = 0.5 * beta * (beta * pv);
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            int I, K;
+            coords(s, I, K);
+            if (I >= nb || K < T0 || skip) continue;
+            double vI[4], vK[4], wI[4], wK[4];
+            load4(vK, x, K, lb);
+            load4(vI, x, I, la);
+            load4(wK, s_p, K, lb);
+            load4(wI, s_p, I, la);
+            __builtin_amdgcn_sched_barrier(0);
+            fix(vK, K, lb);
+            fix(vI, I, la);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) { wK[r] = fma(-kk2, vK[r], wK[r]); wI[r] = fma(-kk2, vI[r], wI[r]); }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) a[s][r][c] = fma(-wI[r], vK[c], fma(-vI[r], wK[c], a[s][r][c]));
+        }
+        put_column(t + 1, s_x[(t + 1) & 1]);
+        eig_lds_barrier();
+    }
+    // the last two columns (column k - 2 is in LDS, its diagonal entry in s_d)
+    if (k >= 2) put_column(k - 1, s_p);
+    if (tid == 0) {
+        if (k >= 2) s_e[k - 2] = s_x[(k - 2) & 1][k - 1];
         s_e[k - 1] = 0.0;
     }
-    __syncthreads();
-    // the tridiagonal matrix travels to the next launch behind the LU scratch
-    double* DE = blk->scratch + (size_t)3 * k * k;
-    for (int i = tid; i < k; i += nt) { DE[i] = s_d[i]; DE[k + i] = s_e[i]; }
+    eig_lds_barrier();
+    double* DE = jb.scratch + (size_t)3 * kfull * kfull;
+    for (int i = tid; i < k; i += 64 * WAVES) { DE[first + i] = s_d[i]; DE[kfull + first + i] = s_e[i]; }
 }
 
 // Eigenvalues and eigenvectors of the tridiagonal matrix (d, e) left by eig_tridiag_kernel, in
@@ -821,7 +1043,12 @@ hipError_t launch_eig_svd(const JacobiBlock* table_dev, const JacobiBlock* singl
     const EigGrid gv{blocks, (max_k + EIG_VAL_PER_WG - 1) / EIG_VAL_PER_WG, 0};
     const EigGrid gi{blocks, (max_k + 63) / 64, 1};      // measured: pinned 0.70 ms, chunk-major 0.74 (84 blocks, k = 264)
     hipLaunchKernelGGL(eig_gemm_kernel<0>, eig_grid(gt), dim3(256), 0, stream, table_dev, sb, gt);
-    hipLaunchKernelGGL(eig_tridiag_kernel, dim3(blocks), dim3(EIG_THREADS), 0, stream, table_dev, sb);
+    // tile rows of the register kernel by the largest matrix of the launch
+    if (max_k > EIG_TILES_K) hipLaunchKernelGGL(eig_tridiag_kernel, dim3(blocks), dim3(EIG_THREADS), 0, stream, table_dev, sb);
+    if (max_k <= 3 * TT) hipLaunchKernelGGL((eig_tridiag_tiles_kernel<3, 6>), dim3(blocks), dim3(384), 0, stream, table_dev, sb);
+    else if (max_k <= 5 * TT) hipLaunchKernelGGL((eig_tridiag_tiles_kernel<5, 8>), dim3(blocks), dim3(512), 0, stream, table_dev, sb);
+    else if (max_k <= 7 * TT) hipLaunchKernelGGL((eig_tridiag_tiles_kernel<7, 8>), dim3(blocks), dim3(512), 0, stream, table_dev, sb);
+    else hipLaunchKernelGGL((eig_tridiag_tiles_kernel<9, 8>), dim3(blocks), dim3(512), 0, stream, table_dev, sb);
     hipLaunchKernelGGL(eig_values_kernel, eig_grid(gv), dim3(256), 0, stream, table_dev, sb, gv);
     hipLaunchKernelGGL(eig_invit_kernel, eig_grid(gi), dim3(64), 0, stream, table_dev, sb, gi);
     hipLaunchKernelGGL(eig_groups_kernel, dim3(blocks), dim3(EIG_THREADS), 0, stream, table_dev, sb);
