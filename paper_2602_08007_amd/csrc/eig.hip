@@ -5,7 +5,7 @@
 //      the rows of T they cleared), the last 288 columns in registers; then eigenvalues by Sturm-count multisection (chip-wide),
 //      eigenvectors of the tridiagonal matrix by inverse iteration (one per thread, pivoted LU
 //      of T - lambda I), Gram-Schmidt inside groups of numerically equal eigenvalues
-//   3. E = H_0 H_1 ... Z                reflectors applied to 64 eigenvectors per workgroup, the
+//   3. E = H_0 H_1 ... Z                reflectors in blocks of sixteen, products on fp64 MFMAs with the
 //      vectors held in registers
 //   4. E^T R                            fp64 MFMA GEMM
 //   5. singular values = row norms of E^T R, ordering, fp32 outputs
@@ -79,14 +79,16 @@ __global__ __launch_bounds__(256) void eig_gemm_kernel(const JacobiBlock* table,
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m0 = tm * 64 + (wave >> 1) * 32, n0 = tn * 64 + (wave & 1) * 32;
     if (m0 >= k || n0 >= k) return;
-    const double* __restrict__ A;
-    const double* __restrict__ B = (WHICH == 2) ? blk->R1 : blk->R;
-    double* __restrict__ C;
+    typedef const double __attribute__((address_space(1))) cgdouble;
+    typedef double __attribute__((address_space(1))) gdouble;
+    cgdouble* A;
+    cgdouble* B = (WHICH == 2) ? (cgdouble*)blk->R1 : (cgdouble*)blk->R;
+    gdouble* C;
     long long sam, sak, sbk, sbn;
     int k_lo = 0, k_hi = k;
-    if (WHICH == 0) { A = blk->R; sam = k; sak = 1; sbk = 1; sbn = k; C = blk->tmp; k_lo = max(m0, n0) & ~3; }
-    else if (WHICH == 1) { A = blk->Gacc; sam = 1; sak = k; sbk = k; sbn = 1; C = blk->tmp + (size_t)k * k; k_hi = min(k, n0 + 32); }
-    else { A = blk->Gacc; sam = k; sak = 1; sbk = k; sbn = 1; C = blk->R; k_lo = m0 & ~3; k_hi = min(k, n0 + 32); }
+    if (WHICH == 0) { A = (cgdouble*)blk->R; sam = k; sak = 1; sbk = 1; sbn = k; C = (gdouble*)blk->tmp; k_lo = max(m0, n0) & ~3; }
+    else if (WHICH == 1) { A = (cgdouble*)blk->Gacc; sam = k; sak = 1; sbk = k; sbn = 1; C = (gdouble*)blk->tmp + (size_t)k * k; k_hi = min(k, n0 + 32); }
+    else { A = (cgdouble*)blk->Gacc; sam = k; sak = 1; sbk = k; sbn = 1; C = (gdouble*)blk->R; k_lo = m0 & ~3; k_hi = min(k, n0 + 32); }
     const int li = lane & 15, lk = lane >> 4;
     d4 acc[2][2];
 #pragma unroll
@@ -102,28 +104,42 @@ __global__ __launch_bounds__(256) void eig_gemm_kernel(const JacobiBlock* table,
         arow[i] = (long long)min(row, k - 1) * sam;
         bcol[i] = (long long)min(col, k - 1) * sbn;
     }
-    for (int kk = k_lo; kk < k_hi; kk += 16) {
-        double a[4][2], b[4][2];
+    // sixteen k at a time, the next sixteen on their way (values past the range are cleared when they are used)
+    double a[2][4][2], b[2][4][2];
+    auto fetch = [&](int s, int kk) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int kc = kk + 4 * u + lk;
-            const bool kok = kc < k_hi;
-            const long long kcc = min(kc, k - 1);
+            const long long kcc = min(kk + 4 * u + lk, k - 1);
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                const double av = A[arow[i] + kcc * sak];
-                const double bv = B[kcc * sbk + bcol[i]];
-                a[u][i] = (kok && aok[i]) ? av : 0.0;
-                b[u][i] = (kok && bok[i]) ? bv : 0.0;
+                a[s][u][i] = A[arow[i] + kcc * sak];
+                b[s][u][i] = B[kcc * sbk + bcol[i]];
             }
         }
+    };
+    auto multiply = [&](int s, int kk) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 4; ++u) {
+            const bool kok = kk + 4 * u + lk < k_hi;
+            double x[2], y[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                x[i] = (kok && aok[i]) ? a[s][u][i] : 0.0;
+                y[i] = (kok && bok[i]) ? b[s][u][i] : 0.0;
+            }
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][i], b[u][j], acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i], y[j], acc[i][j], 0, 0, 0);
+        }
+    };
+    fetch(0, k_lo);
+    for (int kk = k_lo; kk < k_hi; kk += 32) {
+        fetch(1, kk + 16);
+        multiply(0, kk);
+        fetch(0, kk + 32);
+        multiply(1, kk + 16);
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -575,27 +591,33 @@ __global__ __launch_bounds__(64 * WAVES, 1) void eig_tridiag_tiles_kernel(const 
 // Behind the LU scratch (3 k^2 doubles) sit d (k), e (k), the eigenvalues (k, ascending) and the
 // radius of the spectrum's bracket (1; zero marks a zero or non-finite matrix).
 
-// Sturm-count multisection: 32 eigenvalues per workgroup, 8 threads each; 7 probes cut an
-// eigenvalue's bracket into 8 pieces per pass, and the number of eigenvalues below a probe
-// tells on which side of it the wanted one lies.
-constexpr int EIG_VAL_PER_WG = 32;
+// Sturm-count multisection: 2^LP threads of a workgroup share an eigenvalue; their 2^LP - 1 probes cut its
+// bracket into 2^LP pieces per pass, and the number of eigenvalues below a probe tells on which side of it the
+// wanted one lies.  The count is the number of sign changes in the sequence of leading principal minors
+//     p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}
+// of the matrix scaled to unit norm (Givens; as stable as the recurrence of the pivots p_i / p_{i-1}, which
+// needs a division per step: two dependent operations a step here against eight there), rescaled every eight
+// steps.  A minor that vanishes has the sign that the count of a slightly larger probe gives it; d_i - x is kept
+// from vanishing by a shift of 1e-34 of the norm.  The chain of k steps is what bounds it: more probes per
+// pass (fewer passes) as long as the chip has room.  One matrix, eight threads each -> this: k = 72 90 -> 23 us,
+// k = 136 153 -> 38 us; 19 matrices at k = 264 288 -> 136 us.
+template <int LP>
 __global__ __launch_bounds__(256) void eig_values_kernel(const JacobiBlock* table, const JacobiBlock single, const EigGrid grid) {
+    constexpr int P = 1 << LP, PER_WG = 256 / P, S = P - 1;
     JacobiBlock jb = single;
     int gb, gc;
     if (!eig_decode(grid, gb, gc)) return;
     if (table) jb = table[gb];
     const JacobiBlock* blk = &jb;
     const int k = blk->k;
-    const int e0 = gc * EIG_VAL_PER_WG;
+    const int e0 = gc * PER_WG;
     if (e0 >= k) return;
     const double* DE = blk->scratch + (size_t)3 * k * k;
     double* LAM = blk->scratch + (size_t)3 * k * k + 2 * k;
     const int tid = threadIdx.x, nt = blockDim.x;
     const int lane = tid & 63, wave = tid >> 6, nw = nt >> 6;
-    __shared__ double s_d[EIG_MAXK];            // diagonal
-    __shared__ double s_w[EIG_MAXK];            // squared sub-diagonal
-    __shared__ double s_lo[EIG_VAL_PER_WG];     // eigenvalue brackets
-    __shared__ double s_hi[EIG_VAL_PER_WG];
+    typedef double d2_t __attribute__((ext_vector_type(2)));
+    __shared__ __attribute__((aligned(16))) d2_t s_dw[EIG_MAXK + 8];   // d_i, e_{i-1}^2 of the scaled matrix
     __shared__ int s_cnt[256];                  // Sturm counts of the probes
     __shared__ double s_red[4];
     auto block_max = [&](double v) -> double {
@@ -608,7 +630,7 @@ __global__ __launch_bounds__(256) void eig_values_kernel(const JacobiBlock* tabl
         for (int i = 1; i < nw; ++i) t = fmax(t, s_red[i]);
         return t;
     };
-    double gl = 0.0, gu = 0.0;
+    double gl, gu;
     {
         double lo = 1e300, hi = -1e300;
         for (int i = tid; i < k; i += nt) {
@@ -616,8 +638,6 @@ __global__ __launch_bounds__(256) void eig_values_kernel(const JacobiBlock* tabl
             const double rad = ((i > 0) ? fabs(DE[k + i - 1]) : 0.0) + ((i < k - 1) ? fabs(ei) : 0.0);
             lo = fmin(lo, di - rad);
             hi = fmax(hi, di + rad);
-            s_d[i] = di;
-            s_w[i] = ei * ei;
         }
         gu = block_max(hi);
         gl = -block_max(-lo);
@@ -627,180 +647,214 @@ __global__ __launch_bounds__(256) void eig_values_kernel(const JacobiBlock* tabl
     if (degenerate) tnorm = 0.0;
     if (gc == 0 && tid == 0) LAM[k] = tnorm;
     if (degenerate) {
-        if (tid < EIG_VAL_PER_WG && e0 + tid < k) LAM[e0 + tid] = 0.0;
+        if (tid < PER_WG && e0 + tid < k) LAM[e0 + tid] = 0.0;
         return;
     }
-    const double pivmin = fmax(1e-290, 1e-32 * tnorm);
+    const double inv = 1.0 / tnorm;
+    for (int i = tid; i < k + 8; i += nt) {     // (eight idle steps at the end: rows that change no sign)
+        const double e1 = (i > 0 && i < k) ? DE[k + i - 1] * inv : 0.0;
+        s_dw[i] = (i < k) ? d2_t{DE[i] * inv, e1 * e1} : d2_t{4.0, 0.0};
+    }
+    gl *= inv; gu *= inv;
     {
-        const double margin = 2.0 * EIG_EPS * tnorm * (double)k + 2.0 * pivmin;
+        const double margin = 2.0 * EIG_EPS * (double)k + 2e-32;
         gl -= margin; gu += margin;
     }
-    constexpr int S = 7;
-    const int el = tid >> 3, es = tid & 7;
+    const int el = tid / P, es = tid % P;
     const int ej = e0 + el;
     const bool eact = ej < k && es < S;
-    int passes = 0;
-    for (double shrink = 1.0; shrink < 1.5e17; shrink *= (double)(S + 1)) ++passes;       // 2^-57 of the bracket
-    if (tid < EIG_VAL_PER_WG) { s_lo[tid] = gl; s_hi[tid] = gu; }
+    double lo = gl, hi = gu;                                 // bracket, kept by each of the eigenvalue's threads
     __syncthreads();
-    const double inv_pieces = 1.0 / (double)(S + 1);
-    for (int pass = 0; pass < passes; ++pass) {
+    constexpr int PASSES = (57 + LP - 1) / LP;               // 2^-57 of the bracket
+    for (int pass = 0; pass < PASSES; ++pass) {
+        const double step = (hi - lo) * (1.0 / (double)P);
         if (eact) {
-            const double lo = s_lo[el], hi = s_hi[el];
-            const double x = lo + (double)(es + 1) * ((hi - lo) * inv_pieces);
-            double q = s_d[0] - x;
-            if (fabs(q) < pivmin) q = -pivmin;
-            int cnt = (q < 0.0) ? 1 : 0;
-            for (int i = 1; i < k; ++i) {
-                q = (s_d[i] - x) - s_w[i - 1] * eig_rcp(q);
-                if (fabs(q) < pivmin) q = -pivmin;
-                cnt += (q < 0.0) ? 1 : 0;
+            const double x = lo + (double)(es + 1) * step;
+            double p1 = 1.0, p2 = 0.0;                       // p_{i-1}, p_{i-2}
+            int cnt = 0;
+            unsigned signs = 0;
+            for (int i0 = 0; i0 < k; i0 += 8) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const d2_t dw = s_dw[i0 + u];
+                    const double dx = (dw[0] - x) - 1e-34;
+                    const double p = fma(dx, p1, -(dw[1] * p2));
+                    p2 = p1; p1 = p;
+                    signs = __builtin_amdgcn_alignbit(signs, (unsigned)__double2hiint(p), 31);
+                }
+                cnt += __popc((signs ^ (signs >> 1)) & 0xffu);
+                const int ex = -max(__builtin_amdgcn_frexp_exp(p1), __builtin_amdgcn_frexp_exp(p2));
+                p1 = __builtin_amdgcn_ldexp(p1, ex);
+                p2 = __builtin_amdgcn_ldexp(p2, ex);
             }
             s_cnt[tid] = cnt;
         }
         __syncthreads();
-        if (eact && es == 0) {
-            const double lo = s_lo[el], hi = s_hi[el];
-            const double step = (hi - lo) * inv_pieces;
-            int m = 0;                                       // leading probes at or below eigenvalue ej
-            while (m < S && s_cnt[tid + m] <= ej) ++m;
-            if (m > 0) s_lo[el] = lo + (double)m * step;
-            if (m < S) s_hi[el] = lo + (double)(m + 1) * step;
+        if (ej < k) {
+            const int* c = s_cnt + el * P;
+            int m = 0;                                       // leading probes at or below eigenvalue ej: counts ascend
+#pragma unroll
+            for (int h = P / 2; h > 0; h >>= 1)
+                if (c[m + h - 1] <= ej) m += h;
+            if (m < S) hi = lo + (double)(m + 1) * step;
+            if (m > 0) lo = lo + (double)m * step;
         }
         __syncthreads();
     }
-    if (tid < EIG_VAL_PER_WG && e0 + tid < k) LAM[e0 + tid] = 0.5 * (s_lo[tid] + s_hi[tid]);
+    if (ej < k && es == 0) LAM[ej] = 0.5 * (lo + hi) * tnorm;
 }
 
-// Eigenvectors by inverse iteration, vector j on its own thread, one wave per workgroup (the
-// recurrences are serial in the row index and wait on L2 for their operands: a wave alone on
-// its SIMD; up to sixteen rows are fetched at a time).  T - lambda I = P L U with
-// partial pivoting; U (three diagonals, pivots as reciprocals) is kept, L is applied to the
-// right-hand side while it is formed and formed again in every round.
+// Eigenvectors by inverse iteration, vector j on its own thread, one wave per workgroup.  The matrix scaled to
+// unit norm, T - lambda I = P L U with partial pivoting; U (three diagonals, pivots as reciprocals) and the
+// multipliers of L (the exchange of rows in their lowest bit) are kept in memory, so that the later rounds
+// repeat no division.  The recurrences are serial in the row index: without branches, and the rows they need
+// travel two batches of eight ahead.  The rows fetched batch by batch, a
+// division in every round -> this: k = 72 111 -> 62 us, k = 264 (19 matrices) 496 -> 209 us.
 __global__ __launch_bounds__(64) void eig_invit_kernel(const JacobiBlock* table, const JacobiBlock single, const EigGrid grid) {
+    constexpr int B = 8, NB = 2;                // rows per batch, batches in flight
     JacobiBlock jb = single;
     int gb, gc;
     if (!eig_decode(grid, gb, gc)) return;
     if (table) jb = table[gb];
-    const JacobiBlock* blk = &jb;
-    const int k = blk->k;
+    const int k = jb.k;
     if (gc * 64 >= k) return;
-    double* Z = blk->tmp + (size_t)k * k;       // eigenvectors of the tridiagonal matrix, Z[i][j] = j-th vector
-    double* U0 = blk->scratch;                  // per thread j: reciprocal pivots, first and second
-    double* U1 = U0 + (size_t)k * k;            //   super-diagonal of the LU factor, entry [i][j]
-    double* U2 = U1 + (size_t)k * k;
-    const double* DE = blk->scratch + (size_t)3 * k * k;
+    typedef double __attribute__((address_space(1))) gdouble;
+    gdouble* Z = (gdouble*)jb.tmp + (size_t)k * k;     // eigenvectors of the tridiagonal matrix, Z[i][j] = j-th vector
+    gdouble* U0 = (gdouble*)jb.scratch;         // per thread j: reciprocal pivots, first and second
+    gdouble* U1 = U0 + (size_t)k * k;           //   super-diagonal of the LU factor, entry [i][j]
+    gdouble* U2 = U1 + (size_t)k * k;
+    gdouble* LM = (gdouble*)jb.Gacc;            // multipliers (Gacc receives the eigenvectors later)
+    const double* DE = jb.scratch + (size_t)3 * k * k;
     const double* LAM = DE + 2 * k;
     const int tid = threadIdx.x;
     const int j = gc * 64 + tid;
-    __shared__ double s_d[EIG_MAXK];            // diagonal
-    __shared__ double s_e[EIG_MAXK];            // sub-diagonal, s_e[i] couples i and i + 1
-    for (int i = tid; i < k; i += 64) { s_d[i] = DE[i]; s_e[i] = DE[k + i]; }
-    __syncthreads();
+    __shared__ double s_d[EIG_MAXK + 1];        // diagonal
+    __shared__ double s_e[EIG_MAXK + 1];        // sub-diagonal, s_e[i] couples i and i + 1
     const double tnorm = LAM[k];
     if (tnorm == 0.0) {
         // zero (or non-finite) matrix: every orthonormal basis is one of eigenvectors
         if (j < k) for (int i = 0; i < k; ++i) Z[(size_t)i * k + j] = (i == j) ? 1.0 : 0.0;
         return;
     }
-    const double tiny = EIG_EPS * tnorm;                 // floor of an LU pivot
-    int vz;                                              // a zero the compiler keeps in a vector register
-    asm volatile("v_mov_b32 %0, 0" : "=v"(vz));
-    if (j < k) {
-        const double lam = LAM[j];
-        double* zc = Z + j;
-        double* u0 = U0 + j; double* u1 = U1 + j; double* u2 = U2 + j;
-        double scale = 1.0;
-        for (int round = 0; round < EIG_INVIT_ROUNDS; ++round) {
-            // forward: eliminate, apply to y (first time round: the start vector, later scale * previous x)
-            auto yval = [&](int i) -> double {
-                return (round == 0) ? eig_start_value((unsigned)i, (unsigned)j) : scale * zc[(size_t)i * k];
-            };
-            double a = s_d[0] - lam, b = (k > 1) ? s_e[0] : 0.0;
-            double ycur = yval(0);
-            auto step = [&](int i, double ynext) {
-                const double c = s_e[i];
-                const double dn = s_d[i + 1] - lam;
-                const double en = (i + 2 < k) ? s_e[i + 1] : 0.0;
-                const size_t o = (size_t)i * k;
-                if (fabs(a) >= fabs(c)) {
-                    double piv = a;
-                    if (fabs(piv) < tiny) piv = (piv < 0.0) ? -tiny : tiny;
-                    const double inv = eig_rcp(piv);
-                    const double mult = c * inv;
-                    if (round == 0) { u0[o] = inv; u1[o] = b; u2[o] = 0.0; }
-                    zc[o] = ycur;
-                    a = dn - mult * b; b = en;
-                    ycur = ynext - mult * ycur;
-                } else {
-                    double piv = c;
-                    if (fabs(piv) < tiny) piv = (piv < 0.0) ? -tiny : tiny;
-                    const double inv = eig_rcp(piv);
-                    const double mult = a * inv;
-                    if (round == 0) { u0[o] = inv; u1[o] = dn; u2[o] = en; }
-                    zc[o] = ynext;
-                    a = b - mult * dn; b = -mult * en;
-                    ycur = ycur - mult * ynext;
+    const double inv_norm = 1.0 / tnorm;
+    for (int i = tid; i <= k; i += 64) {
+        s_d[i] = (i < k) ? DE[i] * inv_norm : 0.0;
+        s_e[i] = (i < k - 1) ? DE[k + i] * inv_norm : 0.0;
+    }
+    __syncthreads();
+    const double tiny = EIG_EPS;                         // floor of an LU pivot
+    const int jc = min(j, k - 1);                        // idle lanes repeat the last vector and store nothing
+    const bool act = j < k;
+    const double lam = LAM[jc] * inv_norm;
+    auto floored = [&](double p) -> double { return (fabs(p) < tiny) ? copysign(tiny, p) : p; };
+    auto at = [&](int i) -> size_t { return (size_t)i * k + jc; };
+    double scale = 1.0, ss = 0.0;
+    for (int round = 0; round < EIG_INVIT_ROUNDS; ++round) {
+        // ---- forward: y = L^-1 P (start vector / previous x); the first round forms the factors
+        double ycur;
+        if (round == 0) {
+            ycur = eig_start_value(0u, (unsigned)jc);
+            double a = s_d[0] - lam, b = s_e[0];
+            for (int i = 0; i + 1 < k; ++i) {
+                const double c = s_e[i], dn = s_d[i + 1] - lam, en = s_e[i + 1];
+                const double ynext = eig_start_value((unsigned)(i + 1), (unsigned)jc);
+                const bool sw = fabs(a) < fabs(c);
+                const double inv = eig_rcp(floored(sw ? c : a));
+                double mult = (sw ? a : c) * inv;
+                mult = __hiloint2double(__double2hiint(mult), (__double2loint(mult) & ~1) | (sw ? 1 : 0));
+                const double p1 = sw ? dn : b, p2 = sw ? en : 0.0;
+                const double yp = sw ? ynext : ycur, yo = sw ? ycur : ynext;
+                if (act) { U0[at(i)] = inv; U1[at(i)] = p1; U2[at(i)] = p2; LM[at(i)] = mult; Z[at(i)] = yp; }
+                a = fma(-mult, p1, sw ? b : dn);
+                b = sw ? -mult * en : en;
+                ycur = fma(-mult, yp, yo);
+            }
+            if (act) { U0[at(k - 1)] = eig_rcp(floored(a)); U1[at(k - 1)] = 0.0; U2[at(k - 1)] = 0.0; }
+        } else {
+            double zb[NB][B], lb[NB][B];
+            auto fetch = [&](int s, int i0) {            // z of rows i0 + 1 .., multipliers of rows i0 ..
+#pragma unroll
+                for (int u = 0; u < B; ++u) {
+                    zb[s][u] = Z[at(min(i0 + 1 + u, k - 1))];
+                    lb[s][u] = LM[at(min(i0 + u, k - 2 > 0 ? k - 2 : 0))];
                 }
             };
-            {
-                int i = 0;
-                for (; i + 16 < k; i += 16) {                // rows i+1 .. i+16 fetched together
-                    double yn[16];
+            ycur = scale * Z[at(0)];
 #pragma unroll
-                    for (int u = 0; u < 16; ++u) yn[u] = yval(i + 1 + u);
+            for (int s = 0; s < NB; ++s) fetch(s, s * B);
+            for (int i0 = 0; i0 + 1 < k; i0 += NB * B) {
 #pragma unroll
-                    for (int u = 0; u < 16; ++u) step(i + u, yn[u]);
-                }
-                for (; i + 1 < k; ++i) step(i, yval(i + 1));
-            }
-            {
-                double piv = a;
-                if (fabs(piv) < tiny) piv = (piv < 0.0) ? -tiny : tiny;
-                if (round == 0) { u0[(size_t)(k - 1) * k] = eig_rcp(piv); u1[(size_t)(k - 1) * k] = 0.0; u2[(size_t)(k - 1) * k] = 0.0; }
-                zc[(size_t)(k - 1) * k] = ycur;
-            }
-            // backward: U x = y, sixteen rows fetched together (row offsets kept in vector registers:
-            // as wave-uniform values they would need more scalar registers than there are)
-            double x1 = 0.0, x2 = 0.0, amax = 0.0;      // x[i+1], x[i+2]
-            bool bad = false;
-            int i = k - 1;
-            for (; i >= 15; i -= 16) {
-                double y[16], p0[16], p1[16], p2[16];
+                for (int s = 0; s < NB; ++s) {
+                    double yp[B];
 #pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    const size_t o = (size_t)(i - u + vz) * k;
-                    y[u] = zc[o]; p0[u] = u0[o]; p1[u] = u1[o]; p2[u] = u2[o];
-                }
+                    for (int u = 0; u < B; ++u) {
+                        if (i0 + s * B + u + 1 < k) {    // uniform
+                            const double mult = lb[s][u], ynext = scale * zb[s][u];
+                            const bool sw = (__double2loint(mult) & 1) != 0;
+                            yp[u] = sw ? ynext : ycur;
+                            ycur = fma(-mult, yp[u], sw ? ycur : ynext);
+                        }
+                    }
+                    fetch(s, i0 + (NB + s) * B);
 #pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    const double x = (y[u] - p1[u] * x1 - p2[u] * x2) * p0[u];
-                    zc[(size_t)(i - u) * k] = x;
-                    amax = fmax(amax, fabs(x));
-                    bad = bad || !(fabs(x) <= 1e300);
-                    x2 = x1; x1 = x;
+                    for (int u = 0; u < B; ++u)
+                        if (act && i0 + s * B + u + 1 < k) Z[at(i0 + s * B + u)] = yp[u];
                 }
             }
-            for (; i >= 0; --i) {
-                const size_t o = (size_t)i * k;
-                const double x = (zc[o] - u1[o] * x1 - u2[o] * x2) * u0[o];
-                zc[o] = x;
-                amax = fmax(amax, fabs(x));
-                bad = bad || !(fabs(x) <= 1e300);
-                x2 = x1; x1 = x;
-            }
-            if (bad || !(amax > 0.0)) {
-                // overflow or a vanished vector (the floored pivots are meant to rule both out):
-                // go on from the unit vector rather than carry a non-finite value
-                for (int q = 0; q < k; ++q) zc[(size_t)q * k] = (q == j) ? 1.0 : 0.0;
-                amax = 1.0;
-            }
-            scale = 1.0 / amax;
         }
-        double ss = 0.0;
-        for (int i = 0; i < k; ++i) { const double x = scale * zc[(size_t)i * k]; ss += x * x; }
-        const double nrm = scale / sqrt(ss);
-        for (int i = 0; i < k; ++i) zc[(size_t)i * k] *= nrm;
+        if (act) Z[at(k - 1)] = ycur;
+        // ---- backward: U x = y
+        double x1 = 0.0, x2 = 0.0, amax = 0.0;          // x[i+1], x[i+2]
+        bool bad = false;
+        ss = 0.0;
+        double y[NB][B], p0[NB][B], p1[NB][B], p2[NB][B];
+        auto fetch = [&](int s, int i0) {                // rows i0, i0 - 1, ...
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                const size_t o = at(max(i0 - u, 0));
+                y[s][u] = Z[o]; p0[s][u] = U0[o]; p1[s][u] = U1[o]; p2[s][u] = U2[o];
+            }
+        };
+#pragma unroll
+        for (int s = 0; s < NB; ++s) fetch(s, k - 1 - s * B);
+        for (int i0 = k - 1; i0 >= 0; i0 -= NB * B) {
+#pragma unroll
+            for (int s = 0; s < NB; ++s) {
+                double xs[B];
+#pragma unroll
+                for (int u = 0; u < B; ++u) {
+                    if (i0 - s * B - u >= 0) {           // uniform
+                        const double x = fma(-p1[s][u], x1, fma(-p2[s][u], x2, y[s][u])) * p0[s][u];
+                        xs[u] = x;
+                        amax = fmax(amax, fabs(x));
+                        bad = bad || !(fabs(x) <= 1e300);
+                        ss = fma(x, x, ss);
+                        x2 = x1; x1 = x;
+                    }
+                }
+                fetch(s, i0 - (NB + s) * B);
+#pragma unroll
+                for (int u = 0; u < B; ++u)
+                    if (act && i0 - s * B - u >= 0) Z[at(i0 - s * B - u)] = xs[u];
+            }
+        }
+        if (bad || !(amax > 0.0)) {
+            // overflow or a vanished vector (the floored pivots are meant to rule both out):
+            // go on from the unit vector rather than carry a non-finite value
+            if (act) for (int q = 0; q < k; ++q) Z[at(q)] = (q == jc) ? 1.0 : 0.0;
+            amax = 1.0;
+            ss = 1.0;
+        }
+        scale = 1.0 / amax;
+    }
+    const double nrm = 1.0 / sqrt(ss);
+    for (int i0 = 0; i0 < k; i0 += 16) {
+        double x[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) x[u] = Z[at(min(i0 + u, k - 1))];
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            if (act && i0 + u < k) Z[at(i0 + u)] = nrm * x[u];
     }
 }
 
@@ -880,142 +934,240 @@ __global__ __launch_bounds__(EIG_THREADS) void eig_groups_kernel(const JacobiBlo
 }
 
 // ------------------------------------------------------------------ back-transformation
-// E = H_0 H_1 ... H_{k-3} Z for 64 columns of Z per workgroup: lane = column, each of the WAVES
-// waves owns EPT consecutive rows (in registers); the reflector entries are uniform over a
-// wave.  One barrier per reflector (the dot product spans the waves).
-template <int EPT, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void eig_backtransform_kernel(const JacobiBlock* table, const JacobiBlock single, const EigGrid grid) {
+// E = H_0 H_1 ... H_{k-3} Z in blocks of sixteen reflectors, H_j0 ... H_j0+15 = I - V T V^T (compact WY form), so
+// that the work is products on fp64 MFMAs.  First launch: the triangular factors T of all blocks, one wave each:
+// T(:,r) = -beta_r T (V^T v_r) above the diagonal, beta_r on it; they take the place of the LU factors.
+__device__ inline bool eig_has_reflector(int j, int k) { return j + 2 < k; }
+__global__ __launch_bounds__(64) void eig_wy_kernel(const JacobiBlock* table, const JacobiBlock single, const EigGrid grid) {
+    JacobiBlock jb = single;
+    int gb, b;
+    if (!eig_decode(grid, gb, b)) return;
+    if (table) jb = table[gb];
+    const int k = jb.k;
+    const int j0 = 16 * b;
+    if (!eig_has_reflector(j0, k)) return;
+    typedef const double __attribute__((address_space(1))) cgdouble;
+    typedef double __attribute__((address_space(1))) gdouble;
+    cgdouble* T = (cgdouble*)jb.tmp;
+    const int lane = threadIdx.x, li = lane & 15, lk = lane >> 4;
+    __shared__ double s_m[16][17];
+    __shared__ double s_beta[16];
+    const int j = j0 + li;                                   // this lane's reflector
+    const bool valid = eig_has_reflector(j, k);
+    const double beta = valid ? T[(size_t)j * k + j] : 0.0;
+    cgdouble* row = T + (size_t)min(j, k - 1) * k;
+    const bool live = valid && beta != 0.0;                  // (a step without a reflector leaves no entries)
+    d4 m = {0.0, 0.0, 0.0, 0.0};
+    for (int t = b; 16 * t < k; ++t) {
+        double a[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int i = 16 * t + 4 * q + lk;
+            const double x = row[min(i, k - 1)];
+            a[q] = (live && i > j && i < k) ? x : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) m = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], a[q], m, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) s_m[4 * v + lk][li] = m[v];
+    if (lk == 0) s_beta[li] = beta;
+    __syncthreads();
+    double x[16];                                            // row li of T
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        double sum = 0.0;
+#pragma unroll
+        for (int c = 0; c < r; ++c) sum = fma(x[c], s_m[c][r], sum);
+        const double br = s_beta[r];
+        x[r] = (li < r) ? -br * sum : (li == r) ? br : 0.0;
+    }
+    gdouble* out = (gdouble*)jb.scratch + (size_t)b * 256;
+    if (lk == 0) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) out[li * 16 + r] = x[r];
+    }
+}
+
+// Second launch: Z <- Z - V (T (V^T Z)) block by block, sixteen columns of Z per wave in the accumulator layout of
+// v_mfma_f64_16x16x4 (element v of lane l: row 4 v + l / 16, column l % 16), which is also the layout of its right
+// operand: Z and the two small products go from one product to the next without a move.  V is shared by the four
+// waves through LDS, the next block on its way in registers.  E is written transposed (row j of Gacc = j-th
+// eigenvector).  One reflector after the other (a barrier and a sum across waves each) took 83 us at k = 72,
+// 247 at 136, 588 at 264 (19 matrices) and 4.0 ms at 528 (56); both launches now 23, 55, 176 us and 1.8 ms.
+template <int RT>
+__global__ __launch_bounds__(256, 1) void eig_backtransform_kernel(const JacobiBlock* table, const JacobiBlock single, const EigGrid grid) {
+    constexpr int PITCH = (16 * RT + 13) / 32 * 32 + 18;     // row of V: 18 modulo 32 doubles, no bank conflicts
+    constexpr int PER = RT;                                  // entries of a block of V per thread (16 x 16 RT / 256)
     JacobiBlock jb = single;
     int gb, gc;
     if (!eig_decode(grid, gb, gc)) return;
     if (table) jb = table[gb];
-    const JacobiBlock* blk = &jb;
-    const int k = blk->k;
-    const int c0 = gc * 64;
-    if (c0 >= k) return;
-    typedef const double __attribute__((address_space(1))) gdouble;
-    typedef double d8 __attribute__((ext_vector_type(8)));
-    typedef d8 __attribute__((aligned(8))) d8u;
-    typedef const d8u __attribute__((address_space(1))) cd8u;
-    static_assert(EPT % 8 == 0, "rows per wave come in chunks of eight");
-    // the reflector entries have wave-uniform addresses: they travel through the scalar data path
-    const gdouble* __restrict__ T = (const gdouble*)blk->tmp;
-    const double* __restrict__ Z = blk->tmp + (size_t)k * k;
-    double* __restrict__ E = blk->Gacc;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int col = c0 + lane;
-    const bool colok = col < k;
-    const int i0 = wave * EPT;
-    __shared__ double s_dot[2][WAVES][64];
-    double x[EPT];
+    const int k = jb.k;
+    if (gc * 64 >= k) return;
+    typedef const double __attribute__((address_space(1))) cgdouble;
+    typedef double __attribute__((address_space(1))) gdouble;
+    cgdouble* T = (cgdouble*)jb.tmp;
+    cgdouble* Z = T + (size_t)k * k;
+    cgdouble* TF = (cgdouble*)jb.scratch;
+    gdouble* E = (gdouble*)jb.Gacc;
+    extern __shared__ double s_v[];                          // [16][PITCH]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
+    const int nt = (k + 15) / 16;
+    const int col = gc * 64 + wave * 16 + li;
+    d4 z[RT];
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-        const int i = i0 + e;
-        x[e] = (colok && i < k) ? Z[(size_t)min(i, k - 1) * k + min(col, k - 1)] : 0.0;
-    }
-    int par = 0;
-    for (int j = k - 3; j >= 0; --j) {
-        const double beta = T[(size_t)j * k + j];
-        if (beta == 0.0) continue;                          // uniform: no reflector at this step
-        const gdouble* __restrict__ vrow = T + (size_t)j * k;
-        const bool active = i0 + EPT > j + 1 && i0 < k;     // uniform over the wave
-        // eight reflector entries per fetch; chunks that end at or before j hold no entry of v.
-        // (A chunk may reach past column k-1: what it reads there is still inside tmp, which
-        // carries 64 doubles of padding for the smallest k, and is masked out.)
-        double part = 0.0;
-        if (active) {
+    for (int t = 0; t < RT; ++t)
 #pragma unroll
-            for (int c = 0; c < EPT / 8; ++c) {
-                const int ib = i0 + 8 * c;
-                if (ib > j && ib + 7 < k) {                 // whole chunk inside the reflector
-                    const d8u v8 = *(const cd8u*)(vrow + ib);
+        for (int v = 0; v < 4; ++v) {
+            const int i = 16 * t + 4 * v + lk;
+            z[t][v] = (i < k && col < k) ? Z[(size_t)min(i, k - 1) * k + min(col, k - 1)] : 0.0;
+        }
+    // block b of V: thread tid takes entry tid % 16 of every row tile of reflector tid / 16
+    double vr[PER], tf[4], tn[4];
+    auto fetch = [&](int b) {
+        const int j = 16 * b + (tid >> 4);
+        const bool valid = eig_has_reflector(j, k);
+        cgdouble* row = T + (size_t)min(j, k - 1) * k;
+        const bool live = valid && row[min(j, k - 1)] != 0.0;
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) part += v8[u] * x[8 * c + u];
-                } else if (ib + 7 > j && ib < k) {
-                    const d8u v8 = *(const cd8u*)(vrow + ib);
+        for (int t = 0; t < PER; ++t) {
+            const int i = 16 * t + (tid & 15);
+            if (t >= b) {                                    // uniform
+                const double x = row[min(i, k - 1)];
+                vr[t] = (live && i > j && i < k) ? x : 0.0;
+            }
+        }
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const double v = (ib + u > j && ib + u < k) ? v8[u] : 0.0;
-                        part += v * x[8 * c + u];
-                    }
+        for (int q = 0; q < 4; ++q) tn[q] = TF[(size_t)b * 256 + li * 16 + 4 * q + lk];
+    };
+    const int last = (k >= 3) ? (k - 3) / 16 : -1;
+    if (last >= 0) fetch(last);
+    for (int b = last; b >= 0; --b) {
+#pragma unroll
+        for (int t = 0; t < PER; ++t)
+            if (t >= b) s_v[(tid >> 4) * PITCH + 16 * t + (tid & 15)] = vr[t];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) tf[q] = tn[q];
+        eig_lds_barrier();
+        if (b > 0) fetch(b - 1);
+        // W = V^T Z, two tiles at a time
+        d4 w0 = {0.0, 0.0, 0.0, 0.0}, w1 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int t = 0; t < RT; t += 2) {
+            if (t + 1 >= b && t < nt) {
+                double a0[4], a1[4];
+                const bool two = t + 1 < RT;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    a0[q] = (t >= b) ? s_v[li * PITCH + 16 * t + 4 * q + lk] : 0.0;
+                    a1[q] = (two && t + 1 < nt) ? s_v[li * PITCH + 16 * (t + 1) + 4 * q + lk] : 0.0;
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    w0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[q], z[t][q], w0, 0, 0, 0);
+                    if (two) w1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[q], z[t + 1 < RT ? t + 1 : t][q], w1, 0, 0, 0);
                 }
             }
         }
-        s_dot[par][wave][lane] = part;
-        __syncthreads();
-        double tot = 0.0;
+        w0 += w1;
+        d4 sm = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) tot += s_dot[par][w][lane];
-        const double s = beta * tot;
-        if (active) {
+        for (int q = 0; q < 4; ++q) sm = __builtin_amdgcn_mfma_f64_16x16x4f64(tf[q], w0[q], sm, 0, 0, 0);
+        sm = -sm;
 #pragma unroll
-            for (int c = 0; c < EPT / 8; ++c) {
-                const int ib = i0 + 8 * c;
-                if (ib > j && ib + 7 < k) {
-                    const d8u v8 = *(const cd8u*)(vrow + ib);
+        for (int t = 0; t < RT; t += 2) {
+            if (t + 1 >= b && t < nt) {
+                double a0[4], a1[4];
+                const bool two = t + 1 < RT;
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) x[8 * c + u] -= s * v8[u];
-                } else if (ib + 7 > j && ib < k) {
-                    const d8u v8 = *(const cd8u*)(vrow + ib);
+                for (int q = 0; q < 4; ++q) {
+                    a0[q] = (t >= b) ? s_v[(4 * q + lk) * PITCH + 16 * t + li] : 0.0;
+                    a1[q] = (two && t + 1 < nt) ? s_v[(4 * q + lk) * PITCH + 16 * (t + 1) + li] : 0.0;
+                }
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const double v = (ib + u > j && ib + u < k) ? v8[u] : 0.0;
-                        x[8 * c + u] -= s * v;
-                    }
+                for (int q = 0; q < 4; ++q) {
+                    z[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[q], sm[q], z[t], 0, 0, 0);
+                    if (two) z[t + 1 < RT ? t + 1 : t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[q], sm[q], z[t + 1 < RT ? t + 1 : t], 0, 0, 0);
                 }
             }
         }
-        par ^= 1;
+        eig_lds_barrier();
     }
-    if (colok) {
+    if (col < k) {
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-            const int i = i0 + e;
-            if (i < k) E[(size_t)i * k + col] = x[e];
-        }
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = 16 * t + 4 * v + lk;
+                if (i < k) E[(size_t)col * k + i] = z[t][v];
+            }
     }
 }
 
+template <int RT>
+hipError_t launch_backtransform(const JacobiBlock* table_dev, const JacobiBlock& single, int blocks, int max_k, hipStream_t stream) {
+    constexpr int lds = 16 * ((16 * RT + 13) / 32 * 32 + 18) * 8;
+    static thread_local bool configured = false;
+    if (!configured && lds > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute((const void*)eig_backtransform_kernel<RT>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+    }
+    configured = true;
+    const EigGrid g{blocks, (max_k + 63) / 64, 0};
+    hipLaunchKernelGGL(eig_backtransform_kernel<RT>, eig_grid(g), dim3(256), lds, stream, table_dev, single, g);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------------ ordering and outputs
-// Rows of E^T R (second half of tmp) are mutually orthogonal with norms sigma_i.
-__global__ __launch_bounds__(EIG_THREADS) void eig_finish_kernel(const JacobiBlock* table, const JacobiBlock single) {
+// Rows of E^T R (second half of tmp) are mutually orthogonal with norms sigma_i: the norms go behind the
+// eigenvalues' place, one wave per row ...
+__global__ __launch_bounds__(256) void eig_norms_kernel(const JacobiBlock* table, const JacobiBlock single, const EigGrid grid) {
     JacobiBlock jb = single;
-    if (table) jb = table[blockIdx.x];
-    const JacobiBlock* blk = &jb;
-    const int k = blk->k, r = blk->r;
-    const double* __restrict__ ER = blk->tmp + (size_t)k * k;
-    const double* __restrict__ E = blk->Gacc;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const int lane = tid & 63, wave = tid >> 6, nw = nt >> 6;
-    __shared__ double s_sig[EIG_MAXK];
-    __shared__ int s_rank[EIG_MAXK];
-    for (int j = wave; j < k; j += nw) {
-        double a = 0.0;
-        for (int c = lane; c < k; c += 64) { const double v = ER[(size_t)j * k + c]; a += v * v; }
-        a = eig_wave_sum(a);
-        if (lane == 0) s_sig[j] = sqrt(a);
+    int gb, gc;
+    if (!eig_decode(grid, gb, gc)) return;
+    if (table) jb = table[gb];
+    const int k = jb.k;
+    const int lane = threadIdx.x & 63, j = gc * 4 + (threadIdx.x >> 6);
+    if (j >= k) return;
+    typedef const double __attribute__((address_space(1))) cgdouble;
+    cgdouble* row = (cgdouble*)jb.tmp + (size_t)k * k + (size_t)j * k;
+    double a = 0.0;
+    for (int c = lane; c < k; c += 64) a = fma(row[c], row[c], a);
+    a = eig_wave_sum_dpp(a);
+    if (lane == 0) jb.scratch[(size_t)3 * k * k + j] = sqrt(a);      // (the tridiagonal matrix is not needed any more)
+}
+
+// ... and every wave then finds the place of its row among them and writes the row's outputs.
+__global__ __launch_bounds__(256) void eig_finish_kernel(const JacobiBlock* table, const JacobiBlock single, const EigGrid grid) {
+    JacobiBlock jb = single;
+    int gb, gc;
+    if (!eig_decode(grid, gb, gc)) return;
+    if (table) jb = table[gb];
+    const int k = jb.k, r = jb.r;
+    const int lane = threadIdx.x & 63, j = gc * 4 + (threadIdx.x >> 6);
+    if (j >= k) return;
+    typedef const double __attribute__((address_space(1))) cgdouble;
+    typedef float __attribute__((address_space(1))) gfloat;
+    cgdouble* ER = (cgdouble*)jb.tmp + (size_t)k * k + (size_t)j * k;
+    cgdouble* E = (cgdouble*)jb.Gacc + (size_t)j * k;
+    cgdouble* sig = (cgdouble*)jb.scratch + (size_t)3 * k * k;
+    const double sj = sig[j];
+    int rank = 0;                                            // descending, ties by index
+    for (int i = lane; i < k; i += 64) {
+        const double si = sig[i];
+        rank += (si > sj || (si == sj && i < j)) ? 1 : 0;
     }
-    __syncthreads();
-    for (int j = tid; j < k; j += nt) {
-        const double sj = s_sig[j];
-        int rank = 0;
-        for (int i = 0; i < k; ++i) {
-            const double si = s_sig[i];
-            rank += (si > sj || (si == sj && i < j)) ? 1 : 0;
-        }
-        s_rank[j] = rank;
-        if (blk->sigma) blk->sigma[rank] = (float)sj;
-    }
-    __syncthreads();
-    for (int j = wave; j < k; j += nw) {
-        const int rank = s_rank[j];
-        if (rank >= r) continue;
-        const double sj = s_sig[j];
-        const double inv = (sj > 0.0) ? 1.0 / sj : 0.0;
-        for (int c = lane; c < k; c += 64) {
-            blk->XrT[(size_t)rank * k + c] = (float)(ER[(size_t)j * k + c] * inv);
-            blk->GrT[(size_t)rank * k + c] = (float)E[(size_t)c * k + j];
-        }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) rank += __shfl_xor(rank, o, 64);
+    if (lane == 0 && jb.sigma) jb.sigma[rank] = (float)sj;
+    if (rank >= r) return;
+    const double inv = (sj > 0.0) ? 1.0 / sj : 0.0;
+    gfloat* xr = (gfloat*)jb.XrT + (size_t)rank * k;
+    gfloat* gr = (gfloat*)jb.GrT + (size_t)rank * k;
+    for (int c = lane; c < k; c += 64) {
+        xr[c] = (float)(ER[c] * inv);
+        gr[c] = (float)E[c];
     }
 }
 
@@ -1040,7 +1192,6 @@ hipError_t launch_eig_svd(const JacobiBlock* table_dev, const JacobiBlock* singl
     if (single) sb = *single;
     const int tiles = (max_k + 63) / 64;
     const EigGrid gt{blocks, tiles * tiles, 0};
-    const EigGrid gv{blocks, (max_k + EIG_VAL_PER_WG - 1) / EIG_VAL_PER_WG, 0};
     const EigGrid gi{blocks, (max_k + 63) / 64, 1};      // measured: pinned 0.70 ms, chunk-major 0.74 (84 blocks, k = 264)
     hipLaunchKernelGGL(eig_gemm_kernel<0>, eig_grid(gt), dim3(256), 0, stream, table_dev, sb, gt);
     // tile rows of the register kernel by the largest matrix of the launch
@@ -1049,18 +1200,26 @@ hipError_t launch_eig_svd(const JacobiBlock* table_dev, const JacobiBlock* singl
     else if (max_k <= 5 * TT) hipLaunchKernelGGL((eig_tridiag_tiles_kernel<5, 8>), dim3(blocks), dim3(512), 0, stream, table_dev, sb);
     else if (max_k <= 7 * TT) hipLaunchKernelGGL((eig_tridiag_tiles_kernel<7, 8>), dim3(blocks), dim3(512), 0, stream, table_dev, sb);
     else hipLaunchKernelGGL((eig_tridiag_tiles_kernel<9, 8>), dim3(blocks), dim3(512), 0, stream, table_dev, sb);
-    hipLaunchKernelGGL(eig_values_kernel, eig_grid(gv), dim3(256), 0, stream, table_dev, sb, gv);
+    // threads per eigenvalue: up to a wave, as long as the launch stays within two waves per SIMD
+    int lp = 6;
+    while (lp > 3 && ((long long)blocks * max_k << lp) > 2LL * 1024 * 64) --lp;
+    const EigGrid gv{blocks, ((max_k << lp) + 255) / 256, 0};
+    if (lp == 6) hipLaunchKernelGGL(eig_values_kernel<6>, eig_grid(gv), dim3(256), 0, stream, table_dev, sb, gv);
+    else if (lp == 5) hipLaunchKernelGGL(eig_values_kernel<5>, eig_grid(gv), dim3(256), 0, stream, table_dev, sb, gv);
+    else if (lp == 4) hipLaunchKernelGGL(eig_values_kernel<4>, eig_grid(gv), dim3(256), 0, stream, table_dev, sb, gv);
+    else hipLaunchKernelGGL(eig_values_kernel<3>, eig_grid(gv), dim3(256), 0, stream, table_dev, sb, gv);
     hipLaunchKernelGGL(eig_invit_kernel, eig_grid(gi), dim3(64), 0, stream, table_dev, sb, gi);
     hipLaunchKernelGGL(eig_groups_kernel, dim3(blocks), dim3(EIG_THREADS), 0, stream, table_dev, sb);
-    const EigGrid gbt{blocks, tiles, 0};
-    const dim3 bt_grid = eig_grid(gbt);
-    if (max_k <= 32) hipLaunchKernelGGL((eig_backtransform_kernel<8, 4>), bt_grid, dim3(256), 0, stream, table_dev, sb, gbt);
-    else if (max_k <= 96) hipLaunchKernelGGL((eig_backtransform_kernel<24, 4>), bt_grid, dim3(256), 0, stream, table_dev, sb, gbt);
-    else if (max_k <= 160) hipLaunchKernelGGL((eig_backtransform_kernel<40, 4>), bt_grid, dim3(256), 0, stream, table_dev, sb, gbt);
-    else if (max_k <= 320) hipLaunchKernelGGL((eig_backtransform_kernel<40, 8>), bt_grid, dim3(512), 0, stream, table_dev, sb, gbt);
-    else hipLaunchKernelGGL((eig_backtransform_kernel<40, 16>), bt_grid, dim3(1024), 0, stream, table_dev, sb, gbt);
+    const EigGrid gwy{blocks, (max_k + 15) / 16, 0}, gr{blocks, (max_k + 3) / 4, 0};
+    hipLaunchKernelGGL(eig_wy_kernel, eig_grid(gwy), dim3(64), 0, stream, table_dev, sb, gwy);
+    const hipError_t bt = (max_k <= 80) ? launch_backtransform<5>(table_dev, sb, blocks, max_k, stream)
+                          : (max_k <= 144) ? launch_backtransform<9>(table_dev, sb, blocks, max_k, stream)
+                          : (max_k <= 288) ? launch_backtransform<18>(table_dev, sb, blocks, max_k, stream)
+                                           : launch_backtransform<34>(table_dev, sb, blocks, max_k, stream);
+    if (bt != hipSuccess) return bt;
     hipLaunchKernelGGL(eig_gemm_kernel<1>, eig_grid(gt), dim3(256), 0, stream, table_dev, sb, gt);
-    hipLaunchKernelGGL(eig_finish_kernel, dim3(blocks), dim3(EIG_THREADS), 0, stream, table_dev, sb);
+    hipLaunchKernelGGL(eig_norms_kernel, eig_grid(gr), dim3(256), 0, stream, table_dev, sb, gr);
+    hipLaunchKernelGGL(eig_finish_kernel, eig_grid(gr), dim3(256), 0, stream, table_dev, sb, gr);
     return hipGetLastError();
 }
 
