@@ -14,8 +14,8 @@
 // (eight lanes along k, eight along the rows) whose transposing LDS stores touch every bank once: with
 // the lanes along the rows the stores met in two banks and took sixteen passes.  Measured (before, with one
 // stage, per-element guards and element-by-element read-modify-write -> now): the step of one 512 x 1376
-// fp32 matrix at rank 64, 104 -> 39 us; of the 60M model in fp32 at rank 256, 643 -> 304 us; of a
-// 32000 x 2048 embedding and LM head at rank 128, 1060 -> 551 us.
+// fp32 matrix at rank 64, 104 -> 39 us; of the 60M model in fp32 at rank 256, 643 -> 304 us (292 with the
+// early read of W, see the kernel); of a 32000 x 2048 embedding and LM head at rank 128, 1060 -> 551 us (511).
 #include "gemm.h"
 
 #include <type_traits>
@@ -57,14 +57,15 @@ template <bool KS, bool BF16, int ROWS> struct Operand {
     typedef typename std::conditional<BF16, typename std::conditional<KS, u32x2, u32x4>::type, f32x4>::type Reg;
 
     gcptr base;            // first element of the k range; k-contiguous: of the tile's first row
-    unsigned ldb;          // row pitch, bytes
+    long long pitch;       // row pitch, bytes
+    unsigned ldb;          // the same for the vector loads
     int klen;              // k range
     int rows, row0;        // rows of the operand, first row of the tile
     int kl, rl;            // this thread's lane along k, and along the rows
     unsigned roff[KS ? 1 : NCH];
 
     __device__ inline void init(const void* p, long long ld, int rows_, int row0_, int kbeg, int klen_, int tid) {
-        ldb = (unsigned)ld * ESZ; klen = klen_; rows = rows_; row0 = row0_;
+        pitch = ld * ESZ; ldb = (unsigned)pitch; klen = klen_; rows = rows_; row0 = row0_;
         kl = tid % KL; rl = tid / KL;
         if constexpr (KS) {
             base = (gcptr)p + (long long)kbeg * ld * ESZ;
@@ -75,8 +76,9 @@ template <bool KS, bool BF16, int ROWS> struct Operand {
             for (int it = 0; it < NCH; ++it) roff[it] = (unsigned)min(rl + it * (NTHREADS / KL), rows - 1 - row0) * ldb;
         }
     }
-    // smallest extents the vector loads work on
-    __device__ inline bool vector_ok() const { return KS ? rows >= 4 : klen >= KPT; }
+    // smallest extents the vector loads work on, and the largest pitch for which their 32-bit offsets hold
+    // (up to 127 rows and a place within a row)
+    __device__ inline bool vector_ok() const { return (KS ? rows >= 4 : klen >= KPT) && pitch <= (1 << 24); }
 
     __device__ inline void load(Reg (&v)[NCH], int t) const {
         if constexpr (KS) {
@@ -103,8 +105,8 @@ template <bool KS, bool BF16, int ROWS> struct Operand {
             r = min(r, rows - 1);
             const bool ok = k < klen;
             k = min(k, klen - 1);
-            const gcptr p = KS ? base + (long long)k * ldb + (long long)r * ESZ
-                               : base + (long long)(r - row0) * ldb + (long long)k * ESZ;
+            const gcptr p = KS ? base + k * pitch + (long long)r * ESZ
+                               : base + (r - row0) * pitch + (long long)k * ESZ;
             const float x = BF16 ? __uint_as_float((unsigned)*(const TSR_GLOBAL unsigned short*)p << 16) : *(const TSR_GLOBAL float*)p;
             return ok ? x : 0.0f;
         };
@@ -228,6 +230,11 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_kernel(const GemmLaunch L) {
     constexpr int A_ELEMS = NSA * OpA::TILE, BUF = A_ELEMS + NSB * OpB::TILE;
     constexpr int NBUF = (BUF * 4 <= 80 * 1024) ? 2 : 1;       // two workgroups per compute unit either way
     constexpr int FM = TM / 64, FN = TN / 64;
+    // The weight update (both operands k-contiguous) is bound by W's traffic at a short contraction: W's tile
+    // is fetched behind the first two k-tiles, so that it travels while they are multiplied.  Fetched after the
+    // last k-tile -> here: step of a 32000 x 2048 embedding and LM head (rank 128) 557 -> 511 us, of the 60M
+    // model in fp32 (rank 256) 310 -> 292 us.  Three pieces leave no registers for it (and nothing uses it there).
+    constexpr bool EARLY = !A_KS && !B_KS && NSA <= 2 && NSB <= 2;
     __shared__ __attribute__((aligned(16))) unsigned short lds[NBUF * BUF];
 
     const int tid = threadIdx.x;
@@ -274,7 +281,22 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_kernel(const GemmLaunch L) {
     a.init(pp->A, pp->lda, M, row0, kbeg, klen, tid);
     b.init(pp->B, pp->ldb, N, col0, kbeg, klen, tid);
     const int nt = (klen + BK - 1) / BK;
+    const bool early_done = EARLY && nt > 0 && a.vector_ok() && b.vector_ok();
     const bool edge_a = row0 + TM > M, edge_b = col0 + TN > N;
+
+    // Where this lane's accumulators go: column (lane & 31), rows 8*(e/4) + 4*(lane>>5) + e%4 of each 32x32 tile.
+    const int rbase = row0 + wm * (TM / 2) + (lane >> 5) * 4, cbase = col0 + wn * (TN / 2) + (lane & 31);
+    f32x16 old[FM][FN];
+    auto load_old = [&] {          // edges by clamped addresses
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const TSR_GLOBAL float* c = C + (long long)min(rbase + i * 32 + (e >> 2) * 8 + (e & 3), M - 1) * ldc;
+#pragma unroll
+                for (int j = 0; j < FN; ++j) old[i][j][e] = c[min(cbase + j * 32, N - 1)];
+            }
+    };
 
     typename OpA::Reg sa[2][OpA::NCH];
     typename OpB::Reg sb[2][OpB::NCH];
@@ -330,6 +352,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_kernel(const GemmLaunch L) {
         if (a.vector_ok() && b.vector_ok()) {
             a.load(sa[0], 0); b.load(sb[0], 0);
             if (nt > 1) { a.load(sa[1], 1); b.load(sb[1], 1); }
+            if constexpr (EARLY) { if (beta != 0.0f) load_old(); }
             int t = 0;
             for (; t + 3 < nt; t += 2) {
                 step(S0{}, std::true_type{}, t);
@@ -355,34 +378,23 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_kernel(const GemmLaunch L) {
         }
     }
 
-    // epilogue: lane holds column (lane & 31), rows 8*(e/4) + 4*(lane>>5) + e%4 of each 32x32 tile.
-    // With beta the whole tile is read before the first element is written (one trip to memory).
-    TSR_GLOBAL float* cp[FN];
-    bool cok[FN];
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-        const int col = col0 + wn * (TN / 2) + j * 32 + (lane & 31);
-        cok[j] = col < N;
-        cp[j] = C + col;
-    }
-    const int rbase = row0 + wm * (TM / 2) + (lane >> 5) * 4;
-    auto each = [&](auto&& f) {
+    // epilogue; with beta the whole tile is read before the first element is written (one trip to memory)
+    auto write = [&](auto&& value) {
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int j = 0; j < FN; ++j)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    const int row = rbase + i * 32 + (e >> 2) * 8 + (e & 3);
-                    if (row < M && cok[j]) f(cp[j] + (long long)row * ldc, acc[i][j][e], i, j, e);
+                    const int row = rbase + i * 32 + (e >> 2) * 8 + (e & 3), col = cbase + j * 32;
+                    if (row < M && col < N) C[(long long)row * ldc + col] = value(i, j, e);
                 }
     };
     if (beta != 0.0f) {
-        f32x16 old[FM][FN];
-        each([&](const TSR_GLOBAL float* c, float, int i, int j, int e) { old[i][j][e] = *c; });
-        each([&](TSR_GLOBAL float* c, float v, int i, int j, int e) { *c = alpha * v + beta * old[i][j][e]; });
+        if (!EARLY || !early_done) load_old();
+        write([&](int i, int j, int e) { return alpha * acc[i][j][e] + beta * old[i][j][e]; });
     } else {
-        each([&](TSR_GLOBAL float* c, float v, int, int, int) { *c = alpha * v; });
+        write([&](int i, int j, int e) { return alpha * acc[i][j][e]; });
     }
 }
 
