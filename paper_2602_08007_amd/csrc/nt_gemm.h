@@ -90,12 +90,17 @@ struct ShadowBlock {
 // Projection P^T = V^T G^T for one 128- or 64-row panel of a bf16 gradient per workgroup (r = 128
 // or 256): the panel's accumulators (r x 128) stay in registers over the whole contraction, G goes
 // through LDS, V^T comes straight from its fragment-order copy.  G == nullptr: idle workgroup.
+// With workers > 1 the panel is the sum over that many gradients, g_stride bytes apart; PT_low, where
+// given, receives what the rounding of P^T to bf16 leaves (rounded to bf16 itself).
 struct ProjItem {
     const void* G;       // bf16 m x n, leading dimension ldg (16-byte aligned rows, n % 8 == 0)
     const void* VTf;     // ShadowBlock::XTFb of V
     void* PT;            // bf16 r x m, leading dimension ldp
     long long ldg, ldp;
     int m, n, row0;
+    int workers = 1;
+    long long g_stride = 0;
+    void* PT_low = nullptr;
 };
 bool proj_supports_rank(int r);
 // depth: gradient tiles in flight per workgroup: 2 (two workgroups per compute unit) or 4 (one)

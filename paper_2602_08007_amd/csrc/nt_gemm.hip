@@ -951,7 +951,9 @@ __device__ __forceinline__ void proj_panel(const ProjItem& it, unsigned short* l
     const int l32 = lane & 31, h = lane >> 5;
     const int m = it.m, n = it.n, row0 = it.row0;
     const int nsteps = (n + 15) / 16, nk = (n + BK - 1) / BK;
-    const nt_rsrc_t rG = nt_make_rsrc(it.G, ((long long)(m - 1) * it.ldg + ((n + 7) & ~7)) * 2);
+    const long long g_bytes = ((long long)(m - 1) * it.ldg + ((n + 7) & ~7)) * 2;
+    const int total = nk * it.workers;                       // the workers' contractions, one behind the other
+    nt_rsrc_t rG = nt_make_rsrc(it.G, g_bytes);
     const nt_rsrc_t rV = nt_make_rsrc(it.VTf, (long long)RG * nsteps * 1024);
     const unsigned ldg_b = (unsigned)it.ldg * 2u;
 
@@ -964,7 +966,12 @@ __device__ __forceinline__ void proj_panel(const ProjItem& it, unsigned short* l
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
     u32x4 af[DEPTH][FM][BK / 16];                            // V^T fragments of DEPTH k-tiles
-    auto load_a = [&](int slot, int kt) {
+    // loads and stores each walk the k-tiles in order: their places within a worker's contraction
+    int ka = 0, kg = 0, ks = 0;
+    const char* g_at = (const char*)it.G;
+    auto load_a = [&](int slot) {
+        const int kt = ka;
+        ka = (ka + 1 == nk) ? 0 : ka + 1;
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -975,13 +982,18 @@ __device__ __forceinline__ void proj_panel(const ProjItem& it, unsigned short* l
             }
     };
     NtStage<TN * BK / 8 / NT_THREADS, false> st[DEPTH];
-    auto load_g = [&](int slot, int kt) {
-        const int k0 = kt * BK;
-        nt_load<TN, BK, false>(st[slot], rG, ldg_b, row0, k0, true, tid);
+    auto load_g = [&](int slot) {
+        nt_load<TN, BK, false>(st[slot], rG, ldg_b, row0, kg * BK, true, tid);
+        if (++kg == nk) {                                    // on to the next worker's gradient
+            kg = 0;
+            g_at += it.g_stride;
+            rG = nt_make_rsrc(g_at, g_bytes);
+        }
     };
     const int k_in_tile = (tid % (BK / 8)) * 8;
-    auto store_g = [&](int slot, int buf, int kt) {         // kt: the k-tile held by that stage
-        const int k0 = kt * BK;
+    auto store_g = [&](int slot, int buf) {
+        const int k0 = ks * BK;
+        ks = (ks + 1 == nk) ? 0 : ks + 1;
         nt_store<TN, BK, false>(st[slot], lds + buf * (TN * KP), tid, n - (k0 + k_in_tile), k0 + BK > n);
     };
     auto compute = [&](int buf, int slot) {
@@ -1007,26 +1019,28 @@ __device__ __forceinline__ void proj_panel(const ProjItem& it, unsigned short* l
     // and stages are refilled in place, DEPTH k-tiles ahead
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d)
-        if (d < nk) { load_g(d, d); load_a(d, d); }
-    store_g(0, 0, 0);
+        if (d < total) { load_g(d); load_a(d); }
+    store_g(0, 0);
     __syncthreads();
-    if (DEPTH < nk) load_g(0, DEPTH);
-    for (int kt = 0; kt < nk; kt += DEPTH) {
+    if (DEPTH < total) load_g(0);
+    for (int kt = 0; kt < total; kt += DEPTH) {
 #pragma unroll
         for (int u = 0; u < DEPTH; ++u) {
             const int t = kt + u;                            // uniform; the whole group leaves together
-            if (t < nk) {
+            if (t < total) {
                 compute(u & 1, u);
-                if (t + DEPTH < nk) load_a(u, t + DEPTH);
-                if (t + 1 < nk) store_g((u + 1) % DEPTH, (u + 1) & 1, t + 1);
+                if (t + DEPTH < total) load_a(u);
+                if (t + 1 < total) store_g((u + 1) % DEPTH, (u + 1) & 1);
                 __syncthreads();
-                if (t + 1 + DEPTH < nk) load_g((u + 1) % DEPTH, t + 1 + DEPTH);
+                if (t + 1 + DEPTH < total) load_g((u + 1) % DEPTH);
             }
         }
     }
 
     // P^T[ri][row]: lane holds gradient row (lane & 31) of each 32-row group, registers run over ri
-    const nt_rsrc_t rP = nt_make_rsrc(it.PT, ((long long)(RG * 32 - 1) * it.ldp + m) * 2);
+    const long long p_bytes = ((long long)(RG * 32 - 1) * it.ldp + m) * 2;
+    const nt_rsrc_t rP = nt_make_rsrc(it.PT, p_bytes);
+    const nt_rsrc_t rL = nt_make_rsrc(it.PT_low ? it.PT_low : it.PT, p_bytes);
     const unsigned ldp_b = (unsigned)it.ldp * 2u;
 #pragma unroll
     for (int i = 0; i < FM; ++i)
@@ -1037,7 +1051,13 @@ __device__ __forceinline__ void proj_panel(const ProjItem& it, unsigned short* l
             for (int e = 0; e < 16; ++e) {
                 const int ri = (wave * FM + i) * 32 + (e >> 2) * 8 + 4 * h + (e & 3);
                 const unsigned vo = (row < m) ? (unsigned)ri * ldp_b + (unsigned)row * 2u : 0x80000000u;
-                __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16_bits(acc[i][j][e]), rP, (int)vo, 0, 0);
+                const unsigned short hi = f32_to_bf16_bits(acc[i][j][e]);
+                __builtin_amdgcn_raw_buffer_store_b16(hi, rP, (int)vo, 0, 0);
+                if (it.PT_low) {
+                    const float hf = __uint_as_float((unsigned)hi << 16);
+                    const float low = (fabsf(hf) < INFINITY) ? acc[i][j][e] - hf : 0.0f;      // an infinity stays one
+                    __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16_bits(low), rL, (int)vo, 0, 0);
+                }
             }
         }
 }

@@ -84,3 +84,26 @@ def test_refresh_full_sketch_sizes(tsr, k):
         assert float(torch.linalg.norm(X.T @ X - eye)) < 2.0 ** -20 * k
     core = U64.T @ G.double() @ V64
     assert float(torch.linalg.norm(core - torch.diag(s[:r])) / torch.linalg.norm(s)) < 2e-5
+
+
+# panels of 128 rows: 343 and 344 (three groups of workers), 1025 (one), 8 (every worker by itself)
+@pytest.mark.parametrize("m,n,r,workers,summed", [(43801, 136, 128, 8, True), (44000, 131, 128, 7, True),
+                                                  (131077, 257, 256, 4, True), (1000, 136, 128, 8, False)])
+def test_projection_sums_workers(tsr, m, n, r, workers, summed):
+    """The mean core against the fp64 product of the summed gradients with the bases as the path holds them
+    (bf16).  Where the workers are summed before U^T, the sum is kept to two bf16 pieces: the tolerance of the
+    split products; else every worker's P is rounded once."""
+    gen = torch.Generator(device="cuda").manual_seed(7 * m + workers)
+    randn = lambda *s: torch.randn(*s, device="cuda", generator=gen)  # noqa: E731
+    ld = (n + 7) // 8 * 8
+    G = torch.full((workers, m, ld), float("nan"), dtype=torch.bfloat16, device="cuda")
+    G[:, :, :n] = randn(workers, m, n)
+    U, V = torch.linalg.qr(randn(m, r))[0].contiguous(), torch.linalg.qr(randn(n, r))[0].contiguous()
+    z = lambda *s: torch.zeros(*s, device="cuda")  # noqa: E731
+    b = dict(G=G[:, :, :n], W=z(m, n), U=U, V=V, M=z(r, r), Vm=z(r, r), C=z(r, r), D=z(r, r))
+    plan = tsr.Plan([b], n_workers=workers, precision=tsr.TSR_PREC_BF16)
+    for _ in range(2):
+        plan.tsr_step_batched(1, lr=0.0)
+    total = sum(G[w, :, :n].double() for w in range(workers)) / workers
+    ref = U.bfloat16().double().T @ (total @ V.bfloat16().double())
+    check_close(b["C"].cpu(), ref.cpu().numpy(), TOL["split"] if summed else TOL["bf16"], "core")
