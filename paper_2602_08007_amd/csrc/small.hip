@@ -293,313 +293,10 @@ __global__ __launch_bounds__(SMALL_THREADS) void chol_inv_kernel(const CholBlock
     }
 }
 
-// Blocked variant for k <= CHB_MAXK, three launches.  First (this kernel, one workgroup per
-// matrix): 32-wide block columns; per block column the diagonal block is factored and inverted
-// in LDS, the panel below it is multiplied by that inverse and kept in LDS, and the trailing
-// matrix gets its rank-32 update from the LDS panel (fp64 MFMAs), so the fp64 matrix in global
-// memory is read and written once per block column instead of once per column.  It leaves L in
-// the lower triangle of `work` and the inverted diagonal blocks in the second k x k of `work`;
-// chol_inverse_kernel then forms the blocks of L^-1 below the diagonal and chol_output_kernel
-// writes R^-1 (fp32) and R.
 __device__ inline double readlane_f64(double v, int lane) {      // lane: a compile-time constant
     const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
     const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
     return __hiloint2double(hi, lo);
-}
-
-constexpr int CHB = 32;
-constexpr int CHB_P = CHB + 1;
-constexpr int CHB_MAXK = 544;
-
-__global__ __launch_bounds__(SMALL_THREADS) void chol_inv_blocked_kernel(const CholBlock* table, const CholBlock single,
-                                                                         const double tol, const double shift_rel) {
-    const CholBlock* blk = table ? table + blockIdx.x : &single;
-    const int k = blk->k;
-    const float* S = blk->S;
-    double* A = blk->work;                     // lower triangle becomes L, S = L L^T
-    double* X = blk->work + (size_t)k * k;     // X = L^-1 (lower)
-    const int tid = threadIdx.x;
-    const int ti = tid >> 5, tc = tid & 31;    // 32 x 32 thread grid
-    typedef double d4_t __attribute__((ext_vector_type(4)));
-    const int wv = tid >> 6, li16 = tid & 15, lk4 = (tid & 63) >> 4;      // wave; MFMA lane coordinates
-    __shared__ double Ld[CHB][CHB_P];
-    __shared__ double Li[CHB][CHB_P];
-    __shared__ double s_invd[CHB];             // reciprocal diagonal of the current diagonal block
-    extern __shared__ double Pn[];             // [block rows * CHB][CHB_P]
-
-    // (X is written where it is read: diagonal blocks whole, the blocks below them in the inverse phase)
-    const double shift = diagonal_shift(S, k, shift_rel);
-    for (int idx = tid; idx < k * k; idx += SMALL_THREADS) A[idx] = (double)S[idx] + ((idx / k == idx % k) ? shift : 0.0);
-    __syncthreads();
-
-    for (int J = 0; J < k; J += CHB) {
-        const int jb = min(CHB, k - J);
-        // ---- diagonal block -> LDS (identity padding), unblocked factorization
-        Ld[ti][tc] = (ti < jb && tc < jb) ? ((tc <= ti) ? A[(size_t)(J + ti) * k + J + tc] : 0.0) : (ti == tc ? 1.0 : 0.0);
-        __syncthreads();
-        // One wave factors the 32 x 32 block, right-looking: lane i owns row i in registers; at
-        // step j the pivot is read from lane j, and every lane updates the rest of its row with
-        // the entries of column j read from their lanes (independent multiply-adds, no serial
-        // chain beyond the pivot's reciprocal square root).
-        if (tid < 64) {
-            const int i = tid & 31;
-            const bool act = tid < CHB;
-            double arow[CHB];
-#pragma unroll
-            for (int c = 0; c < CHB; ++c) arow[c] = Ld[i][c];
-            const double sdiag = (i < jb) ? (double)S[(size_t)(J + i) * k + J + i] : 1.0;
-#pragma unroll
-            for (int j = 0; j < CHB; ++j) {
-                const double piv = readlane_f64(arow[j], j);
-                const double s0 = readlane_f64(sdiag, j);
-                const bool ok = (piv > 0.0) && (piv > tol * s0);
-                const double pp = ok ? piv : 1.0;
-                double rinv = __builtin_amdgcn_rsq(pp);
-                const double hh = 0.5 * pp;
-                rinv = rinv * (1.5 - hh * rinv * rinv);
-                rinv = rinv * (1.5 - hh * rinv * rinv);
-                const double invd = ok ? rinv : 0.0;
-                const double lij = (i > j) ? arow[j] * invd : ((i == j) ? pp * invd : 0.0);
-                arow[j] = lij;
-                if (act) { if (i >= j) Ld[i][j] = lij; if (i == j) s_invd[j] = invd; }
-#pragma unroll
-                for (int c = j + 1; c < CHB; ++c) arow[c] -= lij * readlane_f64(lij, c);
-            }
-        }
-        __syncthreads();
-        // ---- inverse of the diagonal block (dropped pivots: zero row and column), by halves:
-        // the four 8 x 8 diagonal sub-blocks by forward substitution (a column per lane), then the
-        // blocks below them from  X21 = -X22 (L21 X11)  at sizes 8 and 16, every entry of a product
-        // on its own thread; the panel buffer (free at this point) holds the inner products.
-        Li[ti][tc] = 0.0;
-        __syncthreads();
-        if (tid < CHB) {
-            const int d0 = tid & ~7, c = tid & 7;             // sub-block origin, column inside it
-            double xc[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                double sa = (i == c) ? 1.0 : 0.0;
-#pragma unroll
-                for (int j = 0; j < i; ++j) sa -= Ld[d0 + i][d0 + j] * xc[j];
-                xc[i] = sa * s_invd[d0 + i];
-                Li[d0 + i][d0 + c] = xc[i];
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int half = 8; half <= 16; half *= 2) {
-            // pairs of neighbouring diagonal blocks of size `half`: rows r0 + half .., columns r0 ..
-            const int npair = CHB / (2 * half);
-            const int per = half * half;
-            const bool mine = tid < npair * per;
-            const int pr = tid / per, e = tid % per;
-            const int i = e / half, c = e % half;
-            const int o = pr * 2 * half;                      // origin of the pair
-            if (mine) {
-                double m = 0.0;                               // (L21 X11)[i][c]
-                for (int j = c; j < half; ++j) m += Ld[o + half + i][o + j] * Li[o + j][o + c];
-                Pn[(o + half + i) * CHB_P + o + c] = m;
-            }
-            __syncthreads();
-            if (mine) {
-                double x = 0.0;                               // (X22 M)[i][c]
-                for (int j = 0; j <= i; ++j) x += Li[o + half + i][o + half + j] * Pn[(o + half + j) * CHB_P + o + c];
-                Li[o + half + i][o + c] = -x;
-            }
-            __syncthreads();
-        }
-        if (ti < jb && tc < jb) {
-            A[(size_t)(J + ti) * k + J + tc] = (tc <= ti) ? Ld[ti][tc] : 0.0;
-            X[(size_t)(J + ti) * k + J + tc] = (tc <= ti) ? Li[ti][tc] : 0.0;
-        }
-        // ---- panel: rows below, P = A[rows, J..J+jb) Li^T, on fp64 MFMAs (lane l supplies
-        // A[l % 16][l / 16] and B[l / 16][l % 16], receives D[4 v + l / 16][l % 16]): 16-row
-        // tiles dealt to the waves, the rows of A straight from global memory, Li^T from LDS.
-        // P goes back to A and stays in the panel buffer (rows past the matrix: zeros).
-        const int r0 = J + jb;
-        const int nr = k - r0;
-        const int nrt = (nr + 15) >> 4;
-        for (int t = wv; t < nrt; t += SMALL_THREADS / 64) {       // one wave reads and rewrites its 16 rows
-            const int i0 = t * 16;
-            const int row = i0 + li16;
-            const double* arow_g = A + (size_t)(r0 + min(row, nr - 1)) * k + J;
-            d4_t acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
-            double a[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int c = 4 * q + lk4;
-                a[q] = (row < nr && c < jb) ? arow_g[min(c, jb - 1)] : 0.0;
-            }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], Li[li16][4 * q + lk4], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], Li[16 + li16][4 * q + lk4], acc1, 0, 0, 0);
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int i = i0 + 4 * v + lk4;
-                Pn[i * CHB_P + li16] = acc0[v];
-                Pn[i * CHB_P + 16 + li16] = acc1[v];
-                if (i < nr && li16 < jb) A[(size_t)(r0 + i) * k + J + li16] = acc0[v];
-                if (i < nr && 16 + li16 < jb) A[(size_t)(r0 + i) * k + J + 16 + li16] = acc1[v];
-            }
-        }
-        __syncthreads();
-        // ---- trailing update, lower triangle by 16 x 16 tiles: A[i][c] -= sum_j P[i][j] P[c][j]
-        {
-            const int ntile = nrt * (nrt + 1) / 2;
-            for (int q = wv; q < ntile; q += SMALL_THREADS / 64) {
-                int tr = (int)((sqrtf(8.0f * (float)q + 1.0f) - 1.0f) * 0.5f);
-                while ((tr + 1) * (tr + 2) / 2 <= q) ++tr;
-                while (tr * (tr + 1) / 2 > q) --tr;
-                const int tcx = q - tr * (tr + 1) / 2;
-                const int i0 = tr * 16, c0 = tcx * 16;
-                const double* pa = Pn + (size_t)(i0 + li16) * CHB_P + lk4;
-                const double* pb = Pn + (size_t)(c0 + li16) * CHB_P + lk4;
-                d4_t acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(pa[4 * u], pb[4 * u], acc, 0, 0, 0);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int i = i0 + 4 * v + lk4, c = c0 + li16;
-                    if (i < nr && c <= i) A[(size_t)(r0 + i) * k + r0 + c] -= acc[v];
-                }
-            }
-        }
-        __syncthreads();
-    }
-}
-
-// Second launch of the blocked variant: the blocks of X = L^-1 below the diagonal, block column by
-// block column (forward substitution with 32 right-hand sides):
-//     X[I][J] = -Li_I * sum_{K=J}^{I-1} L[I][K] X[K][J].
-// Block columns are independent; CHOL_INV_SPLIT workgroups per matrix share them (column J costs
-// about nblk - 1 - J block rows, so they are dealt from both ends).  The block column of X stays
-// in LDS (block K - J at rows (K - J) * 32); the 32 x 32 products run on fp64 MFMAs
-// (v_mfma_f64_16x16x4: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16], receives
-// D[4 v + l / 16][l % 16]), one 16 x 16 tile per wave, the blocks of L straight from global memory.
-constexpr int CHOL_INV_SPLIT = 3;
-__global__ __launch_bounds__(256) void chol_inverse_kernel(const CholBlock* table, const CholBlock single, const int n_blocks) {
-    const int b = blockIdx.x / CHOL_INV_SPLIT, part = blockIdx.x % CHOL_INV_SPLIT;
-    if (b >= n_blocks) return;
-    CholBlock cb = single;
-    if (table) cb = table[b];
-    const int k = cb.k;
-    const double* A = cb.work;                 // L in the lower triangle
-    double* X = cb.work + (size_t)k * k;       // diagonal blocks hold the inverted diagonal blocks of L
-    typedef double d4_t __attribute__((ext_vector_type(4)));
-    const int tid = threadIdx.x;
-    const int wv = tid >> 6, li16 = tid & 15, lk4 = (tid & 63) >> 4;
-    const int tr = (wv >> 1) & 1, tcb = wv & 1;
-    __shared__ double Ld[CHB][CHB_P];
-    extern __shared__ double Pn[];             // [block rows * CHB][CHB_P]
-    const int nblk = (k + CHB - 1) / CHB;
-    const int ncol = nblk - 1;                 // block columns with blocks below the diagonal
-    // columns 0, 1, 2, ... go to parts 0, 1, 2, 2, 1, 0, 0, 1, ...: long and short columns mix
-    for (int J = 0; J < ncol; ++J) {
-        const int pos = J % (2 * CHOL_INV_SPLIT);
-        const int owner = (pos < CHOL_INV_SPLIT) ? pos : 2 * CHOL_INV_SPLIT - 1 - pos;
-        if (owner != part) continue;           // uniform over the workgroup
-        for (int e = tid; e < CHB * CHB; e += 256)
-            Pn[(e >> 5) * CHB_P + (e & 31)] = X[(size_t)(J * CHB + (e >> 5)) * k + J * CHB + (e & 31)];   // J < nblk - 1: a full block
-        __syncthreads();
-        for (int I = J + 1; I < nblk; ++I) {
-            const int ib = min(CHB, k - I * CHB);
-            const int lr = 16 * tr + li16;                 // this lane's row of the A operand
-            const bool rok = lr < ib;
-            {
-                d4_t acc = {0.0, 0.0, 0.0, 0.0};
-                const double* lrow = A + (size_t)(I * CHB + min(lr, ib - 1)) * k + lk4;
-                // the blocks of L of this block row travel four products ahead of their use (each
-                // product is eight MFMAs, far shorter than a trip to L2 or beyond)
-                double an[4][8];
-#pragma unroll
-                for (int d = 0; d < 4; ++d)
-                    if (J + d < I) {
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) an[d][q] = lrow[(J + d) * CHB + 4 * q];
-                    }
-                for (int K0 = J; K0 < I; K0 += 4) {
-#pragma unroll
-                    for (int d = 0; d < 4; ++d) {
-                        const int K = K0 + d;
-                        if (K < I) {                               // uniform
-                            double a[8];
-#pragma unroll
-                            for (int q = 0; q < 8; ++q) a[q] = rok ? an[d][q] : 0.0;
-                            if (K + 4 < I) {
-#pragma unroll
-                                for (int q = 0; q < 8; ++q) an[d][q] = lrow[(K + 4) * CHB + 4 * q];
-                            }
-                            const double* xb = Pn + (size_t)((K - J) * CHB + lk4) * CHB_P + 16 * tcb + li16;
-#pragma unroll
-                            for (int q = 0; q < 8; ++q)
-                                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], xb[4 * q * CHB_P], acc, 0, 0, 0);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int v = 0; v < 4; ++v) Ld[16 * tr + 4 * v + lk4][16 * tcb + li16] = acc[v];
-            }
-            __syncthreads();
-            {
-                d4_t acc = {0.0, 0.0, 0.0, 0.0};
-                const double* xd = X + (size_t)(I * CHB + min(lr, ib - 1)) * k + I * CHB;
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const int c = 4 * q + lk4;
-                    const double a = (rok && c < ib) ? xd[min(c, ib - 1)] : 0.0;     // Li_I, lower triangular
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Ld[c][16 * tcb + li16], acc, 0, 0, 0);
-                }
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int r = 16 * tr + 4 * v + lk4, cc = 16 * tcb + li16;
-                    const double val = -acc[v];
-                    Pn[((I - J) * CHB + r) * CHB_P + cc] = val;                      // rows past the matrix: zero
-                    if (r < ib) X[(size_t)(I * CHB + r) * k + J * CHB + cc] = val;
-                }
-            }
-            __syncthreads();
-        }
-    }
-}
-
-// Third launch: Rinv = X^T (upper triangular, fp32) and, if asked for, Rtot = L^T (fp64), by
-// 32 x 32 tiles transposed through LDS; one workgroup per tile of the output.
-__global__ __launch_bounds__(256) void chol_output_kernel(const CholBlock* table, const CholBlock single, const int n_blocks,
-                                                          const int tiles) {
-    const int b = blockIdx.x / (tiles * tiles), t = blockIdx.x % (tiles * tiles);
-    if (b >= n_blocks) return;
-    CholBlock cb = single;
-    if (table) cb = table[b];
-    const int k = cb.k;
-    const int ta = t / tiles, tb = t % tiles;      // output tile: rows ta * 32.., columns tb * 32..
-    if (ta * CHB >= k || tb * CHB >= k) return;
-    const double* A = cb.work;
-    const double* X = cb.work + (size_t)k * k;
-    __shared__ double tx[CHB][CHB_P];
-    __shared__ double tl[CHB][CHB_P];
-    const int tid = threadIdx.x;
-    const bool upper = ta <= tb;                    // tiles below the diagonal are zero
-    if (upper) {
-        for (int e = tid; e < CHB * CHB; e += 256) {
-            const int i = e >> 5, c = e & 31;       // source entry (tb * 32 + i, ta * 32 + c) of the lower triangles
-            const int sr = tb * CHB + i, sc = ta * CHB + c;
-            const bool ok = sr < k && sc < k && sc <= sr;
-            tx[i][c] = ok ? X[(size_t)sr * k + sc] : 0.0;
-            tl[i][c] = (ok && cb.Rtot) ? A[(size_t)sr * k + sc] : 0.0;
-        }
-    }
-    __syncthreads();
-    for (int e = tid; e < CHB * CHB; e += 256) {
-        const int i = e >> 5, c = e & 31;           // output entry (ta * 32 + i, tb * 32 + c)
-        const int orow = ta * CHB + i, ocol = tb * CHB + c;
-        if (orow < k && ocol < k) {
-            cb.Rinv[(size_t)orow * k + ocol] = upper ? (float)tx[c][i] : 0.0f;
-            if (cb.Rtot) cb.Rtot[(size_t)orow * k + ocol] = upper ? tl[c][i] : 0.0;
-        }
-    }
 }
 
 // Variant for k <= 272, one launch: factor and inverse of one matrix in the registers of one workgroup.
@@ -617,7 +314,13 @@ __global__ __launch_bounds__(256) void chol_output_kernel(const CholBlock* table
 // Per call, one matrix per compute unit, the three launches of the blocked variant -> this: k = 72 68 -> 28 us,
 // k = 136 130 -> 62 us, k = 264 315 -> 160 us (there the fp64 products of the early steps take over: about
 // 150 tiles of four products each, at two waves per SIMD).  272 is where the tiles fill the registers; larger
-// matrices take the blocked variant.
+// matrices (up to 544) are cut in two:
+//     [S11    ]   the kernel on S11 (PART 1), L21 = S21 Li1^T, S22 - L21 L21^T, the kernel on that (PART 2);
+//     [S21 S22]   the inverse below the diagonal is -Li2 (L21 Li1).
+// The products (fp64 MFMAs, 64 x 64 tiles over the whole chip) and Li1, Li2 go through `work`.  The variant this
+// replaces, 32-wide block columns of a matrix in memory, spent one workgroup's chain on all of it.
+// Per call at k = 528, 56 matrices, the other groups of a refresh running beside it: 1.29 + 0.69 + 0.18 ms in
+// three launches -> 0.35 + 0.21 + 0.25 + 0.25 + 0.17 ms in five; refresh of the 1B model 107.8 -> 96.3 ms.
 constexpr int CT = 16;
 constexpr int CT_P = CT + 2;                   // LDS row: 144 bytes, operand reads free of bank conflicts
 constexpr int CT_MAXK = 272;
@@ -629,7 +332,12 @@ __device__ inline void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <int NT, int WAVES>
+// Leading part of a matrix cut in two: whole tiles, both parts at most CT_MAXK for k up to 2 CT_MAXK.
+__host__ __device__ inline int chol_lead(int k) { return min(((k + 1) / 2 + CT - 1) / CT * CT, k); }
+
+// PART 0: the whole matrix; 1: its leading part; 2: the trailing part, whose lower triangle (less L21 L21^T) is
+// in `work`.  Parts leave their inverse in the second half of `work` as well, in fp64.
+template <int NT, int WAVES, int PART>
 __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlock* table, const CholBlock single,
                                                                     const double tol, const double shift_rel) {
     constexpr int OFF = (NT * (NT - 1) / 2 + WAVES - 2) / (WAVES - 1);     // off-diagonal tiles per wave
@@ -643,15 +351,22 @@ __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlo
 
     CholBlock cb = single;
     if (table) cb = table[blockIdx.x];
-    const int k = cb.k;
+    const int ld = cb.k;
+    const int lead = chol_lead(ld);
+    const int k = PART == 0 ? ld : PART == 1 ? lead : ld - lead;
+    if (k <= 0) return;
+    const size_t first = PART == 2 ? (size_t)lead * ld + lead : 0;
     const int nt = (k + CT - 1) / CT;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, lk = lane >> 4;
     const bool diag_wave = wave == WAVES - 1;
     typedef const float __attribute__((address_space(1))) gfloat;
-    gfloat* S = (gfloat*)cb.S;
-    float __attribute__((address_space(1)))* Rinv = (float __attribute__((address_space(1)))*)cb.Rinv;
-    double __attribute__((address_space(1)))* Rtot = (double __attribute__((address_space(1)))*)cb.Rtot;
+    typedef double __attribute__((address_space(1))) gdouble;
+    gfloat* S = (gfloat*)cb.S + first;
+    float __attribute__((address_space(1)))* Rinv = (float __attribute__((address_space(1)))*)cb.Rinv + first;
+    gdouble* Rtot = cb.Rtot ? (gdouble*)cb.Rtot + first : nullptr;
+    const gdouble* A = (const gdouble*)cb.work + first;
+    gdouble* X = (gdouble*)cb.work + (size_t)ld * ld + first;
 
     // ---- tiles of this wave: the diagonal ones, or number wave + (WAVES - 1) s of the row-major strict triangle
     int tI[SLOTS], tK[SLOTS];
@@ -667,10 +382,12 @@ __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlo
     }
     double mx = 0.0;
     for (int j = tid; j < nt * CT; j += 64 * WAVES) {
-        const float d = (j < k) ? S[(size_t)j * k + j] : 1.0f;
+        const float d = (j < k) ? S[(size_t)j * ld + j] : 1.0f;
         s_diag[j] = d;
-        if (j < k) mx = fmax(mx, (double)d);
+        if (PART == 0 && j < k) mx = fmax(mx, (double)d);
     }
+    if (PART != 0)                                             // the shift is one for the whole matrix
+        for (int j = tid; j < ld; j += 64 * WAVES) mx = fmax(mx, (double)((gfloat*)cb.S)[(size_t)j * ld + j]);
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) {
         if (tI[s] >= nt) continue;                             // uniform
@@ -679,8 +396,8 @@ __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlo
             const int i = tI[s] * CT + 4 * v + lk, c = tK[s] * CT + li;
             const bool in = i < k && c < k;
             const int lo = min(min(i, c), k - 1), hi = min(max(i, c), k - 1);    // the lower triangle of S is read
-            const float x = S[(size_t)hi * k + lo];
-            acc[s][v] = in ? (double)x : (i == c ? 1.0 : 0.0);
+            const double x = PART == 2 ? A[(size_t)hi * ld + lo] : (double)S[(size_t)hi * ld + lo];
+            acc[s][v] = in ? x : (i == c ? 1.0 : 0.0);
         }
     }
     for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
@@ -701,8 +418,8 @@ __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlo
     // below the block diagonal both results are zero
     for (int a = CT + wave; a < k; a += WAVES)
         for (int b = lane; b < a / CT * CT; b += 64) {
-            Rinv[(size_t)a * k + b] = 0.0f;
-            if (Rtot) Rtot[(size_t)a * k + b] = 0.0;
+            Rinv[(size_t)a * ld + b] = 0.0f;
+            if (Rtot) Rtot[(size_t)a * ld + b] = 0.0;
         }
 
     // A slot's tile coordinates, opaque to the compiler: it would otherwise keep the LDS addresses of every
@@ -764,12 +481,15 @@ __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlo
             if (Rtot)
 #pragma unroll
                 for (int j = 0; j < CT; ++j)
-                    if (J * CT + j < k && g < k) Rtot[(size_t)(J * CT + j) * k + g] = (j <= li) ? a[j] : 0.0;
+                    if (J * CT + j < k && g < k) Rtot[(size_t)(J * CT + j) * ld + g] = (j <= li) ? a[j] : 0.0;
         } else if (lk == 1) {
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
                 out[c][li] = a[c];
-                if (J * CT + c < k && g < k) Rinv[(size_t)g * k + J * CT + c] = (float)a[c];
+                if (J * CT + c < k && g < k) {
+                    Rinv[(size_t)g * ld + J * CT + c] = (float)a[c];
+                    if (PART != 0) X[(size_t)(J * CT + c) * ld + g] = a[c];
+                }
             }
         }
     };
@@ -806,13 +526,18 @@ __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlo
 #pragma unroll
                     for (int v = 0; v < 4; ++v) o[v] = cur[x][li][4 * v + lk];
                     const int r = (x > J ? J : x) * CT + lk, c = (x > J ? x : J) * CT + li;
-                    const size_t at = (size_t)r * k + c;
+                    const size_t at = (size_t)r * ld + c;
+                    if (PART != 0 && x < J) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            if (J * CT + 4 * v + lk < k) X[(size_t)(J * CT + 4 * v + lk) * ld + x * CT + li] = cur[x][4 * v + lk][li];
+                    }
                     if (c < k) {
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
                             if (r + 4 * v < k) {
-                                if (x < J) Rinv[at + (size_t)(4 * v) * k] = (float)o[v];
-                                else if (Rtot) Rtot[at + (size_t)(4 * v) * k] = o[v];
+                                if (x < J) Rinv[at + (size_t)(4 * v) * ld] = (float)o[v];
+                                else if (Rtot) Rtot[at + (size_t)(4 * v) * ld] = o[v];
                             }
                     }
                 }
@@ -880,17 +605,151 @@ __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlo
     }
 }
 
-template <int NT, int WAVES>
+// The products between the two parts, one 64 x 64 output tile per workgroup, 16-deep k-tiles through LDS (the
+// next one in registers meanwhile).  With o = chol_lead(k), A the first and X the second half of `work`:
+//   STAGE 0  A[o..][0..o) = L21 = S21 X11^T, its transpose to Rtot
+//   STAGE 1  A[o..][o..) = S22 - L21 L21^T (tiles on and below the diagonal) and X[o..][0..o) = L21 X11
+//   STAGE 2  -X22 (L21 X11), transposed, to Rinv; zeros below the diagonal of Rinv and Rtot
+// Of X11 and X22 only the lower triangles are defined (and read).
+constexpr int CG = 64, CG_K = 16, CG_P = CG_K + 2;
+
+template <int STAGE>
+__global__ __launch_bounds__(256) void chol_parts_kernel(const CholBlock* table, const CholBlock single, const int tiles) {
+    typedef double d4_t __attribute__((ext_vector_type(4)));
+    typedef double __attribute__((address_space(1))) gdouble;
+    typedef float __attribute__((address_space(1))) gfloat;
+    __shared__ double lds[2][2][CG][CG_P];                     // [buffer][operand][row][k]
+    static_assert(sizeof(lds) >= sizeof(double) * CG * (CG + 1), "the output tile goes through the same memory");
+    CholBlock cb = single;
+    if (table) cb = table[blockIdx.y];
+    const int ld = cb.k, o = chol_lead(ld), k2 = ld - o;
+    const bool gram = STAGE == 1 && (int)blockIdx.x >= tiles * tiles;        // S22 - L21 L21^T
+    const int t = blockIdx.x - (gram ? tiles * tiles : 0);
+    const int i0 = t / tiles * CG, j0 = t % tiles * CG;
+    if (i0 >= k2 || j0 >= (gram ? i0 + 1 : o)) return;         // the whole workgroup
+    const gfloat* S = (const gfloat*)cb.S;
+    gdouble* A = (gdouble*)cb.work;
+    gdouble* X = A + (size_t)ld * ld;
+    const int nrow = k2, ncol = gram ? k2 : o, depth = STAGE == 2 ? k2 : o;
+    // where the triangular factor leaves nothing: k above the tile's last column or row, k below its first column
+    const int kend = STAGE == 0 ? min(depth, j0 + CG) : STAGE == 2 ? min(depth, i0 + CG) : depth;
+    const int kbeg = (STAGE == 1 && !gram) ? j0 : 0;
+    const bool b_across = STAGE == 2 || (STAGE == 1 && !gram);               // the right operand is stored [k][column]
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
+    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+    const int rr = tid >> 2, rk = (tid & 3) * 4;               // staging: row and first k; across: k and first column
+    const int ck = tid >> 4, cc = (tid & 15) * 4;
+    double ra[4], rb[4];
+    auto fetch = [&](int kt) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int kk = kt + rk + q, i = i0 + rr;
+            double v = 0.0;
+            if (i < nrow && kk < depth) {
+                if (STAGE == 0) v = (double)S[(size_t)(o + i) * ld + kk];
+                else if (STAGE == 1) v = A[(size_t)(o + i) * ld + kk];
+                else if (kk <= i) v = X[(size_t)(o + i) * ld + o + kk];
+            }
+            ra[q] = v;
+            v = 0.0;
+            if (b_across) {
+                const int k = kt + ck, j = j0 + cc + q;
+                if (k < depth && j < ncol) {
+                    if (STAGE == 2) v = X[(size_t)(o + k) * ld + j];
+                    else if (j <= k) v = X[(size_t)k * ld + j];
+                }
+            } else {
+                const int j = j0 + rr;
+                if (j < ncol && kk < depth) {
+                    if (gram) v = A[(size_t)(o + j) * ld + kk];
+                    else if (kk <= j) v = X[(size_t)j * ld + kk];
+                }
+            }
+            rb[q] = v;
+        }
+    };
+    d4_t acc[2][2] = {};
+    fetch(kbeg);
+    int buf = 0;
+    for (int kt = kbeg; kt < kend; kt += CG_K, buf ^= 1) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            lds[buf][0][rr][rk + q] = ra[q];
+            if (b_across) lds[buf][1][cc + q][ck] = rb[q];
+            else lds[buf][1][rr][rk + q] = rb[q];
+        }
+        __syncthreads();
+        if (kt + CG_K < kend) fetch(kt + CG_K);
+#pragma unroll
+        for (int q = 0; q < CG_K / 4; ++q) {
+            double a[2], b[2];
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                a[f] = lds[buf][0][wm + f * 16 + li][4 * q + lk];
+                b[f] = lds[buf][1][wn + f * 16 + li][4 * q + lk];
+            }
+#pragma unroll
+            for (int f = 0; f < 2; ++f)
+#pragma unroll
+                for (int g = 0; g < 2; ++g) acc[f][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[f], b[g], acc[f][g], 0, 0, 0);
+        }
+    }
+    __syncthreads();
+    double (*out)[CG + 1] = (double (*)[CG + 1])&lds[0][0][0][0];
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int r = wm + f * 16 + 4 * v + lk, c = wn + g * 16 + li, i = i0 + r, j = j0 + c;
+                const double x = acc[f][g][v];
+                if (STAGE != 1) out[r][c] = x;
+                if (i >= nrow || j >= ncol) continue;
+                if (STAGE == 0) A[(size_t)(o + i) * ld + j] = x;
+                else if (STAGE == 1 && gram) { if (j <= i) A[(size_t)(o + i) * ld + o + j] = (double)S[(size_t)(o + i) * ld + o + j] - x; }
+                else if (STAGE == 1) X[(size_t)(o + i) * ld + j] = x;
+                else {
+                    cb.Rinv[(size_t)(o + i) * ld + j] = 0.0f;
+                    if (cb.Rtot) cb.Rtot[(size_t)(o + i) * ld + j] = 0.0;
+                }
+            }
+    if (STAGE == 1) return;
+    __syncthreads();
+    for (int e = tid; e < CG * CG; e += 256) {                 // transposed outputs, rows of the tile running along i
+        const int r = e & (CG - 1), c = e / CG, i = i0 + r, j = j0 + c;
+        if (i >= nrow || j >= ncol) continue;
+        if (STAGE == 0) { if (cb.Rtot) cb.Rtot[(size_t)j * ld + o + i] = out[r][c]; }
+        else cb.Rinv[(size_t)j * ld + o + i] = (float)-out[r][c];
+    }
+}
+
+template <int NT, int WAVES, int PART = 0>
 static hipError_t launch_chol_tiles(const CholBlock* table_dev, const CholBlock& single, int blocks, double tol, double shift_rel,
                                     hipStream_t stream) {
     constexpr int lds = (2 * NT + 1) * CT * CT_P * 8 + NT * CT * 4;
     static thread_local bool configured = false;
     if (!configured && lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void*)chol_tiles_kernel<NT, WAVES>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipError_t e = hipFuncSetAttribute((const void*)chol_tiles_kernel<NT, WAVES, PART>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
     }
     configured = true;
-    hipLaunchKernelGGL((chol_tiles_kernel<NT, WAVES>), dim3(blocks), dim3(64 * WAVES), lds, stream, table_dev, single, tol, shift_rel);
+    hipLaunchKernelGGL((chol_tiles_kernel<NT, WAVES, PART>), dim3(blocks), dim3(64 * WAVES), lds, stream, table_dev, single, tol, shift_rel);
+    return hipGetLastError();
+}
+
+template <int NT, int WAVES>
+static hipError_t launch_chol_parts(const CholBlock* table_dev, const CholBlock& single, int blocks, int max_k, double tol,
+                                    double shift_rel, hipStream_t stream) {
+    hipError_t e = launch_chol_tiles<NT, WAVES, 1>(table_dev, single, blocks, tol, shift_rel, stream);
+    if (e != hipSuccess) return e;
+    const int tiles = (chol_lead(max_k) + CG - 1) / CG;        // the trailing part is no larger
+    hipLaunchKernelGGL(chol_parts_kernel<0>, dim3(tiles * tiles, blocks), dim3(256), 0, stream, table_dev, single, tiles);
+    hipLaunchKernelGGL(chol_parts_kernel<1>, dim3(2 * tiles * tiles, blocks), dim3(256), 0, stream, table_dev, single, tiles);
+    e = launch_chol_tiles<NT, WAVES, 2>(table_dev, single, blocks, tol, shift_rel, stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(chol_parts_kernel<2>, dim3(tiles * tiles, blocks), dim3(256), 0, stream, table_dev, single, tiles);
     return hipGetLastError();
 }
 
@@ -902,31 +761,10 @@ hipError_t launch_chol_inv(const CholBlock* table_dev, const CholBlock* single, 
     if (max_k <= 5 * CT) return launch_chol_tiles<5, 4>(table_dev, sb, blocks, tol, shift_rel, stream);
     if (max_k <= 9 * CT) return launch_chol_tiles<9, 4>(table_dev, sb, blocks, tol, shift_rel, stream);
     if (max_k <= CT_MAXK) return launch_chol_tiles<17, 8>(table_dev, sb, blocks, tol, shift_rel, stream);
-    if (max_k <= CHB_MAXK) {
-        // panel rows below the first diagonal block; in the inverse phase one block column of X
-        const int pn_rows = ((max_k + CHB - 1) / CHB) * CHB;
-        const int lds = pn_rows * CHB_P * 8;
-        static thread_local bool configured = false;
-        if (!configured) {
-            hipError_t e = hipFuncSetAttribute((const void*)chol_inv_blocked_kernel,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, ((CHB_MAXK + CHB - 1) / CHB) * CHB * CHB_P * 8);
-            if (e != hipSuccess) return e;
-            configured = true;
-        }
-        hipLaunchKernelGGL(chol_inv_blocked_kernel, dim3(blocks), dim3(SMALL_THREADS), lds, stream, table_dev, sb, tol, shift_rel);
-        static thread_local bool configured2 = false;
-        if (!configured2) {
-            hipError_t e = hipFuncSetAttribute((const void*)chol_inverse_kernel,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, ((CHB_MAXK + CHB - 1) / CHB) * CHB * CHB_P * 8);
-            if (e != hipSuccess) return e;
-            configured2 = true;
-        }
-        hipLaunchKernelGGL(chol_inverse_kernel, dim3(blocks * CHOL_INV_SPLIT), dim3(256), lds, stream, table_dev, sb, blocks);
-        const int tiles = (max_k + CHB - 1) / CHB;
-        hipLaunchKernelGGL(chol_output_kernel, dim3(blocks * tiles * tiles), dim3(256), 0, stream, table_dev, sb, blocks, tiles);
-    } else {
-        hipLaunchKernelGGL(chol_inv_kernel, dim3(blocks), dim3(SMALL_THREADS), 0, stream, table_dev, sb, tol, shift_rel);
-    }
+    // both parts fit the tile counts of the two halves of max_k, whatever the other matrices of the launch
+    if (max_k <= 2 * 9 * CT) return launch_chol_parts<9, 4>(table_dev, sb, blocks, max_k, tol, shift_rel, stream);
+    if (max_k <= 2 * CT_MAXK) return launch_chol_parts<17, 8>(table_dev, sb, blocks, max_k, tol, shift_rel, stream);
+    hipLaunchKernelGGL(chol_inv_kernel, dim3(blocks), dim3(SMALL_THREADS), 0, stream, table_dev, sb, tol, shift_rel);
     return hipGetLastError();
 }
 

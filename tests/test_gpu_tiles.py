@@ -60,8 +60,10 @@ def test_lift_sizes(tsr, m, n, r, prec):
 
 
 # the orthonormalisation and the small SVD around their tile sizes: 16-wide tiles (5, 9, 13 and 17 of them per
-# Cholesky kernel, 32-wide ones (3, 5, 7 and 9) in the tridiagonalization, the variants above 272 and 288
-@pytest.mark.parametrize("k", [5, 15, 16, 17, 33, 64, 80, 81, 144, 96, 97, 145, 160, 161, 224, 225, 264, 272, 273, 288, 289])
+# Cholesky kernel; cut in two above 272, with halves of up to 9 and up to 17 tiles, up to 544), 32-wide ones
+# (3, 5, 7 and 9) in the tridiagonalization, the variant above 288
+@pytest.mark.parametrize("k", [5, 15, 16, 17, 33, 64, 80, 81, 144, 96, 97, 145, 160, 161, 224, 225, 264, 272, 273, 288, 289,
+                               303, 417, 528, 543, 544, 545])
 def test_refresh_full_sketch_sizes(tsr, k):
     """A sketch as wide as the matrix is high spans everything: the singular values and the leading
     subspaces are those of the matrix, up to the orthonormality the last pass leaves (Gram matrix of three
