@@ -299,12 +299,11 @@ constexpr double ORTH_DROP = 1e-6;
 // only); X R^-1 as ONE product over a doubled contraction: the rows [Xh | Xl] against the two pieces
 // [Rh | Rh] and [Rl | Rl] of the transposed factor, i.e. (Xh + Xl)(Rh + Rl).
 struct OrthNtPass {
-    std::vector<SplitBlock> st, sx, sr, sr2;  // X -> pieces of X^T; X -> [Xh | Xl]; R^-1 -> the two halves of the pieces of R^-T
-    const SplitBlock* d_st = nullptr; const SplitBlock* d_sx = nullptr; const SplitBlock* d_sr = nullptr;
-    const SplitBlock* d_sr2 = nullptr;
+    std::vector<SplitBlock> sx, sr;           // X -> pieces of X^T, and [Xh | Xl]; R^-1 -> the two halves of the pieces of R^-T
+    const SplitBlock* d_sx = nullptr; const SplitBlock* d_sr = nullptr;
     NtStageH gram, ap;
     int max_rows = 0, max_k = 0;
-    bool empty() const { return st.empty(); }
+    bool empty() const { return sx.empty(); }
 };
 
 struct OrthProgram {
@@ -357,10 +356,8 @@ void build_orth_nt(OrthNtPass& pass, const std::vector<RefreshBlock>& blocks, bo
         unsigned short* Xt = on_rows_m ? b.Pm : b.Pn;            // pieces of X^T (k x ldrows)
         const long long ldrows = on_rows_m ? b.ldm : b.ldn, st_t = (long long)k * ldrows;
         const long long ld2 = 2 * b.ldk, st_r = (long long)k * ld2;      // rows of two pieces side by side
-        pass.st.push_back(SplitBlock{in, Xt, ldrows, st_t, rows, k});
-        pass.sx.push_back(SplitBlock{in, b.Xp, ld2, b.ldk, rows, k});
-        pass.sr.push_back(SplitBlock{b.Rinv, b.Rt, ld2, st_r, k, k});
-        pass.sr2.push_back(SplitBlock{b.Rinv, b.Rt + b.ldk, ld2, st_r, k, k});
+        pass.sx.push_back(SplitBlock{in, Xt, ldrows, st_t, rows, k, nullptr, b.Xp, ld2, b.ldk});
+        pass.sr.push_back(SplitBlock{b.Rinv, b.Rt, ld2, st_r, k, k, b.Rt + b.ldk});
         const int bi = (int)i;
         g.push_back(NtLogical{Xt, Xt, b.S, ldrows, ldrows, k, k, k, rows, bi, bi});
         g.push_back(NtLogical{Xt + st_t, Xt, b.S, ldrows, ldrows, k, k, k, rows, bi, bi});
@@ -435,7 +432,7 @@ int run_orth(const OrthProgram& op, bool grouped, Ctx& cx, int passes) {
         if (p.empty()) return TSR_OK;
         {
             Timed timed(cx, TSR_PROF_ORTH_GEMM);
-            TSR_HIP(launch_split_transpose(p.d_st, (int)p.st.size(), p.max_rows, p.max_k, 2, cx.s));
+            TSR_HIP(launch_split(p.d_sx, (int)p.sx.size(), p.max_rows, p.max_k, cx.s));
         }
         return run_nt_stage(p.gram, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM);
     };
@@ -443,9 +440,7 @@ int run_orth(const OrthProgram& op, bool grouped, Ctx& cx, int passes) {
         if (p.empty()) return TSR_OK;
         {
             Timed timed(cx, TSR_PROF_ORTH_GEMM);
-            TSR_HIP(launch_split_rows(p.d_sx, (int)p.sx.size(), p.max_rows, p.max_k, 2, cx.s));
-            TSR_HIP(launch_split_transpose(p.d_sr, (int)p.sr.size(), p.max_k, p.max_k, 2, cx.s));
-            TSR_HIP(launch_split_transpose(p.d_sr2, (int)p.sr2.size(), p.max_k, p.max_k, 2, cx.s));
+            TSR_HIP(launch_split(p.d_sr, (int)p.sr.size(), p.max_k, p.max_k, cx.s));
         }
         return run_nt_stage(p.ap, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM);
     };
@@ -580,7 +575,7 @@ int run_refresh_front(const RefreshProgram& rp, bool grouped, int q, Ctx& cx) {
         if (!nt) return TSR_OK;
         {
             Timed timed(cx, TSR_PROF_SKETCH_GEMM);
-            TSR_HIP(launch_split_transpose(split, (int)f.gt.size(), rows, f.max_k, NT_REFRESH_PIECES, cx.s));
+            TSR_HIP(launch_split(split, (int)f.gt.size(), rows, f.max_k, cx.s));
         }
         return run_nt_stage(stage, 1.0f, 0.0f, cx, TSR_PROF_SKETCH_GEMM);
     };
@@ -646,7 +641,7 @@ void upload_refresh(RefreshProgram& rp, Arena& ar, Uploader& up) {
     for (OrthProgram* op : {&rp.orthY, &rp.orthZ}) {
         for (OrthNtPass* p : {&op->ntA, &op->ntE}) {
             if (p->empty()) continue;
-            p->d_st = up.put(p->st, ar); p->d_sx = up.put(p->sx, ar); p->d_sr = up.put(p->sr, ar); p->d_sr2 = up.put(p->sr2, ar);
+            p->d_sx = up.put(p->sx, ar); p->d_sr = up.put(p->sr, ar);
             upload_nt_stage(p->gram, ar, up); upload_nt_stage(p->ap, ar, up);
         }
         upload_stage(op->gramA, ar, up); upload_stage(op->qA, ar, up);

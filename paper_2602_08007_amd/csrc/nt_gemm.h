@@ -116,20 +116,24 @@ struct TransposeBlock {
 };
 hipError_t launch_transpose_bf16(const TransposeBlock* table_dev, int blocks, int max_rows, int max_cols, hipStream_t stream);
 
-// An fp32 matrix X (rows x k, contiguous) as `pieces` bf16 matrices of its transpose: piece p
-// (k rows of pitch ld_dst, at dst + p * piece_stride elements) holds the p-th term of
-// x = x0 + x1 (+ x2) with x0 = bf16(x), x1 = bf16(x - x0), ...; columns rows .. up to the next
-// multiple of 8 are written as zeros, nothing beyond (pieces may sit side by side in one row).
+// An fp32 matrix X (rows x k, contiguous) as two bf16 pieces, x = x0 + x1 with x0 = bf16(x) and x1 = bf16(x - x0),
+// in up to three places:
+//   dst       the transpose: piece p has k rows of pitch ld_dst, at dst + p * piece_stride elements; columns
+//             `rows` .. up to the next multiple of 8 are written as zeros, nothing beyond (pieces may sit side by
+//             side in one row);
+//   dst_again the same once more, optional;
+//   rows_dst  as stored, optional: piece p has `rows` rows of pitch rows_ld, at rows_dst + p * rows_stride; columns
+//             k .. up to the next multiple of 8 are written as zeros.
+// The places are 16-byte aligned, their pitches and strides multiples of 8 elements.
 struct SplitBlock {
-    const float* X; void* dst;
+    const float* X; unsigned short* dst;
     long long ld_dst, piece_stride;
     int rows, k;
+    unsigned short* dst_again = nullptr;
+    unsigned short* rows_dst = nullptr;
+    long long rows_ld = 0, rows_stride = 0;
 };
-hipError_t launch_split_transpose(const SplitBlock* table_dev, int blocks, int max_rows, int max_k, int pieces,
-                                  hipStream_t stream);
-// The same pieces without the transposition: piece p (rows of pitch ld_dst, at dst + p * piece_stride) of
-// X (rows x k, contiguous); columns k .. up to the next multiple of 8 are written as zeros.
-hipError_t launch_split_rows(const SplitBlock* table_dev, int blocks, int max_rows, int max_k, int pieces, hipStream_t stream);
+hipError_t launch_split(const SplitBlock* table_dev, int blocks, int max_rows, int max_k, hipStream_t stream);
 
 hipError_t launch_shadows(const ShadowBlock* table_dev, int blocks, int max_rows, int max_r, hipStream_t stream);
 

@@ -1233,76 +1233,74 @@ hipError_t launch_transpose_bf16(const TransposeBlock* table_dev, int blocks, in
     return hipGetLastError();
 }
 
-template <int PIECES>
-__global__ __launch_bounds__(256) void split_transpose_kernel(const SplitBlock* table) {
+// One 64 x 64 patch of X per workgroup, 4 x 4 elements per thread: the pieces go out as stored from the
+// registers, and transposed through LDS, four rows at a time per column (the row of 68 elements spreads the 8-byte
+// accesses over all banks).  Bound by memory, so X is read once for all places and all loads of a thread are under
+// way together.  In place of a transposing kernel (one element per load), a second one for the rows and a second
+// transposition for the copy: 32.5 -> 16.0 ms of launches per refresh of the 1B model (the three groups' added up).
+__global__ __launch_bounds__(256) void split_kernel(const SplitBlock* table) {
+    typedef float f4_u __attribute__((ext_vector_type(4), aligned(4)));
+    typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
+    typedef unsigned u2_t __attribute__((ext_vector_type(2)));
+    constexpr int P = 68;
     const SplitBlock b = table[blockIdx.z];
     const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-    const int rows8 = (b.rows + 7) / 8 * 8;                         // written width of an output row (zeros beyond `rows`)
+    const int rows8 = (b.rows + 7) / 8 * 8, k8 = (b.k + 7) / 8 * 8;       // written widths
     if (r0 >= rows8 || c0 >= b.k) return;
-    __shared__ unsigned short tile[PIECES][64][66];
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int i = ty; i < 64; i += 4) {
-        const int r = r0 + i, c = c0 + tx;
-        float x = (r < b.rows && c < b.k) ? b.X[(long long)r * b.k + c] : 0.0f;
+    __shared__ __attribute__((aligned(16))) unsigned short tile[2][64][P];
+    const int c = (threadIdx.x & 15) * 4, r = (threadIdx.x >> 4) * 4;
+    float x[4][4];
 #pragma unroll
-        for (int p = 0; p < PIECES; ++p) {
-            const __bf16 h = (__bf16)x;
-            tile[p][i][tx] = __builtin_bit_cast(unsigned short, h);
-            x -= (float)h;
+    for (int j = 0; j < 4; ++j) {
+        const float* src = b.X + (long long)(r0 + r + j) * b.k + c0 + c;
+        if (r0 + r + j < b.rows && c0 + c + 3 < b.k) {
+            const f4_u v = *(const f4_u*)src;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[j][i] = v[i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[j][i] = (r0 + r + j < b.rows && c0 + c + i < b.k) ? src[i] : 0.0f;
         }
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        bf4 h[4];                                                         // rows
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                h[j][i] = (__bf16)x[j][i];
+                x[j][i] -= (float)h[j][i];
+            }
+        if (b.rows_dst && c0 + c < k8) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (r0 + r + j < b.rows) *(bf4*)(b.rows_dst + p * b.rows_stride + (long long)(r0 + r + j) * b.rows_ld + c0 + c) = h[j];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *(bf4*)&tile[p][c + i][r] = bf4{h[0][i], h[1][i], h[2][i], h[3][i]};
     }
     __syncthreads();
-    unsigned short* dst = (unsigned short*)b.dst;
-    const int px = threadIdx.x & 31, py = threadIdx.x >> 5;
-    for (int i = py; i < 64; i += 8) {
-        const int c = c0 + i, r = r0 + 2 * px;                       // piece[c][r], piece[c][r + 1]
-        if (c < b.k && r < rows8) {
+    const int rr = (threadIdx.x & 7) * 8;                                 // eight rows of X per thread and column
+    if (r0 + rr >= rows8) return;
 #pragma unroll
-            for (int p = 0; p < PIECES; ++p)
-                *(unsigned*)(dst + (long long)p * b.piece_stride + (long long)c * b.ld_dst + r) =
-                    (unsigned)tile[p][2 * px][i] | ((unsigned)tile[p][2 * px + 1][i] << 16);
-        }
-    }
-}
-
-hipError_t launch_split_transpose(const SplitBlock* table_dev, int blocks, int max_rows, int max_k, int pieces,
-                                  hipStream_t stream) {
-    if (blocks <= 0) return hipSuccess;
-    dim3 grid((max_k + 63) / 64, (max_rows + 8 + 63) / 64, blocks);
-    if (pieces == 2) hipLaunchKernelGGL(split_transpose_kernel<2>, grid, dim3(256), 0, stream, table_dev);
-    else if (pieces == 3) hipLaunchKernelGGL(split_transpose_kernel<3>, grid, dim3(256), 0, stream, table_dev);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
-}
-
-template <int PIECES>
-__global__ __launch_bounds__(256) void split_rows_kernel(const SplitBlock* table) {
-    const SplitBlock b = table[blockIdx.z];
-    const int wp = (b.k + 7) / 8 * 4;                                   // element pairs written per output row (zeros beyond k)
-    const long long pairs = (long long)b.rows * wp;
-    unsigned* dst = (unsigned*)b.dst;
-    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < pairs; i += (long long)gridDim.x * 256) {
-        const int r = (int)(i / wp), c = (int)(i % wp) * 2;
-        float x0 = (c < b.k) ? b.X[(long long)r * b.k + c] : 0.0f;
-        float x1 = (c + 1 < b.k) ? b.X[(long long)r * b.k + c + 1] : 0.0f;
+    for (int p = 0; p < 2; ++p)
 #pragma unroll
-        for (int p = 0; p < PIECES; ++p) {
-            const __bf16 h0 = (__bf16)x0, h1 = (__bf16)x1;
-            dst[((long long)p * b.piece_stride + (long long)r * b.ld_dst + c) / 2] =
-                (unsigned)__builtin_bit_cast(unsigned short, h0) | ((unsigned)__builtin_bit_cast(unsigned short, h1) << 16);
-            x0 -= (float)h0; x1 -= (float)h1;
+        for (int q = 0; q < 2; ++q) {
+            const int cc = (threadIdx.x >> 3) + 32 * q;
+            if (c0 + cc >= b.k) continue;
+            const u2_t lo = *(const u2_t*)&tile[p][cc][rr], hi = *(const u2_t*)&tile[p][cc][rr + 4];
+            const u32x4 v = {lo[0], lo[1], hi[0], hi[1]};
+            const long long at = p * b.piece_stride + (long long)(c0 + cc) * b.ld_dst + r0 + rr;
+            *(u32x4*)(b.dst + at) = v;
+            if (b.dst_again) *(u32x4*)(b.dst_again + at) = v;
         }
-    }
 }
 
-hipError_t launch_split_rows(const SplitBlock* table_dev, int blocks, int max_rows, int max_k, int pieces, hipStream_t stream) {
+hipError_t launch_split(const SplitBlock* table_dev, int blocks, int max_rows, int max_k, hipStream_t stream) {
     if (blocks <= 0) return hipSuccess;
-    long long bx = ((long long)max_rows * ((max_k + 8) / 2) + 255) / 256;
-    if (bx > 2048) bx = 2048;
-    dim3 grid((unsigned)bx, 1, blocks);
-    if (pieces == 2) hipLaunchKernelGGL(split_rows_kernel<2>, grid, dim3(256), 0, stream, table_dev);
-    else if (pieces == 3) hipLaunchKernelGGL(split_rows_kernel<3>, grid, dim3(256), 0, stream, table_dev);
-    else return hipErrorInvalidValue;
+    dim3 grid((max_k + 63) / 64, (max_rows + 63) / 64, blocks);
+    hipLaunchKernelGGL(split_kernel, grid, dim3(256), 0, stream, table_dev);
     return hipGetLastError();
 }
 
