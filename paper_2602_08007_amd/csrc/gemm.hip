@@ -2,20 +2,22 @@
 // per 256-thread workgroup, 32-deep k-tiles staged through LDS as bf16 pieces, fp32 accumulation with
 // v_mfma_f32_32x32x16_bf16 (the four waves own the four quadrants of the tile).
 //
-// Global -> registers (two k-tiles ahead) -> split into bf16 pieces -> LDS in [row][k] order with a
-// padded row -> 16-byte fragment reads.  Both operand orientations end up in the same LDS layout, so the
-// MFMA loop is shared by all variants.
+// Global -> registers (two or three k-tiles ahead) -> split into bf16 pieces -> LDS in [row][k] order ->
+// 16-byte fragment reads.  Both operand orientations end up in the same LDS layout, so the MFMA loop is
+// shared by all variants.
 //
 // What bounds it: with few tiles per compute unit the trips to memory, with many the LDS traffic (with
 // two pieces per operand 64 KB of fragment reads and 40 KB of stores per k-tile against 768 cycles of
-// MFMAs).  Hence two register stages, branch-free loads in the loop (edges by clamped addresses, the rest
-// of a partial k-tile by a mask when it is stored), two LDS buffers with one barrier per k-tile where
-// they fit twice into a compute unit (up to two pieces), and for operands stored across k a lane layout
-// (eight lanes along k, eight along the rows) whose transposing LDS stores touch every bank once: with
-// the lanes along the rows the stores met in two banks and took sixteen passes.  Measured (before, with one
-// stage, per-element guards and element-by-element read-modify-write -> now): the step of one 512 x 1376
-// fp32 matrix at rank 64, 104 -> 39 us; of the 60M model in fp32 at rank 256, 643 -> 304 us (292 with the
-// early read of W, see the kernel); of a 32000 x 2048 embedding and LM head at rank 128, 1060 -> 551 us (511).
+// MFMAs) and the conversions.  Hence two register stages, branch-free loads in the loop (edges by clamped
+// addresses, the rest of a partial k-tile by a mask when it is stored), two LDS buffers with one barrier per
+// k-tile where they fit twice into a compute unit, the next k-tile converted and stored behind the products
+// of the current one, and for operands stored across k a lane layout (eight lanes along k, eight along the
+// rows) whose transposing LDS stores touch every bank once: with the lanes along the rows the stores met in
+// two banks and took sixteen passes.  Measured (with one stage, per-element guards and element-by-element
+// read-modify-write -> two stages -> W read early -> stores behind the products): the step of the 60M model in
+// fp32 at rank 256, 643 -> 304 -> 289 -> 271 us; of a 32000 x 2048 embedding and LM head at rank 128,
+// 1060 -> 551 -> 512 -> 475 us; the refresh of the latter 3608 -> 3399 us by the last of these.  The step of
+// one 512 x 1376 fp32 matrix at rank 64, 104 -> 39 us, is bound by its seven launches since.
 #include "gemm.h"
 
 #include <type_traits>
@@ -40,7 +42,17 @@ typedef u32x2 __attribute__((aligned(2))) u32x2_u;
 typedef const TSR_GLOBAL char* gcptr;
 
 constexpr int BK = 32;          // k-tile depth
-constexpr int KP = BK + 8;      // padded LDS row, bf16 elements (80 bytes: 16-byte aligned rows)
+// Place of element (row, k) in an LDS operand.  ROT: rows of 64 bytes that rotate within their group of four, and
+// 16-byte chunks exchanged within the row, both by the group's number; else rows padded to 80 bytes.  Either way
+// sixteen consecutive rows at one k (fragment reads) and eight rows four apart over all k (transposing stores)
+// touch every bank equally.
+template <bool ROT> constexpr int lds_pitch() { return ROT ? BK : BK + 8; }
+// The row is first + row, `first` a multiple of 16.
+template <bool ROT> __device__ inline int lds_at(int first, int row, int k) {
+    if (!ROT) return (first + row) * lds_pitch<ROT>() + k;
+    const int g = row >> 2;
+    return first * BK + ((row & ~3) | ((row + g) & 3)) * BK + ((((k >> 3) ^ g) & 3) << 3) + (k & 7);
+}
 constexpr int NTHREADS = 256;
 
 // ------------------------------------------------------------------ operand staging
@@ -48,12 +60,12 @@ constexpr int NTHREADS = 256;
 //   k-contiguous, fp32: chunks of 4 k (eight lanes cover the 128 bytes of a row), rows 32 apart;
 //   k-contiguous, bf16: chunks of 8 k (four lanes per row), rows 64 apart;
 //   k-strided: a micro-tile of KPT k x 4 rows per thread, the lanes running along k first.
-template <bool KS, bool BF16, int ROWS> struct Operand {
+template <bool KS, bool BF16, int ROWS, bool ROT> struct Operand {
     static constexpr int KPT = KS ? ROWS / 32 : (BF16 ? 8 : 4);       // k values per chunk
     static constexpr int KL = BK / KPT;                               // lanes along k
     static constexpr int NCH = KS ? KPT : ROWS * KL / NTHREADS;       // loads per thread and k-tile
     static constexpr int ESZ = BF16 ? 2 : 4;
-    static constexpr int TILE = ROWS * KP;                            // one piece of one LDS buffer
+    static constexpr int TILE = ROWS * lds_pitch<ROT>();              // one piece of one LDS buffer
     typedef typename std::conditional<BF16, typename std::conditional<KS, u32x2, u32x4>::type, f32x4>::type Reg;
 
     gcptr base;            // first element of the k range; k-contiguous: of the tile's first row
@@ -138,7 +150,7 @@ template <bool KS, bool BF16, int ROWS> struct Operand {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 if (edge && r + j < 0) continue;
-                unsigned short* d = lds + (r + j) * KP + kl * KPT;
+                unsigned short* d = lds + lds_at<ROT>(0, r + j, kl * KPT);
                 if constexpr (BF16) {
                     unsigned h[KPT / 2];
 #pragma unroll
@@ -158,7 +170,7 @@ template <bool KS, bool BF16, int ROWS> struct Operand {
         } else {
 #pragma unroll
             for (int it = 0; it < NCH; ++it) {
-                unsigned short* d = lds + (rl + it * (NTHREADS / KL)) * KP + kl * KPT;
+                unsigned short* d = lds + lds_at<ROT>(it * (NTHREADS / KL), rl, kl * KPT);
                 if constexpr (BF16) {
                     *(u32x4*)d = v[it];
                 } else {
@@ -225,8 +237,13 @@ private:
 // ------------------------------------------------------------------ the kernel
 template <bool A_KS, bool B_KS, bool A_BF16, int NSA, int NSB, int TM, int TN>
 __global__ __launch_bounds__(NTHREADS, 2) void gemm_kernel(const GemmLaunch L) {
-    typedef Operand<A_KS, A_BF16, TM> OpA;
-    typedef Operand<B_KS, false, TN> OpB;
+    constexpr bool KS = A_KS || B_KS;
+    // Three pieces fit twice into LDS (128 x 64 tiles, two workgroups per compute unit) only without padding.  With
+    // fewer the padded rows are the faster ones (fewer address instructions: step of the 60M model in fp32 271
+    // against 288 us, of the embedding and LM head 475 against 537).
+    constexpr bool ROT = KS && (NSA > 2 || NSB > 2);
+    typedef Operand<A_KS, A_BF16, TM, ROT> OpA;
+    typedef Operand<B_KS, false, TN, ROT> OpB;
     constexpr int A_ELEMS = NSA * OpA::TILE, BUF = A_ELEMS + NSB * OpB::TILE;
     constexpr int NBUF = (BUF * 4 <= 80 * 1024) ? 2 : 1;       // two workgroups per compute unit either way
     constexpr int FM = TM / 64, FN = TN / 64;
@@ -234,6 +251,8 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_kernel(const GemmLaunch L) {
     // is fetched behind the first two k-tiles, so that it travels while they are multiplied.  Fetched after the
     // last k-tile -> here: step of a 32000 x 2048 embedding and LM head (rank 128) 557 -> 511 us, of the 60M
     // model in fp32 (rank 256) 310 -> 292 us.  Three pieces leave no registers for it (and nothing uses it there).
+    // The weight update keeps the plain order: its short contraction is behind the read of W, which fills the registers.
+    constexpr bool AHEAD = NBUF == 2 && KS;
     constexpr bool EARLY = !A_KS && !B_KS && NSA <= 2 && NSB <= 2;
     __shared__ __attribute__((aligned(16))) unsigned short lds[NBUF * BUF];
 
@@ -311,12 +330,12 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_kernel(const GemmLaunch L) {
             for (int p = 0; p < NSA; ++p)
 #pragma unroll
                 for (int i = 0; i < FM; ++i)
-                    fa[p][i] = *(const bf16x8*)(sA + p * OpA::TILE + (wm * (TM / 2) + i * 32 + (lane & 31)) * KP + kofs);
+                    fa[p][i] = *(const bf16x8*)(sA + p * OpA::TILE + lds_at<ROT>(wm * (TM / 2) + i * 32, lane & 31, kofs));
 #pragma unroll
             for (int p = 0; p < NSB; ++p)
 #pragma unroll
                 for (int j = 0; j < FN; ++j)
-                    fb[p][j] = *(const bf16x8*)(sB + p * OpB::TILE + (wn * (TN / 2) + j * 32 + (lane & 31)) * KP + kofs);
+                    fb[p][j] = *(const bf16x8*)(sB + p * OpB::TILE + lds_at<ROT>(wn * (TN / 2) + j * 32, lane & 31, kofs));
             // cross products of the pieces, smallest terms first; keep those of total order
             // below max(NSA, NSB)
             constexpr int ORD = (NSA > NSB) ? NSA : NSB;
@@ -346,6 +365,20 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_kernel(const GemmLaunch L) {
         compute(d);
         if constexpr (NBUF == 1) __syncthreads();
     };
+    // AHEAD: tile t is multiplied from its buffer while tile t + 1 is converted and stored into the other one
+    // and its register stage refilled with tile t + 3 (all: tiles up to t + 3 exist and none of them is partial).
+    auto step_ahead = [&](auto slot, auto all, int t) {
+        constexpr int S = decltype(slot)::value;
+        __syncthreads();
+        compute(lds + S * BUF);
+        if (decltype(all)::value || t + 1 < nt) {
+            unsigned short* d = lds + (S ^ 1) * BUF;
+            const bool partial = !decltype(all)::value && (t + 2) * BK > klen;
+            a.template store<NSA>(sa[S ^ 1], d, t + 1, partial, edge_a);
+            b.template store<NSB>(sb[S ^ 1], d + A_ELEMS, t + 1, partial, edge_b);
+        }
+        if (decltype(all)::value || t + 3 < nt) { a.load(sa[S ^ 1], t + 3); b.load(sb[S ^ 1], t + 3); }
+    };
     typedef std::integral_constant<int, 0> S0;
     typedef std::integral_constant<int, 1> S1;
     if (nt > 0) {
@@ -354,17 +387,32 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_kernel(const GemmLaunch L) {
             if (nt > 1) { a.load(sa[1], 1); b.load(sb[1], 1); }
             if constexpr (EARLY) { if (beta != 0.0f) load_old(); }
             int t = 0;
-            for (; t + 3 < nt; t += 2) {
-                step(S0{}, std::true_type{}, t);
-                step(S1{}, std::true_type{}, t + 1);
-            }
-            if (nt - t == 3) {
-                step(S0{}, std::true_type{}, t);
-                step(S1{}, std::false_type{}, t + 1);
-                step(S0{}, std::false_type{}, t + 2);
+            if constexpr (AHEAD) {
+                const bool partial = BK > klen;
+                a.template store<NSA>(sa[0], lds, 0, partial, edge_a);
+                b.template store<NSB>(sb[0], lds + A_ELEMS, 0, partial, edge_b);
+                if (nt > 2) { a.load(sa[0], 2); b.load(sb[0], 2); }
+                for (; t + 4 < nt; t += 2) {
+                    step_ahead(S0{}, std::true_type{}, t);
+                    step_ahead(S1{}, std::true_type{}, t + 1);
+                }
+                for (; t < nt; t += 2) {                       // the last one to four
+                    step_ahead(S0{}, std::false_type{}, t);
+                    if (t + 1 < nt) step_ahead(S1{}, std::false_type{}, t + 1);
+                }
             } else {
-                step(S0{}, std::false_type{}, t);
-                if (nt - t == 2) step(S1{}, std::false_type{}, t + 1);
+                for (; t + 3 < nt; t += 2) {
+                    step(S0{}, std::true_type{}, t);
+                    step(S1{}, std::true_type{}, t + 1);
+                }
+                if (nt - t == 3) {
+                    step(S0{}, std::true_type{}, t);
+                    step(S1{}, std::false_type{}, t + 1);
+                    step(S0{}, std::false_type{}, t + 2);
+                } else {
+                    step(S0{}, std::false_type{}, t);
+                    if (nt - t == 2) step(S1{}, std::false_type{}, t + 1);
+                }
             }
         } else {
             for (int t = 0; t < nt; ++t) {
