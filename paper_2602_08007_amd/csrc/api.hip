@@ -493,7 +493,7 @@ void build_refresh(RefreshProgram& rp, const std::vector<BlockView>& views, cons
         b.XrT = ar.take<float>((size_t)b.r * k); b.GrT = ar.take<float>((size_t)b.r * k);
         b.work = ar.take<double>(2 * k * k + 64); b.R1 = ar.take<double>(k * k); b.Rmid = ar.take<double>(k * k);
         b.Rtot = ar.take<double>(k * k); b.Gacc = ar.take<double>(k * k);
-        b.eig = (b.k <= EIG_MAXK) ? ar.take<double>(3 * k * k + 3 * k + 8) : nullptr;
+        b.eig = (b.k <= EIG_MAXK) ? ar.take<double>(eig_scratch_doubles(b.k)) : nullptr;
         if (allow_nt && nt_refresh_eligible(v, b.k)) {
             b.nt = true;
             b.ldm = (b.m + 7) / 8 * 8; b.ldn = (b.n + 7) / 8 * 8;

@@ -309,7 +309,7 @@ __global__ __launch_bounds__(EIG_THREADS) void eig_tridiag_kernel(const JacobiBl
         for (int i = lane; i <= c; i += 64) row[i] -= vc * pw_[i] + wc * pv_[i];
     }
     // the tridiagonal matrix travels to the next launches behind the LU scratch
-    double* DE = blk->scratch + (size_t)3 * k * k;
+    double* DE = blk->scratch + eig_tridiag_at(k);
     for (int i = tid; i < stop; i += nt) { DE[i] = s_d[i]; DE[k + i] = s_e[i]; }
 }
 
@@ -581,15 +581,14 @@ __global__ __launch_bounds__(64 * WAVES, 1) void eig_tridiag_tiles_kernel(const 
         s_e[k - 1] = 0.0;
     }
     eig_lds_barrier();
-    double* DE = jb.scratch + (size_t)3 * kfull * kfull;
+    double* DE = jb.scratch + eig_tridiag_at(kfull);
     for (int i = tid; i < k; i += 64 * WAVES) { DE[first + i] = s_d[i]; DE[kfull + first + i] = s_e[i]; }
 }
 
 // Eigenvalues and eigenvectors of the tridiagonal matrix (d, e) left by eig_tridiag_kernel, in
 // three launches: eigenvalues (chip-wide), inverse iteration (one wave per workgroup),
 // orthogonalisation inside groups of numerically equal eigenvalues (one workgroup per matrix).
-// Behind the LU scratch (3 k^2 doubles) sit d (k), e (k), the eigenvalues (k, ascending) and the
-// radius of the spectrum's bracket (1; zero marks a zero or non-finite matrix).
+// The scratch is laid out by eig_layout.h; a radius of zero marks a zero or non-finite matrix.
 
 // Sturm-count multisection: 2^LP threads of a workgroup share an eigenvalue; their 2^LP - 1 probes cut its
 // bracket into 2^LP pieces per pass, and the number of eigenvalues below a probe tells on which side of it the
@@ -612,8 +611,8 @@ __global__ __launch_bounds__(256) void eig_values_kernel(const JacobiBlock* tabl
     const int k = blk->k;
     const int e0 = gc * PER_WG;
     if (e0 >= k) return;
-    const double* DE = blk->scratch + (size_t)3 * k * k;
-    double* LAM = blk->scratch + (size_t)3 * k * k + 2 * k;
+    const double* DE = blk->scratch + eig_tridiag_at(k);
+    double* LAM = blk->scratch + eig_tridiag_at(k) + 2 * k;
     const int tid = threadIdx.x, nt = blockDim.x;
     const int lane = tid & 63, wave = tid >> 6, nw = nt >> 6;
     typedef double d2_t __attribute__((ext_vector_type(2)));
@@ -724,7 +723,7 @@ __global__ __launch_bounds__(64) void eig_invit_kernel(const JacobiBlock* table,
     gdouble* U1 = U0 + (size_t)k * k;           //   super-diagonal of the LU factor, entry [i][j]
     gdouble* U2 = U1 + (size_t)k * k;
     gdouble* LM = (gdouble*)jb.Gacc;            // multipliers (Gacc receives the eigenvectors later)
-    const double* DE = jb.scratch + (size_t)3 * k * k;
+    const double* DE = jb.scratch + eig_tridiag_at(k);
     const double* LAM = DE + 2 * k;
     const int tid = threadIdx.x;
     const int j = gc * 64 + tid;
@@ -867,7 +866,7 @@ __global__ __launch_bounds__(EIG_THREADS) void eig_groups_kernel(const JacobiBlo
     const JacobiBlock* blk = &jb;
     const int k = blk->k;
     double* Z = blk->tmp + (size_t)k * k;
-    const double* LAM = blk->scratch + (size_t)3 * k * k + 2 * k;
+    const double* LAM = blk->scratch + eig_tridiag_at(k) + 2 * k;
     const int tid = threadIdx.x, nt = blockDim.x;
     const int lane = tid & 63, wave = tid >> 6, nw = nt >> 6;
     __shared__ double s_v[EIG_MAXK];            // eigenvalues, ascending
@@ -937,6 +936,7 @@ __global__ __launch_bounds__(EIG_THREADS) void eig_groups_kernel(const JacobiBlo
 // E = H_0 H_1 ... H_{k-3} Z in blocks of sixteen reflectors, H_j0 ... H_j0+15 = I - V T V^T (compact WY form), so
 // that the work is products on fp64 MFMAs.  First launch: the triangular factors T of all blocks, one wave each:
 // T(:,r) = -beta_r T (V^T v_r) above the diagonal, beta_r on it; they take the place of the LU factors.
+// (Only the rows and columns of reflectors that exist are stored; see eig_wy_at.)
 __device__ inline bool eig_has_reflector(int j, int k) { return j + 2 < k; }
 __global__ __launch_bounds__(64) void eig_wy_kernel(const JacobiBlock* table, const JacobiBlock single, const EigGrid grid) {
     JacobiBlock jb = single;
@@ -982,10 +982,12 @@ __global__ __launch_bounds__(64) void eig_wy_kernel(const JacobiBlock* table, co
         const double br = s_beta[r];
         x[r] = (li < r) ? -br * sum : (li == r) ? br : 0.0;
     }
-    gdouble* out = (gdouble*)jb.scratch + (size_t)b * 256;
-    if (lk == 0) {
+    gdouble* out = (gdouble*)jb.scratch;
+    const int rank = eig_wy_rank(k, b);
+    if (lk == 0 && li < rank) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) out[li * 16 + r] = x[r];
+        for (int r = 0; r < 16; ++r)
+            if (r < rank) out[eig_wy_at(b, li, r)] = x[r];
     }
 }
 
@@ -1039,7 +1041,7 @@ __global__ __launch_bounds__(256, 1) void eig_backtransform_kernel(const JacobiB
             }
         }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) tn[q] = TF[(size_t)b * 256 + li * 16 + 4 * q + lk];
+        for (int q = 0; q < 4; ++q) tn[q] = (li < eig_wy_rank(k, b) && 4 * q + lk < eig_wy_rank(k, b)) ? TF[eig_wy_at(b, li, 4 * q + lk)] : 0.0;
     };
     const int last = (k >= 3) ? (k - 3) / 16 : -1;
     if (last >= 0) fetch(last);
@@ -1135,7 +1137,7 @@ __global__ __launch_bounds__(256) void eig_norms_kernel(const JacobiBlock* table
     double a = 0.0;
     for (int c = lane; c < k; c += 64) a = fma(row[c], row[c], a);
     a = eig_wave_sum_dpp(a);
-    if (lane == 0) jb.scratch[(size_t)3 * k * k + j] = sqrt(a);      // (the tridiagonal matrix is not needed any more)
+    if (lane == 0) jb.scratch[eig_tridiag_at(k) + j] = sqrt(a);      // (the tridiagonal matrix is not needed any more)
 }
 
 // ... and every wave then finds the place of its row among them and writes the row's outputs.
@@ -1151,7 +1153,7 @@ __global__ __launch_bounds__(256) void eig_finish_kernel(const JacobiBlock* tabl
     typedef float __attribute__((address_space(1))) gfloat;
     cgdouble* ER = (cgdouble*)jb.tmp + (size_t)k * k + (size_t)j * k;
     cgdouble* E = (cgdouble*)jb.Gacc + (size_t)j * k;
-    cgdouble* sig = (cgdouble*)jb.scratch + (size_t)3 * k * k;
+    cgdouble* sig = (cgdouble*)jb.scratch + eig_tridiag_at(k);
     const double sj = sig[j];
     int rank = 0;                                            // descending, ties by index
     for (int i = lane; i < k; i += 64) {

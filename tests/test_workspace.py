@@ -1,0 +1,155 @@
+"""What the library keeps in the caller's workspace stays inside it."""
+import os
+import shutil
+import subprocess
+
+import pytest
+import torch
+
+import synth_inputs as si
+from oracle import tsr_oracle as orc
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2602_08007_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def tsr():
+    import paper_2602_08007_amd as t
+    return t
+
+
+# ------------------------------------------------------------------ scratch of the small SVD (host)
+EIG_LAYOUT_CHECK = r"""
+#include <cstdio>
+#include "eig_layout.h"
+int main() {
+    for (int k = 1; k <= 544; ++k) {
+        size_t end = (size_t)3 * k * k;                       // the LU factors' last entry, and where d begins
+        if (tsr::eig_tridiag_at(k) < end) { printf("k = %d: the tridiagonal matrix lies in the LU factors\n", k); return 1; }
+        int reflectors = 0;
+        for (int b = 0; 16 * b < k; ++b) {
+            const int rank = tsr::eig_wy_rank(k, b);
+            if (rank < 0 || rank > 16) return 2;
+            reflectors += rank;
+            for (int row = 0; row < rank; ++row)
+                for (int col = 0; col < rank; ++col)
+                    if (tsr::eig_wy_at(b, row, col) >= tsr::eig_tridiag_at(k)) {
+                        printf("k = %d: entry (%d, %d) of factor %d lies outside\n", k, row, col, b);
+                        return 3;
+                    }
+        }
+        if (reflectors != (k > 2 ? k - 2 : 0)) { printf("k = %d: %d reflectors\n", k, reflectors); return 4; }
+        // d, e, eigenvalues, radius
+        if (tsr::eig_scratch_doubles(k) < tsr::eig_tridiag_at(k) + 3 * (size_t)k + 1) return 5;
+    }
+    return 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_small_svd_scratch_holds_what_is_indexed(tmp_path):
+    src, exe = tmp_path / "check.cpp", tmp_path / "check"
+    src.write_text(EIG_LAYOUT_CHECK)
+    build = subprocess.run(["g++", "-std=c++17", "-Wall", "-I", CSRC, "-o", str(exe), str(src)], capture_output=True, text=True)
+    assert build.returncode == 0, build.stderr
+    run = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert run.returncode == 0, run.stdout
+
+
+# ------------------------------------------------------------------ bytes behind the workspace (GPU)
+SENTINEL = 0x5A
+TAIL = 8192
+
+
+class Guarded:
+    """A workspace of exactly nbytes with sentinel bytes behind it."""
+
+    def __init__(self, nbytes):
+        self.buf = torch.full((nbytes + TAIL,), SENTINEL, dtype=torch.uint8, device="cuda")
+        self.ws = self.buf[:nbytes]
+
+    def check(self):
+        assert bool((self.buf[self.ws.numel():] == SENTINEL).all()), "bytes behind the workspace were written"
+
+
+# One product in two bf16 pieces (the second of the three orthonormalisation passes) enters Q R = X undiminished:
+# off by at most 3 x 2^-17 of |a||b| (second pieces up to 2^-17 of the first, their product dropped).  Long sums
+# average it out; here a sum has one to seventeen terms.
+TWO_PIECES = 3 * 2.0 ** -17
+
+
+def _check_bases(G, U, V, sigma=None):
+    """Singular values and bases of a sketch that spans everything: that product, and fp32 sums of k terms (off by
+    k x 2^-24 of the sum of their sizes, four in a row)."""
+    k, r = min(G.shape), U.shape[1]
+    s = torch.linalg.svdvals(G.double())
+    U64, V64 = U.cpu().double(), V.cpu().double()
+    eye = torch.eye(r, dtype=torch.float64)
+    if sigma is not None:
+        assert float((sigma.cpu().double()[:k] - s).abs().max() / s[0]) < TWO_PIECES + (k + 4) * 2.0 ** -22
+    for X in (U64, V64):
+        assert float(torch.linalg.norm(X.T @ X - eye)) < 2.0 ** -20 * max(k, 4)
+    core = U64.T @ G.double() @ V64
+    assert float(torch.linalg.norm(core - torch.diag(s[:r])) / torch.linalg.norm(s)) < TWO_PIECES + 2e-5
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("k", list(range(1, 10)) + [15, 16, 17, 81, 145, 273, 289, 544])
+def test_refresh_stays_in_its_workspace(tsr, k):
+    p = min(2, k - 1)
+    r, m, n = k - p, k, k + 9
+    key = si.stream_key(811, k)
+    G = si.normal((m, n), si.stream_key(key, 1))
+    om = si.omega(n, k, si.stream_key(key, 2)).cuda()
+    new = lambda: (torch.full((m, r), float("nan"), device="cuda"), torch.full((n, r), float("nan"), device="cuda"),  # noqa: E731
+                   torch.full((k,), float("nan"), device="cuda"))
+    g = Guarded(tsr.tsr_refresh_workspace_bytes(m, n, r, p))
+    U, V, sigma = new()
+    tsr.tsr_refresh_rsvd(G.cuda(), om, r, p, 1, U, V, sigma, ws=g.ws)
+    g.check()
+    _check_bases(G, U, V, sigma)
+    g = Guarded(tsr.tsr_refresh_workers_workspace_bytes(m, n, r, p, 2))
+    U, V, sigma = new()
+    tsr.tsr_refresh_rsvd_workers(torch.stack([G, G]).cuda(), om, r, p, 1, U, V, sigma, ws=g.ws)
+    g.check()
+    _check_bases(G, U, V, sigma)
+    for A in (G, torch.empty(n, m).copy_(G.T)):
+        g = Guarded(tsr.tsr_refresh_exact_workspace_bytes(*A.shape, r))
+        U, V, sigma = new()
+        if A.shape != G.shape:
+            U, V = V, U
+        tsr.tsr_refresh_exact_svd(A.cuda(), r, U, V, sigma, ws=g.ws)
+        g.check()
+        _check_bases(A, U, V, sigma)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("groups", [1, 3])
+def test_plan_of_tiny_blocks_refreshes_then_steps(tsr, groups, monkeypatch):
+    """Sketches of 3 to 9 columns beside each other in one plan: bases of every block, and the following step
+    against the oracle (its tables and the other blocks' buffers lie behind each block's scratch)."""
+    monkeypatch.setenv("TSR_TUNE_REFRESH_GROUPS", str(groups))
+    p, q, dims = 2, 1, [(k, k + 9) for k in range(3, 10)] * 2
+    blocks, omegas, grads = [], [], []
+    for i, (m, n) in enumerate(dims):
+        key, r = si.stream_key(812, i), m - p
+        G = si.normal((m, n), si.stream_key(key, 1))
+        grads.append(G)
+        z = lambda *s: torch.zeros(*s, device="cuda")  # noqa: E731
+        blocks.append(dict(G=G.cuda(), W=z(m, n), U=z(m, r), V=z(n, r), M=z(r, r), Vm=z(r, r), C=z(r, r), D=z(r, r)))
+        omegas.append(si.omega(n, m, si.stream_key(key, 2)).cuda())
+    plan = tsr.Plan(blocks, with_refresh=True, p=p)
+    plan.tsr_refresh_batched(omegas, q)
+    plan.tsr_step_batched(1, lr=1.0, eps=1.0)
+    torch.cuda.synchronize()
+    for G, b in zip(grads, blocks):
+        _check_bases(G, b["U"], b["V"])
+        C = orc.project_core(G, orc.f64(b["U"]), orc.f64(b["V"]))
+        scale = float(abs(C).max())
+        assert float(abs(orc.f64(b["C"]) - C).max()) < 1e-4 * scale
+        # first Adam step from zero moments, eps = 1: D = C / (|C| + 1); then W = -U D V^T
+        W = -orc.f64(b["U"]) @ (C / (abs(C) + 1.0)) @ orc.f64(b["V"]).T
+        assert float(abs(orc.f64(b["W"]) - W).max()) < 1e-4 * float(abs(W).max())
+
