@@ -109,7 +109,7 @@ void build_stage(GemmStage& st, const GemmVariant& var, const std::vector<Logica
         // [i, e) = consecutive gemms summed into one output; their partials are one buffer
         size_t e = i + 1;
         while (e < gemms.size() && gemms[i].group >= 0 && gemms[e].group == gemms[i].group) ++e;
-        const size_t mn = ((size_t)gemms[i].M * gemms[i].N + 3) / 4 * 4;   // partials start on 16-byte boundaries
+        const size_t mn = (size_t)gemms[i].M * gemms[i].N;
         float* part = nullptr;
         int group_splits = 0;
         if (!st.direct) {

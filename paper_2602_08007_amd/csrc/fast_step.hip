@@ -151,7 +151,7 @@ void build_nt_stage(NtStageH& st, const NtVariant& var, const std::vector<NtLogi
     while (i < gemms.size()) {
         size_t e = i + 1;
         while (e < gemms.size() && gemms[i].group >= 0 && gemms[e].group == gemms[i].group) ++e;
-        const size_t mn = ((size_t)gemms[i].M * gemms[i].N + 3) / 4 * 4;   // partials start on 16-byte boundaries
+        const size_t mn = (size_t)gemms[i].M * gemms[i].N;
         float* part = nullptr;
         if (!direct) {
             int gs = 0;

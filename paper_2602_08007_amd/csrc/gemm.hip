@@ -495,7 +495,6 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceProblem*
     const long long total = (long long)p.M * p.N;
     const bool dense = p.ldc == p.N;
     const long long nv = total / 4;                           // whole vectors; the last elements one by one
-    const bool vec = (p.stride % 4) == 0 || p.splits == 1;    // partials on 16-byte boundaries
     auto finish = [&](long long i, float s) {
         const long long o = dense ? i : (long long)((unsigned long long)i / (unsigned)p.N) * p.ldc + (long long)((unsigned long long)i % (unsigned)p.N);
         float v = alpha * s;
@@ -504,32 +503,30 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceProblem*
     };
     const long long step = (long long)gridDim.x * blockDim.x;
     const long long me = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (vec) {
-        for (long long q = me; q < nv; q += step) {
-            const TSR_GLOBAL f32x4* src = (const TSR_GLOBAL f32x4*)(part + 4 * q);
-            const long long st = p.stride / 4;
-            f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
-            int k = 0;
-            for (; k + 8 <= p.splits; k += 8) {
-                f32x4 x[8];
+    for (long long q = me; q < nv; q += step) {
+        // (the stride between partials is M x N: 16-byte loads at any element)
+        const TSR_GLOBAL float* src = part + 4 * q;
+        f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+        int k = 0;
+        for (; k + 8 <= p.splits; k += 8) {
+            f32x4 x[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) x[u] = src[(k + u) * st];
+            for (int u = 0; u < 8; ++u) x[u] = *(const TSR_GLOBAL f32x4_u*)(src + (k + u) * p.stride);
 #pragma unroll
-                for (int u = 0; u < 8; ++u) s += x[u];
-            }
-            for (; k < p.splits; ++k) s += src[k * st];
-            if (dense) {
-                f32x4 v = alpha * s;
-                TSR_GLOBAL f32x4_u* o = (TSR_GLOBAL f32x4_u*)(out + 4 * q);
-                if (beta != 0.0f) v += beta * (f32x4)*o;
-                *o = v;
-            } else {
+            for (int u = 0; u < 8; ++u) s += x[u];
+        }
+        for (; k < p.splits; ++k) s += *(const TSR_GLOBAL f32x4_u*)(src + k * p.stride);
+        if (dense) {
+            f32x4 v = alpha * s;
+            TSR_GLOBAL f32x4_u* o = (TSR_GLOBAL f32x4_u*)(out + 4 * q);
+            if (beta != 0.0f) v += beta * (f32x4)*o;
+            *o = v;
+        } else {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) finish(4 * q + u, s[u]);
-            }
+            for (int u = 0; u < 4; ++u) finish(4 * q + u, s[u]);
         }
     }
-    for (long long i = (vec ? 4 * nv : 0) + me; i < total; i += step) {
+    for (long long i = 4 * nv + me; i < total; i += step) {
         float s = 0.0f;
         for (int k = 0; k < p.splits; ++k) s += part[(long long)k * p.stride + i];
         finish(i, s);

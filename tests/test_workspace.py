@@ -153,3 +153,50 @@ def test_plan_of_tiny_blocks_refreshes_then_steps(tsr, groups, monkeypatch):
         W = -orc.f64(b["U"]) @ (C / (abs(C) + 1.0)) @ orc.f64(b["V"]).T
         assert float(abs(orc.f64(b["W"]) - W).max()) < 1e-4 * float(abs(W).max())
 
+
+
+# ------------------------------------------------------------------ the built-in scratch (host, GPU)
+def _arena(*sizes):
+    """Bytes of buffers of these sizes, each on a 256-byte boundary."""
+    return sum((s + 255) // 256 * 256 for s in sizes)
+
+
+def _partials(m, n, k, want_tiles=512):
+    """fp32 partial results of an m x n product over k: 128 x 128 tiles, k cut into pieces of at least 256 until
+    there are `want_tiles` of them."""
+    tiles = -(-m // 128) * -(-n // 128)
+    s = min(max(1, want_tiles // tiles), max(1, k // 256))
+    s = -(-k // (-(-(-(-k // s)) // 32) * 32))
+    return 4 * m * n * s if s > 1 else 0
+
+
+def _project_bytes(m, n, r):
+    return _arena(4 * m * r, _partials(m, r, n), _partials(r, r, m))
+
+
+# odd products that fill the 16 MiB to the last kilobyte
+EDGES = [(9961, 1000, 97), (13118, 1000, 75), (13952, 300, 183), (19876, 300, 141), (40360, 300, 81)]
+
+
+def test_static_scratch_takes_what_fits_it(tsr):
+    limit = tsr.TSR_PROJECT_STATIC_SCRATCH_BYTES
+    shapes = list(EDGES)
+    for n, r in ((1000, 97), (1000, 75), (300, 183), (777, 33), (5000, 61), (2500, 255)):
+        shapes += [(m, n, r) for m in range(r, limit // (4 * r), 3)]
+    taken = [s for s in shapes if 0.98 * limit < _project_bytes(*s) <= limit]
+    assert set(EDGES) <= set(taken) and len(taken) > 300
+    refused = [s for s in taken if tsr.tsr_project_workspace_bytes(*s) > limit]
+    assert not refused, refused[:5]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,r", EDGES[1:3])
+def test_static_scratch_at_its_limit(tsr, m, n, r):
+    key = si.stream_key(813, m)
+    G = si.normal((m, n), si.stream_key(key, 1))
+    U, V = si.orthonormal(m, r, si.stream_key(key, 2)).float(), si.orthonormal(n, r, si.stream_key(key, 3)).float()
+    C = torch.full((r, r), float("nan"), device="cuda")
+    tsr.tsr_project_core_static(G.cuda(), U.cuda(), V.cuda(), C)
+    ref = U.double().T @ (G.double() @ V.double())
+    # two products in two bf16 pieces; the core of a white gradient is sqrt(r / min(m, n)) of what the sums hold
+    assert float(torch.linalg.norm(C.cpu().double() - ref) / torch.linalg.norm(ref)) < 2 * TWO_PIECES * (min(m, n) / r) ** 0.5
