@@ -24,7 +24,10 @@
  *     (leading dimension = number of columns).
  *   - Every data pointer is a DEVICE pointer unless the comment says "host".  The caller
  *     owns every buffer, including the workspace; the library allocates no device memory
- *     and keeps no hidden device state.  Workspaces must be 256-byte aligned.
+ *     and keeps no hidden device state.  Workspaces must be 256-byte aligned.  A workspace
+ *     query returns what the fastest form of the call takes; in a smaller workspace the call
+ *     cuts its contractions into fewer pieces (down to about a tenth of the size, and slower),
+ *     and only where that does not fit either is it refused with TSR_WORKSPACE_TOO_SMALL.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Calls only
  *     enqueue work on that stream and return; results are ready once the stream has
  *     drained.  Calls on one stream are ordered.

@@ -73,15 +73,16 @@ int pick_shape(const std::vector<LogicalGemm>& gemms, int want_tiles) {
 
 // Decide k-splits, carve partial buffers from `ar`, and list the tiles.
 // want_tiles: keep splitting k while the launch has fewer tiles than this.
-// coarse_k: lower bound of the k pieces in place of the built-in one (fewer partials, less workspace).
+// In a tight arena k is cut into pieces of at least 256, which is the split of the smallest workspace (partials
+// are what a program's size hangs on), and tiles that are listed there are the largest.
 // lower_only: the outputs are symmetric and only tiles on or below the diagonal are computed
 // (the rest of the output is left unwritten).
 void build_stage(GemmStage& st, const GemmVariant& var, const std::vector<LogicalGemm>& gemms, Arena& ar,
-                 int want_tiles = 512, bool lower_only = false, int coarse_k = 0) {
+                 int want_tiles = 512, bool lower_only = false) {
     st = GemmStage{};
     st.var = var;
     if (gemms.empty()) return;
-    st.var.shape = pick_shape(gemms, want_tiles);
+    st.var.shape = (ar.tight && ar.tables) ? (int)GEMM_128x128 : pick_shape(gemms, want_tiles);
     const int TM = gemm_tile_m(st.var.shape), TN = gemm_tile_n(st.var.shape);
     long long base_tiles = 0;
     bool shared_out = false;
@@ -94,8 +95,8 @@ void build_stage(GemmStage& st, const GemmVariant& var, const std::vector<Logica
     bool any_split = false;
     for (size_t i = 0; i < gemms.size(); ++i) {
         const int K = gemms[i].K;
-        // pieces of at least 128 (64 where that leaves most of the chip idle), or what the caller asks for
-        const int least = coarse_k ? coarse_k : (base_tiles * (K / 128) < 256) ? 64 : 128;
+        // pieces of at least 128 (64 where that leaves most of the chip idle)
+        const int least = ar.tight ? 256 : (base_tiles * (K / 128) < 256) ? 64 : 128;
         int s = std::min(want_split, std::max(1, K / least));
         int chunk = ceil_div(ceil_div(K, s), 32) * 32;
         s = ceil_div(K, chunk);
@@ -202,8 +203,7 @@ struct ProjectProgram {
 };
 
 // P buffers: one m x r fp32 per (block, worker), carved from `ar`.
-void build_project(ProjectProgram& pg, const std::vector<BlockView>& blocks, int n_workers, int prec, Arena& ar,
-                   int coarse_k = 0) {
+void build_project(ProjectProgram& pg, const std::vector<BlockView>& blocks, int n_workers, int prec, Arena& ar) {
     std::vector<LogicalGemm> gv[2], utp;
     int group = 0;
     for (const BlockView& b : blocks) {
@@ -217,20 +217,29 @@ void build_project(ProjectProgram& pg, const std::vector<BlockView>& blocks, int
         }
     }
     const int pv = (prec == TSR_PREC_BF16) ? 1 : 2;
-    build_stage(pg.gv[TSR_F32], variant(0, 1, 0, pv, pv), gv[TSR_F32], ar, 512, false, coarse_k);
-    build_stage(pg.gv[TSR_BF16], variant(0, 1, 1, 1, pv), gv[TSR_BF16], ar, 512, false, coarse_k);
-    build_stage(pg.utp, variant(1, 1, 0, pv, pv), utp, ar, 512, false, coarse_k);
+    build_stage(pg.gv[TSR_F32], variant(0, 1, 0, pv, pv), gv[TSR_F32], ar);
+    build_stage(pg.gv[TSR_BF16], variant(0, 1, 1, 1, pv), gv[TSR_BF16], ar);
+    build_stage(pg.utp, variant(1, 1, 0, pv, pv), utp, ar);
 }
 
-// The program of one matrix (the single calls).  Where the partial cores of the fine k split would take
-// the workspace beyond the built-in scratch of tsr_project_core_static, k is cut into pieces of 256.
-void build_project_one(ProjectProgram& pg, const std::vector<BlockView>& block, int prec, Arena& ar) {
-    Arena probe(nullptr);
-    build_project(pg, block, 1, prec, probe);
-    const int coarse_k = probe.used() > (size_t)TSR_PROJECT_STATIC_SCRATCH_BYTES ? 256 : 0;
-    if (ar.base == nullptr && coarse_k == 0) { ar.off += probe.used(); return; }
-    pg = ProjectProgram{};
-    build_project(pg, block, 1, prec, ar, coarse_k);
+// A single call's program, in the caller's workspace: building it writes nothing there, so it is sized by being
+// built.  Where it does not fit into `most` bytes it is built tight.
+template <typename Build> int build_within(void* ws, size_t ws_bytes, size_t most, Build&& build) {
+    for (const bool tight : {false, true}) {
+        Arena ar(ws, tight);
+        build(ar);
+        if (ar.used() <= (tight ? ws_bytes : std::min(most, ws_bytes))) return TSR_OK;
+    }
+    return TSR_WORKSPACE_TOO_SMALL;
+}
+
+// The program of one matrix.  Beyond the built-in scratch of tsr_project_core_static it is tight in any case, so
+// that this entry point takes what fits there and computes the same bits as tsr_project_core.
+int build_project_one(ProjectProgram& pg, const std::vector<BlockView>& block, int prec, void* ws, size_t ws_bytes) {
+    return build_within(ws, ws_bytes, (size_t)TSR_PROJECT_STATIC_SCRATCH_BYTES, [&](Arena& ar) {
+        pg = ProjectProgram{};
+        build_project(pg, block, 1, prec, ar);
+    });
 }
 
 int run_project(const ProjectProgram& pg, bool grouped, float alpha, float beta, Ctx& cx) {
@@ -356,8 +365,8 @@ void build_orth_nt(OrthNtPass& pass, const std::vector<RefreshBlock>& blocks, bo
         unsigned short* Xt = on_rows_m ? b.Pm : b.Pn;            // pieces of X^T (k x ldrows)
         const long long ldrows = on_rows_m ? b.ldm : b.ldn, st_t = (long long)k * ldrows;
         const long long ld2 = 2 * b.ldk, st_r = (long long)k * ld2;      // rows of two pieces side by side
-        pass.sx.push_back(SplitBlock{in, Xt, ldrows, st_t, rows, k, nullptr, b.Xp, ld2, b.ldk});
-        pass.sr.push_back(SplitBlock{b.Rinv, b.Rt, ld2, st_r, k, k, b.Rt + b.ldk});
+        pass.sx.push_back(SplitBlock{in, Xt, st_t, (int)ldrows, rows, k, (int)ld2, nullptr, b.Xp, b.ldk});
+        pass.sr.push_back(SplitBlock{b.Rinv, b.Rt, st_r, (int)ld2, k, k, 0, b.Rt + b.ldk});
         const int bi = (int)i;
         g.push_back(NtLogical{Xt, Xt, b.S, ldrows, ldrows, k, k, k, rows, bi, bi});
         g.push_back(NtLogical{Xt + st_t, Xt, b.S, ldrows, ldrows, k, k, k, rows, bi, bi});
@@ -522,9 +531,9 @@ void build_refresh_stages(RefreshProgram& rp, const float* const* omegas, Arena&
             NtRefresh& f = rp.nt;
             const long long sn = (long long)b.k * b.ldn, sm = (long long)b.k * b.ldm;
             f.gt.push_back(TransposeBlock{b.G, b.Gt, b.ldg, b.ldm, b.m, b.n});
-            f.s_om.push_back(SplitBlock{om, b.Pn, b.ldn, sn, b.n, b.k});
-            f.s_qrow.push_back(SplitBlock{b.Zalt, b.Pn, b.ldn, sn, b.n, b.k});
-            f.s_q.push_back(SplitBlock{b.Yalt, b.Pm, b.ldm, sm, b.m, b.k});
+            f.s_om.push_back(SplitBlock{om, b.Pn, sn, (int)b.ldn, b.n, b.k});
+            f.s_qrow.push_back(SplitBlock{b.Zalt, b.Pn, sn, (int)b.ldn, b.n, b.k});
+            f.s_q.push_back(SplitBlock{b.Yalt, b.Pm, sm, (int)b.ldm, b.m, b.k});
             ntg.push_back(NtLogical{b.G, b.Pn, b.Y, b.ldg, b.ldn, b.k, b.m, b.k, b.n, (int)i, -1, sn});
             ntgt.push_back(NtLogical{b.Gt, b.Pm, b.Z, b.ldm, b.ldm, b.k, b.n, b.k, b.m, (int)i, -1, sm});
             f.max_m = std::max(f.max_m, b.m); f.max_n = std::max(f.max_n, b.n); f.max_k = std::max(f.max_k, b.k);
@@ -738,10 +747,15 @@ size_t tsr_project_workspace_bytes(int m, int n, int r) {
     if (check_block(m, n, r) != TSR_OK) return 0;
     std::vector<BlockView> v;
     one_block_view(v, nullptr, TSR_F32, m, n, r, n, nullptr, n, nullptr, nullptr, nullptr, nullptr);
-    Arena ar(nullptr);
-    ProjectProgram pg;
-    build_project_one(pg, v, TSR_PREC_SPLIT, ar);
-    return ar.used();
+    size_t need = 0;
+    for (const bool tight : {false, true}) {
+        Arena ar(nullptr, tight);
+        ProjectProgram pg;
+        build_project(pg, v, 1, TSR_PREC_SPLIT, ar);
+        need = ar.used();
+        if (need <= (size_t)TSR_PROJECT_STATIC_SCRATCH_BYTES) break;
+    }
+    return need;
 }
 
 int tsr_project_core(const void* G, int g_dtype, int m, int n, long long ldg, const float* U, const float* V,
@@ -753,12 +767,10 @@ int tsr_project_core(const void* G, int g_dtype, int m, int n, long long ldg, co
     if (!G || !U || !V || !C || !ws) return TSR_INVALID_ARG;
     if (ldg < n) return TSR_BAD_SHAPE;
     if (!aligned256(ws)) return TSR_INVALID_ARG;
-    if (ws_bytes < tsr_project_workspace_bytes(m, n, r)) return TSR_WORKSPACE_TOO_SMALL;
     std::vector<BlockView> v;
     one_block_view(v, G, g_dtype, m, n, r, ldg, nullptr, n, (float*)U, (float*)V, C, nullptr);
-    Arena ar(ws);
     ProjectProgram pg;
-    build_project_one(pg, v, precision, ar);
+    TSR_TRY(build_project_one(pg, v, precision, ws, ws_bytes));
     Ctx cx{(hipStream_t)stream, nullptr};
     return run_project(pg, false, alpha, accumulate ? 1.0f : 0.0f, cx);
 }
@@ -809,9 +821,8 @@ int tsr_project_core_static(const void* G, int g_dtype, int m, int n, long long 
     // written earlier in the same call: nothing has to start at zero, so nothing is cleared
     std::vector<BlockView> v;
     one_block_view(v, G, g_dtype, m, n, r, ldg, nullptr, n, (float*)U, (float*)V, C, nullptr);
-    Arena ar(ws);
     ProjectProgram pg;
-    build_project_one(pg, v, precision, ar);
+    TSR_TRY(build_project_one(pg, v, precision, ws, TSR_PROJECT_STATIC_SCRATCH_BYTES));
     Ctx cx{(hipStream_t)stream, nullptr};
     return run_project(pg, false, alpha, accumulate ? 1.0f : 0.0f, cx);
 }
@@ -881,12 +892,10 @@ int tsr_backproject_apply(float* W, int m, int n, long long ldw, const float* U,
     if (!W || !U || !V || !D || !ws) return TSR_INVALID_ARG;
     if (ldw < n) return TSR_BAD_SHAPE;
     if (!aligned256(ws)) return TSR_INVALID_ARG;
-    if (ws_bytes < tsr_backproject_workspace_bytes(m, n, r)) return TSR_WORKSPACE_TOO_SMALL;
     std::vector<BlockView> v;
     one_block_view(v, nullptr, TSR_F32, m, n, r, n, W, ldw, (float*)U, (float*)V, nullptr, (float*)D);
-    Arena ar(ws);
     LiftProgram lp;
-    build_lift(lp, v, precision, ar);
+    TSR_TRY(build_within(ws, ws_bytes, ws_bytes, [&](Arena& ar) { build_lift(lp, v, precision, ar); }));
     Ctx cx{(hipStream_t)stream, nullptr};
     return run_lift(lp, false, lr, wd, scale, cx);
 }
@@ -910,14 +919,12 @@ int tsr_refresh_rsvd(const void* G, int g_dtype, int m, int n, long long ldg, co
     if (!G || !Omega || !U || !V || !ws) return TSR_INVALID_ARG;
     if (ldg < n) return TSR_BAD_SHAPE;
     if (!aligned256(ws)) return TSR_INVALID_ARG;
-    if (ws_bytes < tsr_refresh_workspace_bytes(m, n, r, p)) return TSR_WORKSPACE_TOO_SMALL;
     std::vector<BlockView> v;
     one_block_view(v, G, g_dtype, m, n, r, ldg, nullptr, n, U, V, nullptr, nullptr);
-    Arena ar(ws);
     RefreshProgram rp;
     const float* oms[1] = {Omega};
     float* sigs[1] = {sigma};
-    build_refresh(rp, v, oms, p, sigs, ar);
+    TSR_TRY(build_within(ws, ws_bytes, ws_bytes, [&](Arena& ar) { build_refresh(rp, v, oms, p, sigs, ar); }));
     Ctx cx{(hipStream_t)stream, nullptr};
     return run_refresh(rp, false, q, cx);
 }
@@ -941,13 +948,9 @@ int tsr_refresh_rsvd_workers(const void* G, int g_dtype, int m, int n, long long
     if (ldg < n) return TSR_BAD_SHAPE;
     if (n_workers > 1 && g_stride < (long long)(m - 1) * ldg + n) return TSR_BAD_SHAPE;
     if (!aligned256(ws)) return TSR_INVALID_ARG;
-    if (ws_bytes < tsr_refresh_workers_workspace_bytes(m, n, r, p, n_workers)) return TSR_WORKSPACE_TOO_SMALL;
     const size_t k = (size_t)r + p;
     const size_t esz = (g_dtype == TSR_BF16) ? 2 : 4;
-    Arena ar(ws);
-    float* Qs = ar.take<float>((size_t)n_workers * m * k);     // the workers' Q_i, stacked
-    float* Bs = ar.take<float>((size_t)n_workers * n * k);     // the workers' B_i^T, stacked
-    const size_t mark = ar.used();
+    float *Qs = nullptr, *Bs = nullptr;
     Ctx cx{(hipStream_t)stream, nullptr};
     const float* oms[1] = {Omega};
     float* sigs[1] = {sigma};
@@ -957,9 +960,12 @@ int tsr_refresh_rsvd_workers(const void* G, int g_dtype, int m, int n, long long
         std::vector<BlockView> v;
         one_block_view(v, (const char*)G + (size_t)w * g_stride * esz, g_dtype, m, n, r, ldg, nullptr, n, U, V, nullptr,
                        nullptr);
-        Arena sub(ws);
-        sub.off = mark;
-        build_refresh(rp, v, oms, p, sigs, sub);
+        TSR_TRY(build_within(ws, ws_bytes, ws_bytes, [&](Arena& ar) {
+            Qs = ar.take<float>((size_t)n_workers * m * k);    // the workers' Q_i, stacked
+            Bs = ar.take<float>((size_t)n_workers * n * k);    // the workers' B_i^T, stacked
+            ar.off = ar.used();
+            build_refresh(rp, v, oms, p, sigs, ar);
+        }));
         TSR_TRY(run_refresh_front(rp, false, q, cx));
         const RefreshBlock& b = rp.blocks[0];
         TSR_HIP(hipMemcpyAsync(Qs + (size_t)w * m * k, b.Yalt, (size_t)m * k * sizeof(float), hipMemcpyDeviceToDevice, cx.s));
@@ -998,13 +1004,17 @@ void build_one_sided_lift(OneSidedProgram& op, float* W, int m, int n, long long
 
 extern "C" {
 
-size_t tsr_one_sided_workspace_bytes(int m, int n, int r) {
-    if (m <= 0 || n <= 0 || r <= 0 || r > m) return 0;
-    Arena ar(nullptr);
+static size_t one_sided_bytes(int m, int n, int r, bool tight) {
+    Arena ar(nullptr, tight);
     OneSidedProgram op;
     build_one_sided_project(op, nullptr, TSR_F32, m, n, n, nullptr, r, nullptr, TSR_PREC_SPLIT, ar);
     build_one_sided_lift(op, nullptr, m, n, n, nullptr, nullptr, r, TSR_PREC_SPLIT, ar);
     return ar.used();
+}
+
+size_t tsr_one_sided_workspace_bytes(int m, int n, int r) {
+    if (m <= 0 || n <= 0 || r <= 0 || r > m) return 0;
+    return one_sided_bytes(m, n, r, false);
 }
 
 int tsr_project_one_sided(const void* G, int g_dtype, int m, int n, long long ldg, const float* U, int r, float alpha,
@@ -1015,10 +1025,9 @@ int tsr_project_one_sided(const void* G, int g_dtype, int m, int n, long long ld
     if (!G || !U || !Ct || !ws) return TSR_INVALID_ARG;
     if (ldg < n) return TSR_BAD_SHAPE;
     if (!aligned256(ws)) return TSR_INVALID_ARG;
-    if (ws_bytes < tsr_one_sided_workspace_bytes(m, n, r)) return TSR_WORKSPACE_TOO_SMALL;
-    Arena ar(ws);
     OneSidedProgram op;
-    build_one_sided_project(op, G, g_dtype, m, n, ldg, U, r, Ct, precision, ar);
+    TSR_TRY(build_within(ws, ws_bytes, ws_bytes,
+                         [&](Arena& ar) { build_one_sided_project(op, G, g_dtype, m, n, ldg, U, r, Ct, precision, ar); }));
     Ctx cx{(hipStream_t)stream, nullptr};
     return run_stage(op.proj[g_dtype], false, alpha, accumulate ? 1.0f : 0.0f, cx, TSR_PROF_GV);
 }
@@ -1030,7 +1039,7 @@ int tsr_backproject_one_sided(float* W, int m, int n, long long ldw, const float
     if (!W || !U || !Dt || !ws) return TSR_INVALID_ARG;
     if (ldw < n) return TSR_BAD_SHAPE;
     if (!aligned256(ws)) return TSR_INVALID_ARG;
-    if (ws_bytes < tsr_one_sided_workspace_bytes(m, n, r)) return TSR_WORKSPACE_TOO_SMALL;
+    if (ws_bytes < one_sided_bytes(m, n, r, true)) return TSR_WORKSPACE_TOO_SMALL;     // (sized for either call)
     Arena ar(ws);
     OneSidedProgram op;
     build_one_sided_lift(op, W, m, n, ldw, U, Dt, r, precision, ar);
@@ -1069,13 +1078,11 @@ int tsr_refresh_exact_svd(const void* G, int g_dtype, int m, int n, long long ld
     if (!G || !U || !V || !ws) return TSR_INVALID_ARG;
     if (ldg < n) return TSR_BAD_SHAPE;
     if (!aligned256(ws)) return TSR_INVALID_ARG;
-    if (ws_bytes < tsr_refresh_exact_workspace_bytes(m, n, r)) return TSR_WORKSPACE_TOO_SMALL;
     std::vector<BlockView> v;
     const int transpose = exact_svd_view(v, m, n, r, U, V);
-    Arena ar(ws);
     RefreshProgram rp;
     float* sigs[1] = {sigma};
-    build_refresh(rp, v, nullptr, s - r, sigs, ar);
+    TSR_TRY(build_within(ws, ws_bytes, ws_bytes, [&](Arena& ar) { build_refresh(rp, v, nullptr, s - r, sigs, ar); }));
     const RefreshBlock& b = rp.blocks[0];
     Ctx cx{(hipStream_t)stream, nullptr};
     TSR_HIP(launch_identity(b.Yalt, s, cx.s));                                          // Q = I (s x s)
@@ -1119,10 +1126,9 @@ int tsr_realign_moment(const float* U_old, const float* V_old, const float* U_ne
     TSR_TRY(check_block(m, n, r));
     if (!U_old || !V_old || !U_new || !V_new || !M || !ws) return TSR_INVALID_ARG;
     if (!aligned256(ws)) return TSR_INVALID_ARG;
-    if (ws_bytes < tsr_realign_workspace_bytes(m, n, r)) return TSR_WORKSPACE_TOO_SMALL;
-    Arena ar(ws);
     RealignProgram rp;
-    build_realign(rp, U_old, V_old, U_new, V_new, m, n, r, M, ar);
+    TSR_TRY(build_within(ws, ws_bytes, ws_bytes,
+                         [&](Arena& ar) { build_realign(rp, U_old, V_old, U_new, V_new, m, n, r, M, ar); }));
     Ctx cx{(hipStream_t)stream, nullptr};
     TSR_TRY(run_stage(rp.a, false, 1.0f, 0.0f, cx, TSR_PROF_BASIS_GEMM));
     TSR_TRY(run_stage(rp.b, false, 1.0f, 0.0f, cx, TSR_PROF_BASIS_GEMM));
@@ -1218,14 +1224,12 @@ static void build_plan(tsr_plan& pl, Arena& ar) {
     }
 }
 
-size_t tsr_plan_workspace_bytes(const tsr_matrix_desc* descs, int count, int n_workers, int precision,
-                                int with_refresh, int p) {
-    if (check_descs(descs, count, n_workers, with_refresh, p, false) != TSR_OK) return 0;
-    if (check_prec(precision) != TSR_OK) return 0;
+static size_t plan_bytes(const tsr_matrix_desc* descs, int count, int n_workers, int precision, int with_refresh, int p,
+                         bool tight) {
     tsr_plan pl;
     views_from_descs(pl.blocks, descs, count);
     pl.n_workers = n_workers; pl.precision = precision; pl.with_refresh = with_refresh != 0; pl.p = p;
-    Arena ar(nullptr);
+    Arena ar(nullptr, tight, true);
     build_plan(pl, ar);
     size_t need = ar.used();
     if (pl.use_fast) {
@@ -1234,11 +1238,18 @@ size_t tsr_plan_workspace_bytes(const tsr_matrix_desc* descs, int count, int n_w
         generic.blocks = pl.blocks;
         generic.n_workers = n_workers; generic.precision = precision; generic.with_refresh = with_refresh != 0;
         generic.p = p; generic.force_generic = true;
-        Arena ar2(nullptr);
+        Arena ar2(nullptr, tight, true);
         build_plan(generic, ar2);
         need = std::max(need, ar2.used());
     }
     return need;
+}
+
+size_t tsr_plan_workspace_bytes(const tsr_matrix_desc* descs, int count, int n_workers, int precision,
+                                int with_refresh, int p) {
+    if (check_descs(descs, count, n_workers, with_refresh, p, false) != TSR_OK) return 0;
+    if (check_prec(precision) != TSR_OK) return 0;
+    return plan_bytes(descs, count, n_workers, precision, with_refresh, p, false);
 }
 
 int tsr_plan_create(const tsr_matrix_desc* descs, int count, int n_workers, int precision, int with_refresh, int p,
@@ -1248,14 +1259,15 @@ int tsr_plan_create(const tsr_matrix_desc* descs, int count, int n_workers, int 
     TSR_TRY(check_descs(descs, count, n_workers, with_refresh, p, true));
     TSR_TRY(check_prec(precision));
     if (!ws || !aligned256(ws)) return TSR_INVALID_ARG;
-    if (ws_bytes < tsr_plan_workspace_bytes(descs, count, n_workers, precision, with_refresh, p))
+    const bool tight = ws_bytes < plan_bytes(descs, count, n_workers, precision, with_refresh, p, false);
+    if (tight && ws_bytes < plan_bytes(descs, count, n_workers, precision, with_refresh, p, true))
         return TSR_WORKSPACE_TOO_SMALL;
     tsr_plan* pl = new (std::nothrow) tsr_plan;
     if (!pl) return TSR_INVALID_ARG;
     views_from_descs(pl->blocks, descs, count);
     pl->n_workers = n_workers; pl->precision = precision; pl->with_refresh = with_refresh != 0; pl->p = p;
     pl->ws = (char*)ws;
-    Arena ar(ws);
+    Arena ar(ws, tight, true);
     build_plan(*pl, ar);
     if (!pl->up.host.empty()) {
         hipError_t e = hipMemcpyAsync((char*)ws + pl->up.first, pl->up.host.data(), pl->up.host.size(),

@@ -319,7 +319,7 @@ void build_fast_step(FastStep& fs, const std::vector<BlockView>& blocks, int n_w
                 for (auto& g : fs.projs) if (g.r == b.r) pg = &g;
                 if (!pg) { fs.projs.emplace_back(); pg = &fs.projs.back(); pg->r = b.r; pg->panel_rows = proj_rows; pg->depth = proj_depth; }
                 for (int row0 = 0; row0 < b.m; row0 += proj_rows) {
-                    pg->items.push_back(ProjItem{Gw, VTf, PT, b.ldg, ldm, b.m, b.n, row0, w_end - w, b.g_stride * esz, PT_low});
+                    pg->items.push_back(ProjItem{Gw, VTf, PT, b.g_stride * esz, (int)b.ldg, b.m, b.n, row0, w_end - w, (int)(PT_low ? PT_low - PT : 0)});
                     proj_block[b.r].push_back(bi);
                     proj_work[b.r].push_back((long long)b.n * (w_end - w) + 64);
                 }

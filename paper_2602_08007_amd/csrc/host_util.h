@@ -34,9 +34,11 @@ inline size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 struct Arena {
     char* base;
     size_t off = 0;
-    explicit Arena(void* b) : base((char*)b) {}
-    template <typename T> T* take(size_t count) {
-        off = align_up(off);
+    bool tight = false;       // the smallest workspace a program runs in: k cut into fewer pieces (build_stage), tables close together
+    bool tables = false;      // launch tables (tiles among them) are carved from it, too
+    explicit Arena(void* b, bool tight_ = false, bool tables_ = false) : base((char*)b), tight(tight_), tables(tables_) {}
+    template <typename T> T* take(size_t count, size_t align = ALIGN) {
+        off = (off + align - 1) / align * align;
         T* p = base ? (T*)(base + off) : (T*)nullptr;
         off += count * sizeof(T);
         return p;
@@ -83,7 +85,7 @@ struct Uploader {
     std::vector<char> host;
     size_t first = (size_t)-1;
     template <typename T> const T* put(const std::vector<T>& v, Arena& ar) {
-        T* d = ar.take<T>(v.size());
+        T* d = ar.take<T>(v.size(), ar.tight ? 16 : ALIGN);
         if (ar.base) {
             const size_t o = (size_t)((char*)d - ar.base);
             if (first == (size_t)-1) first = o;

@@ -90,17 +90,16 @@ struct ShadowBlock {
 // Projection P^T = V^T G^T for one 128- or 64-row panel of a bf16 gradient per workgroup (r = 128
 // or 256): the panel's accumulators (r x 128) stay in registers over the whole contraction, G goes
 // through LDS, V^T comes straight from its fragment-order copy.  G == nullptr: idle workgroup.
-// With workers > 1 the panel is the sum over that many gradients, g_stride bytes apart; PT_low, where
-// given, receives what the rounding of P^T to bf16 leaves (rounded to bf16 itself).
+// With workers > 1 the panel is the sum over that many gradients, g_stride bytes apart; with `low` set, what the
+// rounding of P^T to bf16 leaves (rounded to bf16 itself) goes that many elements behind P^T.
 struct ProjItem {
     const void* G;       // bf16 m x n, leading dimension ldg (16-byte aligned rows, n % 8 == 0)
     const void* VTf;     // ShadowBlock::XTFb of V
-    void* PT;            // bf16 r x m, leading dimension ldp
-    long long ldg, ldp;
-    int m, n, row0;
-    int workers = 1;
+    unsigned short* PT;  // bf16 r x m, leading dimension m rounded up to 8
     long long g_stride = 0;
-    void* PT_low = nullptr;
+    int ldg, m, n, row0;
+    int workers = 1;
+    int low = 0;
 };
 bool proj_supports_rank(int r);
 // depth: gradient tiles in flight per workgroup: 2 (two workgroups per compute unit) or 4 (one)
@@ -127,11 +126,12 @@ hipError_t launch_transpose_bf16(const TransposeBlock* table_dev, int blocks, in
 // The places are 16-byte aligned, their pitches and strides multiples of 8 elements.
 struct SplitBlock {
     const float* X; unsigned short* dst;
-    long long ld_dst, piece_stride;
-    int rows, k;
+    long long piece_stride;
+    int ld_dst, rows, k;
+    int rows_ld = 0;
     unsigned short* dst_again = nullptr;
     unsigned short* rows_dst = nullptr;
-    long long rows_ld = 0, rows_stride = 0;
+    long long rows_stride = 0;
 };
 hipError_t launch_split(const SplitBlock* table_dev, int blocks, int max_rows, int max_k, hipStream_t stream);
 

@@ -1038,10 +1038,10 @@ __device__ __forceinline__ void proj_panel(const ProjItem& it, unsigned short* l
     }
 
     // P^T[ri][row]: lane holds gradient row (lane & 31) of each 32-row group, registers run over ri
-    const long long p_bytes = ((long long)(RG * 32 - 1) * it.ldp + m) * 2;
+    const unsigned ldp_b = ((unsigned)m + 7u) / 8u * 16u;
+    const long long p_bytes = (long long)(RG * 32 - 1) * ldp_b + m * 2LL;
     const nt_rsrc_t rP = nt_make_rsrc(it.PT, p_bytes);
-    const nt_rsrc_t rL = nt_make_rsrc(it.PT_low ? it.PT_low : it.PT, p_bytes);
-    const unsigned ldp_b = (unsigned)it.ldp * 2u;
+    const nt_rsrc_t rL = nt_make_rsrc(it.PT + it.low, p_bytes);
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -1053,7 +1053,7 @@ __device__ __forceinline__ void proj_panel(const ProjItem& it, unsigned short* l
                 const unsigned vo = (row < m) ? (unsigned)ri * ldp_b + (unsigned)row * 2u : 0x80000000u;
                 const unsigned short hi = f32_to_bf16_bits(acc[i][j][e]);
                 __builtin_amdgcn_raw_buffer_store_b16(hi, rP, (int)vo, 0, 0);
-                if (it.PT_low) {
+                if (it.low) {
                     const float hf = __uint_as_float((unsigned)hi << 16);
                     const float low = (fabsf(hf) < INFINITY) ? acc[i][j][e] - hf : 0.0f;      // an infinity stays one
                     __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16_bits(low), rL, (int)vo, 0, 0);

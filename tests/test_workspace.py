@@ -200,3 +200,129 @@ def test_static_scratch_at_its_limit(tsr, m, n, r):
     ref = U.double().T @ (G.double() @ V.double())
     # two products in two bf16 pieces; the core of a white gradient is sqrt(r / min(m, n)) of what the sums hold
     assert float(torch.linalg.norm(C.cpu().double() - ref) / torch.linalg.norm(ref)) < 2 * TWO_PIECES * (min(m, n) / r) ** 0.5
+
+
+# ------------------------------------------------------------------ workspaces smaller than the query's
+# Sizes that earlier builds of the library asked for, which a program may hold: the queries return more by now
+# (k is cut into more pieces), and what these sizes are enough for is still computed in them.
+HELD = [("project", (477, 376, 330), 629760), ("project", (4029, 492, 56), 1078272),
+        ("refresh", (463, 491, 4, 16), 188160), ("refresh", (512, 1376, 64, 8), 4243968),
+        ("refresh_workers", (324, 509, 20, 4, 2), 371712), ("realign", (296, 1760, 1), 1024), ("realign", (512, 2048, 128), 851968),
+        ("one_sided", (4029, 492, 56), 1542912), ("refresh_exact", (200, 700, 50), 6326016)]
+# blocks (m, n, r, row pitch), gradient type, workers, precision, refresh, p
+HELD_PLANS = [([(390, 2407, 375, 2407), (76, 86, 9, 86)], 0, 1, 0, 1, 0, 52995328), ([(256, 688, 64, 688)] * 6, 1, 1, 1, 1, 8, 17071616),
+              ([(768, 2048, 128, 2048)] * 5, 1, 8, 1, 0, 0, 57043968), ([(1000, 300, 64, 300)] * 3, 0, 2, 0, 0, 0, 2604032)]
+
+
+def _operands(name, dims):
+    """Tensors of one call, and the call itself as a function of its workspace (None: one of the query's size)."""
+    import paper_2602_08007_amd as t
+    gen = torch.Generator(device="cuda").manual_seed(17)
+    randn = lambda *s: torch.randn(*s, device="cuda", generator=gen)  # noqa: E731
+    new = lambda *s: torch.full(s, float("nan"), device="cuda")  # noqa: E731
+    m, n, r = dims[:3]
+    G, U, V = randn(m, n), torch.linalg.qr(randn(m, r))[0].contiguous(), torch.linalg.qr(randn(n, r))[0].contiguous()
+    G += 30.0 * (U * torch.linspace(2.0, 1.0, r, device="cuda")) @ V.t()
+    if name == "project":
+        return lambda ws: (t.tsr_project_core(G, U, V, new(r, r), ws=ws),)
+    if name == "one_sided":
+        return lambda ws: (t.tsr_project_one_sided(G, U, new(n, r), ws=ws), t.tsr_backproject_one_sided(G.clone(), U, V, 1.0, ws=ws))
+    if name == "realign":
+        U2, V2, M = torch.linalg.qr(U + 0.01 * randn(m, r))[0].contiguous(), torch.linalg.qr(V + 0.01 * randn(n, r))[0].contiguous(), randn(r, r)
+        return lambda ws: (t.tsr_realign_moment(U, V, U2, V2, M.clone(), ws=ws),)
+
+    def refresh(ws):
+        Un, Vn, sigma = new(m, r), new(n, r), new(min(m, n) if name == "refresh_exact" else r + dims[3])
+        if name == "refresh_exact":
+            t.tsr_refresh_exact_svd(G, r, Un, Vn, sigma, ws=ws)
+        elif name == "refresh":
+            t.tsr_refresh_rsvd(G, om, r, dims[3], 1, Un, Vn, sigma, ws=ws)
+        else:
+            t.tsr_refresh_rsvd_workers(torch.stack([G] * dims[4]), om, r, dims[3], 1, Un, Vn, sigma, ws=ws)
+        return sigma[:r], Un @ Un.t(), Vn @ Vn.t()
+    om = randn(n, r + dims[3]) if len(dims) > 3 else None
+    return refresh
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,dims,held", HELD)
+def test_calls_run_in_a_workspace_held_from_earlier(tsr, name, dims, held):
+    assert getattr(tsr, "tsr_%s_workspace_bytes" % name)(*dims) > held
+    call = _operands(name, dims)
+    g = Guarded(held)
+    got = call(g.ws)
+    g.check()
+    # the same sums in fewer pieces: two results in two bf16 pieces (each off by TWO_PIECES per product, two
+    # products), the projectors by that over the relative gap of the spectrum (signal 30 to 60, noise up to the
+    # sum of the square roots of the sides: a factor of two at these sizes)
+    for a, b in zip(got, call(None)):
+        assert bool(torch.isfinite(a).all())
+        assert float(torch.linalg.norm(a.double() - b.double()) / torch.linalg.norm(b.double())) < 4 * 2 * TWO_PIECES
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dims,g_dtype,workers,prec,refresh,p,held", HELD_PLANS)
+def test_plans_run_in_a_workspace_held_from_earlier(tsr, dims, g_dtype, workers, prec, refresh, p, held):
+    import ctypes
+
+    def blocks():
+        gen = torch.Generator(device="cuda").manual_seed(18)
+        randn = lambda *s: torch.randn(*s, device="cuda", generator=gen)  # noqa: E731
+        out, oms = [], []
+        for m, n, r, ld in dims:
+            U, V = torch.linalg.qr(randn(m, r))[0].contiguous(), torch.linalg.qr(randn(n, r))[0].contiguous()
+            G = torch.zeros(workers, m, ld, device="cuda", dtype=torch.bfloat16 if g_dtype else torch.float32)
+            G[:, :, :n] = (200.0 * (U * torch.linspace(2.0, 1.0, r, device="cuda")) @ V.t() + randn(workers, m, n)).to(G.dtype)
+            z = lambda *s: torch.zeros(*s, device="cuda")  # noqa: E731
+            out.append(dict(G=G[:, :, :n] if workers > 1 else G[0, :, :n], W=z(m, n), U=U, V=V, M=z(r, r), Vm=z(r, r), C=z(r, r),
+                            D=z(r, r)))
+            oms.append(randn(n, r + p))
+        return out, oms
+
+    def run(plan, bl, oms):
+        if refresh:
+            plan.tsr_refresh_batched(oms, 1)
+        plan.tsr_step_batched(1, lr=1.0, eps=100.0)
+        torch.cuda.synchronize()
+        return [b["W"] for b in bl]
+
+    bl, oms = blocks()
+    plan = tsr.Plan(bl, n_workers=workers, precision=prec, with_refresh=bool(refresh), p=p)
+    assert plan.ws.numel() > held
+    want = run(plan, bl, oms)
+    bl, oms = blocks()
+    probe = tsr.Plan(bl, n_workers=workers, precision=prec, with_refresh=bool(refresh), p=p)      # (its descriptors)
+    g = Guarded(held)
+    small = object.__new__(tsr.Plan)
+    small._handle, small.count, small._keep = ctypes.c_void_p(), len(bl), bl
+    assert tsr.lib.tsr_plan_create(probe._descs, len(bl), workers, prec, refresh, p, g.ws.data_ptr(), held,
+                                   torch.cuda.current_stream().cuda_stream, ctypes.byref(small._handle)) == 0
+    assert small.tsr_plan_kernel_path() == plan.tsr_plan_kernel_path()
+    got = run(small, bl, oms)
+    g.check()
+    small.close()
+    # bf16 operands: two roundings (2^-9 each) that fall differently when a sum in fp32 does; else two pieces
+    tol = 2 * 2.0 ** -9 if prec else 4 * 2 * TWO_PIECES
+    for a, b in zip(got, want):
+        assert float(torch.linalg.norm(a.double() - b.double()) / torch.linalg.norm(b.double())) < tol
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the calls below pass addresses that hold nothing")
+@pytest.mark.parametrize("name,dims,held", HELD)
+def test_held_sizes_are_not_refused(tsr, name, dims, held):
+    """Without a GPU a call that is accepted ends at its first launch (-5, HIP error); one that is refused for its
+    workspace ends before (-4).  A workspace below the smallest is refused."""
+    import ctypes
+    a, ws, null = ctypes.c_void_p(0x10000), ctypes.c_void_p(0x100000), ctypes.c_void_p(0)
+    m, n, r = dims[:3]
+    lib = tsr.lib
+    call = {
+        "project": lambda b: lib.tsr_project_core(a, 0, m, n, n, a, a, r, 1.0, 0, a, 0, ws, b, null),
+        "refresh": lambda b: lib.tsr_refresh_rsvd(a, 0, m, n, n, a, r, dims[3], 1, a, a, a, ws, b, null),
+        "refresh_workers": lambda b: lib.tsr_refresh_rsvd_workers(a, 0, m, n, n, m * n, dims[4], a, r, dims[3], 1, a, a, a, ws, b, null),
+        "realign": lambda b: lib.tsr_realign_moment(a, a, a, a, m, n, r, a, ws, b, null),
+        "one_sided": lambda b: lib.tsr_project_one_sided(a, 0, m, n, n, a, r, 1.0, 0, a, 0, ws, b, null),
+        "refresh_exact": lambda b: lib.tsr_refresh_exact_svd(a, 0, m, n, n, r, a, a, a, ws, b, null),
+    }[name]
+    assert call(held) != -4
+    assert call(256) == -4
