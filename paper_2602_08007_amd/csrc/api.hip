@@ -71,7 +71,8 @@ int pick_shape(const std::vector<LogicalGemm>& gemms, int want_tiles) {
     return (area128 * 5 >= area64 * 6) ? GEMM_128x64 : GEMM_128x128;
 }
 
-// Decide k-splits, carve partial buffers from `ar`, and list the tiles.
+// Decide k-splits, carve partial buffers from `ar`, and list the tiles (for the tables of a plan; the launch of a
+// single matrix decodes them from the block index).
 // want_tiles: keep splitting k while the launch has fewer tiles than this.
 // In a tight arena k is cut into pieces of at least 256, which is the split of the smallest workspace (partials
 // are what a program's size hangs on), and tiles that are listed there are the largest.
@@ -138,7 +139,7 @@ void build_stage(GemmStage& st, const GemmVariant& var, const std::vector<Logica
                 prefix += ksplit[j];
             }
             const int tmn = ceil_div(g.M, TM), tnn = ceil_div(g.N, TN);
-            for (int ks = 0; ks < ksplit[j]; ++ks)
+            for (int ks = 0; ar.tables && ks < ksplit[j]; ++ks)
                 for (int tm = 0; tm < tmn; ++tm)
                     for (int tn = 0; tn < tnn; ++tn)
                         if (!lower_only || tn * TN <= tm * TM + TM - 1) st.tiles.push_back(GemmTile{(int)j, tm, tn, ks});

@@ -326,3 +326,21 @@ def test_held_sizes_are_not_refused(tsr, name, dims, held):
     }[name]
     assert call(held) != -4
     assert call(256) == -4
+
+
+# ------------------------------------------------------------------ host work of a single call (host)
+def test_a_single_call_is_built_in_constant_time(tsr):
+    """The launch of one matrix decodes its tiles from the block index: nothing the host prepares for it grows
+    with the matrix (the query builds the same program as the call)."""
+    import time
+
+    def best(*dims):
+        t = float("inf")
+        for _ in range(50):
+            start = time.perf_counter()
+            for _ in range(20):
+                tsr.tsr_project_workspace_bytes(*dims)
+            t = min(t, time.perf_counter() - start)
+        return t
+    # 25008 tiles of 128 x 128 against four
+    assert best(200000, 8192, 512) < 5 * best(256, 256, 128)
