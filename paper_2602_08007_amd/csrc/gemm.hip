@@ -463,11 +463,11 @@ struct Entry { GemmVariant v; gemm_fn fn[GEMM_SHAPES]; };
 
 static const Entry kTable[] = {
     // A = G (k contiguous), B k-strided: G V, G Omega, G Qrow; also U D, Y Rinv, Q X
-    TSR_GEMM(0, 1, 1, 1, 1), TSR_GEMM(0, 1, 1, 1, 2), TSR_GEMM(0, 1, 1, 1, 3),
+    TSR_GEMM(0, 1, 1, 1, 1), TSR_GEMM(0, 1, 1, 1, 2),
     TSR_GEMM(0, 1, 0, 1, 1), TSR_GEMM(0, 1, 0, 2, 2), TSR_GEMM(0, 1, 0, 3, 3),
     // A k-strided, B k-strided: U^T P, Y^T Y, G^T Q
     TSR_GEMM(1, 1, 0, 1, 1), TSR_GEMM(1, 1, 0, 2, 2), TSR_GEMM(1, 1, 0, 3, 3),
-    TSR_GEMM(1, 1, 1, 1, 1), TSR_GEMM(1, 1, 1, 1, 2), TSR_GEMM(1, 1, 1, 1, 3),
+    TSR_GEMM(1, 1, 1, 1, 1), TSR_GEMM(1, 1, 1, 1, 2),
     // A k-contiguous, B k-contiguous: T V^T
     TSR_GEMM(0, 0, 0, 1, 1), TSR_GEMM(0, 0, 0, 2, 2), TSR_GEMM(0, 0, 0, 3, 3),
 };
