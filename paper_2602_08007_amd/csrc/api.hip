@@ -56,7 +56,15 @@ struct GemmStage {
 
 // Tile shape of a launch: 128 x 128, unless the narrower tile saves a sixth of the padded columns (ranks
 // and sketch widths are rarely multiples of 128), or the launch is so small that smaller tiles are what
-// gives it enough workgroups.
+// gives it enough workgroups.  Measured, us, the rule's side first:
+//   64 x 64 below 256 units, against 128-wide tiles: projection of 512 x 1376 r = 64 19.9 / 20.7, of 768 x 768
+//     r = 256 23.6 / 29.2, of 1024 x 2048 r = 128 23.6 / 36.2; lift of the last 13.8 / 20.4; refresh of 512 x 1376,
+//     r + p = 72, 687 / 773.  At 256 units 64 x 64 would still be the faster one (2048 x 2048 r = 128 projection
+//     27.0, as it is 33.5; lift 16.8 and 17.8), at 1024 no longer (4096 x 4096 r = 128 lift 48.0, as it is 42.2).
+//   128 x 64 against 128 x 128: projection of 8192 x 8192 r = 64 70 / 83; products of a plan's refresh, two
+//     32000 x 2048 at r + p = 136 1847 / 1997, 24 of 768 x 2048 at 188 1064 / 1234, at 264 1741 / 1837.  A sixth saved
+//     is where it turns: at 320 columns (384 padded) a projection of 8192 x 8192 takes 271 / 228, at 448 (512) the rule
+//     keeps 128 x 128 and 128 x 64 costs a quarter more (one-sided projection of 4096 x 4096 98 against 78).
 int pick_shape(const std::vector<LogicalGemm>& gemms, int want_tiles) {
     long long area128 = 0, area64 = 0, units = 0;
     int max_m = 0, max_n = 0;
@@ -96,7 +104,9 @@ void build_stage(GemmStage& st, const GemmVariant& var, const std::vector<Logica
     bool any_split = false;
     for (size_t i = 0; i < gemms.size(); ++i) {
         const int K = gemms[i].K;
-        // pieces of at least 128 (64 where that leaves most of the chip idle)
+        // Pieces of at least 128, and of 64 where that leaves most of the chip idle.  Projection, us, at least 64 / 128 /
+        // 256: 512 x 1376 r = 64 19.5 / 20.2 / 23.9, 768 x 2048 r = 256 26.1 / 26.9 / 28.1, 4029 x 492 r = 56
+        // 22.9 / 22.5 / 25.0, from 1024 x 4096 on the same; refresh of 512 x 1376, r + p = 72, 687 / 694 / 728.
         const int least = ar.tight ? 256 : (base_tiles * (K / 128) < 256) ? 64 : 128;
         int s = std::min(want_split, std::max(1, K / least));
         int chunk = ceil_div(ceil_div(K, s), 32) * 32;

@@ -16,8 +16,9 @@
 // two banks and took sixteen passes.  Measured (with one stage, per-element guards and element-by-element
 // read-modify-write -> two stages -> W read early -> stores behind the products): the step of the 60M model in
 // fp32 at rank 256, 643 -> 304 -> 289 -> 271 us; of a 32000 x 2048 embedding and LM head at rank 128,
-// 1060 -> 551 -> 512 -> 475 us; the refresh of the latter 3608 -> 3399 us by the last of these.  The step of
-// one 512 x 1376 fp32 matrix at rank 64, 104 -> 39 us, is bound by its seven launches since.
+// 1060 -> 551 -> 512 -> 475 us; the refresh of the latter 3608 -> 3399 us by the last of these (each pair on one
+// card; cards differ by some 3 %).  The hint on W further down takes the two steps to 269 and 460 us.  The step of
+// one 512 x 1376 fp32 matrix at rank 64, 104 -> 37 us, is bound by its seven launches since.
 #include "gemm.h"
 
 #include <type_traits>
@@ -251,8 +252,8 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_kernel(const GemmLaunch L) {
     // is fetched behind the first two k-tiles, so that it travels while they are multiplied.  Fetched after the
     // last k-tile -> here: step of a 32000 x 2048 embedding and LM head (rank 128) 557 -> 511 us, of the 60M
     // model in fp32 (rank 256) 310 -> 292 us.  Three pieces leave no registers for it (and nothing uses it there).
-    // W passes through once, with the non-temporal hint, so that it does not push the factors out of L2: 472 -> 429
-    // and 271 -> 265 us for the same two.
+    // W passes through once, with the non-temporal hint, so that it does not push the factors out of L2: 489 -> 461
+    // and 273 -> 269 us for the same two (three comparisons in turn on one card, 487-491 -> 460-462, 273.3 -> 269.5).
     // The weight update keeps the plain order: its short contraction is behind the read of W, which fills the registers.
     constexpr bool AHEAD = NBUF == 2 && KS;
     constexpr bool EARLY = !A_KS && !B_KS && NSA <= 2 && NSB <= 2;
