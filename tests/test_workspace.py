@@ -203,7 +203,7 @@ def test_static_scratch_at_its_limit(tsr, m, n, r):
 
 
 # ------------------------------------------------------------------ workspaces smaller than the query's
-# Sizes that earlier builds of the library asked for, which a program may hold: the queries return more by now
+# Sizes that earlier versions of the library asked for, which a program may hold: the queries return more by now
 # (k is cut into more pieces), and what these sizes are enough for is still computed in them.
 HELD = [("project", (477, 376, 330), 629760), ("project", (4029, 492, 56), 1078272),
         ("refresh", (463, 491, 4, 16), 188160), ("refresh", (512, 1376, 64, 8), 4243968),
