@@ -307,16 +307,20 @@ __device__ inline double readlane_f64(double v, int lane) {      // lane: a comp
 // and shared through LDS; then every tile below row J takes its update
 //     A_IK -= L_IJ L_KJ^T (K > J)         E_Ic -= L_IJ X_Jc (c <= J)
 // where the tile of column c, done as part of L after step c, holds E, the part of the inverse under way,
-// from then on.  So nothing but the input and the results touches memory, and the inverse costs no
-// launches of its own.  What bounds it is the serial chain of the diagonal tiles (sixteen dependent
-// reciprocal square roots each): the last wave owns the diagonal tiles, takes the next one first and
-// factors it while the other waves work on the rest.
-// Per call, one matrix per compute unit, the three launches of the blocked variant -> this: k = 72 68 -> 28 us,
-// k = 136 130 -> 62 us, k = 264 315 -> 160 us (there the fp64 products of the early steps take over: about
-// 150 tiles of four products each, at two waves per SIMD).  272 is where the tiles fill the registers; larger
-// matrices (up to 544) are cut in two:
+// from then on.  With the tiles and X held transposed both updates are the same product, slot K times the
+// transpose of slot I.  So nothing but the input and the results touches memory, and the inverse costs no
+// launches of its own.  What bounds it up to k = 144 is the serial chain of the diagonal tiles, above that the fp64
+// products of the early steps (a quarter of the chip's rate per SIMD: 64 cycles per 16 x 16 x 4).  The last wave has
+// no tiles of its own: it takes the next diagonal tile through LDS and factors it while the others work on theirs,
+// four columns at a time with products between (3600 cycles; a column at a time, with broadcasts of every entry by
+// v_readlane, took 7300, and 11 500 beside a wave with products).
+// Per call, one matrix per compute unit, before -> with that: k = 72 29.5 -> 17.1 us (eight waves; with four 19.4),
+// k = 136 63 -> 38.8 us, k = 264 172 -> 138 us (twelve waves; eight 161, sixteen 159).  272 is where the tiles fill
+// the registers; larger matrices (up to 544) are cut in two:
 //     [S11    ]   the kernel on S11 (PART 1), L21 = S21 Li1^T, S22 - L21 L21^T, the kernel on that (PART 2);
 //     [S21 S22]   the inverse below the diagonal is -Li2 (L21 Li1).
+// (In two halves from 160 on it takes 115 / 130 us for one matrix of k = 264, but 150 / 137 for 56 and at k = 200
+// 87 / 83 and 103 / 88.)
 // The products (fp64 MFMAs, 64 x 64 tiles over the whole chip) and Li1, Li2 go through `work`.  The variant this
 // replaces, 32-wide block columns of a matrix in memory, spent one workgroup's chain on all of it.
 // Per call at k = 528, 56 matrices, the other groups of a refresh running beside it: 1.29 + 0.69 + 0.18 ms in
@@ -324,6 +328,7 @@ __device__ inline double readlane_f64(double v, int lane) {      // lane: a comp
 constexpr int CT = 16;
 constexpr int CT_P = CT + 2;                   // LDS row: 144 bytes, operand reads free of bank conflicts
 constexpr int CT_MAXK = 272;
+constexpr int NEG_A = 1;                       // of a double-precision MFMA: the left operand negated
 
 // Workgroup barrier that orders LDS only: the results on their way to global memory are not waited for.
 __device__ inline void lds_barrier() {
@@ -340,14 +345,15 @@ __host__ __device__ inline int chol_lead(int k) { return min(((k + 1) / 2 + CT -
 template <int NT, int WAVES, int PART>
 __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlock* table, const CholBlock single,
                                                                     const double tol, const double shift_rel) {
-    constexpr int OFF = (NT * (NT - 1) / 2 + WAVES - 2) / (WAVES - 1);     // off-diagonal tiles per wave
-    constexpr int SLOTS = OFF > NT ? OFF : NT;
+    constexpr int SLOTS = (NT * (NT + 1) / 2 + WAVES - 2) / (WAVES - 1);   // tiles per wave; the last wave has none
+    constexpr int TILE = CT * CT_P * 8;                        // bytes of a tile in LDS
     typedef double d4_t __attribute__((ext_vector_type(4)));
     typedef double tile_t[CT][CT_P];
     extern __shared__ double smem[];
-    // two buffers of NT tiles; slot x: L_xJ (x > J), X_Jx (x < J), Li_J (x = J)
-    tile_t& dg = ((tile_t*)smem)[2 * NT];                      // the diagonal tile being factored
-    float* s_diag = (float*)(smem + (2 * NT + 1) * CT * CT_P);  // diagonal of S
+    // two buffers of NT tiles; slot x of step J: L_xJ (x > J), X_Jx^T (x <= J)
+    tile_t* raw = (tile_t*)smem + 2 * NT;                      // the next diagonal tile, two buffers
+    tile_t* low_diag = raw + 2;                                // L_JJ, two buffers
+    float* s_diag = (float*)(smem + (2 * NT + 4) * CT * CT_P);  // diagonal of S
 
     CholBlock cb = single;
     if (table) cb = table[blockIdx.x];
@@ -359,7 +365,6 @@ __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlo
     const int nt = (k + CT - 1) / CT;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, lk = lane >> 4;
-    const bool diag_wave = wave == WAVES - 1;
     typedef const float __attribute__((address_space(1))) gfloat;
     typedef double __attribute__((address_space(1))) gdouble;
     gfloat* S = (gfloat*)cb.S + first;
@@ -368,239 +373,280 @@ __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlo
     const gdouble* A = (const gdouble*)cb.work + first;
     gdouble* X = (gdouble*)cb.work + (size_t)ld * ld + first;
 
-    // ---- tiles of this wave: the diagonal ones, or number wave + (WAVES - 1) s of the row-major strict triangle
-    int tI[SLOTS], tK[SLOTS];
+    // diagonal of S to LDS; the shift; zeros below the block diagonal of both results
+    auto diagonal_shift_tiles = [&]() {
+        double mx = 0.0;
+        for (int j = tid; j < nt * CT; j += 64 * WAVES) {
+            const float d = (j < k) ? S[(size_t)j * ld + j] : 1.0f;
+            s_diag[j] = d;
+            if (PART == 0 && j < k) mx = fmax(mx, (double)d);
+        }
+        if (PART != 0)                                         // the shift is one for the whole matrix
+            for (int j = tid; j < ld; j += 64 * WAVES) mx = fmax(mx, (double)((gfloat*)cb.S)[(size_t)j * ld + j]);
+        for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
+        if (lane == 0) smem[wave] = mx;
+        lds_barrier();
+        mx = smem[0];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) mx = fmax(mx, smem[w]);
+        lds_barrier();
+        for (int a = CT + wave; a < k; a += WAVES)
+            for (int b = lane; b < a / CT * CT; b += 64) {
+                Rinv[(size_t)a * ld + b] = 0.0f;
+                if (Rtot) Rtot[(size_t)a * ld + b] = 0.0;
+            }
+        return shift_rel * mx;
+    };
+    auto put = [&](tile_t& d, const d4_t& x) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) d[4 * v + lk][li] = x[v];
+    };
+    // four k values of row li of a tile, k = 4 q + lk: a left operand, or the transpose as a right operand
+    auto row4 = [&](const tile_t& d, double (&x)[4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = d[li][4 * q + lk];
+    };
+    auto col4 = [&](const tile_t& d, double (&x)[4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = d[4 * q + lk][li];
+    };
+    // Factor the diagonal tile t (symmetric, accumulator layout) and invert the factor, four columns at a time.
+    // Register v of the accumulator layout, element [4 v + l / 16][l % 16], is by symmetry the four columns from
+    // 4 v on in the layout of a left operand, and as it stands that of a right operand; so with X4 the inverse of
+    // the 4 x 4 factor on the diagonal (every lane computes its factor, and column l / 16 of X4),
+    //     L_v = T_v X4^T      T -= L_v L_v^T      X_v = X4 E_v      E -= L_v X_v      (E: the identity)
+    // are one product each.  A dropped pivot leaves a zero column in L and a zero row and column in the inverse.
+    auto factor = [&](int J, d4_t t, tile_t& inv_t, tile_t& low_t) {
+        double low[CT];                                        // pivots up to here are dropped
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            low[c] = fmax(tol * (double)s_diag[J * CT + c], 0.0);
+            asm("" : "+v"(low[c]));                            // (a select below, not a branch on a uniform value)
+        }
+        d4_t E, Xv = {0.0, 0.0, 0.0, 0.0}, Lv, left;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) E[v] = (4 * v + lk == li) ? 1.0 : 0.0;
+        const d4_t zero = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            double d[4][4], x[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int a = b; a < 4; ++a) d[a][b] = readlane_f64(t[v], 16 * b + 4 * v + a);
+            double sel = 0.0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                // 1 / sqrt(pivot), zero for a dropped one: the hardware's first digits and one third-order step
+                const double piv = d[j][j];
+                const double r0 = __builtin_amdgcn_rsq(piv);
+                const double e = fma(-(piv * r0), r0, 1.0);
+                const double inv = (piv > low[4 * v + j]) ? fma(r0 * e, fma(0.375, e, 0.5), r0) : 0.0;
+                double rhs = (lk == j) ? 1.0 : 0.0;            // column lk of X4
+#pragma unroll
+                for (int b = 0; b < j; ++b) rhs = fma(-d[j][b], x[b], rhs);
+                x[j] = rhs * inv;
+                sel = (li == 4 * v + j) ? x[j] : sel;
+#pragma unroll
+                for (int a = j + 1; a < 4; ++a) d[a][j] *= inv;
+#pragma unroll
+                for (int b = j + 1; b < 4; ++b)
+#pragma unroll
+                    for (int a = b; a < 4; ++a) d[a][b] = fma(-d[a][j], d[b][j], d[a][b]);
+                // the inverse's update with the four columns before, in the shadow of this chain
+                if (j == 1 && v > 0) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    E = __builtin_amdgcn_mfma_f64_16x16x4f64(Lv[v - 1], Xv[v - 1], E, 0, 0, NEG_A);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            const double p = (li >= 4 * v) ? t[v] : 0.0;       // finished rows
+            left = __builtin_amdgcn_mfma_f64_16x16x4f64(sel, p, zero, 0, 0, 0);
+            Lv[v] = left[v];
+            if (v < 3) t = __builtin_amdgcn_mfma_f64_16x16x4f64(Lv[v], Lv[v], t, 0, 0, NEG_A);
+            __builtin_amdgcn_sched_barrier(0);
+            left = __builtin_amdgcn_mfma_f64_16x16x4f64(sel, E[v], zero, 0, 0, 0);
+            Xv[v] = left[v];
+            low_t[li][4 * v + lk] = (4 * v + lk <= li) ? Lv[v] : 0.0;
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) inv_t[li][4 * v + lk] = Xv[v];
+    };
+
+    // ---- finish column J of L and row J of the inverse, the tiles dealt to all waves; slot J holds Li_J^T
+    auto buffer = [&](int J) { return (tile_t*)smem + ((J & 1) ? NT : 0); };
+    auto finish = [&](int J) {
+        tile_t* cur = buffer(J);
+        for (int y = wave; y + 1 < nt; y += WAVES) {
+            const int x = y + (y >= J);
+            double a[4], b[4];
+            col4(cur[J], b);
+            if (x > J) col4(cur[x], a);                    // A_xJ, there transposed
+            else row4(cur[x], a);                          // E_Jx^T
+            __builtin_amdgcn_sched_barrier(0);             // all operands on their way before the first product
+            d4_t p = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) p = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], p, 0, 0, 0);
+            put(cur[x], p);
+        }
+        lds_barrier();
+    };
+
+    // ---- results of step J to memory: L_xJ^T -> Rtot (x >= J), X_Jx^T -> Rinv (x <= J).
+    auto results = [&](int J) {
+        const tile_t* cur = buffer(J);
+        // element (4 v + lk, li) of tile (R, C)
+        auto store = [&](auto* dst, int R, int C, const double (&o)[4]) {
+            const unsigned at = (R * CT + lk) * ld + C * CT + li, rows = 4 * ld;
+            if ((max(R, C) + 1) * CT <= k) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) dst[at + v * rows] = o[v];
+            } else if (C * CT + li < k) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (R * CT + lk + 4 * v < k) dst[at + v * rows] = o[v];
+            }
+        };
+        for (int x = wave; x < nt; x += WAVES - 1) {
+            double o[4];
+            if (x <= J) {
+                col4(cur[x], o);
+                store(Rinv, x, J, o);
+                if (PART != 0) {
+                    row4(cur[x], o);
+                    store(X, J, x, o);
+                }
+            }
+            if (Rtot && x >= J) {
+                row4(x == J ? low_diag[J & 1] : cur[x], o);
+                store(Rtot, J, x, o);
+            }
+        }
+    };
+
+    if (wave == WAVES - 1) {
+        (void)diagonal_shift_tiles();
+        lds_barrier();
+        for (int J = -1; J < nt; ++J) {
+            if (J >= 0) finish(J);
+            if (J + 1 >= nt) break;
+            // ---- the next diagonal tile: update with step J, factor
+            d4_t t;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) t[v] = raw[(J + 1) & 1][4 * v + lk][li];
+            __builtin_amdgcn_s_setprio(3);
+            if (J >= 0) {
+                double a[4];
+                row4(buffer(J)[J + 1], a);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) t = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], a[q], t, 0, 0, NEG_A);
+            }
+            factor(J + 1, t, buffer(J + 1)[J + 1], low_diag[(J + 1) & 1]);
+            __builtin_amdgcn_s_setprio(0);
+            lds_barrier();
+        }
+        return;
+    }
+
+    // ---- tiles of this wave: number wave + (WAVES - 1) s of the row-major triangle, (I, K) as the LDS offsets of
+    // slots I and K.  Tile (I, K) is held transposed.
+    unsigned tile_at[SLOTS];
     d4_t acc[SLOTS];
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) {
         const int t = s * (WAVES - 1) + wave;
-        int I = (int)((sqrtf(8.0f * (float)t + 1.0f) + 1.0f) * 0.5f);
-        while (I * (I + 1) / 2 <= t) ++I;
-        while (I * (I - 1) / 2 > t) --I;
-        tI[s] = diag_wave ? s : __builtin_amdgcn_readfirstlane(I);
-        tK[s] = diag_wave ? s : __builtin_amdgcn_readfirstlane(t - I * (I - 1) / 2);
+        int I = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+        while ((I + 1) * (I + 2) / 2 <= t) ++I;
+        while (I * (I + 1) / 2 > t) --I;
+        const int K = min(t - I * (I + 1) / 2, NT - 1);
+        tile_at[s] = __builtin_amdgcn_readfirstlane(I * TILE + (K * TILE << 16));
     }
-    double mx = 0.0;
-    for (int j = tid; j < nt * CT; j += 64 * WAVES) {
-        const float d = (j < k) ? S[(size_t)j * ld + j] : 1.0f;
-        s_diag[j] = d;
-        if (PART == 0 && j < k) mx = fmax(mx, (double)d);
-    }
-    if (PART != 0)                                             // the shift is one for the whole matrix
-        for (int j = tid; j < ld; j += 64 * WAVES) mx = fmax(mx, (double)((gfloat*)cb.S)[(size_t)j * ld + j]);
+    // A slot's coordinates, opaque to the compiler: it would otherwise keep the LDS addresses of every
+    // slot in vector registers across the loop (and spill).
+    auto coords = [&](int s, unsigned& I, unsigned& K) {
+        unsigned x = tile_at[s];
+        asm volatile("" : "+s"(x));
+        I = x & 0xffff; K = x >> 16;
+    };
+    const unsigned end = nt * TILE;
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) {
-        if (tI[s] >= nt) continue;                             // uniform
+        const int I = (tile_at[s] & 0xffff) / TILE, K = (tile_at[s] >> 16) / TILE;
+        if (I >= nt) continue;                                 // uniform
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int i = tI[s] * CT + 4 * v + lk, c = tK[s] * CT + li;
+            const int i = I * CT + li, c = K * CT + 4 * v + lk;
             const bool in = i < k && c < k;
             const int lo = min(min(i, c), k - 1), hi = min(max(i, c), k - 1);    // the lower triangle of S is read
             const double x = PART == 2 ? A[(size_t)hi * ld + lo] : (double)S[(size_t)hi * ld + lo];
             acc[s][v] = in ? x : (i == c ? 1.0 : 0.0);
         }
     }
-    for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
-    if (lane == 0) smem[wave] = mx;
-    __syncthreads();
-    mx = smem[0];
+    const double shift = diagonal_shift_tiles();
 #pragma unroll
-    for (int w = 1; w < WAVES; ++w) mx = fmax(mx, smem[w]);
-    const double shift = shift_rel * mx;
-    __syncthreads();
-    if (diag_wave) {
+    for (int s = 0; s < SLOTS; ++s) {
+        const unsigned I = tile_at[s] & 0xffff, K = tile_at[s] >> 16;
+        if (I != K) continue;
 #pragma unroll
-        for (int s = 0; s < NT; ++s)
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                if (4 * v + lk == li && s * CT + li < k) acc[s][v] += shift;
+        for (int v = 0; v < 4; ++v)
+            if (4 * v + lk == li && (int)(I / TILE) * CT + li < k) acc[s][v] += shift;
     }
-    // below the block diagonal both results are zero
-    for (int a = CT + wave; a < k; a += WAVES)
-        for (int b = lane; b < a / CT * CT; b += 64) {
-            Rinv[(size_t)a * ld + b] = 0.0f;
-            if (Rtot) Rtot[(size_t)a * ld + b] = 0.0;
-        }
+    if (wave == 0) put(raw[0], acc[0]);                        // the first diagonal tile
+    lds_barrier();
 
-    // A slot's tile coordinates, opaque to the compiler: it would otherwise keep the LDS addresses of every
-    // slot in vector registers across the loop (and spill).
-    auto coords = [&](int s, int& I, int& K) {
-        I = tI[s]; K = tK[s];
-        asm volatile("" : "+s"(I), "+s"(K));
-    };
-    auto put = [&](tile_t& d, const d4_t& x) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) d[4 * v + lk][li] = x[v];
-    };
-    // Factor the tile in dg and invert the factor, both by the same updates: lane l < 16 holds row l of the
-    // tile, lane 16 + l column l of the inverse (which starts as the identity).  A dropped pivot leaves a
-    // zero column in L and a zero row and column in the inverse.  (Above the diagonal a lane's values are
-    // meaningless and never read by another lane.)
-    auto factor = [&](int J, tile_t& out) {
-        double a[CT];
-#pragma unroll
-        for (int c = 0; c < CT; ++c) a[c] = (lk == 0) ? dg[li][c] : ((c == li) ? 1.0 : 0.0);
-        const double thr = tol * (double)s_diag[J * CT + li];
-        // 1 / sqrt(pivot), zero for a dropped one: the hardware's first digits and one third-order step
-        double piv = readlane_f64(a[0], 0), t0 = readlane_f64(thr, 0);
-        double r0 = __builtin_amdgcn_rsq(piv);
-        double e = fma(-(piv * r0), r0, 1.0);
-        double invd = (piv > 0.0 && piv > t0) ? fma(r0 * e, fma(0.375, e, 0.5), r0) : 0.0;
-#pragma unroll
-        for (int j = 0; j < CT; ++j) {
-            const double aj = a[j] * invd;
-            a[j] = aj;
-            if (j + 1 < CT) {
-                // the next pivot's column first; its reciprocal root is under way while the other columns follow
-                a[j + 1] -= aj * readlane_f64(aj, j + 1);
-                double l[CT];
-#pragma unroll
-                for (int c = j + 2; c < CT; ++c) l[c] = readlane_f64(aj, c);
-                piv = readlane_f64(a[j + 1], j + 1);
-                t0 = readlane_f64(thr, j + 1);
-                r0 = __builtin_amdgcn_rsq(piv);
-                const double m = piv * r0;
-                constexpr int N = CT;
-                auto part = [&](int q) {                       // a quarter of the remaining columns
-#pragma unroll
-                    for (int c = 0; c < N; ++c)
-                        if (c >= j + 2 && (c - j - 2) % 4 == q) a[c] -= aj * l[c];
-                };
-                part(0);
-                e = fma(-m, r0, 1.0);
-                part(1);
-                const double s2 = fma(0.375, e, 0.5), re = r0 * e;
-                part(2);
-                invd = (piv > 0.0 && piv > t0) ? fma(re, s2, r0) : 0.0;
-                part(3);
-            }
-        }
-        // outputs of the diagonal tile: Rtot = L^T (lane = its column), Rinv = X^T (lane = its row)
-        const int g = J * CT + li;
-        if (lk == 0) {
-            if (Rtot)
-#pragma unroll
-                for (int j = 0; j < CT; ++j)
-                    if (J * CT + j < k && g < k) Rtot[(size_t)(J * CT + j) * ld + g] = (j <= li) ? a[j] : 0.0;
-        } else if (lk == 1) {
-#pragma unroll
-            for (int c = 0; c < CT; ++c) {
-                out[c][li] = a[c];
-                if (J * CT + c < k && g < k) {
-                    Rinv[(size_t)g * ld + J * CT + c] = (float)a[c];
-                    if (PART != 0) X[(size_t)(J * CT + c) * ld + g] = a[c];
-                }
-            }
+    // the raw value of a tile that the next step finishes goes to LDS, and the diagonal tile of the step after it
+    auto put_raw = [&](int s, int J) {
+        unsigned I, K;
+        coords(s, I, K);
+        const unsigned next = (J + 1) * TILE;
+        const bool column = K == next && I > next, row = I == next && K < next, diag = I == K && I == next + TILE;
+        if (I < end && (column || row || diag)) {
+            const char* d = diag ? (const char*)(raw + (J & 1)) : (const char*)buffer(J + 1) + (column ? I : K);
+            put(*(tile_t*)d, acc[s]);
         }
     };
-
+    // (the waves of a SIMD, four numbers apart, write results at different times: one before, one after the products)
+    const bool early = (wave & 4) == 0;
     for (int J = -1; J < nt; ++J) {
-        tile_t* cur = (tile_t*)smem + ((J & 1) ? NT : 0);
-        tile_t* nxt = (tile_t*)smem + ((J & 1) ? 0 : NT);
+        const tile_t* cur = buffer(J);
         if (J >= 0) {
-            // ---- finish column J of L and row J of the inverse, the tiles dealt to all waves
-            tile_t& Li = cur[J];
-            for (int x = wave; x < nt; x += WAVES) {
-                if (x != J) {
-                    // row of the left factor and column of the right one of this lane, four k apart per element
-                    const double *pa, *pb;
-                    int sb;
-                    if (x > J) { pa = &cur[x][li][lk]; pb = &Li[li][lk]; sb = 4; }
-                    else { pa = &Li[li][lk]; pb = &cur[x][lk][li]; sb = 4 * CT_P; }
-                    double a[4], b[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) { a[q] = pa[4 * q]; b[q] = pb[sb * q]; }
-                    __builtin_amdgcn_sched_barrier(0);         // all operands on their way before the first product
-                    d4_t p = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) p = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], p, 0, 0, 0);
-                    put(cur[x], p);
-                }
-            }
-            lds_barrier();
-            // ---- results of step J to memory, transposed: L_xJ -> Rtot, X_Jx -> Rinv
-            if (!diag_wave) {
-                for (int x = wave; x < nt; x += WAVES - 1) {
-                    if (x == J) continue;
-                    double o[4];
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) o[v] = cur[x][li][4 * v + lk];
-                    const int r = (x > J ? J : x) * CT + lk, c = (x > J ? x : J) * CT + li;
-                    const size_t at = (size_t)r * ld + c;
-                    if (PART != 0 && x < J) {
-#pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            if (J * CT + 4 * v + lk < k) X[(size_t)(J * CT + 4 * v + lk) * ld + x * CT + li] = cur[x][4 * v + lk][li];
-                    }
-                    if (c < k) {
-#pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            if (r + 4 * v < k) {
-                                if (x < J) Rinv[at + (size_t)(4 * v) * ld] = (float)o[v];
-                                else if (Rtot) Rtot[at + (size_t)(4 * v) * ld] = o[v];
-                            }
-                    }
-                }
-            }
+            finish(J);
+            if (early || J + 1 >= nt) results(J);
+            if (J + 1 >= nt) break;
         }
-        if (J + 1 >= nt) break;
-        // ---- update of tile (I, K) with step J (a finished tile, I <= J, may take one too: it is dead)
-        auto fetch = [&](int I, int K, double (&a)[4], double (&b)[4]) {
-            const double* pa = &cur[I][li][lk];
-            const double* pb = (K > J) ? &cur[K][li][lk] : &cur[K][lk][li];
-            const int sb = (K > J) ? 4 : 4 * CT_P;
+        // ---- every tile below row J: minus slot K times the transpose of slot I.  A tile of column J starts from
+        // zero, as a tile of E.  Two tiles at a time, their products interleaved; a wave's tiles come in row order.
+        const unsigned at_J = J * TILE;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) { a[q] = -pa[4 * q]; b[q] = pb[sb * q]; }
-        };
-        if (diag_wave) {
-#pragma unroll
-            for (int s = 0; s < NT; ++s)
-                if (tI[s] == J + 1) {
-                    if (J >= 0) {
-                        double a[4], b[4];
-                        fetch(J + 1, J + 1, a, b);
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) acc[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], acc[s], 0, 0, 0);
-                    }
-                    put(dg, acc[s]);
-                }
-            __builtin_amdgcn_s_setprio(3);
-            factor(J + 1, nxt[J + 1]);
-            __builtin_amdgcn_s_setprio(0);
-        }
-        // two tiles at a time, their products interleaved
-        if (J >= 0) {
-#pragma unroll
-            for (int s = 0; s < SLOTS; s += 2) {
-                constexpr int LAST = SLOTS - 1;
-                const int s1 = s < LAST ? s + 1 : s;
-                int I0, K0, I1, K1;
-                coords(s, I0, K0);
-                coords(s1, I1, K1);
-                if (I1 <= J || I0 >= nt) continue;             // a wave's tiles come in row order
+        for (int s = 0; s < SLOTS; s += 2) {
+            constexpr int LAST = SLOTS - 1;
+            const int s1 = s < LAST ? s + 1 : s;
+            unsigned I0, K0, I1, K1;
+            coords(s, I0, K0);
+            coords(s1, I1, K1);
+            if (J >= 0 && I1 > at_J && I0 < end) {
                 double a[2][4], b[2][4];
-                fetch(I0, K0, a[0], b[0]);
-                if (s < LAST) fetch(I1, K1, a[1], b[1]);
+                row4(*(const tile_t*)((const char*)cur + K0), a[0]);
+                row4(*(const tile_t*)((const char*)cur + I0), b[0]);
+                if (s < LAST) {
+                    row4(*(const tile_t*)((const char*)cur + K1), a[1]);
+                    row4(*(const tile_t*)((const char*)cur + I1), b[1]);
+                }
+                if (K0 == at_J) acc[s] = d4_t{0.0, 0.0, 0.0, 0.0};
+                if (s < LAST && K1 == at_J) acc[s1] = d4_t{0.0, 0.0, 0.0, 0.0};
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    acc[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0][q], b[0][q], acc[s], 0, 0, 0);
-                    if (s < LAST) acc[s1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1][q], b[1][q], acc[s1], 0, 0, 0);
+                    acc[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0][q], b[0][q], acc[s], 0, 0, NEG_A);
+                    if (s < LAST) acc[s1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1][q], b[1][q], acc[s1], 0, 0, NEG_A);
                 }
             }
+            if (s >= 2) { put_raw(s - 2, J); put_raw(s - 1, J); }
         }
-        // the raw values of the tiles that the next step finishes go to LDS; a tile of column J + 1 starts
-        // from zero as a tile of E
-        if (!diag_wave) {
+        constexpr int LEFT = (SLOTS - 1) / 2 * 2;
 #pragma unroll
-            for (int s = 0; s < OFF; ++s) {
-                int I, K;
-                coords(s, I, K);
-                if (I >= nt || I <= J || (K != J + 1 && I != J + 1)) continue;
-                put(nxt[K == J + 1 ? I : K], acc[s]);
-                if (K == J + 1) acc[s] = d4_t{0.0, 0.0, 0.0, 0.0};
-            }
-        }
+        for (int s = LEFT; s < SLOTS; ++s) put_raw(s, J);
+        if (J >= 0 && !early) results(J);
         lds_barrier();
     }
 }
@@ -728,7 +774,7 @@ __global__ __launch_bounds__(256) void chol_parts_kernel(const CholBlock* table,
 template <int NT, int WAVES, int PART = 0>
 static hipError_t launch_chol_tiles(const CholBlock* table_dev, const CholBlock& single, int blocks, double tol, double shift_rel,
                                     hipStream_t stream) {
-    constexpr int lds = (2 * NT + 1) * CT * CT_P * 8 + NT * CT * 4;
+    constexpr int lds = (2 * NT + 4) * CT * CT_P * 8 + NT * CT * 4;
     static thread_local bool configured = false;
     if (!configured && lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void*)chol_tiles_kernel<NT, WAVES, PART>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -758,12 +804,12 @@ hipError_t launch_chol_inv(const CholBlock* table_dev, const CholBlock* single, 
     if (blocks <= 0) return hipSuccess;
     CholBlock sb{};
     if (single) sb = *single;
-    if (max_k <= 5 * CT) return launch_chol_tiles<5, 4>(table_dev, sb, blocks, tol, shift_rel, stream);
-    if (max_k <= 9 * CT) return launch_chol_tiles<9, 4>(table_dev, sb, blocks, tol, shift_rel, stream);
-    if (max_k <= CT_MAXK) return launch_chol_tiles<17, 8>(table_dev, sb, blocks, tol, shift_rel, stream);
+    if (max_k <= 5 * CT) return launch_chol_tiles<5, 8>(table_dev, sb, blocks, tol, shift_rel, stream);
+    if (max_k <= 9 * CT) return launch_chol_tiles<9, 8>(table_dev, sb, blocks, tol, shift_rel, stream);
+    if (max_k <= CT_MAXK) return launch_chol_tiles<17, 12>(table_dev, sb, blocks, tol, shift_rel, stream);
     // both parts fit the tile counts of the two halves of max_k, whatever the other matrices of the launch
-    if (max_k <= 2 * 9 * CT) return launch_chol_parts<9, 4>(table_dev, sb, blocks, max_k, tol, shift_rel, stream);
-    if (max_k <= 2 * CT_MAXK) return launch_chol_parts<17, 8>(table_dev, sb, blocks, max_k, tol, shift_rel, stream);
+    if (max_k <= 2 * 9 * CT) return launch_chol_parts<9, 8>(table_dev, sb, blocks, max_k, tol, shift_rel, stream);
+    if (max_k <= 2 * CT_MAXK) return launch_chol_parts<17, 12>(table_dev, sb, blocks, max_k, tol, shift_rel, stream);
     hipLaunchKernelGGL(chol_inv_kernel, dim3(blocks), dim3(SMALL_THREADS), 0, stream, table_dev, sb, tol, shift_rel);
     return hipGetLastError();
 }

@@ -88,6 +88,31 @@ def test_refresh_full_sketch_sizes(tsr, k):
     assert float(torch.linalg.norm(core - torch.diag(s[:r])) / torch.linalg.norm(s)) < 2e-5
 
 
+# the factorization takes four columns at a time, sixteen per tile: dropped columns from every place of a panel on,
+# from the first of a tile on, and tiles of nothing else
+@pytest.mark.parametrize("rank", [1, 2, 3, 4, 5, 15, 16, 17, 21, 32, 35])
+def test_refresh_dropped_columns(tsr, rank):
+    """An exactly rank-deficient gradient: the directions beyond its rank are dropped pivots (zero columns of the
+    factor), and the leading ones span the gradient.  fp32 sums of up to 150 products: 150 x 2^-24, over the four
+    products in a row as above."""
+    m, n, r, p = 120, 150, 40, 8
+    key = si.stream_key(704, rank)
+    G = (si.normal((m, rank), si.stream_key(key, 1)).double() @ si.normal((rank, n), si.stream_key(key, 2)).double()).float()
+    U = torch.full((m, r), float("nan"), device="cuda")
+    V = torch.full((n, r), float("nan"), device="cuda")
+    sigma = torch.full((r + p,), float("nan"), device="cuda")
+    tsr.tsr_refresh_rsvd(dev(G), dev(si.omega(n, r + p, si.stream_key(key, 3))), r, p, 1, U, V, sigma)
+    U64, V64, s = U.cpu().double(), V.cpu().double(), torch.linalg.svdvals(G.double())
+    assert bool(torch.isfinite(U64).all() and torch.isfinite(V64).all())
+    tol = 4 * 150 * 2.0 ** -24
+    assert float((sigma.cpu().double()[:rank] - s[:rank]).abs().max() / s[0]) < tol
+    assert float(sigma[rank:].abs().max() / s[0]) < tol
+    # (a direction of rounding may survive the drop, of length one but not orthogonal to the others: the leading ones count)
+    U64, V64 = U64[:, :rank], V64[:, :rank]
+    back = U64 @ (U64.T @ G.double() @ V64) @ V64.T
+    assert float(torch.linalg.norm(back - G.double()) / torch.linalg.norm(G.double())) < tol
+
+
 # panels of 128 rows: 343 and 344 (three groups of workers), 1025 (one), 8 (every worker by itself)
 @pytest.mark.parametrize("m,n,r,workers,summed", [(43801, 136, 128, 8, True), (44000, 131, 128, 7, True),
                                                   (131077, 257, 256, 4, True), (1000, 136, 128, 8, False)])
