@@ -245,7 +245,8 @@ int tsr_realign_moment(const float* U_old, const float* V_old, const float* U_ne
  * p is the refresh oversampling (the plan reserves refresh scratch only if with_refresh).
  * tsr_plan_create synchronizes the stream once (table upload); of the other calls only
  * tsr_refresh_batched does (see there).  A plan with refresh of 8 blocks and more also owns
- * up to three HIP streams and four events (host objects, released by tsr_plan_destroy). */
+ * up to four events and uses up to three HIP streams, which all plans of a device share
+ * (host objects; the streams are released with the last such plan). */
 typedef struct tsr_plan tsr_plan;
 size_t tsr_plan_workspace_bytes(const tsr_matrix_desc* descs, int count, int n_workers,
                                 int precision, int with_refresh, int p);
@@ -280,7 +281,7 @@ int tsr_step_batched(tsr_plan* plan, int t, const tsr_hyper* h, void* stream);
  * refresh step).  Omegas is a HOST array of `count` device pointers (block i: n_i x (r_i + p)).
  * Plans of 8 blocks and more run the refresh as a few groups of blocks (three by default, at
  * most four) side by side: group
- * 0 on `stream`, the others on streams the plan owns (default priority), which start after the
+ * 0 on `stream`, the others on the shared streams of the device's plans (default priority), which start after the
  * work already queued on `stream` and which `stream` waits for before the call returns its
  * place in the queue to the caller; for the caller the call is ordered on `stream` like every
  * other.  The call waits on the host for its small table uploads before it enqueues the kernels.

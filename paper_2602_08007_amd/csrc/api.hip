@@ -692,6 +692,51 @@ int refresh_group_count(int blocks) {
     return g;
 }
 
+constexpr int MAX_DEVICES = 64;
+
+// The streams the groups of a refresh run on beside the caller's, shared by all plans of a device and given back
+// with the last of them.  A process has four hardware queues, which streams are dealt to as they are created: with
+// two streams of its own per plan, those of the second or third plan shared a queue with each other or with the
+// caller's stream, and their groups ran one after the other (refresh of the 60M model, three plans in turn: 4.50,
+// 4.52 and 7.6 ms; now 4.5 each).  Plans that refresh at the same time, from several threads, follow one another on
+// these streams; `queueing` keeps the groups of a call together.
+struct SideStreams {
+    std::mutex mutex, queueing;
+    int users = 0;
+    std::vector<hipStream_t> streams;
+};
+SideStreams g_side[MAX_DEVICES];
+
+void drop_side_streams(SideStreams& pool) {
+    for (hipStream_t st : pool.streams) (void)hipStreamDestroy(st);
+    pool.streams.clear();
+}
+
+// `count` streams of the current device; nullptr if there are none to be had.
+SideStreams* acquire_side_streams(size_t count, std::vector<hipStream_t>& out) {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) return nullptr;
+    SideStreams& pool = g_side[dev];
+    std::lock_guard<std::mutex> lock(pool.mutex);
+    while (pool.streams.size() < count) {
+        hipStream_t st = nullptr;
+        if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) {
+            if (pool.users == 0) drop_side_streams(pool);
+            return nullptr;
+        }
+        pool.streams.push_back(st);
+    }
+    ++pool.users;
+    out.assign(pool.streams.begin(), pool.streams.begin() + count);
+    return &pool;
+}
+
+void release_side_streams(SideStreams* pool) {
+    if (!pool) return;
+    std::lock_guard<std::mutex> lock(pool->mutex);
+    if (--pool->users == 0) drop_side_streams(*pool);
+}
+
 // ====================================================================== C ABI
 struct tsr_plan {
     std::vector<BlockView> blocks;
@@ -708,6 +753,7 @@ struct tsr_plan {
     // side streams when no stage timing is asked for
     std::vector<RefreshProgram> groups;
     std::vector<std::vector<int>> group_blocks;     // indices into refresh.blocks
+    SideStreams* side_pool = nullptr;
     std::vector<hipStream_t> side;                  // groups 1.. (group 0 runs on the caller's stream)
     std::vector<hipEvent_t> joined;
     hipEvent_t fork = nullptr;
@@ -716,9 +762,9 @@ struct tsr_plan {
     Prof prof;
     ~tsr_plan() {
         prof.clear();
-        for (hipStream_t st : side) (void)hipStreamDestroy(st);
         for (hipEvent_t ev : joined) (void)hipEventDestroy(ev);
         if (fork) (void)hipEventDestroy(fork);
+        release_side_streams(side_pool);
     }
 };
 
@@ -795,7 +841,6 @@ int tsr_project_core(const void* G, int g_dtype, int m, int n, long long ldg, co
 static __device__ __align__(256) unsigned char scratch[TSR_PROJECT_STATIC_SCRATCH_BYTES];
 
 namespace {
-constexpr int MAX_DEVICES = 64;
 void* g_scratch_ptr[MAX_DEVICES] = {nullptr};
 std::mutex g_scratch_mutex;
 
@@ -1287,21 +1332,18 @@ int tsr_plan_create(const tsr_matrix_desc* descs, int count, int n_workers, int 
         if (e != hipSuccess) { delete pl; return hip_fail(e); }
     }
     if (pl->groups.size() > 1) {
-        // side streams at the default priority; without them the refresh runs as one program
+        // side streams at the default priority; without them the refresh runs as one program on the caller's stream
         bool ok = hipEventCreateWithFlags(&pl->fork, hipEventDisableTiming) == hipSuccess;
         for (size_t g = 1; ok && g < pl->groups.size(); ++g) {
-            hipStream_t sg = nullptr; hipEvent_t ev = nullptr;
-            ok = hipStreamCreateWithFlags(&sg, hipStreamNonBlocking) == hipSuccess;
-            if (ok) pl->side.push_back(sg);
-            ok = ok && hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess;
+            hipEvent_t ev = nullptr;
+            ok = hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess;
             if (ev) pl->joined.push_back(ev);
         }
-        if (!ok) {
-            // no side streams to be had: the refresh then runs as one program on the caller's stream
+        if (ok) pl->side_pool = acquire_side_streams(pl->groups.size() - 1, pl->side);
+        if (!pl->side_pool) {
             (void)hipGetLastError();
-            for (hipStream_t sg : pl->side) (void)hipStreamDestroy(sg);
             for (hipEvent_t ev : pl->joined) (void)hipEventDestroy(ev);
-            pl->side.clear(); pl->joined.clear();
+            pl->joined.clear();
         }
     }
     *plan_out = pl;
@@ -1370,6 +1412,7 @@ int tsr_refresh_batched(tsr_plan* plan, const float* const* Omegas, int q, void*
         Ctx cx{st, &plan->prof};
         return run_refresh(rp, true, q, cx);
     }
+    std::lock_guard<std::mutex> lock(plan->side_pool->queueing);
     // fork: the side streams start after everything queued on the caller's stream so far
     TSR_HIP(hipEventRecord(plan->fork, st));
     // From here on an error does not return early: whatever was queued on a side stream is still

@@ -884,6 +884,53 @@ def test_refresh_batched_in_groups(tsr, groups, monkeypatch):
     plan.close()
 
 
+def test_refresh_of_plans_that_share_streams(tsr):
+    """Three plans of one device, refreshed in turn without a wait between, then from a thread and a stream each:
+    every plan gives what it gives alone, bit for bit; one of them is closed while the others go on."""
+    import threading
+    shapes = [(192, 256), (256, 192), (320, 320), (130, 264)] * 3
+    r, p, q = 16, 8, 1
+    omegas = [dev(si.omega(n, r + p, si.stream_key(724, i))) for i, (m, n) in enumerate(shapes)]
+    plans, blocks_of, alone = [], [], []
+    for k in range(3):
+        blocks, _ = make_blocks(shapes, r, 1, torch.float32, 721 + k, noise=1e-3)
+        plans.append(tsr.Plan(blocks, with_refresh=True, p=p))
+        blocks_of.append(blocks)
+    torch.cuda.synchronize()
+    for plan, blocks in zip(plans, blocks_of):
+        plan.tsr_refresh_batched(omegas, q)
+        torch.cuda.synchronize()
+        alone.append([(b["U"].clone(), b["V"].clone()) for b in blocks])
+
+    def check(which):
+        torch.cuda.synchronize()
+        for k in which:
+            for b, (U, V) in zip(blocks_of[k], alone[k]):
+                assert torch.equal(b["U"], U) and torch.equal(b["V"], V)
+                b["U"].zero_(); b["V"].zero_()
+
+    for plan in plans:
+        plan.tsr_refresh_batched(omegas, q)
+    check(range(3))
+
+    def work(plan, stream):
+        with torch.cuda.stream(stream):
+            for _ in range(3):
+                plan.tsr_refresh_batched(omegas, q)
+    threads = [threading.Thread(target=work, args=(plan, torch.cuda.Stream())) for plan in plans]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    check(range(3))
+    plans[1].close()
+    for k in (2, 0):
+        plans[k].tsr_refresh_batched(omegas, q)
+    check((0, 2))
+    for k in (0, 2):
+        plans[k].close()
+
+
 def test_determinism_bitwise(tsr):
     # split-k partials are reduced in a fixed order: two runs give identical bits
     m, n, r = 512, 1376, 64
