@@ -235,10 +235,11 @@ void build_project(ProjectProgram& pg, const std::vector<BlockView>& blocks, int
 
 // A single call's program, in the caller's workspace: building it writes nothing there, so it is sized by being
 // built.  Where it does not fit into `most` bytes it is built tight.
-template <typename Build> int build_within(void* ws, size_t ws_bytes, size_t most, Build&& build) {
+template <typename Build> int build_within(void* ws, size_t ws_bytes, size_t most, Build&& build, size_t* used = nullptr) {
     for (const bool tight : {false, true}) {
         Arena ar(ws, tight);
         build(ar);
+        if (used) *used = ar.used();
         if (ar.used() <= (tight ? ws_bytes : std::min(most, ws_bytes))) return TSR_OK;
     }
     return TSR_WORKSPACE_TOO_SMALL;
@@ -246,17 +247,57 @@ template <typename Build> int build_within(void* ws, size_t ws_bytes, size_t mos
 
 // The program of one matrix.  Beyond the built-in scratch of tsr_project_core_static it is tight in any case, so
 // that this entry point takes what fits there and computes the same bits as tsr_project_core.
-int build_project_one(ProjectProgram& pg, const std::vector<BlockView>& block, int prec, void* ws, size_t ws_bytes) {
+int build_project_one(ProjectProgram& pg, const std::vector<BlockView>& block, int prec, void* ws, size_t ws_bytes, size_t* used) {
     return build_within(ws, ws_bytes, (size_t)TSR_PROJECT_STATIC_SCRATCH_BYTES, [&](Arena& ar) {
         pg = ProjectProgram{};
         build_project(pg, block, 1, prec, ar);
-    });
+    }, used);
+}
+
+// A matrix whose launches would have 64 x 64 tiles anyway (fewer than 256 units of work, see pick_shape) takes the
+// kernels made for one of r <= 128, two launches for the projection and one for the lift.  Measured on the device, us,
+// the four and two launches of the general kernels first: 512 x 1376 r = 64 projection 17.0 / 9.3, lift 9.2 / 6.1;
+// 200 x 333 r = 17 14.6 / 7.3 and 8.6 / 5.8; 4029 x 492 r = 56 21.2 / 13.5 and 11.7 / 9.2; with r between 96 and 128 the
+// kernels take about the same time, 768 x 2048 r = 96 20.0 / 18.0 and 11.4 / 11.0, 1024 x 2048 r = 128 21.8 / 20.9 and
+// 13.0 / 12.4, and the host's three launches less remain (some 11 us of a step).
+bool one_small_matrix(int m, int n, int r, bool project) {
+    const long long units = (long long)ceil_div(m, 128) * (project ? std::max(1, n / 128) : ceil_div(n, 128));
+    return r <= ONE_MAX_R && units < 256;
+}
+
+// Projection of one matrix: about 128 workgroups (64 and 256 are slower from 512 x 1376 on), as many partial cores as
+// fit into `bytes` of scratch, which is what the program on the general kernels takes; false if not one per 64 rows does.
+bool project_one_plan(ProjectOne& q, const BlockView& b, void* ws, size_t bytes) {
+    if (!one_small_matrix(b.m, b.n, b.r, true)) return false;
+    const size_t slabs = ceil_div(b.m, 64), core = (size_t)b.r * b.r * sizeof(float);
+    const size_t chunks = std::min(std::max<size_t>(1, 128 / slabs), bytes / (slabs * core));
+    if (chunks == 0) return false;
+    q = ProjectOne{b.G, b.U, b.V, (float*)ws, b.ldg, b.m, b.n, b.r, 1, 0};
+    q.kchunk = std::max(64, ceil_div(ceil_div(b.n, (int)chunks), 32) * 32);
+    q.chunks = ceil_div(b.n, q.kchunk);
+    return true;
 }
 
 int run_project(const ProjectProgram& pg, bool grouped, float alpha, float beta, Ctx& cx) {
     TSR_TRY(run_stage(pg.gv[TSR_F32], grouped, 1.0f, 0.0f, cx, TSR_PROF_GV));
     TSR_TRY(run_stage(pg.gv[TSR_BF16], grouped, 1.0f, 0.0f, cx, TSR_PROF_GV));
     return run_stage(pg.utp, grouped, alpha, beta, cx, TSR_PROF_UTP);
+}
+
+int project_one_matrix(const std::vector<BlockView>& block, int prec, float alpha, float beta, void* ws, size_t ws_bytes,
+                       hipStream_t stream) {
+    ProjectProgram pg;
+    size_t used = 0;
+    TSR_TRY(build_project_one(pg, block, prec, ws, ws_bytes, &used));
+    ProjectOne q;
+    if (project_one_plan(q, block[0], ws, used)) {
+        const int partials = ceil_div(q.m, 64) * q.chunks;
+        TSR_HIP(launch_project_one(q, block[0].g_dtype == TSR_BF16, prec != TSR_PREC_BF16, partials, stream));
+        TSR_HIP(launch_splitk_reduce_wide(q.part, block[0].C, (long long)q.r * q.r, partials, q.r * q.r, alpha, beta, stream));
+        return TSR_OK;
+    }
+    Ctx cx{stream, nullptr};
+    return run_project(pg, false, alpha, beta, cx);
 }
 
 struct LiftProgram {
@@ -826,10 +867,7 @@ int tsr_project_core(const void* G, int g_dtype, int m, int n, long long ldg, co
     if (!aligned256(ws)) return TSR_INVALID_ARG;
     std::vector<BlockView> v;
     one_block_view(v, G, g_dtype, m, n, r, ldg, nullptr, n, (float*)U, (float*)V, C, nullptr);
-    ProjectProgram pg;
-    TSR_TRY(build_project_one(pg, v, precision, ws, ws_bytes));
-    Ctx cx{(hipStream_t)stream, nullptr};
-    return run_project(pg, false, alpha, accumulate ? 1.0f : 0.0f, cx);
+    return project_one_matrix(v, precision, alpha, accumulate ? 1.0f : 0.0f, ws, ws_bytes, (hipStream_t)stream);
 }
 
 // ---------------------------------------------------------------- project, nothing allocated
@@ -877,10 +915,7 @@ int tsr_project_core_static(const void* G, int g_dtype, int m, int n, long long 
     // written earlier in the same call: nothing has to start at zero, so nothing is cleared
     std::vector<BlockView> v;
     one_block_view(v, G, g_dtype, m, n, r, ldg, nullptr, n, (float*)U, (float*)V, C, nullptr);
-    ProjectProgram pg;
-    TSR_TRY(build_project_one(pg, v, precision, ws, TSR_PROJECT_STATIC_SCRATCH_BYTES));
-    Ctx cx{(hipStream_t)stream, nullptr};
-    return run_project(pg, false, alpha, accumulate ? 1.0f : 0.0f, cx);
+    return project_one_matrix(v, precision, alpha, accumulate ? 1.0f : 0.0f, ws, TSR_PROJECT_STATIC_SCRATCH_BYTES, (hipStream_t)stream);
 }
 
 // ---------------------------------------------------------------- average
@@ -952,6 +987,14 @@ int tsr_backproject_apply(float* W, int m, int n, long long ldw, const float* U,
     one_block_view(v, nullptr, TSR_F32, m, n, r, n, W, ldw, (float*)U, (float*)V, nullptr, (float*)D);
     LiftProgram lp;
     TSR_TRY(build_within(ws, ws_bytes, ws_bytes, [&](Arena& ar) { build_lift(lp, v, precision, ar); }));
+    if (one_small_matrix(m, n, r, false)) {
+        const int slabs = ceil_div(m, 64), tiles = ceil_div(n, 64);
+        // up to 256 workgroups; 512 with fewer tiles each: 1001 x 1365 r = 96 11.8 / 13.3 us, 4029 x 492 r = 56 9.2 / 10.1
+        LiftOne q{W, U, V, D, ldw, m, n, r, 0, ceil_div(slabs * tiles, 256), -lr * scale, 1.0f - lr * wd};
+        q.groups = ceil_div(tiles, q.per_group);
+        TSR_HIP(launch_lift_one(q, precision != TSR_PREC_BF16, slabs * q.groups, (hipStream_t)stream));
+        return TSR_OK;
+    }
     Ctx cx{(hipStream_t)stream, nullptr};
     return run_lift(lp, false, lr, wd, scale, cx);
 }

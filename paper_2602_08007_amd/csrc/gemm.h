@@ -62,4 +62,26 @@ struct ReduceProblem {
 hipError_t launch_splitk_reduce(const ReduceProblem* probs_dev, const ReduceProblem* single,
                                 int count, int max_elems, float alpha, float beta, hipStream_t stream);
 
+// out[i] = alpha * (sum of `splits` partials `stride` apart)[i] + beta * out[i], i < total: one problem, few outputs
+hipError_t launch_splitk_reduce_wide(const float* part, float* out, long long stride, int splits, int total, float alpha, float beta,
+                                     hipStream_t stream);
+
+// The step of one small matrix, r <= ONE_MAX_R.  Projection: workgroup (slab, chunk), slab-major, leaves
+// U_s^T (G_sc V_c), r x r, for 64 rows s and kchunk columns c (a multiple of 32) in part[workgroup].
+constexpr int ONE_MAX_R = 128;
+struct ProjectOne {
+    const void* G; const float* U; const float* V; float* part;
+    long long ldg;
+    int m, n, r, chunks, kchunk;
+};
+hipError_t launch_project_one(const ProjectOne& q, int g_bf16, int split, int blocks, hipStream_t stream);
+// Lift: W = beta W + alpha U D V^T; workgroup (slab, group), slab-major: 64 rows, per_group tiles of 64 columns.
+struct LiftOne {
+    float* W; const float* U; const float* V; const float* D;
+    long long ldw;
+    int m, n, r, groups, per_group;
+    float alpha, beta;
+};
+hipError_t launch_lift_one(const LiftOne& q, int split, int blocks, hipStream_t stream);
+
 }  // namespace tsr

@@ -17,8 +17,7 @@
 // read-modify-write -> two stages -> W read early -> stores behind the products): the step of the 60M model in
 // fp32 at rank 256, 643 -> 304 -> 289 -> 271 us; of a 32000 x 2048 embedding and LM head at rank 128,
 // 1060 -> 551 -> 512 -> 475 us; the refresh of the latter 3608 -> 3399 us by the last of these (each pair on one
-// card; cards differ by some 3 %).  The hint on W further down takes the two steps to 269 and 460 us.  The step of
-// one 512 x 1376 fp32 matrix at rank 64, 104 -> 37 us, is bound by its seven launches since.
+// card; cards differ by some 3 %).  The hint on W further down takes the two steps to 269 and 460 us.
 #include "gemm.h"
 
 #include <type_traits>
@@ -486,6 +485,272 @@ hipError_t launch_gemm(const GemmLaunch& L, const GemmVariant& v, hipStream_t st
     return hipErrorInvalidValue;
 }
 
+// ------------------------------------------------------------------ the step of one small matrix
+// A single call on a small matrix is bound by its launches, on the host (3-4 us each) as on the device (3-6 us each,
+// of which the trips to memory are the most).  So the two products of the projection are one launch here (and the
+// sum of its partial cores a second), and the two products of the lift one: seven launches of a step become four,
+// 38.1 -> 28.0 us for 512 x 1376 fp32 at r = 64, 38.5 -> 28.6 us for 1001 x 1365 bf16 at r = 96.  What is left is the
+// host's (four launches and the caller's program around them; the kernels take 18 and 29 us).
+// Both keep the arithmetic of the general kernel: the intermediate in fp32, cut into pieces for the second product.
+// Used for r <= 128, where the intermediate of 64 rows fits the registers and LDS of a workgroup, and matrices whose
+// launches would have 64 x 64 tiles anyway (pick_shape).
+
+// acc += A B over one k-tile in LDS
+template <int NSA, int NSB, int FM, int FN, typename OpA, typename OpB>
+__device__ inline void multiply_tiles(f32x16 (&acc)[FM][FN], const unsigned short* sA, const unsigned short* sB, int a_row0,
+                                      int b_row0, int a_pitch, int a_piece, int lane) {
+#pragma unroll
+    for (int kk = 0; kk < BK / 16; ++kk) {
+        const int kofs = kk * 16 + (lane >> 5) * 8;
+        bf16x8 fa[NSA][FM], fb[NSB][FN];
+#pragma unroll
+        for (int p = 0; p < NSA; ++p)
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+                fa[p][i] = *(const bf16x8*)(sA + p * a_piece + (a_row0 + i * 32 + (lane & 31)) * a_pitch + kofs);
+#pragma unroll
+        for (int p = 0; p < NSB; ++p)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+                fb[p][j] = *(const bf16x8*)(sB + p * OpB::TILE + lds_at<false>(b_row0 + j * 32, lane & 31, kofs));
+        constexpr int ORD = (NSA > NSB) ? NSA : NSB;           // smallest terms first
+#pragma unroll
+        for (int o = ORD - 1; o >= 0; --o)
+#pragma unroll
+            for (int pa = 0; pa < NSA; ++pa) {
+                const int pb = o - pa;
+                if (pb < 0 || pb >= NSB) continue;
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[pa][i], fb[pb][j], acc[i][j], 0, 0, 0);
+            }
+    }
+}
+
+// acc += A B over the operands' k range: two register stages, two LDS buffers (of NSA pieces of A and NSB of B), a
+// barrier per k-tile.
+template <int NSA, int NSB, int FM, int FN, typename OpA, typename OpB>
+__device__ inline void product(f32x16 (&acc)[FM][FN], OpA& a, OpB& b, int klen, bool edge_a, bool edge_b, unsigned short* lds,
+                               int wm, int wn, int lane) {
+    constexpr int A_ELEMS = NSA * OpA::TILE, BUF = A_ELEMS + NSB * OpB::TILE;
+    const int nt = (klen + BK - 1) / BK;
+    typename OpA::Reg sa[2][OpA::NCH];
+    typename OpB::Reg sb[2][OpB::NCH];
+    const bool vectors = a.vector_ok() && b.vector_ok();
+    auto fetch = [&](auto slot, int t) {
+        constexpr int S = decltype(slot)::value;
+        if (vectors) { a.load(sa[S], t); b.load(sb[S], t); }
+        else { a.load_scalar(sa[S], t); b.load_scalar(sb[S], t); }
+    };
+    auto step = [&](auto slot, int t) {
+        constexpr int S = decltype(slot)::value;
+        unsigned short* d = lds + S * BUF;
+        const bool partial = vectors && (t + 1) * BK > klen;
+        a.template store<NSA>(sa[S], d, t, partial, edge_a && vectors);
+        b.template store<NSB>(sb[S], d + A_ELEMS, t, partial, edge_b && vectors);
+        __syncthreads();
+        if (t + 2 < nt) fetch(slot, t + 2);
+        multiply_tiles<NSA, NSB, FM, FN, OpA, OpB>(acc, d, d + A_ELEMS, wm * FM * 32, wn * FN * 32, lds_pitch<false>(), OpA::TILE, lane);
+    };
+    typedef std::integral_constant<int, 0> S0;
+    typedef std::integral_constant<int, 1> S1;
+    if (nt > 0) fetch(S0{}, 0);
+    if (nt > 1) fetch(S1{}, 1);
+    for (int t = 0; t < nt; t += 2) {
+        step(S0{}, t);
+        if (t + 1 < nt) step(S1{}, t + 1);
+    }
+}
+
+template <int FM, int FN> __device__ inline void clear(f32x16 (&acc)[FM][FN]) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+}
+
+// x -> NS bf16 pieces at d, d + piece, ...
+template <int NS> __device__ inline void put4(float (&x)[4], unsigned short* d, int piece) {
+#pragma unroll
+    for (int p = 0; p < NS; ++p) {
+        bf16x4 h;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            h[j] = (__bf16)x[j];
+            if (p + 1 < NS) x[j] -= (float)h[j];
+        }
+        *(bf16x4*)(d + p * piece) = h;
+    }
+}
+
+// One partial core per workgroup: U_s^T (G_sc V_c) for 64 rows s and a range c of columns.
+template <bool G_BF16, int NSA, int NSB, int RP>
+__global__ __launch_bounds__(NTHREADS, 2) void project_one_kernel(const ProjectOne q) {
+    constexpr int TM = 64, FN = RP / 64;
+    typedef Operand<false, G_BF16, TM, false> OpG;
+    typedef Operand<true, false, RP, false> OpV;
+    constexpr int FIRST = 2 * (NSA * OpG::TILE + NSB * OpV::TILE), SECOND = 4 * NSB * OpV::TILE;
+    __shared__ __attribute__((aligned(16))) unsigned short lds[FIRST > SECOND ? FIRST : SECOND];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
+    const int slab = blockIdx.x / q.chunks, chunk = blockIdx.x % q.chunks;
+    const int row0 = slab * TM, rows = min(q.m - row0, TM);
+    const int kbeg = chunk * q.kchunk, klen = min(q.n - kbeg, q.kchunk);
+    const bool edge_r = q.r < RP;
+
+    // the rows of U, behind the first product
+    OpV u;
+    u.init(q.U, q.r, q.r, 0, row0, rows, tid);
+    typename OpV::Reg su[2][OpV::NCH];
+    const bool vectors = u.vector_ok();
+    auto fetch_u = [&](auto half) {
+        constexpr int H = decltype(half)::value;
+        if (vectors) u.load(su[H], H);
+        else u.load_scalar(su[H], H);
+    };
+    fetch_u(std::integral_constant<int, 0>{});
+    if (rows > BK) fetch_u(std::integral_constant<int, 1>{});
+
+    f32x16 P[1][FN];
+    clear(P);
+    {
+        OpG a; OpV b;
+        a.init(q.G, q.ldg, q.m, row0, kbeg, klen, tid);
+        b.init(q.V, q.r, q.r, 0, kbeg, klen, tid);
+        product<NSA, NSB, 1, FN>(P, a, b, klen, row0 + TM > q.m, edge_r, lds, wm, wn, lane);
+    }
+    __syncthreads();
+    // U_s and P, both with the slab's rows as the contraction: [32 rows][operand][piece][column][row]
+    constexpr int HALF = 2 * NSB * OpV::TILE;
+    u.template store<NSB>(su[0], lds, 0, vectors && rows < BK, edge_r && vectors);
+    if (rows > BK) u.template store<NSB>(su[1], lds + HALF, 1, vectors && rows < 2 * BK, edge_r && vectors);
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; e += 4) {
+            float x[4] = {P[0][j][e], P[0][j][e + 1], P[0][j][e + 2], P[0][j][e + 3]};
+            put4<NSB>(x, lds + wm * HALF + NSB * OpV::TILE + lds_at<false>((wn * FN + j) * 32, lane & 31, (e >> 2) * 8 + (lane >> 5) * 4),
+                      OpV::TILE);
+        }
+    __syncthreads();
+    f32x16 C[FN][FN];
+    clear(C);
+    for (int h = 0; h * BK < rows; ++h)
+        multiply_tiles<NSB, NSB, FN, FN, OpV, OpV>(C, lds + h * HALF, lds + h * HALF + NSB * OpV::TILE, wm * FN * 32, wn * FN * 32,
+                                                   lds_pitch<false>(), OpV::TILE, lane);
+    TSR_GLOBAL float* out = (TSR_GLOBAL float*)q.part + (long long)blockIdx.x * q.r * q.r;
+#pragma unroll
+    for (int i = 0; i < FN; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int row = (wm * FN + i) * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3), col = (wn * FN + j) * 32 + (lane & 31);
+                if (row < q.r && col < q.r) out[row * q.r + col] = C[i][j][e];
+            }
+}
+
+// 64 rows of T = U D, kept as pieces in LDS, then W = beta W + alpha T V^T for a few 64 x 64 tiles of these rows.
+template <int NS, int RP>
+__global__ __launch_bounds__(NTHREADS, 2) void lift_one_kernel(const LiftOne q) {
+    constexpr int TM = 64, FN = RP / 64, KT = RP / BK, TP = RP + 8;
+    typedef Operand<false, false, TM, false> OpU;              // also the rows of V
+    typedef Operand<true, false, RP, false> OpD;
+    constexpr int T_ELEMS = NS * TM * TP, FIRST = 2 * NS * (OpU::TILE + OpD::TILE), SECOND = T_ELEMS + KT * NS * OpU::TILE;
+    __shared__ __attribute__((aligned(16))) unsigned short lds[FIRST > SECOND ? FIRST : SECOND];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
+    const int slab = blockIdx.x / q.groups, group = blockIdx.x % q.groups;
+    const int row0 = slab * TM, tiles = (q.n + 63) / 64, kt_used = (q.r + BK - 1) / BK;
+    const int tile_end = min(tiles, (group + 1) * q.per_group);
+
+    OpU v;
+    typename OpU::Reg sv[KT][OpU::NCH];
+    f32x16 old;
+    const int rbase = row0 + wm * 32 + (lane >> 5) * 4, cbase = wn * 32 + (lane & 31);
+    bool vectors = false;
+    auto fetch = [&](int tile) {                               // rows of V and the tile of W, edges by clamped addresses
+        v.init(q.V, q.r, q.n, tile * 64, 0, q.r, tid);
+        vectors = v.vector_ok();
+#pragma unroll
+        for (int t = 0; t < KT; ++t) {
+            if (t >= kt_used) continue;
+            if (vectors) v.load(sv[t], t);
+            else v.load_scalar(sv[t], t);
+        }
+        if (q.beta != 0.0f)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                old[e] = __builtin_nontemporal_load((const TSR_GLOBAL float*)q.W + (long long)min(rbase + (e >> 2) * 8 + (e & 3), q.m - 1) * q.ldw +
+                                                    min(tile * 64 + cbase, q.n - 1));
+    };
+    fetch(group * q.per_group);
+    {
+        f32x16 T[1][FN];
+        clear(T);
+        OpU a; OpD b;
+        a.init(q.U, q.r, q.m, row0, 0, q.r, tid);
+        b.init(q.D, q.r, q.r, 0, 0, q.r, tid);
+        product<NS, NS, 1, FN>(T, a, b, q.r, row0 + TM > q.m, q.r < RP, lds, wm, wn, lane);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int row = wm * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3), col = (wn * FN + j) * 32 + (lane & 31);
+                float x = (col < q.r) ? T[0][j][e] : 0.0f;
+#pragma unroll
+                for (int p = 0; p < NS; ++p) {
+                    const __bf16 h = (__bf16)x;
+                    lds[p * TM * TP + row * TP + col] = __builtin_bit_cast(unsigned short, h);
+                    x -= (float)h;
+                }
+            }
+    }
+    unsigned short* sV = lds + T_ELEMS;
+    for (int tile = group * q.per_group; tile < tile_end; ++tile) {
+#pragma unroll
+        for (int t = 0; t < KT; ++t)
+            if (t < kt_used) v.template store<NS>(sv[t], sV + t * NS * OpU::TILE, t, vectors && (t + 1) * BK > q.r, false);
+        const f32x16 w = old;
+        __syncthreads();
+        if (tile + 1 < tile_end) fetch(tile + 1);
+        f32x16 acc[1][1];
+        clear(acc);
+        for (int t = 0; t < kt_used; ++t)
+            multiply_tiles<NS, NS, 1, 1, OpU, OpU>(acc, lds + t * BK, sV + t * NS * OpU::TILE, wm * 32, wn * 32, TP, TM * TP, lane);
+        const int col = tile * 64 + cbase;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int row = rbase + (e >> 2) * 8 + (e & 3);
+            float x = q.alpha * acc[0][0][e];
+            if (q.beta != 0.0f) x += q.beta * w[e];
+            if (row < q.m && col < q.n) __builtin_nontemporal_store(x, (TSR_GLOBAL float*)q.W + (long long)row * q.ldw + col);
+        }
+        __syncthreads();
+    }
+}
+
+hipError_t launch_project_one(const ProjectOne& q, int g_bf16, int split, int blocks, hipStream_t stream) {
+    typedef void (*fn)(const ProjectOne);
+    static const fn table[2][2][2] = {
+        {{project_one_kernel<false, 1, 1, 64>, project_one_kernel<false, 1, 1, 128>},
+         {project_one_kernel<false, 2, 2, 64>, project_one_kernel<false, 2, 2, 128>}},
+        {{project_one_kernel<true, 1, 1, 64>, project_one_kernel<true, 1, 1, 128>},
+         {project_one_kernel<true, 1, 2, 64>, project_one_kernel<true, 1, 2, 128>}}};
+    hipLaunchKernelGGL(table[g_bf16 != 0][split != 0][q.r > 64], dim3(blocks), dim3(NTHREADS), 0, stream, q);
+    return hipGetLastError();
+}
+
+hipError_t launch_lift_one(const LiftOne& q, int split, int blocks, hipStream_t stream) {
+    typedef void (*fn)(const LiftOne);
+    static const fn table[2][2] = {{lift_one_kernel<1, 64>, lift_one_kernel<1, 128>}, {lift_one_kernel<2, 64>, lift_one_kernel<2, 128>}};
+    hipLaunchKernelGGL(table[split != 0][q.r > 64], dim3(blocks), dim3(NTHREADS), 0, stream, q);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------------ split-k reduction
 // Four neighbouring elements per thread, the partials of all splits fetched eight at a time.
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceProblem* probs, const ReduceProblem single,
@@ -532,6 +797,54 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceProblem*
         for (int k = 0; k < p.splits; ++k) s += part[(long long)k * p.stride + i];
         finish(i, s);
     }
+}
+
+// The same for few outputs and many partials of one problem: sixteen vectors of outputs per workgroup, sixteen threads
+// share the partials of each (neighbouring threads neighbouring vectors), their sums added in order.  Dense outputs.
+__global__ __launch_bounds__(256) void splitk_reduce_wide_kernel(const float* part_, float* out_, long long stride, int splits, int total,
+                                                                 const float alpha, const float beta) {
+    constexpr int G = 16;
+    __shared__ f32x4 sums[G][G];
+    const TSR_GLOBAL float* part = (const TSR_GLOBAL float*)part_;
+    TSR_GLOBAL float* out = (TSR_GLOBAL float*)out_;
+    const int x = threadIdx.x % G, g = threadIdx.x / G;
+    const int i = 4 * (blockIdx.x * G + x);
+    const int per = (splits + G - 1) / G, k0 = g * per, k1 = min(splits, k0 + per);
+    const bool whole = i + 4 <= total;
+    f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+    auto at = [&](int k) {
+        const TSR_GLOBAL float* p = part + k * stride + i;
+        if (whole) return (f32x4)*(const TSR_GLOBAL f32x4_u*)p;
+        f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) if (i + u < total) v[u] = p[u];
+        return v;
+    };
+    int k = k0;
+    for (; k + 8 <= k1; k += 8) {
+        f32x4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = at(k + u);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; k < k1; ++k) s += at(k);
+    sums[g][x] = s;
+    __syncthreads();
+    if (g != 0) return;
+#pragma unroll
+    for (int u = 1; u < G; ++u) s += sums[u][x];
+    s = alpha * s;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (i + u < total) out[i + u] = s[u] + (beta != 0.0f ? beta * out[i + u] : 0.0f);
+}
+
+hipError_t launch_splitk_reduce_wide(const float* part, float* out, long long stride, int splits, int total, float alpha, float beta,
+                                     hipStream_t stream) {
+    if (total <= 0) return hipSuccess;
+    hipLaunchKernelGGL(splitk_reduce_wide_kernel, dim3((total + 63) / 64), dim3(256), 0, stream, part, out, stride, splits, total, alpha, beta);
+    return hipGetLastError();
 }
 
 hipError_t launch_splitk_reduce(const ReduceProblem* probs_dev, const ReduceProblem* single, int count,

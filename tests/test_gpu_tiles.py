@@ -28,10 +28,12 @@ def _bases(m, n, r, key):
     return si.orthonormal(m, r, si.stream_key(key, 1)).float(), si.orthonormal(n, r, si.stream_key(key, 2)).float()
 
 
-# 64 x 64 tiles (few units of work), 128 x 64 (rank 30 at many units), 128 x 128; k remainders of 1 and 31
+# the kernels for one small matrix (r <= 128: ranks of one and two 64-wide blocks and their remainders, rows and
+# columns around 64, contractions below a vector's width), 64 x 64 tiles (r = 129), 128 x 64 (rank 30 at many units), 128 x 128; k remainders of 1 and 31
 # beside whole k-tiles; row remainders of 1, 2 and 127; extents below a vector's (2, 3, 5 and 7)
 SIZES = [(2, 3, 2), (5, 7, 3), (7, 65, 5), (64, 64, 64), (65, 97, 33), (127, 129, 65), (1026, 3713, 65), (1151, 4127, 30),
-         (641, 4097, 129)]
+         (641, 4097, 129),
+         (1, 1, 1), (33, 31, 4), (63, 129, 63), (130, 1000, 128), (1000, 100, 97), (1001, 1365, 96), (200, 131, 130)]
 
 
 @pytest.mark.parametrize("m,n,r", SIZES)
