@@ -38,6 +38,7 @@ struct LogicalGemm {
     int M, N, K;
     float* out; long long ldc;
     int group = -1;                // consecutive entries with the same group >= 0 are summed into `out`
+    int b_upper = 0;               // B is upper triangular (see GemmProblem)
 };
 
 struct GemmStage {
@@ -139,6 +140,7 @@ void build_stage(GemmStage& st, const GemmVariant& var, const std::vector<Logica
             GemmProblem& p = st.probs[j];
             p.A = g.A; p.B = g.B; p.lda = g.lda; p.ldb = g.ldb;
             p.M = g.M; p.N = g.N; p.K = g.K;
+            p.b_upper = st.direct ? g.b_upper : 0;
             if (st.direct) {
                 p.C = g.out; p.ldc = g.ldc; p.c_split_stride = 0;
                 p.kchunk = std::max(32, ceil_div(g.K, 32) * 32);
@@ -423,7 +425,7 @@ void build_orth_nt(OrthNtPass& pass, const std::vector<RefreshBlock>& blocks, bo
         g.push_back(NtLogical{Xt, Xt, b.S, ldrows, ldrows, k, k, k, rows, bi, bi});
         g.push_back(NtLogical{Xt + st_t, Xt, b.S, ldrows, ldrows, k, k, k, rows, bi, bi});
         g.push_back(NtLogical{Xt, Xt + st_t, b.S, ldrows, ldrows, k, k, k, rows, bi, bi});
-        a1.push_back(NtLogical{b.Xp, b.Rt, out, ld2, ld2, k, rows, k, (int)ld2, bi, -1, st_r});
+        a1.push_back(NtLogical{b.Xp, b.Rt, out, ld2, ld2, k, rows, k, (int)ld2, bi, -1, st_r, (int)b.ldk});
         pass.max_rows = std::max(pass.max_rows, rows); pass.max_k = std::max(pass.max_k, k);
     }
     if (g.empty()) return;
@@ -447,12 +449,12 @@ void build_orth(OrthProgram& op, const std::vector<RefreshBlock>& blocks, bool o
         const int k = b.k;
         if (!(b.nt && orth_nt)) {
             gA.push_back(LogicalGemm{X, X, k, k, k, k, rows, b.S, k});
-            qA.push_back(LogicalGemm{X, b.Rinv, k, k, rows, k, k, Xalt, k});
+            qA.push_back(LogicalGemm{X, b.Rinv, k, k, rows, k, k, Xalt, k, -1, 1});
             gE.push_back(LogicalGemm{Xalt, Xalt, k, k, k, k, rows, b.S, k});
-            qE.push_back(LogicalGemm{Xalt, b.Rinv, k, k, rows, k, k, X, k});
+            qE.push_back(LogicalGemm{Xalt, b.Rinv, k, k, rows, k, k, X, k, -1, 1});
         }
         gB.push_back(LogicalGemm{X, X, k, k, k, k, rows, b.S, k});
-        qB.push_back(LogicalGemm{X, b.Rinv, k, k, rows, k, k, Xalt, k});
+        qB.push_back(LogicalGemm{X, b.Rinv, k, k, rows, k, k, Xalt, k, -1, 1});
         // the three triangular factors (X = Q R3 R2 R1) go to R1, Rmid and Gacc (free until the small
         // SVD); where their product is needed, fp64 MFMA GEMMs form it afterwards (run_refresh_back)
         op.cholA.push_back(CholBlock{b.S, b.Rinv, b.R1, b.work, k});

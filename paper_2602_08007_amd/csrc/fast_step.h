@@ -33,6 +33,7 @@ struct NtLogical {
     int block;      // owning matrix block (tiles of one block stay on one XCD)
     int group;      // consecutive entries with the same group >= 0 are summed into `out`
     long long b_piece_stride = 0;   // NtVariant::b_pieces > 1: elements between the pieces of B
+    int b_upper = 0;                // see NtProblem
 };
 
 // Tile lists, k splits and partial buffers of one launch (want_tiles: split k while the launch has

@@ -169,6 +169,7 @@ void build_nt_stage(NtStageH& st, const NtVariant& var, const std::vector<NtLogi
             NtProblem& p = st.probs[j];
             p.A = g.A; p.B = g.B; p.lda = g.lda; p.ldb = g.ldb; p.M = g.M; p.N = g.N; p.K = g.K;
             p.b_piece_stride = g.b_piece_stride;
+            p.b_upper = direct ? g.b_upper : 0;
             if (direct) {
                 p.C = g.out; p.ldc = g.ldc; p.c_split_stride = 0; p.kchunk = std::max(64, cdiv(g.K, 64) * 64);
                 ksplit[j] = 1;
@@ -187,7 +188,8 @@ void build_nt_stage(NtStageH& st, const NtVariant& var, const std::vector<NtLogi
                                 if (lower_only && ((group_m > 0) ? t2 : t3) * TN > tm * TM + TM - 1) continue;
                                 st.tiles.push_back(NtTile{(int)j, tm, (group_m > 0) ? t2 : t3, ks});
                                 tile_block.push_back(g.block);
-                                tile_work.push_back(std::min(p.kchunk, g.K) + 64);
+                                const int cols = (((group_m > 0) ? t2 : t3) + 1) * TN;
+                                tile_work.push_back(std::min(p.kchunk, (p.b_upper > cols) ? 2 * cols : g.K) + 64);
                             }
         }
         i = e;

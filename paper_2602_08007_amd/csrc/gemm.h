@@ -19,6 +19,7 @@ struct GemmProblem {
     long long c_split_stride;  // elements between the partial outputs of consecutive k-splits
     int M, N, K;
     int kchunk;         // K range handled by one tile (multiple of 32); K if no split
+    int b_upper;        // B is upper triangular (element (j, k) zero for k > j): only launches without split
 };
 
 struct GemmTile {       // one workgroup's work

@@ -287,8 +287,10 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_kernel(const GemmLaunch L) {
     const float alpha = L.alpha, beta = L.beta;
     TSR_GLOBAL float* C = (TSR_GLOBAL float*)pp->C + (long long)ks * pp->c_split_stride;
     const int kbeg = ks * pp->kchunk;
-    const int klen = min(pp->K - kbeg, pp->kchunk);
     const int row0 = tm * TM, col0 = tn * TN;
+    int klen = min(pp->K - kbeg, pp->kchunk);
+    // A third of the work of X R^-1 at k = 264 and 528 (below the diagonal of the factor: zeros)
+    if (pp->b_upper) klen = min(klen, col0 + TN);
 
     f32x16 acc[FM][FN];
 #pragma unroll

@@ -23,6 +23,8 @@ struct NtProblem {
     int kchunk;             // multiple of 64
     const AdamTBlock* adam; // fused Adam epilogue (NtVariant::fused_adam): this core's moment arrays
     long long b_piece_stride;   // NtVariant::b_pieces > 1: elements between the bf16 pieces of B
+    int b_upper;            // > 0: B is two copies, this many k apart, of an upper triangular matrix (element (j, k) zero
+                            // for k > j); the wide-tile kernel leaves the zeros out, launches without split only
 };
 
 struct NtTile { int prob, tm, tn, ks; };     // prob < 0: idle workgroup

@@ -369,7 +369,16 @@ __global__ __launch_bounds__(NT_THREADS, 1) void nt_wide_kernel(const NtLaunch L
     for (int p = 0; p < NP; ++p)
         rB[p] = nt_make_rsrc((const char*)pp->B + (long long)p * pp->b_piece_stride * 2, ((long long)(N - 1) * ldb + k8) * 2);
     const unsigned lda_b = (unsigned)lda * 2u, ldb_b = (unsigned)ldb * 2u;
-    const int nk = (kend > kbeg) ? (kend - kbeg + BK - 1) / BK : 0;
+    int nk = (kend > kbeg) ? (kend - kbeg + BK - 1) / BK : 0;
+    // A triangular B: k tiles [0, nh) of the first copy, then as many of the second
+    int nh = 0x7fffffff, jump = 0;
+    bool whole = false;                                      // (no k-tile reaches past the range)
+    if (NP > 1 && pp->b_upper > col0 + TN) {
+        nh = (col0 + TN) / BK;
+        jump = pp->b_upper - nh * BK;
+        nk = 2 * nh;
+        whole = true;
+    }
 
     f32x16 acc[FM][FN];
 #pragma unroll
@@ -386,7 +395,8 @@ __global__ __launch_bounds__(NT_THREADS, 1) void nt_wide_kernel(const NtLaunch L
     const int swz_row = tid >> 2;                            // row of chunk u = swz_row + 64 u
     auto load_chunk = [&](int slot, int tile, int x) {      // unconditional: tiles at or beyond nk read as zero
         const unsigned poison = (tile < nk) ? 0u : 0x80000000u;
-        const int k0 = kbeg + tile * BK + k_in_tile;
+        int k0 = kbeg + tile * BK + k_in_tile;
+        if constexpr (NP > 1) k0 += (tile >= nh) ? jump : 0;
         if (x < CHA) {
             const unsigned voff = ((unsigned)(row0 + swz_row + 64 * x) * lda_b + (unsigned)k0 * 2u) | poison;
             st[slot][x] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rA, (int)voff, 0, 0));
@@ -398,7 +408,7 @@ __global__ __launch_bounds__(NT_THREADS, 1) void nt_wide_kernel(const NtLaunch L
     };
     // k guard of a stage: all ones, or the mask of the elements before kend in the last k-tile of the range
     auto tail_mask = [&](int tile) -> u32x4 {
-        const int valid = kend - (kbeg + tile * BK + k_in_tile);
+        const int valid = (NP > 1 && whole) ? BK : kend - (kbeg + tile * BK + k_in_tile);
         u32x4 m;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
