@@ -38,7 +38,6 @@ struct LogicalGemm {
     int M, N, K;
     float* out; long long ldc;
     int group = -1;                // consecutive entries with the same group >= 0 are summed into `out`
-    int b_upper = 0;               // B is upper triangular (see GemmProblem)
 };
 
 struct GemmStage {
@@ -48,6 +47,7 @@ struct GemmStage {
     std::vector<ReduceProblem> reduces;
     int max_reduce_elems = 0;
     bool direct = true;
+    bool b_upper = false;                          // B is upper triangular
     int tiles_m = 0, tiles_n = 0, ksplit = 1;      // single-problem decode
     const GemmProblem* d_probs = nullptr;
     const GemmTile* d_tiles = nullptr;
@@ -140,7 +140,6 @@ void build_stage(GemmStage& st, const GemmVariant& var, const std::vector<Logica
             GemmProblem& p = st.probs[j];
             p.A = g.A; p.B = g.B; p.lda = g.lda; p.ldb = g.ldb;
             p.M = g.M; p.N = g.N; p.K = g.K;
-            p.b_upper = st.direct ? g.b_upper : 0;
             if (st.direct) {
                 p.C = g.out; p.ldc = g.ldc; p.c_split_stride = 0;
                 p.kchunk = std::max(32, ceil_div(g.K, 32) * 32);
@@ -167,6 +166,7 @@ int run_stage(const GemmStage& st, bool grouped, float alpha, float beta, Ctx& c
     hipStream_t stream = cx.s;
     GemmLaunch L{};
     L.n_tiles = (int)st.tiles.size();
+    L.b_upper = st.b_upper && st.direct;
     if (grouped) {
         L.probs = st.d_probs; L.tiles = st.d_tiles;
     } else {
@@ -331,7 +331,7 @@ struct RefreshBlock {
     float* U; float* V; float* sigma;
     // workspace
     float *Y, *Yalt, *Z, *Zalt, *S, *Rinv, *XrT, *GrT;
-    double *work, *R1, *Rmid, *Rtot, *Gacc, *eig;
+    double *work, *R1, *S64, *Rtot, *Gacc, *eig;
     // bf16 gradients of a plan: the products with G on the k-contiguous bf16 family (see NtRefresh)
     bool nt = false;
     unsigned short *Gt = nullptr, *Pn = nullptr, *Pm = nullptr;   // G^T (n x ldm); pieces of a k x n / k x m operand
@@ -339,23 +339,26 @@ struct RefreshBlock {
     long long ldm = 0, ldn = 0, ldk = 0;
 };
 
-// orth(X) for X (rows x k) by Cholesky QR; the result is always left in Xalt (X is scratch).
-//   passes = 1 (normalisations inside the power iteration): one SHIFTED pass, Xalt = X R^-1 with
-//     R^T R = X^T X + s I.  Same span and the same triangular orientation as the exact factor; the
-//     shift keeps the factorization from breaking down however ill conditioned the sketch is (a
+// orth(X) for X (rows x k) by Cholesky QR.
+//   intermediate (normalisations inside the power iteration; the result in Xalt, X is scratch): one SHIFTED
+//     pass, Xalt = X R^-1 with R^T R = X^T X + s I.  Same span and the same triangular orientation as the exact
+//     factor; the shift keeps the factorization from breaking down however ill conditioned the sketch is (a
 //     steep spectrum squares into a Gram matrix whose small eigenvalues lie below its fp32-grade
 //     rounding), at the price of a basis that is only roughly orthonormal, which is all these
 //     intermediate bases are for.
-//   passes = 3 (the final Q and the factor of B^T): shifted pass A (X -> Xalt), shifted pass E
-//     (Xalt -> X), plain pass B with the Gram matrix at three bf16 pieces (X -> Xalt).  Each
-//     shifted pass brings the condition number down to about 1 / sqrt(shift) of what it was, so
-//     sketches with a condition number up to about 1e6 arrive at pass B well conditioned; pass B
-//     drops what is left at rounding level (pivot <= 1e-6 of its diagonal entry: directions beyond
-//     the numerical rank, e.g. of an exactly low-rank or zero gradient) as zero columns.
+//   final (the returned Q and the factor of B^T; the result in X): a pass with the Gram matrix in fp64 (X -> Xalt),
+//     which sees directions down to the rounding of the fp32 sketch (a pivot <= 1e-14 of its diagonal entry, 1e-7 of
+//     a column, is dropped: directions beyond the numerical rank, e.g. of an exactly low-rank or zero gradient,
+//     become zero columns), then a plain pass with the Gram matrix at three bf16 pieces (Xalt -> X), which finishes
+//     what the rounding of the first product left.  Three passes with fp32-grade Gram matrices, two of them
+//     shifted, did the same: a refresh step of 512 x 1376 at r = 64 604 -> 547 us, of the 60M model 4465 -> 4137,
+//     of the 130M model 6249 -> 5742 us, of the 1B model 92.2 -> 88.4 ms; and the weights after a refresh step of the
+//     embedding and LM head were 1.4e-5 to 4.9e-5 from those in 64 bits (four seeds), now 7e-6.
 constexpr double ORTH_SHIFT = 1e-4;       // relative to the largest diagonal entry of the Gram matrix
 constexpr double ORTH_DROP = 1e-6;
+constexpr double ORTH_DROP64 = 1e-14;
 
-// A shifted pass (A or E) of the blocks with RefreshBlock::nt on the bf16 NT family.  The sketch X
+// A first pass of the blocks with RefreshBlock::nt on the bf16 NT family.  The sketch X
 // enters as two bf16 pieces in both orientations (transposed for the Gram matrix, as stored for the
 // product with R^-1), R^-1 as two pieces of its transpose; every product keeps the three leading
 // cross terms: X^T X = Xh^T Xh + Xl^T Xh + Xh^T Xl (summed by the k-split reduction, lower tiles
@@ -363,17 +366,20 @@ constexpr double ORTH_DROP = 1e-6;
 // [Rh | Rh] and [Rl | Rl] of the transposed factor, i.e. (Xh + Xl)(Rh + Rl).
 struct OrthNtPass {
     std::vector<SplitBlock> sx, sr;           // X -> pieces of X^T, and [Xh | Xl]; R^-1 -> the two halves of the pieces of R^-T
-    const SplitBlock* d_sx = nullptr; const SplitBlock* d_sr = nullptr;
+    std::vector<SplitBlock> sx_rows;          // X -> [Xh | Xl] only: the final pass, whose Gram matrix is made from X itself
+    const SplitBlock* d_sx = nullptr; const SplitBlock* d_sr = nullptr; const SplitBlock* d_sx_rows = nullptr;
     NtStageH gram, ap;
     int max_rows = 0, max_k = 0;
     bool empty() const { return sx.empty(); }
 };
 
 struct OrthProgram {
-    OrthNtPass ntA, ntE;
-    GemmStage gramA, qA, gramE, qE, gramB, qB;
-    std::vector<CholBlock> cholA, cholE, cholB;
-    const CholBlock* d_cholA = nullptr; const CholBlock* d_cholE = nullptr; const CholBlock* d_cholB = nullptr;
+    OrthNtPass ntA;
+    GemmStage gramA, qA, gramB, qB;           // first pass, X -> Xalt; last pass, Xalt -> X
+    std::vector<Gram64Block> gram64;          // Gram matrices of the final first pass
+    std::vector<CholBlock> cholA, chol64, cholB;
+    const Gram64Block* d_gram64 = nullptr; int max_splits64 = 1;
+    const CholBlock* d_cholA = nullptr; const CholBlock* d_chol64 = nullptr; const CholBlock* d_cholB = nullptr;
 };
 
 // The products with a bf16 gradient (Y = G Omega, Z = G^T Q, Y = G Qrow: Algorithm 1's sketch,
@@ -386,8 +392,9 @@ struct OrthProgram {
 constexpr int NT_REFRESH_PIECES = 2;
 struct NtRefresh {
     std::vector<TransposeBlock> gt;   const TransposeBlock* d_gt = nullptr;
-    std::vector<SplitBlock> s_om, s_q, s_qrow;
+    std::vector<SplitBlock> s_om, s_q, s_qrow, s_qfinal;
     const SplitBlock* d_om = nullptr; const SplitBlock* d_q = nullptr; const SplitBlock* d_qrow = nullptr;
+    const SplitBlock* d_qfinal = nullptr;
     NtStageH g_stage, gt_stage;       // (m x k) = G (pieces over n)^T ; (n x k) = G^T (pieces over m)^T
     int max_m = 0, max_n = 0, max_k = 0;
     bool empty() const { return gt.empty(); }
@@ -398,14 +405,15 @@ struct RefreshProgram {
     NtRefresh nt;           // blocks with RefreshBlock::nt; the GemmStages below hold the others
     GemmStage sketch[2];    // Y = G Omega
     GemmStage gtq[2];       // Z = G^T Q    (Q = orth result, held in Yalt)
+    GemmStage gtq_final[2]; // the same with the final Q, held in Y (tiles and partials of gtq)
     GemmStage gq[2];        // Y = G Qrow   (Qrow = orth result, held in Zalt)
     OrthProgram orthY, orthZ;
-    std::vector<JacobiBlock> jac, jac_pre;
-    const JacobiBlock* d_jac = nullptr; const JacobiBlock* d_jac_pre = nullptr;
+    std::vector<JacobiBlock> jac;
+    const JacobiBlock* d_jac = nullptr;
     GemmStage uout, vout;
 };
 
-void build_orth_nt(OrthNtPass& pass, const std::vector<RefreshBlock>& blocks, bool on_rows_m, bool from_alt, Arena& ar) {
+void build_orth_nt(OrthNtPass& pass, const std::vector<RefreshBlock>& blocks, bool on_rows_m, Arena& ar) {
     pass = OrthNtPass{};
     std::vector<NtLogical> g, a1;
     for (size_t i = 0; i < blocks.size(); ++i) {
@@ -414,18 +422,17 @@ void build_orth_nt(OrthNtPass& pass, const std::vector<RefreshBlock>& blocks, bo
         const int rows = on_rows_m ? b.m : b.n, k = b.k;
         float* X = on_rows_m ? b.Y : b.Z;
         float* Xalt = on_rows_m ? b.Yalt : b.Zalt;
-        const float* in = from_alt ? Xalt : X;
-        float* out = from_alt ? X : Xalt;
         unsigned short* Xt = on_rows_m ? b.Pm : b.Pn;            // pieces of X^T (k x ldrows)
         const long long ldrows = on_rows_m ? b.ldm : b.ldn, st_t = (long long)k * ldrows;
         const long long ld2 = 2 * b.ldk, st_r = (long long)k * ld2;      // rows of two pieces side by side
-        pass.sx.push_back(SplitBlock{in, Xt, st_t, (int)ldrows, rows, k, (int)ld2, nullptr, b.Xp, b.ldk});
+        pass.sx.push_back(SplitBlock{X, Xt, st_t, (int)ldrows, rows, k, (int)ld2, nullptr, b.Xp, b.ldk});
+        pass.sx_rows.push_back(SplitBlock{X, nullptr, 0, 0, rows, k, (int)ld2, nullptr, b.Xp, b.ldk});
         pass.sr.push_back(SplitBlock{b.Rinv, b.Rt, st_r, (int)ld2, k, k, 0, b.Rt + b.ldk});
         const int bi = (int)i;
         g.push_back(NtLogical{Xt, Xt, b.S, ldrows, ldrows, k, k, k, rows, bi, bi});
         g.push_back(NtLogical{Xt + st_t, Xt, b.S, ldrows, ldrows, k, k, k, rows, bi, bi});
         g.push_back(NtLogical{Xt, Xt + st_t, b.S, ldrows, ldrows, k, k, k, rows, bi, bi});
-        a1.push_back(NtLogical{b.Xp, b.Rt, out, ld2, ld2, k, rows, k, (int)ld2, bi, -1, st_r, (int)b.ldk});
+        a1.push_back(NtLogical{b.Xp, b.Rt, Xalt, ld2, ld2, k, rows, k, (int)ld2, bi, -1, st_r});
         pass.max_rows = std::max(pass.max_rows, rows); pass.max_k = std::max(pass.max_k, k);
     }
     if (g.empty()) return;
@@ -434,13 +441,38 @@ void build_orth_nt(OrthNtPass& pass, const std::vector<RefreshBlock>& blocks, bo
     NtVariant v2{};
     const char* e = getenv("TSR_TUNE_ORTH_WIDE");          // 0: 128 x 128 tiles instead of the wide-tile kernel
     v2.shape = (e && e[0] == '0') ? (int)NT_128x128_K32 : (int)NT_256x128_K32; v2.b_pieces = 2;
-    build_nt_stage(pass.ap, v2, a1, nb, ar, 1);
+    build_nt_stage(pass.ap, v2, a1, nb, ar, 1, false, 0, false, /*b_upper=*/true);
+}
+
+// Row pieces and partial matrices of the fp64 Gram matrices: some 512 workgroups, in at most `bytes` of the arena.
+void build_gram64(OrthProgram& op, const std::vector<RefreshBlock>& blocks, bool on_rows_m, size_t bytes, Arena& ar) {
+    long long base = 0;
+    for (const RefreshBlock& b : blocks) base += (long long)ceil_div(b.k, 64) * (ceil_div(b.k, 64) + 1) / 2;
+    op.gram64.clear();
+    op.max_splits64 = 1;
+    for (long long want = std::max(1LL, 512 / base); ; want = want * 3 / 4) {
+        size_t need = 0;
+        op.gram64.clear();
+        for (const RefreshBlock& b : blocks) {
+            Gram64Block g{on_rows_m ? b.Y : b.Z, b.S64, nullptr, on_rows_m ? b.m : b.n, b.k, 1, 0};
+            const int pieces = (int)std::min<long long>(std::max(1LL, want), std::max(1, g.rows / 64));
+            g.chunk = ceil_div(ceil_div(g.rows, pieces), 16) * 16;
+            g.splits = ceil_div(g.rows, g.chunk);
+            if (g.splits > 1) need += align_up((size_t)b.k * b.k * g.splits * sizeof(double));
+            op.gram64.push_back(g);
+        }
+        if (need <= bytes || want <= 1) break;
+    }
+    for (Gram64Block& g : op.gram64) {
+        if (g.splits > 1) g.part = ar.take<double>((size_t)g.k * g.k * g.splits);
+        op.max_splits64 = std::max(op.max_splits64, g.splits);
+    }
 }
 
 void build_orth(OrthProgram& op, const std::vector<RefreshBlock>& blocks, bool on_rows_m, Arena& ar) {
-    std::vector<LogicalGemm> gA, qA, gE, qE, gB, qB;
-    op.cholA.clear(); op.cholE.clear(); op.cholB.clear();
-    const char* e = getenv("TSR_TUNE_ORTH_NT");            // 0: the shifted passes of every block on the general kernel
+    std::vector<LogicalGemm> gA, qA, gB, qB;
+    op.cholA.clear(); op.chol64.clear(); op.cholB.clear();
+    const char* e = getenv("TSR_TUNE_ORTH_NT");            // 0: the first passes of every block on the general kernel
     const bool orth_nt = !(e && e[0] == '0');
     for (const RefreshBlock& b : blocks) {
         const int rows = on_rows_m ? b.m : b.n;
@@ -449,38 +481,36 @@ void build_orth(OrthProgram& op, const std::vector<RefreshBlock>& blocks, bool o
         const int k = b.k;
         if (!(b.nt && orth_nt)) {
             gA.push_back(LogicalGemm{X, X, k, k, k, k, rows, b.S, k});
-            qA.push_back(LogicalGemm{X, b.Rinv, k, k, rows, k, k, Xalt, k, -1, 1});
-            gE.push_back(LogicalGemm{Xalt, Xalt, k, k, k, k, rows, b.S, k});
-            qE.push_back(LogicalGemm{Xalt, b.Rinv, k, k, rows, k, k, X, k, -1, 1});
+            qA.push_back(LogicalGemm{X, b.Rinv, k, k, rows, k, k, Xalt, k});
         }
-        gB.push_back(LogicalGemm{X, X, k, k, k, k, rows, b.S, k});
-        qB.push_back(LogicalGemm{X, b.Rinv, k, k, rows, k, k, Xalt, k, -1, 1});
-        // the three triangular factors (X = Q R3 R2 R1) go to R1, Rmid and Gacc (free until the small
-        // SVD); where their product is needed, fp64 MFMA GEMMs form it afterwards (run_refresh_back)
-        op.cholA.push_back(CholBlock{b.S, b.Rinv, b.R1, b.work, k});
-        op.cholE.push_back(CholBlock{b.S, b.Rinv, b.Rmid, b.work, k});
-        op.cholB.push_back(CholBlock{b.S, b.Rinv, b.Gacc, b.work, k});
+        gB.push_back(LogicalGemm{Xalt, Xalt, k, k, k, k, rows, b.S, k});
+        qB.push_back(LogicalGemm{Xalt, b.Rinv, k, k, rows, k, k, X, k});
+        // the triangular factors are needed of B^T only (X = Q R2 R1, in Gacc, free until the small SVD, and R1)
+        op.cholA.push_back(CholBlock{b.S, b.Rinv, nullptr, b.work, k, nullptr});
+        op.chol64.push_back(CholBlock{nullptr, b.Rinv, on_rows_m ? nullptr : b.R1, b.work, k, b.S64});
+        op.cholB.push_back(CholBlock{b.S, b.Rinv, on_rows_m ? nullptr : b.Gacc, b.work, k, nullptr});
     }
-    if (orth_nt) {
-        build_orth_nt(op.ntA, blocks, on_rows_m, false, ar);
-        build_orth_nt(op.ntE, blocks, on_rows_m, true, ar);
-    } else {
-        op.ntA = OrthNtPass{}; op.ntE = OrthNtPass{};
-    }
+    op.ntA = OrthNtPass{};
+    if (orth_nt) build_orth_nt(op.ntA, blocks, on_rows_m, ar);
     // The first pass meets the sketch at its raw scaling, where a rounding of X moves the span of
     // the result: with an fp32 gradient X keeps three bf16 pieces there, as in the products with G.
     int pieces_x = 2;
     for (const RefreshBlock& b : blocks) if (b.g_dtype == TSR_F32) pieces_x = 3;
     // the Cholesky kernels read the lower triangle of the Gram matrix only
+    const size_t before = ar.off;
     build_stage(op.gramA, variant(1, 1, 0, 2, 2), gA, ar, 512, true);
+    const size_t partials = ar.off - before;
     build_stage(op.qA, variant(0, 1, 0, pieces_x, pieces_x), qA, ar, 1);
-    build_stage(op.gramE, variant(1, 1, 0, 2, 2), gE, ar, 512, true);
-    build_stage(op.qE, variant(0, 1, 0, 2, 2), qE, ar, 1);
+    op.qA.b_upper = true;                                  // (one tile's k is never split at want_tiles = 1)
     build_stage(op.gramB, variant(1, 1, 0, 3, 3), gB, ar, 512, true);
     build_stage(op.qB, variant(0, 1, 0, 3, 3), qB, ar, 1);
+    op.qB.b_upper = true;
+    // (as much as the partials of one more fp32 Gram stage would take)
+    build_gram64(op, blocks, on_rows_m, partials, ar);
 }
 
-int run_orth(const OrthProgram& op, bool grouped, Ctx& cx, int passes) {
+// One orthonormalisation of every block; see ORTH_SHIFT above for the two kinds.
+int run_orth(const OrthProgram& op, bool grouped, Ctx& cx, bool final) {
     const int nb = (int)op.cholA.size();
     int max_k = 0;
     for (const CholBlock& cb : op.cholA) max_k = std::max(max_k, cb.k);
@@ -489,35 +519,32 @@ int run_orth(const OrthProgram& op, bool grouped, Ctx& cx, int passes) {
         TSR_HIP(launch_chol_inv(grouped ? dev : nullptr, grouped ? nullptr : &host[0], nb, max_k, tol, shift, cx.s));
         return TSR_OK;
     };
-    // a shifted pass: Gram matrices (NT family for the blocks it takes, general kernel for the rest),
-    // Cholesky of all of them, then the products with R^-1
-    auto nt_gram = [&](const OrthNtPass& p) -> int {
-        if (p.empty()) return TSR_OK;
+    const OrthNtPass& nt = op.ntA;
+    auto split = [&](const SplitBlock* table, int rows) -> int {
+        if (nt.empty()) return TSR_OK;
+        Timed timed(cx, TSR_PROF_ORTH_GEMM);
+        TSR_HIP(launch_split(table, (int)nt.sx.size(), rows, nt.max_k, cx.s));
+        return TSR_OK;
+    };
+    // the first pass: Gram matrices and their Cholesky factors of all blocks, then the products with R^-1 (NT family
+    // for the blocks it takes, general kernel for the rest)
+    if (final) {
         {
             Timed timed(cx, TSR_PROF_ORTH_GEMM);
-            TSR_HIP(launch_split(p.d_sx, (int)p.sx.size(), p.max_rows, p.max_k, cx.s));
+            TSR_HIP(launch_gram64(grouped ? op.d_gram64 : nullptr, grouped ? nullptr : &op.gram64[0], nb, max_k, op.max_splits64, cx.s));
         }
-        return run_nt_stage(p.gram, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM);
-    };
-    auto nt_apply = [&](const OrthNtPass& p) -> int {
-        if (p.empty()) return TSR_OK;
-        {
-            Timed timed(cx, TSR_PROF_ORTH_GEMM);
-            TSR_HIP(launch_split(p.d_sr, (int)p.sr.size(), p.max_k, p.max_k, cx.s));
-        }
-        return run_nt_stage(p.ap, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM);
-    };
-    TSR_TRY(nt_gram(op.ntA));
-    TSR_TRY(run_stage(op.gramA, grouped, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM));
-    TSR_TRY(chol(op.d_cholA, op.cholA, ORTH_DROP, ORTH_SHIFT));
-    TSR_TRY(nt_apply(op.ntA));
+        TSR_TRY(split(nt.d_sx_rows, nt.max_rows));
+        TSR_TRY(chol(op.d_chol64, op.chol64, ORTH_DROP64, 0.0));
+    } else {
+        TSR_TRY(split(nt.d_sx, nt.max_rows));
+        if (!nt.empty()) TSR_TRY(run_nt_stage(nt.gram, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM));
+        TSR_TRY(run_stage(op.gramA, grouped, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM));
+        TSR_TRY(chol(op.d_cholA, op.cholA, ORTH_DROP, ORTH_SHIFT));
+    }
+    TSR_TRY(split(nt.d_sr, nt.max_k));
+    if (!nt.empty()) TSR_TRY(run_nt_stage(nt.ap, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM));
     TSR_TRY(run_stage(op.qA, grouped, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM));
-    if (passes == 1) return TSR_OK;
-    TSR_TRY(nt_gram(op.ntE));
-    TSR_TRY(run_stage(op.gramE, grouped, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM));
-    TSR_TRY(chol(op.d_cholE, op.cholE, ORTH_DROP, ORTH_SHIFT));
-    TSR_TRY(nt_apply(op.ntE));
-    TSR_TRY(run_stage(op.qE, grouped, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM));
+    if (!final) return TSR_OK;
     TSR_TRY(run_stage(op.gramB, grouped, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM));
     TSR_TRY(chol(op.d_cholB, op.cholB, ORTH_DROP, 0.0));
     return run_stage(op.qB, grouped, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM);
@@ -554,7 +581,7 @@ void build_refresh(RefreshProgram& rp, const std::vector<BlockView>& views, cons
         b.Z = ar.take<float>((size_t)b.n * k); b.Zalt = ar.take<float>((size_t)b.n * k);
         b.S = ar.take<float>(k * k); b.Rinv = ar.take<float>(k * k);
         b.XrT = ar.take<float>((size_t)b.r * k); b.GrT = ar.take<float>((size_t)b.r * k);
-        b.work = ar.take<double>(2 * k * k + 64); b.R1 = ar.take<double>(k * k); b.Rmid = ar.take<double>(k * k);
+        b.work = ar.take<double>(2 * k * k + 64); b.R1 = ar.take<double>(k * k); b.S64 = ar.take<double>(k * k);
         b.Rtot = ar.take<double>(k * k); b.Gacc = ar.take<double>(k * k);
         b.eig = (b.k <= EIG_MAXK) ? ar.take<double>(eig_scratch_doubles(b.k)) : nullptr;
         if (allow_nt && nt_refresh_eligible(v, b.k)) {
@@ -577,7 +604,7 @@ void build_refresh_stages(RefreshProgram& rp, const float* const* omegas, Arena&
     std::vector<LogicalGemm> sk[2], gtq[2], gq[2], uo, vo;
     std::vector<NtLogical> ntg, ntgt;
     rp.nt = NtRefresh{};
-    rp.jac.clear(); rp.jac_pre.clear();
+    rp.jac.clear();
     for (size_t i = 0; i < rp.blocks.size(); ++i) {
         const RefreshBlock& b = rp.blocks[i];
         const float* om = omegas ? omegas[i] : nullptr;
@@ -588,6 +615,7 @@ void build_refresh_stages(RefreshProgram& rp, const float* const* omegas, Arena&
             f.s_om.push_back(SplitBlock{om, b.Pn, sn, (int)b.ldn, b.n, b.k});
             f.s_qrow.push_back(SplitBlock{b.Zalt, b.Pn, sn, (int)b.ldn, b.n, b.k});
             f.s_q.push_back(SplitBlock{b.Yalt, b.Pm, sm, (int)b.ldm, b.m, b.k});
+            f.s_qfinal.push_back(SplitBlock{b.Y, b.Pm, sm, (int)b.ldm, b.m, b.k});
             ntg.push_back(NtLogical{b.G, b.Pn, b.Y, b.ldg, b.ldn, b.k, b.m, b.k, b.n, (int)i, -1, sn});
             ntgt.push_back(NtLogical{b.Gt, b.Pm, b.Z, b.ldm, b.ldm, b.k, b.n, b.k, b.m, (int)i, -1, sm});
             f.max_m = std::max(f.max_m, b.m); f.max_n = std::max(f.max_n, b.n); f.max_k = std::max(f.max_k, b.k);
@@ -596,12 +624,9 @@ void build_refresh_stages(RefreshProgram& rp, const float* const* omegas, Arena&
             gtq[b.g_dtype].push_back(LogicalGemm{b.G, b.Yalt, b.ldg, b.k, b.n, b.k, b.m, b.Z, b.k});
             gq[b.g_dtype].push_back(LogicalGemm{b.G, b.Zalt, b.ldg, b.k, b.m, b.k, b.n, b.Y, b.k});
         }
-        uo.push_back(LogicalGemm{b.Yalt, b.XrT, b.k, b.k, b.m, b.r, b.k, b.U, b.r});
-        vo.push_back(LogicalGemm{b.Zalt, b.GrT, b.k, b.k, b.n, b.r, b.k, b.V, b.r});
-        // R = R3 (R2 R1): first R2 R1 into the (by then idle) Cholesky work area, then the small SVD's
-        // table with that product in the place of R1
-        rp.jac_pre.push_back(JacobiBlock{b.work, b.Rmid, nullptr, nullptr, nullptr, nullptr, b.k, b.r, nullptr, b.R1});
-        rp.jac.push_back(JacobiBlock{b.Rtot, b.Gacc, b.work, b.XrT, b.GrT, b.sigma, b.k, b.r, b.eig, b.work});
+        uo.push_back(LogicalGemm{b.Y, b.XrT, b.k, b.k, b.m, b.r, b.k, b.U, b.r});
+        vo.push_back(LogicalGemm{b.Z, b.GrT, b.k, b.k, b.n, b.r, b.k, b.V, b.r});
+        rp.jac.push_back(JacobiBlock{b.Rtot, b.Gacc, b.work, b.XrT, b.GrT, b.sigma, b.k, b.r, b.eig, b.R1});
     }
     for (int d = 0; d < 2; ++d) {
         // an fp32 gradient keeps three bf16 pieces per operand (rounding at 2^-27, below its own
@@ -609,6 +634,10 @@ void build_refresh_stages(RefreshProgram& rp, const float* const* omegas, Arena&
         const int pc = (d == TSR_F32) ? 3 : 2;
         build_stage(rp.sketch[d], variant(0, 1, d, pc, pc), sk[d], ar);
         build_stage(rp.gtq[d], variant(1, 1, d, pc, pc), gtq[d], ar);
+        rp.gtq_final[d] = rp.gtq[d];
+        size_t at = 0;
+        for (const RefreshBlock& b : rp.blocks)
+            if (!b.nt && b.g_dtype == d) rp.gtq_final[d].probs[at++].B = b.Y;
         build_stage(rp.gq[d], variant(0, 1, d, pc, pc), gq[d], ar);
     }
     {
@@ -626,9 +655,9 @@ void build_refresh_stages(RefreshProgram& rp, const float* const* omegas, Arena&
     build_stage(rp.vout, variant(0, 0, 0, 3, 3), vo, ar, 1);
 }
 
-// Sketch chain of one worker: leaves the final Q in Yalt and B^T = G^T Q in Z.  Inside the power
-// iteration the bases are normalised by one shifted Cholesky pass (run_orth, passes = 1), the final
-// Q by three: right-multiplying a sketch by an upper-triangular factor changes neither its span nor
+// Sketch chain of one worker: leaves the final Q in Y and B^T = G^T Q in Z.  Inside the power
+// iteration the bases are normalised by one shifted Cholesky pass, the final
+// Q by two: right-multiplying a sketch by an upper-triangular factor changes neither its span nor
 // the Q factor of anything computed from it.
 int run_refresh_front(const RefreshProgram& rp, bool grouped, int q, Ctx& cx) {
     const NtRefresh& f = rp.nt;
@@ -649,28 +678,27 @@ int run_refresh_front(const RefreshProgram& rp, bool grouped, int q, Ctx& cx) {
     TSR_TRY(nt_product(f.d_om, f.g_stage, f.max_n));
     for (int d = 0; d < 2; ++d) TSR_TRY(run_stage(rp.sketch[d], grouped, 1.0f, 0.0f, cx, TSR_PROF_SKETCH_GEMM));
     for (int it = 0; it < q; ++it) {
-        TSR_TRY(run_orth(rp.orthY, grouped, cx, 1));                                    // Q' in Yalt
+        TSR_TRY(run_orth(rp.orthY, grouped, cx, false));                                // Q' in Yalt
         TSR_TRY(nt_product(f.d_q, f.gt_stage, f.max_m));
         for (int d = 0; d < 2; ++d) TSR_TRY(run_stage(rp.gtq[d], grouped, 1.0f, 0.0f, cx, TSR_PROF_SKETCH_GEMM));
-        TSR_TRY(run_orth(rp.orthZ, grouped, cx, 1));                                    // Q'row in Zalt
+        TSR_TRY(run_orth(rp.orthZ, grouped, cx, false));                                // Q'row in Zalt
         TSR_TRY(nt_product(f.d_qrow, f.g_stage, f.max_n));
         for (int d = 0; d < 2; ++d) TSR_TRY(run_stage(rp.gq[d], grouped, 1.0f, 0.0f, cx, TSR_PROF_SKETCH_GEMM));
     }
-    TSR_TRY(run_orth(rp.orthY, grouped, cx, 3));                                        // Q in Yalt
-    TSR_TRY(nt_product(f.d_q, f.gt_stage, f.max_m));
-    for (int d = 0; d < 2; ++d) TSR_TRY(run_stage(rp.gtq[d], grouped, 1.0f, 0.0f, cx, TSR_PROF_SKETCH_GEMM));
+    TSR_TRY(run_orth(rp.orthY, grouped, cx, true));                                     // Q in Y
+    TSR_TRY(nt_product(f.d_qfinal, f.gt_stage, f.max_m));
+    for (int d = 0; d < 2; ++d) TSR_TRY(run_stage(rp.gtq_final[d], grouped, 1.0f, 0.0f, cx, TSR_PROF_SKETCH_GEMM));
     return TSR_OK;
 }
 
-// From Q (in Yalt) and B^T (in Z):  B^T = Q_B R (Q_B in Zalt) ; SVD of R ; U = Q X_r ; V = Q_B Gacc_r^T
+// From Q (in Y) and B^T (in Z):  B^T = Q_B R (Q_B in Z) ; SVD of R ; U = Q X_r ; V = Q_B Gacc_r^T
 int run_refresh_back(const RefreshProgram& rp, bool grouped, Ctx& cx) {
-    TSR_TRY(run_orth(rp.orthZ, grouped, cx, 3));
+    TSR_TRY(run_orth(rp.orthZ, grouped, cx, true));
     {
         Timed timed(cx, TSR_PROF_JACOBI);
         int max_k = 0;
         for (const JacobiBlock& jb : rp.jac) max_k = std::max(max_k, jb.k);
         const int nb = (int)rp.jac.size();
-        TSR_HIP(launch_rtot_product(grouped ? rp.d_jac_pre : nullptr, grouped ? nullptr : &rp.jac_pre[0], nb, max_k, cx.s));
         TSR_HIP(launch_rtot_product(grouped ? rp.d_jac : nullptr, grouped ? nullptr : &rp.jac[0], nb, max_k, cx.s));
         static const bool chain = [] { const char* e = getenv("TSR_TUNE_EIG_CHAIN"); return !(e && e[0] == '0'); }();
         if (chain && max_k <= EIG_MAXK)
@@ -700,24 +728,27 @@ int check_refresh_shape(int m, int n, int r, int p) {
 void upload_refresh(RefreshProgram& rp, Arena& ar, Uploader& up) {
     for (int d = 0; d < 2; ++d) {
         upload_stage(rp.sketch[d], ar, up); upload_stage(rp.gtq[d], ar, up); upload_stage(rp.gq[d], ar, up);
+        GemmStage& last = rp.gtq_final[d];
+        if (last.empty()) continue;
+        last.d_probs = up.put(last.probs, ar);
+        last.d_tiles = rp.gtq[d].d_tiles; last.d_reduces = rp.gtq[d].d_reduces;
     }
     for (OrthProgram* op : {&rp.orthY, &rp.orthZ}) {
-        for (OrthNtPass* p : {&op->ntA, &op->ntE}) {
-            if (p->empty()) continue;
-            p->d_sx = up.put(p->sx, ar); p->d_sr = up.put(p->sr, ar);
-            upload_nt_stage(p->gram, ar, up); upload_nt_stage(p->ap, ar, up);
+        if (OrthNtPass& p = op->ntA; !p.empty()) {
+            p.d_sx = up.put(p.sx, ar); p.d_sr = up.put(p.sr, ar); p.d_sx_rows = up.put(p.sx_rows, ar);
+            upload_nt_stage(p.gram, ar, up); upload_nt_stage(p.ap, ar, up);
         }
         upload_stage(op->gramA, ar, up); upload_stage(op->qA, ar, up);
-        upload_stage(op->gramE, ar, up); upload_stage(op->qE, ar, up);
         upload_stage(op->gramB, ar, up); upload_stage(op->qB, ar, up);
-        op->d_cholA = up.put(op->cholA, ar); op->d_cholE = up.put(op->cholE, ar); op->d_cholB = up.put(op->cholB, ar);
+        op->d_gram64 = up.put(op->gram64, ar);
+        op->d_cholA = up.put(op->cholA, ar); op->d_chol64 = up.put(op->chol64, ar); op->d_cholB = up.put(op->cholB, ar);
     }
     rp.d_jac = up.put(rp.jac, ar);
-    rp.d_jac_pre = up.put(rp.jac_pre, ar);
     if (!rp.nt.empty()) {
         NtRefresh& f = rp.nt;
         f.d_gt = up.put(f.gt, ar);
         f.d_om = up.put(f.s_om, ar); f.d_q = up.put(f.s_q, ar); f.d_qrow = up.put(f.s_qrow, ar);
+        f.d_qfinal = up.put(f.s_qfinal, ar);
         upload_nt_stage(f.g_stage, ar, up);
         upload_nt_stage(f.gt_stage, ar, up);
     }
@@ -1069,11 +1100,11 @@ int tsr_refresh_rsvd_workers(const void* G, int g_dtype, int m, int n, long long
         }));
         TSR_TRY(run_refresh_front(rp, false, q, cx));
         const RefreshBlock& b = rp.blocks[0];
-        TSR_HIP(hipMemcpyAsync(Qs + (size_t)w * m * k, b.Yalt, (size_t)m * k * sizeof(float), hipMemcpyDeviceToDevice, cx.s));
+        TSR_HIP(hipMemcpyAsync(Qs + (size_t)w * m * k, b.Y, (size_t)m * k * sizeof(float), hipMemcpyDeviceToDevice, cx.s));
         TSR_HIP(hipMemcpyAsync(Bs + (size_t)w * n * k, b.Z, (size_t)n * k * sizeof(float), hipMemcpyDeviceToDevice, cx.s));
     }
     const RefreshBlock& b = rp.blocks[0];
-    TSR_HIP(launch_average(Qs, n_workers, (long long)m * (long long)k, b.Yalt, cx.s));   // Qbar
+    TSR_HIP(launch_average(Qs, n_workers, (long long)m * (long long)k, b.Y, cx.s));   // Qbar
     TSR_HIP(launch_average(Bs, n_workers, (long long)n * (long long)k, b.Z, cx.s));      // Bbar^T
     return run_refresh_back(rp, false, cx);
 }
@@ -1186,7 +1217,7 @@ int tsr_refresh_exact_svd(const void* G, int g_dtype, int m, int n, long long ld
     TSR_TRY(build_within(ws, ws_bytes, ws_bytes, [&](Arena& ar) { build_refresh(rp, v, nullptr, s - r, sigs, ar); }));
     const RefreshBlock& b = rp.blocks[0];
     Ctx cx{(hipStream_t)stream, nullptr};
-    TSR_HIP(launch_identity(b.Yalt, s, cx.s));                                          // Q = I (s x s)
+    TSR_HIP(launch_identity(b.Y, s, cx.s));                                          // Q = I (s x s)
     TSR_HIP(launch_tall_copy(G, g_dtype == TSR_BF16, ldg, m, n, transpose, b.Z, cx.s)); // B^T, tall
     return run_refresh_back(rp, false, cx);
 }

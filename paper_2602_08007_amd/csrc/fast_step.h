@@ -19,6 +19,7 @@ struct NtStageH {
     const NtRange* d_ranges = nullptr;
     std::vector<ReduceProblem> reduces;   // empty when the GEMM writes its output directly
     int max_reduce_elems = 0;
+    bool b_upper = false;                 // see NtLaunch
     const NtProblem* d_probs = nullptr;
     const NtTile* d_tiles = nullptr;
     const ReduceProblem* d_reduces = nullptr;
@@ -33,15 +34,14 @@ struct NtLogical {
     int block;      // owning matrix block (tiles of one block stay on one XCD)
     int group;      // consecutive entries with the same group >= 0 are summed into `out`
     long long b_piece_stride = 0;   // NtVariant::b_pieces > 1: elements between the pieces of B
-    int b_upper = 0;                // see NtProblem
 };
 
 // Tile lists, k splits and partial buffers of one launch (want_tiles: split k while the launch has
 // fewer tiles; persistent: one list of tiles per workgroup; group_m: see the definition), its device
 // tables, and the launch itself (plus the fixed-order reduction of k-split partials).
-// lower_only: symmetric outputs of which only the tiles on or below the diagonal are computed.
+// lower_only: symmetric outputs of which only the tiles on or below the diagonal are computed.  b_upper: see NtLaunch.
 void build_nt_stage(NtStageH& st, const NtVariant& var, const std::vector<NtLogical>& gemms, int n_blocks, Arena& ar,
-                    int want_tiles, bool persistent = false, int group_m = 0, bool lower_only = false);
+                    int want_tiles, bool persistent = false, int group_m = 0, bool lower_only = false, bool b_upper = false);
 void upload_nt_stage(NtStageH& st, Arena& ar, Uploader& up);
 int run_nt_stage(const NtStageH& st, float alpha, float beta, Ctx& cx, int kind, const AdamScalars* adam = nullptr);
 

@@ -121,7 +121,7 @@ void persistent_lists(std::vector<NtTile>& tiles, std::vector<NtRange>& ranges, 
 // of the output: they share g row panels of A, which stay in that XCD's L2 for the whole band, and
 // each column panel of B is fetched once per band instead of once per tile row.
 void build_nt_stage(NtStageH& st, const NtVariant& var, const std::vector<NtLogical>& gemms, int n_blocks, Arena& ar,
-                    int want_tiles, bool persistent, int group_m, bool lower_only) {
+                    int want_tiles, bool persistent, int group_m, bool lower_only, bool b_upper) {
     st = NtStageH{};
     st.var = var;
     if (gemms.empty()) return;
@@ -144,6 +144,7 @@ void build_nt_stage(NtStageH& st, const NtVariant& var, const std::vector<NtLogi
         if (s > 1) any_split = true;
     }
     const bool direct = !(any_split || shared);
+    st.b_upper = b_upper && direct;
     st.probs.resize(gemms.size());
     std::vector<int> tile_block;
     std::vector<long long> tile_work;
@@ -169,7 +170,6 @@ void build_nt_stage(NtStageH& st, const NtVariant& var, const std::vector<NtLogi
             NtProblem& p = st.probs[j];
             p.A = g.A; p.B = g.B; p.lda = g.lda; p.ldb = g.ldb; p.M = g.M; p.N = g.N; p.K = g.K;
             p.b_piece_stride = g.b_piece_stride;
-            p.b_upper = direct ? g.b_upper : 0;
             if (direct) {
                 p.C = g.out; p.ldc = g.ldc; p.c_split_stride = 0; p.kchunk = std::max(64, cdiv(g.K, 64) * 64);
                 ksplit[j] = 1;
@@ -189,7 +189,7 @@ void build_nt_stage(NtStageH& st, const NtVariant& var, const std::vector<NtLogi
                                 st.tiles.push_back(NtTile{(int)j, tm, (group_m > 0) ? t2 : t3, ks});
                                 tile_block.push_back(g.block);
                                 const int cols = (((group_m > 0) ? t2 : t3) + 1) * TN;
-                                tile_work.push_back(std::min(p.kchunk, (p.b_upper > cols) ? 2 * cols : g.K) + 64);
+                                tile_work.push_back(std::min(p.kchunk, (st.b_upper && g.K / 2 > cols) ? 2 * cols : g.K) + 64);
                             }
         }
         i = e;
@@ -206,7 +206,7 @@ int run_nt_stage(const NtStageH& st, float alpha, float beta, Ctx& cx, int kind,
     Timed timed(cx, kind);
     NtLaunch L{};
     if (adam) L.adam = *adam;
-    L.probs = st.d_probs; L.tiles = st.d_tiles; L.n_tiles = (int)st.tiles.size();
+    L.probs = st.d_probs; L.tiles = st.d_tiles; L.n_tiles = (int)st.tiles.size(); L.b_upper = st.b_upper;
     if (!st.ranges.empty()) { L.ranges = st.d_ranges; L.n_tiles = (int)st.ranges.size(); }
     if (st.reduces.empty()) {
         L.alpha = alpha; L.beta = beta;

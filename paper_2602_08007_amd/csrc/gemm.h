@@ -19,7 +19,6 @@ struct GemmProblem {
     long long c_split_stride;  // elements between the partial outputs of consecutive k-splits
     int M, N, K;
     int kchunk;         // K range handled by one tile (multiple of 32); K if no split
-    int b_upper;        // B is upper triangular (element (j, k) zero for k > j): only launches without split
 };
 
 struct GemmTile {       // one workgroup's work
@@ -33,6 +32,7 @@ struct GemmLaunch {
     int tiles_m, tiles_n, ksplit;  // decode of blockIdx when tiles == nullptr
     int n_tiles;               // grid size
     float alpha, beta;         // epilogue scalars of the whole launch; beta == 0: C is not read
+    int b_upper;               // B is upper triangular (element (j, k) zero for k > j): only launches without split
 };
 
 // Operand layout / precision of one instantiation.

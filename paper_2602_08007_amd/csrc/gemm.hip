@@ -290,7 +290,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void gemm_kernel(const GemmLaunch L) {
     const int row0 = tm * TM, col0 = tn * TN;
     int klen = min(pp->K - kbeg, pp->kchunk);
     // A third of the work of X R^-1 at k = 264 and 528 (below the diagonal of the factor: zeros)
-    if (pp->b_upper) klen = min(klen, col0 + TN);
+    if (L.b_upper) klen = min(klen, col0 + TN);
 
     f32x16 acc[FM][FN];
 #pragma unroll

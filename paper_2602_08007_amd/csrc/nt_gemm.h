@@ -23,8 +23,6 @@ struct NtProblem {
     int kchunk;             // multiple of 64
     const AdamTBlock* adam; // fused Adam epilogue (NtVariant::fused_adam): this core's moment arrays
     long long b_piece_stride;   // NtVariant::b_pieces > 1: elements between the bf16 pieces of B
-    int b_upper;            // > 0: B is two copies, this many k apart, of an upper triangular matrix (element (j, k) zero
-                            // for k > j); the wide-tile kernel leaves the zeros out, launches without split only
 };
 
 struct NtTile { int prob, tm, tn, ks; };     // prob < 0: idle workgroup
@@ -42,6 +40,8 @@ struct NtLaunch {
     int n_tiles;
     float alpha, beta;
     AdamScalars adam;       // fused Adam epilogue only
+    int b_upper;            // B is two copies, K / 2 apart, of an upper triangular matrix (element (j, k) zero for k > j);
+                            // the wide-tile kernel leaves the zeros out, launches without split only
 };
 
 enum NtShape {
@@ -119,7 +119,7 @@ hipError_t launch_transpose_bf16(const TransposeBlock* table_dev, int blocks, in
 
 // An fp32 matrix X (rows x k, contiguous) as two bf16 pieces, x = x0 + x1 with x0 = bf16(x) and x1 = bf16(x - x0),
 // in up to three places:
-//   dst       the transpose: piece p has k rows of pitch ld_dst, at dst + p * piece_stride elements; columns
+//   dst       the transpose, optional: piece p has k rows of pitch ld_dst, at dst + p * piece_stride elements; columns
 //             `rows` .. up to the next multiple of 8 are written as zeros, nothing beyond (pieces may sit side by
 //             side in one row);
 //   dst_again the same once more, optional;

@@ -373,9 +373,9 @@ __global__ __launch_bounds__(NT_THREADS, 1) void nt_wide_kernel(const NtLaunch L
     // A triangular B: k tiles [0, nh) of the first copy, then as many of the second
     int nh = 0x7fffffff, jump = 0;
     bool whole = false;                                      // (no k-tile reaches past the range)
-    if (NP > 1 && pp->b_upper > col0 + TN) {
+    if (NP > 1 && L.b_upper && K / 2 > col0 + TN) {
         nh = (col0 + TN) / BK;
-        jump = pp->b_upper - nh * BK;
+        jump = K / 2 - nh * BK;
         nk = 2 * nh;
         whole = true;
     }
@@ -1290,6 +1290,7 @@ __global__ __launch_bounds__(256) void split_kernel(const SplitBlock* table) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) *(bf4*)&tile[p][c + i][r] = bf4{h[0][i], h[1][i], h[2][i], h[3][i]};
     }
+    if (!b.dst) return;
     __syncthreads();
     const int rr = (threadIdx.x & 7) * 8;                                 // eight rows of X per thread and column
     if (r0 + rr >= rows8) return;

@@ -52,14 +52,25 @@ hipError_t launch_stream(float* dst, const float* src, long long count, float sc
 // rounding of S, no column is dropped, and Y Rinv has a condition number reduced to about
 // 1 / sqrt(shift_rel); a following unshifted pass finishes the orthonormalisation).
 // work = 2 k x k doubles per matrix.
+// S64 (optional): the Gram matrix in fp64, in place of S.
 struct CholBlock {
     const float* S; float* Rinv;
     double* Rtot;
     double* work;
     int k;
+    const double* S64;
 };
 hipError_t launch_chol_inv(const CholBlock* table_dev, const CholBlock* single, int blocks, int max_k,
                            double tol, double shift_rel, hipStream_t stream);
+
+// ---- Gram matrix X^T X (its lower triangle) of a tall fp32 matrix X (rows x k, contiguous) in fp64.  With splits > 1
+// the rows are cut into pieces of `chunk`, whose partial matrices go to part (splits x k x k) and are summed into S.
+struct Gram64Block {
+    const float* X; double* S; double* part;
+    int rows, k, splits, chunk;
+};
+hipError_t launch_gram64(const Gram64Block* table_dev, const Gram64Block* single, int blocks, int max_k, int max_splits,
+                         hipStream_t stream);
 
 // ---- SVD of the k x k upper-triangular factor R (fp64): an orthogonal Gacc with
 // Gacc R = diag(sigma) X^T (rows mutually orthogonal), from the symmetric eigenproblem of R R^T.

@@ -194,17 +194,122 @@ hipError_t launch_stream(float* dst, const float* src, long long count, float sc
     return hipGetLastError();
 }
 
+// ------------------------------------------------------------------ Gram matrix in fp64
+// One 64 x 64 tile on or below the diagonal per workgroup and range of rows, 32 x 32 per wave (2 x 2 fp64 MFMAs,
+// v_mfma_f64_16x16x4; the quadrant above the diagonal is left out).  Both operands come as they lie in memory: a
+// lane's element of a 4 x 16 operand is one float, four rows of 64 bytes per load, sixteen rows under way while the
+// last sixteen are multiplied (1024 cycles of MFMAs against sixteen loads), so neither LDS nor more bandwidth is asked
+// for: bound by the matrix cores' fp64 rate.
+__global__ __launch_bounds__(256) void gram64_kernel(const Gram64Block* table, const Gram64Block single, const int tiles) {
+    typedef double d4_t __attribute__((ext_vector_type(4)));
+    typedef const float __attribute__((address_space(1))) gfloat;
+    Gram64Block b = single;
+    if (table) b = table[blockIdx.y];
+    const int split = blockIdx.x / tiles, t = blockIdx.x % tiles;
+    int tm = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+    while ((tm + 1) * (tm + 2) / 2 <= t) ++tm;
+    while (tm * (tm + 1) / 2 > t) --tm;
+    const int tn = t - tm * (tm + 1) / 2;
+    if (split >= b.splits || tm * 64 >= b.k) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+    const int i0 = tm * 64 + (wave >> 1) * 32, j0 = tn * 64 + (wave & 1) * 32;
+    if (i0 >= b.k || j0 > i0) return;
+    const int begin = split * b.chunk, end = min(b.rows, begin + b.chunk);
+    gfloat* X = (gfloat*)b.X;
+    unsigned ci[2], cj[2];
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+        ci[f] = min(i0 + 16 * f + li, b.k - 1);
+        cj[f] = min(j0 + 16 * f + li, b.k - 1);
+    }
+    d4_t acc[2][2] = {};
+    float a[2][4][2], c[2][4][2];
+    auto fetch = [&](int s, int r0) {                          // rows past the range: clamped here, cleared when used
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            gfloat* row = X + (size_t)min(r0 + 4 * q + lk, end - 1) * b.k;
+#pragma unroll
+            for (int f = 0; f < 2; ++f) { a[s][q][f] = row[ci[f]]; c[s][q][f] = row[cj[f]]; }
+        }
+    };
+    auto multiply = [&](int s, int r0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool in = r0 + 4 * q + lk < end;
+            double x[2], y[2];
+#pragma unroll
+            for (int f = 0; f < 2; ++f) { x[f] = in ? (double)a[s][q][f] : 0.0; y[f] = in ? (double)c[s][q][f] : 0.0; }
+#pragma unroll
+            for (int f = 0; f < 2; ++f)
+#pragma unroll
+                for (int g = 0; g < 2; ++g) acc[f][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[f], y[g], acc[f][g], 0, 0, 0);
+        }
+    };
+    if (begin < end) {
+        fetch(0, begin);
+        for (int r = begin; r < end; r += 32) {
+            fetch(1, r + 16);
+            multiply(0, r);
+            fetch(0, r + 32);
+            multiply(1, r + 16);
+        }
+    }
+    double* out = b.splits > 1 ? b.part + (size_t)split * b.k * b.k : b.S;
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = i0 + 16 * f + 4 * v + lk, j = j0 + 16 * g + li;
+                if (i < b.k && j <= i) out[(size_t)i * b.k + j] = acc[f][g][v];
+            }
+}
+
+__global__ __launch_bounds__(256) void gram64_sum_kernel(const Gram64Block* table, const Gram64Block single) {
+    Gram64Block b = single;
+    if (table) b = table[blockIdx.y];
+    const int n = b.k * b.k, i = blockIdx.x * 256 + threadIdx.x;
+    if (b.splits <= 1 || i >= n || i % b.k > i / b.k) return;
+    double s = 0.0;
+    int p = 0;
+    for (; p + 8 <= b.splits; p += 8) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = b.part[(size_t)(p + u) * n + i];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += x[u];
+    }
+    for (; p < b.splits; ++p) s += b.part[(size_t)p * n + i];
+    b.S[i] = s;
+}
+
+hipError_t launch_gram64(const Gram64Block* table_dev, const Gram64Block* single, int blocks, int max_k, int max_splits,
+                         hipStream_t stream) {
+    if (blocks <= 0 || max_k <= 0) return hipSuccess;
+    Gram64Block sb{};
+    if (single) sb = *single;
+    const int t = (max_k + 63) / 64, tiles = t * (t + 1) / 2;
+    hipLaunchKernelGGL(gram64_kernel, dim3(tiles * max_splits, blocks), dim3(256), 0, stream, table_dev, sb, tiles);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || max_splits <= 1) return e;
+    hipLaunchKernelGGL(gram64_sum_kernel, dim3((max_k * max_k + 255) / 256, blocks), dim3(256), 0, stream, table_dev, sb);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------------ Cholesky + inverse
 constexpr int SMALL_THREADS = 1024;
 constexpr int SMALL_MAXK = 1024;
 
-// shift_rel * (largest diagonal entry of the k x k fp32 matrix S), computed by the whole workgroup
-__device__ inline double diagonal_shift(const float* S, int k, double shift_rel) {
+__device__ inline double gram_entry(const CholBlock& b, size_t at) { return b.S64 ? b.S64[at] : (double)b.S[at]; }
+
+// shift_rel * (largest diagonal entry of the k x k matrix S), computed by the whole workgroup
+__device__ inline double diagonal_shift(const CholBlock& b, int k, double shift_rel) {
     __shared__ double s_wave_max[SMALL_THREADS / 64];
     __shared__ double s_shift;
     const int tid = threadIdx.x, nt = blockDim.x;
     double mx = 0.0;
-    for (int j = tid; j < k; j += nt) mx = fmax(mx, (double)S[(size_t)j * k + j]);
+    for (int j = tid; j < k; j += nt) mx = fmax(mx, gram_entry(b, (size_t)j * k + j));
     for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
     if ((tid & 63) == 0) s_wave_max[tid >> 6] = mx;
     __syncthreads();
@@ -221,7 +326,6 @@ __global__ __launch_bounds__(SMALL_THREADS) void chol_inv_kernel(const CholBlock
                                                                  const double tol, const double shift_rel) {
     const CholBlock* blk = table ? table + blockIdx.x : &single;
     const int k = blk->k;
-    const float* S = blk->S;
     double* A = blk->work;                     // lower triangle becomes L, S = L L^T
     double* X = blk->work + (size_t)k * k;     // X = L^-1 (lower)
     const int tid = threadIdx.x, nt = blockDim.x;
@@ -229,14 +333,14 @@ __global__ __launch_bounds__(SMALL_THREADS) void chol_inv_kernel(const CholBlock
     __shared__ double colj[SMALL_MAXK];
     __shared__ double s_invd;
 
-    const double shift = diagonal_shift(S, k, shift_rel);
-    for (int idx = tid; idx < k * k; idx += nt) A[idx] = (double)S[idx] + ((idx / k == idx % k) ? shift : 0.0);
+    const double shift = diagonal_shift(*blk, k, shift_rel);
+    for (int idx = tid; idx < k * k; idx += nt) A[idx] = gram_entry(*blk, idx) + ((idx / k == idx % k) ? shift : 0.0);
     __syncthreads();
 
     for (int j = 0; j < k; ++j) {
         if (tid == 0) {
             const double a = A[(size_t)j * k + j];
-            const double s0 = (double)S[(size_t)j * k + j];
+            const double s0 = gram_entry(*blk, (size_t)j * k + j);
             if (a > 0.0 && a > tol * s0) {
                 const double d = sqrt(a);
                 A[(size_t)j * k + j] = d;
@@ -353,7 +457,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlo
     // two buffers of NT tiles; slot x of step J: L_xJ (x > J), X_Jx^T (x <= J)
     tile_t* raw = (tile_t*)smem + 2 * NT;                      // the next diagonal tile, two buffers
     tile_t* low_diag = raw + 2;                                // L_JJ, two buffers
-    float* s_diag = (float*)(smem + (2 * NT + 4) * CT * CT_P);  // diagonal of S
+    double* s_diag = smem + (2 * NT + 4) * CT * CT_P;          // diagonal of S
 
     CholBlock cb = single;
     if (table) cb = table[blockIdx.x];
@@ -367,7 +471,9 @@ __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlo
     const int li = lane & 15, lk = lane >> 4;
     typedef const float __attribute__((address_space(1))) gfloat;
     typedef double __attribute__((address_space(1))) gdouble;
-    gfloat* S = (gfloat*)cb.S + first;
+    gfloat* S = (gfloat*)cb.S;
+    const gdouble* S64 = (const gdouble*)cb.S64;
+    auto entry = [&](size_t at) { return S64 ? (double)S64[at] : (double)S[at]; };   // of the whole matrix
     float __attribute__((address_space(1)))* Rinv = (float __attribute__((address_space(1)))*)cb.Rinv + first;
     gdouble* Rtot = cb.Rtot ? (gdouble*)cb.Rtot + first : nullptr;
     const gdouble* A = (const gdouble*)cb.work + first;
@@ -377,12 +483,12 @@ __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlo
     auto diagonal_shift_tiles = [&]() {
         double mx = 0.0;
         for (int j = tid; j < nt * CT; j += 64 * WAVES) {
-            const float d = (j < k) ? S[(size_t)j * ld + j] : 1.0f;
+            const double d = (j < k) ? entry(first + (size_t)j * ld + j) : 1.0;
             s_diag[j] = d;
-            if (PART == 0 && j < k) mx = fmax(mx, (double)d);
+            if (PART == 0 && j < k) mx = fmax(mx, d);
         }
         if (PART != 0)                                         // the shift is one for the whole matrix
-            for (int j = tid; j < ld; j += 64 * WAVES) mx = fmax(mx, (double)((gfloat*)cb.S)[(size_t)j * ld + j]);
+            for (int j = tid; j < ld; j += 64 * WAVES) mx = fmax(mx, entry((size_t)j * ld + j));
         for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
         if (lane == 0) smem[wave] = mx;
         lds_barrier();
@@ -420,7 +526,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlo
         double low[CT];                                        // pivots up to here are dropped
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
-            low[c] = fmax(tol * (double)s_diag[J * CT + c], 0.0);
+            low[c] = fmax(tol * s_diag[J * CT + c], 0.0);
             asm("" : "+v"(low[c]));                            // (a select below, not a branch on a uniform value)
         }
         d4_t E, Xv = {0.0, 0.0, 0.0, 0.0}, Lv, left;
@@ -578,7 +684,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlo
             const int i = I * CT + li, c = K * CT + 4 * v + lk;
             const bool in = i < k && c < k;
             const int lo = min(min(i, c), k - 1), hi = min(max(i, c), k - 1);    // the lower triangle of S is read
-            const double x = PART == 2 ? A[(size_t)hi * ld + lo] : (double)S[(size_t)hi * ld + lo];
+            const double x = PART == 2 ? A[(size_t)hi * ld + lo] : entry(first + (size_t)hi * ld + lo);
             acc[s][v] = in ? x : (i == c ? 1.0 : 0.0);
         }
     }
@@ -673,7 +779,7 @@ __global__ __launch_bounds__(256) void chol_parts_kernel(const CholBlock* table,
     const int t = blockIdx.x - (gram ? tiles * tiles : 0);
     const int i0 = t / tiles * CG, j0 = t % tiles * CG;
     if (i0 >= k2 || j0 >= (gram ? i0 + 1 : o)) return;         // the whole workgroup
-    const gfloat* S = (const gfloat*)cb.S;
+    auto entry = [&](size_t at) { return cb.S64 ? (double)((const gdouble*)cb.S64)[at] : (double)((const gfloat*)cb.S)[at]; };
     gdouble* A = (gdouble*)cb.work;
     gdouble* X = A + (size_t)ld * ld;
     const int nrow = k2, ncol = gram ? k2 : o, depth = STAGE == 2 ? k2 : o;
@@ -693,7 +799,7 @@ __global__ __launch_bounds__(256) void chol_parts_kernel(const CholBlock* table,
             const int kk = kt + rk + q, i = i0 + rr;
             double v = 0.0;
             if (i < nrow && kk < depth) {
-                if (STAGE == 0) v = (double)S[(size_t)(o + i) * ld + kk];
+                if (STAGE == 0) v = entry((size_t)(o + i) * ld + kk);
                 else if (STAGE == 1) v = A[(size_t)(o + i) * ld + kk];
                 else if (kk <= i) v = X[(size_t)(o + i) * ld + o + kk];
             }
@@ -754,7 +860,7 @@ __global__ __launch_bounds__(256) void chol_parts_kernel(const CholBlock* table,
                 if (STAGE != 1) out[r][c] = x;
                 if (i >= nrow || j >= ncol) continue;
                 if (STAGE == 0) A[(size_t)(o + i) * ld + j] = x;
-                else if (STAGE == 1 && gram) { if (j <= i) A[(size_t)(o + i) * ld + o + j] = (double)S[(size_t)(o + i) * ld + o + j] - x; }
+                else if (STAGE == 1 && gram) { if (j <= i) A[(size_t)(o + i) * ld + o + j] = entry((size_t)(o + i) * ld + o + j) - x; }
                 else if (STAGE == 1) X[(size_t)(o + i) * ld + j] = x;
                 else {
                     cb.Rinv[(size_t)(o + i) * ld + j] = 0.0f;
@@ -774,7 +880,7 @@ __global__ __launch_bounds__(256) void chol_parts_kernel(const CholBlock* table,
 template <int NT, int WAVES, int PART = 0>
 static hipError_t launch_chol_tiles(const CholBlock* table_dev, const CholBlock& single, int blocks, double tol, double shift_rel,
                                     hipStream_t stream) {
-    constexpr int lds = (2 * NT + 4) * CT * CT_P * 8 + NT * CT * 4;
+    constexpr int lds = (2 * NT + 4) * CT * CT_P * 8 + NT * CT * 8;
     static thread_local bool configured = false;
     if (!configured && lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void*)chol_tiles_kernel<NT, WAVES, PART>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);

@@ -90,6 +90,29 @@ def test_refresh_full_sketch_sizes(tsr, k):
     assert float(torch.linalg.norm(core - torch.diag(s[:r])) / torch.linalg.norm(s)) < 2e-5
 
 
+# the fp64 Gram matrices cut the rows into pieces (multiples of 16) and the columns into 64-wide tiles of 32-wide
+# quadrants: a remainder of one row, row counts around a piece's, one tile, one quadrant more, two tiles
+@pytest.mark.parametrize("rows,k", [(1000, 20), (1025, 33), (4097, 64), (130, 65), (33000, 9), (2049, 97)])
+def test_refresh_tall_full_sketch(tsr, rows, k):
+    """As above with many rows on either side (B^T is as tall as G^T): singular values and orthonormality."""
+    p = 4
+    r = k - p
+    for m, n in ((rows, k), (k, rows)):
+        key = si.stream_key(705, m, n)
+        G = si.normal((m, n), si.stream_key(key, 1))
+        U = torch.full((m, r), float("nan"), device="cuda")
+        V = torch.full((n, r), float("nan"), device="cuda")
+        sigma = torch.full((k,), float("nan"), device="cuda")
+        tsr.tsr_refresh_rsvd(dev(G), dev(si.omega(n, k, si.stream_key(key, 2))), r, p, 0, U, V, sigma)
+        s = torch.linalg.svdvals(G.double())
+        # fp32 sums of up to `rows` products with errors of random sign
+        tol = 4 * (rows ** 0.5 + 4) * 2.0 ** -24
+        assert float((sigma.cpu().double() - s).abs().max() / s[0]) < tol
+        eye = torch.eye(r, dtype=torch.float64)
+        for X in (U.cpu().double(), V.cpu().double()):
+            assert float(torch.linalg.norm(X.T @ X - eye)) < 2.0 ** -20 * k
+
+
 # the factorization takes four columns at a time, sixteen per tile: dropped columns from every place of a panel on,
 # from the first of a tile on, and tiles of nothing else
 @pytest.mark.parametrize("rank", [1, 2, 3, 4, 5, 15, 16, 17, 21, 32, 35])
