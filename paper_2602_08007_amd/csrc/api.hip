@@ -413,6 +413,24 @@ struct RefreshProgram {
     GemmStage uout, vout;
 };
 
+// Tile of the wide kernel for products with r + p columns: 256 x 192 where that leaves fewer columns of padding and
+// there is more than one tile to a row (r + p = 528: refresh step of the 1B model 88.1 -> 86.6 ms; 392, no difference).
+// With a single tile the narrower one is faster (r + p = 136, 24 layers of the 130M model's shapes, 3.02 against 3.10 ms),
+// as it is where the columns are the same (r + p = 264: 5.72 against 5.97 ms).
+int nt_refresh_shape(const std::vector<RefreshBlock>& blocks) {
+    long long at128 = 0, at192 = 0, tiles_m = 0, tiles_n = 0;
+    int max_k = 0;
+    for (const RefreshBlock& b : blocks) {
+        tiles_m += (long long)ceil_div(b.m, 256) * ceil_div(b.k, 192);
+        tiles_n += (long long)ceil_div(b.n, 256) * ceil_div(b.k, 192);
+        at128 += (long long)(b.m + b.n) * (ceil_div(b.k, 128) * 128);
+        at192 += (long long)(b.m + b.n) * (ceil_div(b.k, 192) * 192);
+        max_k = std::max(max_k, b.k);
+    }
+    // (and only where the fewer tiles are still too many for a k split, whose partials would outgrow the workspace)
+    return (max_k > 192 && at192 < at128 && std::min(tiles_m, tiles_n) > 256) ? NT_256x192_K32 : NT_256x128_K32;
+}
+
 void build_orth_nt(OrthNtPass& pass, const std::vector<RefreshBlock>& blocks, bool on_rows_m, Arena& ar) {
     pass = OrthNtPass{};
     std::vector<NtLogical> g, a1;
@@ -440,7 +458,7 @@ void build_orth_nt(OrthNtPass& pass, const std::vector<RefreshBlock>& blocks, bo
     build_nt_stage(pass.gram, NtVariant{NT_128x128, 0, 0}, g, nb, ar, 512, false, 0, /*lower_only=*/true);
     NtVariant v2{};
     const char* e = getenv("TSR_TUNE_ORTH_WIDE");          // 0: 128 x 128 tiles instead of the wide-tile kernel
-    v2.shape = (e && e[0] == '0') ? (int)NT_128x128_K32 : (int)NT_256x128_K32; v2.b_pieces = 2;
+    v2.shape = (e && e[0] == '0') ? (int)NT_128x128_K32 : nt_refresh_shape(blocks); v2.b_pieces = 2;
     build_nt_stage(pass.ap, v2, a1, nb, ar, 1, false, 0, false, /*b_upper=*/true);
 }
 
@@ -645,7 +663,7 @@ void build_refresh_stages(RefreshProgram& rp, const float* const* omegas, Arena&
         // two workgroups per compute unit (measured on the 1B workload: 23.2 against 26.0 ms, equal on the 130M one)
         const char* e = getenv("TSR_TUNE_REFRESH_WIDE");
         NtVariant var{};
-        var.shape = (e && e[0] == '0') ? (int)NT_128x128_K32 : (int)NT_256x128_K32; var.b_pieces = NT_REFRESH_PIECES;
+        var.shape = (e && e[0] == '0') ? (int)NT_128x128_K32 : nt_refresh_shape(rp.blocks); var.b_pieces = NT_REFRESH_PIECES;
         build_nt_stage(rp.nt.g_stage, var, ntg, (int)rp.blocks.size(), ar, 512);
         build_nt_stage(rp.nt.gt_stage, var, ntgt, (int)rp.blocks.size(), ar, 512);
     }

@@ -53,14 +53,15 @@ enum NtShape {
     NT_256x256_K32 = 5,     // wide-tile kernel, one workgroup per compute unit
     NT_128x128_WS = 6,      // wave-specialised read-modify-write kernel: persistent launches (ranges) of fp32
                             // C = beta C + alpha A B^T with K == 512 in every problem, nothing else
-    NT_SHAPES = 7
+    NT_256x192_K32 = 7,     // wide-tile kernel, two pieces of B only
+    NT_SHAPES = 8
 };
 inline int nt_tile_m(int s) {
-    static const int tm[NT_SHAPES] = {128, 64, 64, 128, 256, 256, 128};
+    static const int tm[NT_SHAPES] = {128, 64, 64, 128, 256, 256, 128, 256};
     return tm[s];
 }
 inline int nt_tile_n(int s) {
-    static const int tn[NT_SHAPES] = {128, 256, 64, 128, 128, 256, 128};
+    static const int tn[NT_SHAPES] = {128, 256, 64, 128, 128, 256, 128, 192};
     return tn[s];
 }
 

@@ -347,7 +347,7 @@ __global__ __launch_bounds__(NT_THREADS, 1) void nt_wide_kernel(const NtLaunch L
     constexpr int CH = CHA + NP * CHB;                      // 16-byte chunks per thread and k-tile
     constexpr int NFRAG = FM + NP * FN;                     // fragment reads per k step
     constexpr int NMFMA = FM * FN * NP;                     // MFMAs per k step
-    static_assert(NMFMA % 8 == 0 && NFRAG % 4 == 0 && CH % 4 == 0, "the schedule issues the MFMAs of a k step in eight groups");
+    static_assert(NMFMA % 8 == 0, "the schedule issues the MFMAs of a k step in eight groups");
     constexpr int GRP = NMFMA / 8;
     extern __shared__ __attribute__((aligned(16))) unsigned short lds[];
 
@@ -1123,6 +1123,7 @@ static const NtEntry kNt[] = {
     { NT_256x256_K32, 0, 0, nt_wide_kernel<4, 4, 1, 0>, nullptr, 2 * (256 + 256) * 32 * 2, 1, 1 },
     { NT_256x256_K32, 0, 1, nt_wide_kernel<4, 4, 1, 1>, nullptr, 2 * (256 + 256) * 32 * 2, 1, 1 },
     { NT_256x128_K32, 0, 0, nt_wide_kernel<4, 2, 2, 0>, nullptr, 2 * (256 + 2 * 128) * 32 * 2, 1, 2 },
+    { NT_256x192_K32, 0, 0, nt_wide_kernel<4, 3, 2, 0>, nullptr, 2 * (256 + 2 * 192) * 32 * 2, 1, 2 },
     NT_ENTRY_PIECES(NT_128x128_K32, 128, 128, 2, 2, 32, 2, 2),
 };
 
