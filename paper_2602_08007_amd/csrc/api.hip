@@ -45,7 +45,7 @@ struct GemmStage {
     std::vector<GemmProblem> probs;
     std::vector<GemmTile> tiles;
     std::vector<ReduceProblem> reduces;
-    int max_reduce_elems = 0;
+    int max_reduce_elems = 0, max_splits = 1;
     bool direct = true;
     bool b_upper = false;                          // B is upper triangular
     int tiles_m = 0, tiles_n = 0, ksplit = 1;      // single-problem decode
@@ -133,6 +133,7 @@ void build_stage(GemmStage& st, const GemmVariant& var, const std::vector<Logica
             r.M = gemms[i].M; r.N = gemms[i].N; r.splits = group_splits;
             st.reduces.push_back(r);
             st.max_reduce_elems = std::max(st.max_reduce_elems, (int)std::min<size_t>(mn, 1u << 30));
+            st.max_splits = std::max(st.max_splits, group_splits);
         }
         int prefix = 0;
         for (size_t j = i; j < e; ++j) {
@@ -181,7 +182,7 @@ int run_stage(const GemmStage& st, bool grouped, float alpha, float beta, Ctx& c
         L.alpha = 1.0f; L.beta = 0.0f;
         TSR_HIP(launch_gemm(L, st.var, stream));
         TSR_HIP(launch_splitk_reduce(grouped ? st.d_reduces : nullptr, grouped ? nullptr : &st.reduces[0],
-                                     (int)st.reduces.size(), st.max_reduce_elems, alpha, beta, stream));
+                                     (int)st.reduces.size(), st.max_reduce_elems, st.max_splits, alpha, beta, stream));
     }
     return TSR_OK;
 }
@@ -295,7 +296,8 @@ int project_one_matrix(const std::vector<BlockView>& block, int prec, float alph
     if (project_one_plan(q, block[0], ws, used)) {
         const int partials = ceil_div(q.m, 64) * q.chunks;
         TSR_HIP(launch_project_one(q, block[0].g_dtype == TSR_BF16, prec != TSR_PREC_BF16, partials, stream));
-        TSR_HIP(launch_splitk_reduce_wide(q.part, block[0].C, (long long)q.r * q.r, partials, q.r * q.r, alpha, beta, stream));
+        ReduceProblem sum{q.part, block[0].C, (long long)q.r * q.r, q.r, q.r, q.r, partials};
+        TSR_HIP(launch_splitk_reduce(nullptr, &sum, 1, q.r * q.r, partials, alpha, beta, stream));
         return TSR_OK;
     }
     Ctx cx{stream, nullptr};
@@ -304,23 +306,33 @@ int project_one_matrix(const std::vector<BlockView>& block, int prec, float alph
 
 struct LiftProgram {
     GemmStage ud;           // T = U D
-    GemmStage tvt;          // W = beta W + alpha T V^T
+    GemmStage vd;           // T = V D^T, blocks with much longer columns than rows
+    GemmStage tvt;          // W = beta W + alpha T V^T, or U T^T
 };
 
+// The intermediate lies on the shorter side where the longer one has at least four times its rows (32000 x 2048 embedding
+// and LM head, r = 128: 20 -> 7 us); a launch of its own costs more than is saved below that.
 void build_lift(LiftProgram& lp, const std::vector<BlockView>& blocks, int prec, Arena& ar) {
-    std::vector<LogicalGemm> ud, tvt;
+    std::vector<LogicalGemm> ud, vd, tvt;
     for (const BlockView& b : blocks) {
         float* T = ar.take<float>((size_t)b.m * b.r);
-        ud.push_back(LogicalGemm{b.U, b.D, b.r, b.r, b.m, b.r, b.r, T, b.r});
-        tvt.push_back(LogicalGemm{T, b.V, b.r, b.r, b.m, b.n, b.r, b.W, b.ldw});
+        if (b.m >= 4 * (long long)b.n) {
+            vd.push_back(LogicalGemm{b.V, b.D, b.r, b.r, b.n, b.r, b.r, T, b.r});
+            tvt.push_back(LogicalGemm{b.U, T, b.r, b.r, b.m, b.n, b.r, b.W, b.ldw});
+        } else {
+            ud.push_back(LogicalGemm{b.U, b.D, b.r, b.r, b.m, b.r, b.r, T, b.r});
+            tvt.push_back(LogicalGemm{T, b.V, b.r, b.r, b.m, b.n, b.r, b.W, b.ldw});
+        }
     }
     const int pv = (prec == TSR_PREC_BF16) ? 1 : 2;
     build_stage(lp.ud, variant(0, 1, 0, pv, pv), ud, ar, /*want_tiles=*/1);
+    build_stage(lp.vd, variant(0, 0, 0, pv, pv), vd, ar, /*want_tiles=*/1);
     build_stage(lp.tvt, variant(0, 0, 0, pv, pv), tvt, ar, /*want_tiles=*/1);
 }
 
 int run_lift(const LiftProgram& lp, bool grouped, float lr, float wd, float scale, Ctx& cx) {
     TSR_TRY(run_stage(lp.ud, grouped, 1.0f, 0.0f, cx, TSR_PROF_UD));
+    TSR_TRY(run_stage(lp.vd, grouped, 1.0f, 0.0f, cx, TSR_PROF_UD));
     // W - lr (scale dW + wd W) = (1 - lr wd) W + (-lr scale) dW
     return run_stage(lp.tvt, grouped, -lr * scale, 1.0f - lr * wd, cx, TSR_PROF_TVT);
 }
@@ -1366,6 +1378,7 @@ static void build_plan(tsr_plan& pl, Arena& ar) {
         for (int d = 0; d < 2; ++d) upload_stage(pl.project.gv[d], ar, up);
         upload_stage(pl.project.utp, ar, up);
         upload_stage(pl.lift.ud, ar, up);
+        upload_stage(pl.lift.vd, ar, up);
         upload_stage(pl.lift.tvt, ar, up);
     }
     if (pl.with_refresh) {

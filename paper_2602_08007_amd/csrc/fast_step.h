@@ -18,7 +18,7 @@ struct NtStageH {
     std::vector<NtRange> ranges;          // persistent launch: one list of tiles per workgroup
     const NtRange* d_ranges = nullptr;
     std::vector<ReduceProblem> reduces;   // empty when the GEMM writes its output directly
-    int max_reduce_elems = 0;
+    int max_reduce_elems = 0, max_splits = 1;
     bool b_upper = false;                 // see NtLaunch
     const NtProblem* d_probs = nullptr;
     const NtTile* d_tiles = nullptr;

@@ -163,6 +163,7 @@ void build_nt_stage(NtStageH& st, const NtVariant& var, const std::vector<NtLogi
             r.M = gemms[i].M; r.N = gemms[i].N; r.splits = gs;
             st.reduces.push_back(r);
             st.max_reduce_elems = std::max(st.max_reduce_elems, (int)std::min<size_t>(mn, 1u << 30));
+            st.max_splits = std::max(st.max_splits, gs);
         }
         int prefix = 0;
         for (size_t j = i; j < e; ++j) {
@@ -214,7 +215,7 @@ int run_nt_stage(const NtStageH& st, float alpha, float beta, Ctx& cx, int kind,
     } else {
         L.alpha = 1.0f; L.beta = 0.0f;
         TSR_HIP(launch_nt_gemm(L, st.var, cx.s));
-        TSR_HIP(launch_splitk_reduce(st.d_reduces, nullptr, (int)st.reduces.size(), st.max_reduce_elems, alpha, beta,
+        TSR_HIP(launch_splitk_reduce(st.d_reduces, nullptr, (int)st.reduces.size(), st.max_reduce_elems, st.max_splits, alpha, beta,
                                      cx.s));
     }
     return TSR_OK;

@@ -60,12 +60,9 @@ struct ReduceProblem {
     long long stride, ldc;
     int M, N, splits;
 };
+// max_elems, max_splits: of the problems.
 hipError_t launch_splitk_reduce(const ReduceProblem* probs_dev, const ReduceProblem* single,
-                                int count, int max_elems, float alpha, float beta, hipStream_t stream);
-
-// out[i] = alpha * (sum of `splits` partials `stride` apart)[i] + beta * out[i], i < total: one problem, few outputs
-hipError_t launch_splitk_reduce_wide(const float* part, float* out, long long stride, int splits, int total, float alpha, float beta,
-                                     hipStream_t stream);
+                                int count, int max_elems, int max_splits, float alpha, float beta, hipStream_t stream);
 
 // The step of one small matrix, r <= ONE_MAX_R.  Projection: workgroup (slab, chunk), slab-major, leaves
 // U_s^T (G_sc V_c), r x r, for 64 rows s and kchunk columns c (a multiple of 32) in part[workgroup].

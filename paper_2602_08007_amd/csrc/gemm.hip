@@ -801,25 +801,26 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceProblem*
     }
 }
 
-// The same for few outputs and many partials of one problem: sixteen vectors of outputs per workgroup, sixteen threads
-// share the partials of each (neighbouring threads neighbouring vectors), their sums added in order.  Dense outputs.
-__global__ __launch_bounds__(256) void splitk_reduce_wide_kernel(const float* part_, float* out_, long long stride, int splits, int total,
+// The same for few outputs and many partials: sixteen vectors of outputs per workgroup, sixteen threads share the
+// partials of each (neighbouring threads neighbouring vectors), their sums added in order.
+__global__ __launch_bounds__(256) void splitk_reduce_wide_kernel(const ReduceProblem* probs, const ReduceProblem single,
                                                                  const float alpha, const float beta) {
     constexpr int G = 16;
     __shared__ f32x4 sums[G][G];
-    const TSR_GLOBAL float* part = (const TSR_GLOBAL float*)part_;
-    TSR_GLOBAL float* out = (TSR_GLOBAL float*)out_;
-    const int x = threadIdx.x % G, g = threadIdx.x / G;
+    const ReduceProblem p = probs ? probs[blockIdx.y] : single;
+    const TSR_GLOBAL float* part = (const TSR_GLOBAL float*)p.part;
+    TSR_GLOBAL float* out = (TSR_GLOBAL float*)p.out;
+    const int x = threadIdx.x % G, g = threadIdx.x / G, total = p.M * p.N;
     const int i = 4 * (blockIdx.x * G + x);
-    const int per = (splits + G - 1) / G, k0 = g * per, k1 = min(splits, k0 + per);
+    const int per = (p.splits + G - 1) / G, k0 = g * per, k1 = min(p.splits, k0 + per);
     const bool whole = i + 4 <= total;
     f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
     auto at = [&](int k) {
-        const TSR_GLOBAL float* p = part + k * stride + i;
-        if (whole) return (f32x4)*(const TSR_GLOBAL f32x4_u*)p;
+        const TSR_GLOBAL float* q = part + k * p.stride + i;
+        if (whole) return (f32x4)*(const TSR_GLOBAL f32x4_u*)q;
         f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int u = 0; u < 4; ++u) if (i + u < total) v[u] = p[u];
+        for (int u = 0; u < 4; ++u) if (i + u < total) v[u] = q[u];
         return v;
     };
     int k = k0;
@@ -838,24 +839,26 @@ __global__ __launch_bounds__(256) void splitk_reduce_wide_kernel(const float* pa
     for (int u = 1; u < G; ++u) s += sums[u][x];
     s = alpha * s;
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-        if (i + u < total) out[i + u] = s[u] + (beta != 0.0f ? beta * out[i + u] : 0.0f);
-}
-
-hipError_t launch_splitk_reduce_wide(const float* part, float* out, long long stride, int splits, int total, float alpha, float beta,
-                                     hipStream_t stream) {
-    if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(splitk_reduce_wide_kernel, dim3((total + 63) / 64), dim3(256), 0, stream, part, out, stride, splits, total, alpha, beta);
-    return hipGetLastError();
+    for (int u = 0; u < 4; ++u) {
+        if (i + u >= total) continue;
+        const long long o = (p.ldc == p.N) ? i + u : (long long)((i + u) / p.N) * p.ldc + (i + u) % p.N;
+        out[o] = s[u] + (beta != 0.0f ? beta * out[o] : 0.0f);
+    }
 }
 
 hipError_t launch_splitk_reduce(const ReduceProblem* probs_dev, const ReduceProblem* single, int count,
-                                int max_elems, float alpha, float beta, hipStream_t stream) {
+                                int max_elems, int max_splits, float alpha, float beta, hipStream_t stream) {
     if (count <= 0 || max_elems <= 0) return hipSuccess;
     int bx = (max_elems + 1023) / 1024;
     if (bx > 1024) bx = 1024;
     ReduceProblem s{};
     if (single) s = *single;
+    // Threads that share the partials where there are many of them and too few outputs to fill the chip: cores of the
+    // 32000 x 2048 embedding and LM head (256 partials) 15 -> 8 us, the refresh of 512 x 1376 at r = 64 4.1 -> 3.5 us each.
+    if (max_splits >= 8 && (long long)bx * count < 256) {
+        hipLaunchKernelGGL(splitk_reduce_wide_kernel, dim3((max_elems + 63) / 64, count), dim3(256), 0, stream, probs_dev, s, alpha, beta);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3(bx, count), dim3(256), 0, stream, probs_dev, s, alpha, beta);
     return hipGetLastError();
 }
