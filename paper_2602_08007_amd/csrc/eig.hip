@@ -34,6 +34,35 @@ __device__ inline double eig_wave_sum(double v) {
     return v;
 }
 
+// Cross-lane sums without LDS: data-parallel moves inside the 16-lane rows, row and half swaps beyond.
+template <int CTRL> __device__ inline double eig_dpp(double x) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_MIRROR8 = 0x141, DPP_MIRROR16 = 0x140, DPP_ROR8 = 0x128;
+// (a, b) -> (a of the lower 32 lanes, b of the lower 32 lanes) + (a of the upper, b of the upper): the sum of
+// a over the halves in lanes 0-31, that of b in lanes 32-63
+__device__ inline double eig_sum32(double a, double b) {
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+// likewise over the two 16-lane rows of a half: a's sum in the even rows, b's in the odd ones
+__device__ inline double eig_sum16(double a, double b) {
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ inline double eig_wave_sum_dpp(double x) {         // result in every lane
+    x += eig_dpp<DPP_XOR1>(x);
+    x += eig_dpp<DPP_XOR2>(x);
+    x += eig_dpp<DPP_MIRROR8>(x);
+    x += eig_dpp<DPP_MIRROR16>(x);
+    x = eig_sum16(x, x);
+    return eig_sum32(x, x);
+}
+
 // 1 / x to full precision for finite non-zero x of ordinary size (no scaling, no fix-up)
 __device__ inline double eig_rcp(double x) {
     double r = __builtin_amdgcn_rcp(x);
@@ -171,7 +200,10 @@ __device__ inline double eig_start_value(unsigned i, unsigned j) {
 // diagonal in strips of 64 columns, and an entry (c, i) below the diagonal adds to two sums of p = T v, p_i
 // (kept per lane and strip over all rows of the wave, summed over the waves through LDS at the end) and p_c
 // (summed over the lanes once per row); the upper triangle is dead storage but for the reflectors.
-// (v, w) are indexed from t for the pending pair and from t+1 for the new one.
+// (v, w) are indexed from t for the pending pair and from t+1 for the new one.  The sums over the lanes go by
+// data-parallel moves; through LDS, six round trips a row, they were a tenth of it (56 matrices of k = 528 9.45 -> 8.52 ms,
+// refresh step of the 1B model 86.5 -> 85.1 ms).  Slower: three rows in flight a wave instead of two (registers spill),
+// eight waves with the vectors in registers (10.2 ms).
 constexpr int EIG_TILES_K = 288;
 __global__ __launch_bounds__(EIG_THREADS) void eig_tridiag_kernel(const JacobiBlock* table, const JacobiBlock single) {
     JacobiBlock jb = single;
@@ -196,7 +228,7 @@ __global__ __launch_bounds__(EIG_THREADS) void eig_tridiag_kernel(const JacobiBl
     __shared__ double s_red[EIG_THREADS / 64];
 
     auto block_sum = [&](double v) -> double {
-        v = eig_wave_sum(v);
+        v = eig_wave_sum_dpp(v);
         __syncthreads();
         if (lane == 0) s_red[wave] = v;
         __syncthreads();
@@ -264,7 +296,7 @@ __global__ __launch_bounds__(EIG_THREADS) void eig_tridiag_kernel(const JacobiBl
                     if (i < c) rowacc += xi * nv_[i];
                 }
             }
-            rowacc = eig_wave_sum(rowacc);
+            rowacc = eig_wave_sum_dpp(rowacc);
             if (lane == 0) s_prow[c] = rowacc;
         };
         for (int c = wave; c < n1; c += 2 * nw) {
@@ -314,34 +346,6 @@ __global__ __launch_bounds__(EIG_THREADS) void eig_tridiag_kernel(const JacobiBl
 }
 
 // ---- Tridiagonalization with the matrix in registers, for the trailing part of at most 288 columns.
-// Cross-lane sums without LDS: data-parallel moves inside the 16-lane rows, row and half swaps beyond.
-template <int CTRL> __device__ inline double eig_dpp(double x) {
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_MIRROR8 = 0x141, DPP_MIRROR16 = 0x140, DPP_ROR8 = 0x128;
-// (a, b) -> (a of the lower 32 lanes, b of the lower 32 lanes) + (a of the upper, b of the upper): the sum of
-// a over the halves in lanes 0-31, that of b in lanes 32-63
-__device__ inline double eig_sum32(double a, double b) {
-    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
-    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
-}
-// likewise over the two 16-lane rows of a half: a's sum in the even rows, b's in the odd ones
-__device__ inline double eig_sum16(double a, double b) {
-    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
-    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
-}
-__device__ inline double eig_wave_sum_dpp(double x) {         // result in every lane
-    x += eig_dpp<DPP_XOR1>(x);
-    x += eig_dpp<DPP_XOR2>(x);
-    x += eig_dpp<DPP_MIRROR8>(x);
-    x += eig_dpp<DPP_MIRROR16>(x);
-    x = eig_sum16(x, x);
-    return eig_sum32(x, x);
-}
 // Barrier that orders LDS only (the reflectors on their way to memory are not waited for).
 __device__ inline void eig_lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
