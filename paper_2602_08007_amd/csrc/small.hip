@@ -414,7 +414,7 @@ __device__ inline double readlane_f64(double v, int lane) {      // lane: a comp
 // from then on.  With the tiles and X held transposed both updates are the same product, slot K times the
 // transpose of slot I.  So nothing but the input and the results touches memory, and the inverse costs no
 // launches of its own.  What bounds it up to k = 144 is the serial chain of the diagonal tiles, above that the fp64
-// products of the early steps (a quarter of the chip's rate per SIMD: 64 cycles per 16 x 16 x 4).  The last wave has
+// products of the early steps (64 cycles of a SIMD per 16 x 16 x 4).  The last wave has
 // no tiles of its own: it takes the next diagonal tile through LDS and factors it while the others work on theirs,
 // four columns at a time with products between (3600 cycles; a column at a time, with broadcasts of every entry by
 // v_readlane, took 7300, and 11 500 beside a wave with products).
@@ -665,7 +665,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void chol_tiles_kernel(const CholBlo
         while ((I + 1) * (I + 2) / 2 <= t) ++I;
         while (I * (I + 1) / 2 > t) --I;
         const int K = min(t - I * (I + 1) / 2, NT - 1);
-        tile_at[s] = __builtin_amdgcn_readfirstlane(I * TILE + (K * TILE << 16));
+        tile_at[s] = __builtin_amdgcn_readfirstlane((int)((unsigned)(I * TILE) | (unsigned)(K * TILE) << 16));
     }
     // A slot's coordinates, opaque to the compiler: it would otherwise keep the LDS addresses of every
     // slot in vector registers across the loop (and spill).
