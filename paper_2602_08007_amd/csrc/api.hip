@@ -474,7 +474,8 @@ void build_orth_nt(OrthNtPass& pass, const std::vector<RefreshBlock>& blocks, bo
     build_nt_stage(pass.ap, v2, a1, nb, ar, 1, false, 0, false, /*b_upper=*/true);
 }
 
-// Row pieces and partial matrices of the fp64 Gram matrices: some 512 workgroups, in at most `bytes` of the arena.
+// Row pieces and partial matrices of the fp64 Gram matrices: some 512 workgroups, fewer where `bytes` of the arena hold
+// fewer partial matrices.
 void build_gram64(OrthProgram& op, const std::vector<RefreshBlock>& blocks, bool on_rows_m, size_t bytes, Arena& ar) {
     long long base = 0;
     for (const RefreshBlock& b : blocks) base += (long long)ceil_div(b.k, 64) * (ceil_div(b.k, 64) + 1) / 2;
@@ -527,16 +528,18 @@ void build_orth(OrthProgram& op, const std::vector<RefreshBlock>& blocks, bool o
     int pieces_x = 2;
     for (const RefreshBlock& b : blocks) if (b.g_dtype == TSR_F32) pieces_x = 3;
     // the Cholesky kernels read the lower triangle of the Gram matrix only
-    const size_t before = ar.off;
     build_stage(op.gramA, variant(1, 1, 0, 2, 2), gA, ar, 512, true);
-    const size_t partials = ar.off - before;
     build_stage(op.qA, variant(0, 1, 0, pieces_x, pieces_x), qA, ar, 1);
     op.qA.b_upper = true;                                  // (one tile's k is never split at want_tiles = 1)
+    Arena shared = ar;
+    shared.off = align_up(shared.off);
     build_stage(op.gramB, variant(1, 1, 0, 3, 3), gB, ar, 512, true);
+    // The partial fp64 Gram matrices of the first pass lie where the second pass puts its own partials, later.
+    // (Those are there for every block; gramA has none of the blocks on the NT family, whose Gram matrices were
+    // computed by one workgroup a tile over all rows: refresh of two 32000 x 2048 in bf16 at r + p = 24 3.00 -> 1.53 ms.)
+    build_gram64(op, blocks, on_rows_m, ar.off > shared.off ? ar.off - shared.off : 0, shared);
     build_stage(op.qB, variant(0, 1, 0, 3, 3), qB, ar, 1);
     op.qB.b_upper = true;
-    // (as much as the partials of one more fp32 Gram stage would take)
-    build_gram64(op, blocks, on_rows_m, partials, ar);
 }
 
 // One orthonormalisation of every block; see ORTH_SHIFT above for the two kinds.

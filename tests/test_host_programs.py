@@ -1,0 +1,110 @@
+"""What the host code decides, without a GPU: a small program links the built library, takes the place of the HIP
+runtime's calls and of the launches it looks at, and prints what these were given."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_2602_08007_amd")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <vector>
+#include "small.h"
+#include "tsr.h"
+static char *ws, *ws_end;
+extern "C" {
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t)malloc(1); return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)malloc(1); return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) { free(s); return hipSuccess; }
+}
+namespace tsr {
+hipError_t launch_gram64(const Gram64Block* table, const Gram64Block* single, int blocks, int, int max_splits, hipStream_t) {
+    for (int i = 0; i < blocks; ++i) {
+        const Gram64Block& b = table ? table[i] : *single;
+        const size_t bytes = b.splits > 1 ? (size_t)b.k * b.k * b.splits * sizeof(double) : 0;
+        const bool inside = !bytes || ((char*)b.part >= ws && (char*)b.part + bytes <= ws_end);
+        printf("gram64 %d %d %d %d %d\n", b.rows, b.k, b.splits, b.chunk, inside && b.splits <= max_splits);
+    }
+    return hipSuccess;
+}
+}
+// g_dtype r p, then m n per block
+int main(int argc, char** argv) {
+    const int g = atoi(argv[1]), r = atoi(argv[2]), p = atoi(argv[3]), count = (argc - 4) / 2;
+    std::vector<tsr_matrix_desc> d(count);
+    float* a = (float*)0x10000;
+    for (int i = 0; i < count; ++i) {
+        d[i] = tsr_matrix_desc{};
+        d[i].m = atoi(argv[4 + 2 * i]); d[i].n = atoi(argv[5 + 2 * i]); d[i].r = r;
+        d[i].G = a; d[i].g_dtype = g; d[i].ldg = (d[i].n + 7) / 8 * 8; d[i].ldw = d[i].n;
+        d[i].W = d[i].U = d[i].V = d[i].M = d[i].Vm = d[i].C = d[i].D = a;
+    }
+    const size_t bytes = tsr_plan_workspace_bytes(d.data(), count, 1, g, 1, p);
+    ws = (char*)aligned_alloc(256, bytes);                     // (nothing but tables is written to it)
+    ws_end = ws + bytes;
+    tsr_plan* plan = nullptr;
+    if (tsr_plan_create(d.data(), count, 1, g, 1, p, ws, bytes, nullptr, &plan) != TSR_OK) return 1;
+    std::vector<const float*> omegas(count, a);
+    if (tsr_refresh_batched(plan, omegas.data(), 1, nullptr) != TSR_OK) return 2;
+    tsr_plan_destroy(plan);
+    return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    if shutil.which("g++") is None or not os.path.isdir(os.path.join(ROCM, "include", "hip")):
+        pytest.skip("needs g++ and the HIP headers")
+    import paper_2602_08007_amd as tsr  # noqa: F401  (builds the library if it is not there)
+    where = tmp_path_factory.mktemp("host")
+    src, exe = where / "program.cpp", where / "program"
+    src.write_text(PROGRAM)
+    build = subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROCM, "include"),
+                            "-I", os.path.join(PKG, "csrc"), "-I", os.path.join(ROOT, "include"), str(src), "-o", str(exe),
+                            "-rdynamic", os.path.join(PKG, "libtsr.so"), "-Wl,-rpath," + PKG,
+                            "-L" + os.path.join(ROCM, "lib"), "-lamdhip64", "-Wl,-rpath," + os.path.join(ROCM, "lib")],
+                           capture_output=True, text=True)
+    assert build.returncode == 0, build.stderr
+
+    def run(*args):
+        out = subprocess.run([str(exe), *map(str, args)], capture_output=True, text=True)
+        assert out.returncode == 0, (out.returncode, out.stderr)
+        return [ln.split() for ln in out.stdout.splitlines()]
+    return run
+
+
+@pytest.mark.parametrize("g", [0, 1])
+@pytest.mark.parametrize("r,dims", [(16, [(32000, 2048)] * 2), (128, [(32000, 2048)] * 2), (24, [(32000, 1024)]),
+                                    (16, [(2048, 2048)] * 4 + [(2048, 5461)] * 2 + [(5461, 2048)])])
+def test_gram_matrices_are_cut_into_row_pieces(program, g, r, dims):
+    """The fp64 Gram matrices of a few tall blocks: about 200 workgroups a launch and more, no workgroup with more than
+    2048 rows (some 60 us), the partial matrices inside the workspace.  Blocks with bf16 gradients as well, whose other
+    Gram matrices are computed elsewhere."""
+    rows = [tuple(map(int, ln[1:])) for ln in program(g, r, 8, *[x for d in dims for x in d]) if ln[0] == "gram64"]
+    assert len(rows) % len(dims) == 0 and len(rows) >= 2 * len(dims)
+    for at in range(0, len(rows), len(dims)):
+        launch = rows[at:at + len(dims)]
+        workgroups = 0
+        for n, k, splits, chunk, inside in launch:
+            assert inside and k == r + 8 and splits * chunk >= n
+            assert -(-n // splits) <= 2048, (n, k, splits)
+            tiles = -(-k // 64)
+            workgroups += splits * tiles * (tiles + 1) // 2
+        if max(n for n, *_ in launch) >= 32000:
+            assert workgroups >= 190, launch
