@@ -66,7 +66,7 @@ typedef enum tsr_dtype { TSR_F32 = 0, TSR_BF16 = 1 } tsr_dtype;
  *                   for the "fp32 path" (cores / weights within 1e-4 of an fp64 result).
  *   TSR_PREC_BF16   operands that stream from the big matrices (G, V in G V; T, V in
  *                   T V^T) are rounded once to bf16: for bf16 gradients (within 1e-2).
- * The refresh always uses split arithmetic (three pieces where orthogonality depends on it). */
+ * The refresh always uses split arithmetic (fp64 where orthogonality depends on it). */
 typedef enum tsr_precision { TSR_PREC_SPLIT = 0, TSR_PREC_BF16 = 1 } tsr_precision;
 
 /* One matrix block of a model, for the batched calls.  All pointers are device pointers. */
@@ -166,11 +166,10 @@ int tsr_backproject_apply(float* W, int m, int n, long long ldw,
  * Omega is n x (r+p), N(0,1), supplied by the caller (the paper shares it by RNG seed).
  * Requires r + p <= min(m, n).  Writes U (m x r), V (n x r) and, if sigma != NULL, the
  * r + p singular values of B in descending order.
- * orth is a Cholesky-based thin QR with fp64 factorization of the Gram matrix, repeated
- * twice for the final Q and for the factor of B^T and applied once to the sketches inside
- * the power iteration (same span, same Q factor of what follows; they only need to stay
- * well conditioned); a Gram matrix that is singular to working precision (a gradient of rank below
- * r + p, e.g. all zeros) gives zero columns in place of the undetermined directions.
+ * orth is a Cholesky-based thin QR with fp64 factorization of the Gram matrix: two passes with products in fp64 for the
+ * final Q and for the factor of B^T, one shifted pass for the sketches inside the power iteration (same span, same Q
+ * factor of what follows; they only need to stay well conditioned).  Directions that the sketch does not determine (a
+ * gradient of rank below r + p, e.g. all zeros) come out as zero columns, or as columns of the sketch's rounding.
  * Workspace: tsr_refresh_workspace_bytes(m, n, r, p). */
 size_t tsr_refresh_workspace_bytes(int m, int n, int r, int p);
 int tsr_refresh_rsvd(const void* G, int g_dtype, int m, int n, long long ldg,

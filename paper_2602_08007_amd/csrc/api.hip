@@ -358,19 +358,22 @@ struct RefreshBlock {
 //     steep spectrum squares into a Gram matrix whose small eigenvalues lie below its fp32-grade
 //     rounding), at the price of a basis that is only roughly orthonormal, which is all these
 //     intermediate bases are for.
-//   final (the returned Q and the factor of B^T; the result in X): a pass with the Gram matrix in fp64 (X -> Xalt),
-//     which sees directions down to the rounding of the fp32 sketch (a pivot <= 1e-14 of its diagonal entry, 1e-7 of
-//     a column, is dropped: directions beyond the numerical rank, e.g. of an exactly low-rank or zero gradient,
-//     become zero columns), then a plain pass with the Gram matrix at three bf16 pieces (Xalt -> X), which finishes
-//     what the rounding of the first product left.  Three passes with fp32-grade Gram matrices, two of them
-//     shifted, did the same: a refresh step of 512 x 1376 at r = 64 604 -> 547 us, of the 60M model 4465 -> 4137,
-//     of the 130M model 6249 -> 5742 us, of the 1B model 92.2 -> 88.4 ms; and the weights after a refresh step of the
-//     embedding and LM head were 1.4e-5 to 4.9e-5 from those in 64 bits (four seeds), now 7e-6.
+//   final (the returned Q and the factor of B^T; the result in X): two passes with Gram matrix and product in fp64.
+//     What the product adds to a direction is then one fp32 rounding of the result, whatever the size of R^-1, so a
+//     direction is as good as the fp32 sketch has it: rows of a gradient that are 1e-4 of the others keep a relative
+//     error of 1e-5 after a power iteration (4e-3 with products in two bf16 pieces, and 4e-5 with three passes of
+//     those, two of them shifted; medians of six seeds, 2000 x 512 in bf16).  The first pass (X -> Xalt) is shifted, or its
+//     factor would be the fp64 rounding of X^T X where directions lie below 1e-7 of the largest; these come out of it
+//     up to 1e5 times larger.  The last (Xalt -> X) drops a direction with a pivot <= 1e-8 of its diagonal entry: none
+//     beyond is amplified by more than 1e4, hence columns orthonormal to 1e4 x 2^-24 and better.  What is dropped (a zero
+//     column: all of a zero gradient, say) is dependent in the sketch as it is rounded; of a gradient of lower rank
+//     than r + p the rounding of the sketch may remain in its place, as a column orthogonal to the others.
 constexpr double ORTH_SHIFT = 1e-4;       // relative to the largest diagonal entry of the Gram matrix
 constexpr double ORTH_DROP = 1e-6;
-constexpr double ORTH_DROP64 = 1e-14;
+constexpr double ORTH64_SHIFT = 1e-10;
+constexpr double ORTH64_DROP = 1e-8;
 
-// A first pass of the blocks with RefreshBlock::nt on the bf16 NT family.  The sketch X
+// An intermediate pass of the blocks with RefreshBlock::nt on the bf16 NT family.  The sketch X
 // enters as two bf16 pieces in both orientations (transposed for the Gram matrix, as stored for the
 // product with R^-1), R^-1 as two pieces of its transpose; every product keeps the three leading
 // cross terms: X^T X = Xh^T Xh + Xl^T Xh + Xh^T Xl (summed by the k-split reduction, lower tiles
@@ -378,20 +381,23 @@ constexpr double ORTH_DROP64 = 1e-14;
 // [Rh | Rh] and [Rl | Rl] of the transposed factor, i.e. (Xh + Xl)(Rh + Rl).
 struct OrthNtPass {
     std::vector<SplitBlock> sx, sr;           // X -> pieces of X^T, and [Xh | Xl]; R^-1 -> the two halves of the pieces of R^-T
-    std::vector<SplitBlock> sx_rows;          // X -> [Xh | Xl] only: the final pass, whose Gram matrix is made from X itself
-    const SplitBlock* d_sx = nullptr; const SplitBlock* d_sr = nullptr; const SplitBlock* d_sx_rows = nullptr;
+    const SplitBlock* d_sx = nullptr; const SplitBlock* d_sr = nullptr;
     NtStageH gram, ap;
     int max_rows = 0, max_k = 0;
     bool empty() const { return sx.empty(); }
 };
 
+struct OrthPass64 {                           // a pass of the final orthonormalisation
+    std::vector<Gram64Block> gram; const Gram64Block* d_gram = nullptr;
+    std::vector<CholBlock> chol; const CholBlock* d_chol = nullptr;
+    std::vector<Apply64Block> apply; const Apply64Block* d_apply = nullptr;
+};
 struct OrthProgram {
-    OrthNtPass ntA;
-    GemmStage gramA, qA, gramB, qB;           // first pass, X -> Xalt; last pass, Xalt -> X
-    std::vector<Gram64Block> gram64;          // Gram matrices of the final first pass
-    std::vector<CholBlock> cholA, chol64, cholB;
-    const Gram64Block* d_gram64 = nullptr; int max_splits64 = 1;
-    const CholBlock* d_cholA = nullptr; const CholBlock* d_chol64 = nullptr; const CholBlock* d_cholB = nullptr;
+    OrthNtPass ntA;                           // the intermediate pass, X -> Xalt
+    GemmStage gramA, qA;
+    std::vector<CholBlock> cholA; const CholBlock* d_cholA = nullptr;
+    OrthPass64 first, last;                   // X -> Xalt, Xalt -> X
+    int max_splits64 = 1, max_rows = 0;
 };
 
 // The products with a bf16 gradient (Y = G Omega, Z = G^T Q, Y = G Qrow: Algorithm 1's sketch,
@@ -456,7 +462,6 @@ void build_orth_nt(OrthNtPass& pass, const std::vector<RefreshBlock>& blocks, bo
         const long long ldrows = on_rows_m ? b.ldm : b.ldn, st_t = (long long)k * ldrows;
         const long long ld2 = 2 * b.ldk, st_r = (long long)k * ld2;      // rows of two pieces side by side
         pass.sx.push_back(SplitBlock{X, Xt, st_t, (int)ldrows, rows, k, (int)ld2, nullptr, b.Xp, b.ldk});
-        pass.sx_rows.push_back(SplitBlock{X, nullptr, 0, 0, rows, k, (int)ld2, nullptr, b.Xp, b.ldk});
         pass.sr.push_back(SplitBlock{b.Rinv, b.Rt, st_r, (int)ld2, k, k, 0, b.Rt + b.ldk});
         const int bi = (int)i;
         g.push_back(NtLogical{Xt, Xt, b.S, ldrows, ldrows, k, k, k, rows, bi, bi});
@@ -479,51 +484,56 @@ void build_orth_nt(OrthNtPass& pass, const std::vector<RefreshBlock>& blocks, bo
 void build_gram64(OrthProgram& op, const std::vector<RefreshBlock>& blocks, bool on_rows_m, size_t bytes, Arena& ar) {
     long long base = 0;
     for (const RefreshBlock& b : blocks) base += (long long)ceil_div(b.k, 64) * (ceil_div(b.k, 64) + 1) / 2;
-    op.gram64.clear();
+    std::vector<Gram64Block>& gram = op.first.gram;
     op.max_splits64 = 1;
     for (long long want = std::max(1LL, 512 / base); ; want = want * 3 / 4) {
         size_t need = 0;
-        op.gram64.clear();
+        gram.clear();
         for (const RefreshBlock& b : blocks) {
             Gram64Block g{on_rows_m ? b.Y : b.Z, b.S64, nullptr, on_rows_m ? b.m : b.n, b.k, 1, 0};
             const int pieces = (int)std::min<long long>(std::max(1LL, want), std::max(1, g.rows / 64));
             g.chunk = ceil_div(ceil_div(g.rows, pieces), 16) * 16;
             g.splits = ceil_div(g.rows, g.chunk);
             if (g.splits > 1) need += align_up((size_t)b.k * b.k * g.splits * sizeof(double));
-            op.gram64.push_back(g);
+            gram.push_back(g);
         }
         if (need <= bytes || want <= 1) break;
     }
-    for (Gram64Block& g : op.gram64) {
+    for (Gram64Block& g : gram) {
         if (g.splits > 1) g.part = ar.take<double>((size_t)g.k * g.k * g.splits);
         op.max_splits64 = std::max(op.max_splits64, g.splits);
     }
+    op.last.gram = gram;                                   // (the same partial matrices: one pass follows the other)
+    for (size_t i = 0; i < blocks.size(); ++i) op.last.gram[i].X = on_rows_m ? blocks[i].Yalt : blocks[i].Zalt;
 }
 
 void build_orth(OrthProgram& op, const std::vector<RefreshBlock>& blocks, bool on_rows_m, Arena& ar) {
-    std::vector<LogicalGemm> gA, qA, gB, qB;
-    op.cholA.clear(); op.chol64.clear(); op.cholB.clear();
-    const char* e = getenv("TSR_TUNE_ORTH_NT");            // 0: the first passes of every block on the general kernel
+    std::vector<LogicalGemm> gA, qA, gAll;
+    op = OrthProgram{};
+    const char* e = getenv("TSR_TUNE_ORTH_NT");            // 0: the intermediate passes of every block on the general kernel
     const bool orth_nt = !(e && e[0] == '0');
     for (const RefreshBlock& b : blocks) {
         const int rows = on_rows_m ? b.m : b.n;
         float* X = on_rows_m ? b.Y : b.Z;
         float* Xalt = on_rows_m ? b.Yalt : b.Zalt;
         const int k = b.k;
+        gAll.push_back(LogicalGemm{X, X, k, k, k, k, rows, b.S, k});
         if (!(b.nt && orth_nt)) {
-            gA.push_back(LogicalGemm{X, X, k, k, k, k, rows, b.S, k});
+            gA.push_back(gAll.back());
             qA.push_back(LogicalGemm{X, b.Rinv, k, k, rows, k, k, Xalt, k});
         }
-        gB.push_back(LogicalGemm{Xalt, Xalt, k, k, k, k, rows, b.S, k});
-        qB.push_back(LogicalGemm{Xalt, b.Rinv, k, k, rows, k, k, X, k});
-        // the triangular factors are needed of B^T only (X = Q R2 R1, in Gacc, free until the small SVD, and R1)
         op.cholA.push_back(CholBlock{b.S, b.Rinv, nullptr, b.work, k, nullptr});
-        op.chol64.push_back(CholBlock{nullptr, b.Rinv, on_rows_m ? nullptr : b.R1, b.work, k, b.S64});
-        op.cholB.push_back(CholBlock{b.S, b.Rinv, on_rows_m ? nullptr : b.Gacc, b.work, k, nullptr});
+        // the triangular factors are needed of B^T only (X = Q R2 R1, in Gacc, free until the small SVD, and R1)
+        op.first.chol.push_back(CholBlock{nullptr, b.Rinv, on_rows_m ? nullptr : b.R1, b.work, k, b.S64});
+        op.last.chol.push_back(CholBlock{nullptr, b.Rinv, on_rows_m ? nullptr : b.Gacc, b.work, k, b.S64});
+        op.first.apply.push_back(Apply64Block{X, b.Rinv, Xalt, rows, k});
+        op.last.apply.push_back(Apply64Block{Xalt, b.Rinv, X, rows, k});
+        op.max_rows = std::max(op.max_rows, rows);
     }
-    op.ntA = OrthNtPass{};
+    Arena partials = ar;
+    partials.off = align_up(partials.off);
     if (orth_nt) build_orth_nt(op.ntA, blocks, on_rows_m, ar);
-    // The first pass meets the sketch at its raw scaling, where a rounding of X moves the span of
+    // An intermediate pass meets the sketch at its raw scaling, where a rounding of X moves the span of
     // the result: with an fp32 gradient X keeps three bf16 pieces there, as in the products with G.
     int pieces_x = 2;
     for (const RefreshBlock& b : blocks) if (b.g_dtype == TSR_F32) pieces_x = 3;
@@ -531,15 +541,16 @@ void build_orth(OrthProgram& op, const std::vector<RefreshBlock>& blocks, bool o
     build_stage(op.gramA, variant(1, 1, 0, 2, 2), gA, ar, 512, true);
     build_stage(op.qA, variant(0, 1, 0, pieces_x, pieces_x), qA, ar, 1);
     op.qA.b_upper = true;                                  // (one tile's k is never split at want_tiles = 1)
-    Arena shared = ar;
-    shared.off = align_up(shared.off);
-    build_stage(op.gramB, variant(1, 1, 0, 3, 3), gB, ar, 512, true);
-    // The partial fp64 Gram matrices of the first pass lie where the second pass puts its own partials, later.
-    // (Those are there for every block; gramA has none of the blocks on the NT family, whose Gram matrices were
-    // computed by one workgroup a tile over all rows: refresh of two 32000 x 2048 in bf16 at r + p = 24 3.00 -> 1.53 ms.)
-    build_gram64(op, blocks, on_rows_m, ar.off > shared.off ? ar.off - shared.off : 0, shared);
-    build_stage(op.qB, variant(0, 1, 0, 3, 3), qB, ar, 1);
-    op.qB.b_upper = true;
+    // The fp64 Gram matrices have their partials where the intermediate pass has its own, and beyond these as much as
+    // the general kernel would take for fp32 ones of all blocks.  (gramA alone has none of the blocks on the NT
+    // family: within its share those were computed by one workgroup a tile over all rows, refresh of two
+    // 32000 x 2048 in bf16 at r + p = 24 3.00 ms, now 1.52.)
+    GemmStage measured;
+    Arena room(nullptr, ar.tight, ar.tables);
+    build_stage(measured, variant(1, 1, 0, 3, 3), gAll, room, 512, true);
+    const size_t limit = std::max(ar.off, partials.off) + room.off;
+    build_gram64(op, blocks, on_rows_m, limit - partials.off, partials);
+    ar.off = std::max(ar.off, partials.off);
 }
 
 // One orthonormalisation of every block; see ORTH_SHIFT above for the two kinds.
@@ -552,6 +563,21 @@ int run_orth(const OrthProgram& op, bool grouped, Ctx& cx, bool final) {
         TSR_HIP(launch_chol_inv(grouped ? dev : nullptr, grouped ? nullptr : &host[0], nb, max_k, tol, shift, cx.s));
         return TSR_OK;
     };
+    if (final) {
+        for (const OrthPass64* pass : {&op.first, &op.last}) {
+            {
+                Timed timed(cx, TSR_PROF_ORTH_GEMM);
+                TSR_HIP(launch_gram64(grouped ? pass->d_gram : nullptr, grouped ? nullptr : &pass->gram[0], nb, max_k, op.max_splits64, cx.s));
+            }
+            const bool first = pass == &op.first;
+            TSR_TRY(chol(pass->d_chol, pass->chol, first ? 0.0 : ORTH64_DROP, first ? ORTH64_SHIFT : 0.0));
+            Timed timed(cx, TSR_PROF_ORTH_GEMM);
+            TSR_HIP(launch_apply64(grouped ? pass->d_apply : nullptr, grouped ? nullptr : &pass->apply[0], nb, op.max_rows, max_k, cx.s));
+        }
+        return TSR_OK;
+    }
+    // Gram matrices and their Cholesky factors of all blocks, then the products with R^-1 (NT family for the blocks it
+    // takes, general kernel for the rest)
     const OrthNtPass& nt = op.ntA;
     auto split = [&](const SplitBlock* table, int rows) -> int {
         if (nt.empty()) return TSR_OK;
@@ -559,28 +585,13 @@ int run_orth(const OrthProgram& op, bool grouped, Ctx& cx, bool final) {
         TSR_HIP(launch_split(table, (int)nt.sx.size(), rows, nt.max_k, cx.s));
         return TSR_OK;
     };
-    // the first pass: Gram matrices and their Cholesky factors of all blocks, then the products with R^-1 (NT family
-    // for the blocks it takes, general kernel for the rest)
-    if (final) {
-        {
-            Timed timed(cx, TSR_PROF_ORTH_GEMM);
-            TSR_HIP(launch_gram64(grouped ? op.d_gram64 : nullptr, grouped ? nullptr : &op.gram64[0], nb, max_k, op.max_splits64, cx.s));
-        }
-        TSR_TRY(split(nt.d_sx_rows, nt.max_rows));
-        TSR_TRY(chol(op.d_chol64, op.chol64, ORTH_DROP64, 0.0));
-    } else {
-        TSR_TRY(split(nt.d_sx, nt.max_rows));
-        if (!nt.empty()) TSR_TRY(run_nt_stage(nt.gram, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM));
-        TSR_TRY(run_stage(op.gramA, grouped, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM));
-        TSR_TRY(chol(op.d_cholA, op.cholA, ORTH_DROP, ORTH_SHIFT));
-    }
+    TSR_TRY(split(nt.d_sx, nt.max_rows));
+    if (!nt.empty()) TSR_TRY(run_nt_stage(nt.gram, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM));
+    TSR_TRY(run_stage(op.gramA, grouped, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM));
+    TSR_TRY(chol(op.d_cholA, op.cholA, ORTH_DROP, ORTH_SHIFT));
     TSR_TRY(split(nt.d_sr, nt.max_k));
     if (!nt.empty()) TSR_TRY(run_nt_stage(nt.ap, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM));
-    TSR_TRY(run_stage(op.qA, grouped, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM));
-    if (!final) return TSR_OK;
-    TSR_TRY(run_stage(op.gramB, grouped, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM));
-    TSR_TRY(chol(op.d_cholB, op.cholB, ORTH_DROP, 0.0));
-    return run_stage(op.qB, grouped, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM);
+    return run_stage(op.qA, grouped, 1.0f, 0.0f, cx, TSR_PROF_ORTH_GEMM);
 }
 
 void build_refresh_stages(RefreshProgram& rp, const float* const* omegas, Arena& ar);
@@ -768,13 +779,14 @@ void upload_refresh(RefreshProgram& rp, Arena& ar, Uploader& up) {
     }
     for (OrthProgram* op : {&rp.orthY, &rp.orthZ}) {
         if (OrthNtPass& p = op->ntA; !p.empty()) {
-            p.d_sx = up.put(p.sx, ar); p.d_sr = up.put(p.sr, ar); p.d_sx_rows = up.put(p.sx_rows, ar);
+            p.d_sx = up.put(p.sx, ar); p.d_sr = up.put(p.sr, ar);
             upload_nt_stage(p.gram, ar, up); upload_nt_stage(p.ap, ar, up);
         }
         upload_stage(op->gramA, ar, up); upload_stage(op->qA, ar, up);
-        upload_stage(op->gramB, ar, up); upload_stage(op->qB, ar, up);
-        op->d_gram64 = up.put(op->gram64, ar);
-        op->d_cholA = up.put(op->cholA, ar); op->d_chol64 = up.put(op->chol64, ar); op->d_cholB = up.put(op->cholB, ar);
+        op->d_cholA = up.put(op->cholA, ar);
+        for (OrthPass64* pass : {&op->first, &op->last}) {
+            pass->d_gram = up.put(pass->gram, ar); pass->d_chol = up.put(pass->chol, ar); pass->d_apply = up.put(pass->apply, ar);
+        }
     }
     rp.d_jac = up.put(rp.jac, ar);
     if (!rp.nt.empty()) {

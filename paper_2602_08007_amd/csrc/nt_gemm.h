@@ -120,7 +120,7 @@ hipError_t launch_transpose_bf16(const TransposeBlock* table_dev, int blocks, in
 
 // An fp32 matrix X (rows x k, contiguous) as two bf16 pieces, x = x0 + x1 with x0 = bf16(x) and x1 = bf16(x - x0),
 // in up to three places:
-//   dst       the transpose, optional: piece p has k rows of pitch ld_dst, at dst + p * piece_stride elements; columns
+//   dst       the transpose: piece p has k rows of pitch ld_dst, at dst + p * piece_stride elements; columns
 //             `rows` .. up to the next multiple of 8 are written as zeros, nothing beyond (pieces may sit side by
 //             side in one row);
 //   dst_again the same once more, optional;

@@ -1291,7 +1291,6 @@ __global__ __launch_bounds__(256) void split_kernel(const SplitBlock* table) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) *(bf4*)&tile[p][c + i][r] = bf4{h[0][i], h[1][i], h[2][i], h[3][i]};
     }
-    if (!b.dst) return;
     __syncthreads();
     const int rr = (threadIdx.x & 7) * 8;                                 // eight rows of X per thread and column
     if (r0 + rr >= rows8) return;

@@ -72,6 +72,15 @@ struct Gram64Block {
 hipError_t launch_gram64(const Gram64Block* table_dev, const Gram64Block* single, int blocks, int max_k, int max_splits,
                          hipStream_t stream);
 
+// ---- out = X Rinv, products and sums in fp64, for a tall X (rows x k) and an upper triangular Rinv (k x k); all fp32
+// and contiguous.  max_rows, max_k: of the blocks.
+struct Apply64Block {
+    const float* X; const float* Rinv; float* out;
+    int rows, k;
+};
+hipError_t launch_apply64(const Apply64Block* table_dev, const Apply64Block* single, int blocks, int max_rows, int max_k,
+                          hipStream_t stream);
+
 // ---- SVD of the k x k upper-triangular factor R (fp64): an orthogonal Gacc with
 // Gacc R = diag(sigma) X^T (rows mutually orthogonal), from the symmetric eigenproblem of R R^T.
 // Outputs, for the r largest sigma in descending order: XrT (r x k fp32) rows x_j^T, GrT

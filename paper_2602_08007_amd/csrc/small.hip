@@ -232,10 +232,10 @@ __global__ __launch_bounds__(256) void gram64_kernel(const Gram64Block* table, c
             for (int f = 0; f < 2; ++f) { a[s][q][f] = row[ci[f]]; c[s][q][f] = row[cj[f]]; }
         }
     };
-    auto multiply = [&](int s, int r0) {
+    auto multiply = [&](int s, int r0, bool whole) {           // (selects in the loop cost a tenth of the time)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const bool in = r0 + 4 * q + lk < end;
+            const bool in = whole || r0 + 4 * q + lk < end;
             double x[2], y[2];
 #pragma unroll
             for (int f = 0; f < 2; ++f) { x[f] = in ? (double)a[s][q][f] : 0.0; y[f] = in ? (double)c[s][q][f] : 0.0; }
@@ -247,11 +247,17 @@ __global__ __launch_bounds__(256) void gram64_kernel(const Gram64Block* table, c
     };
     if (begin < end) {
         fetch(0, begin);
-        for (int r = begin; r < end; r += 32) {
+        int r = begin;
+        for (; r + 32 <= end; r += 32) {
             fetch(1, r + 16);
-            multiply(0, r);
+            multiply(0, r, true);
             fetch(0, r + 32);
-            multiply(1, r + 16);
+            multiply(1, r + 16, true);
+        }
+        if (r < end) {
+            fetch(1, r + 16);
+            multiply(0, r, false);
+            multiply(1, r + 16, false);
         }
     }
     double* out = b.splits > 1 ? b.part + (size_t)split * b.k * b.k : b.S;
@@ -294,6 +300,101 @@ hipError_t launch_gram64(const Gram64Block* table_dev, const Gram64Block* single
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || max_splits <= 1) return e;
     hipLaunchKernelGGL(gram64_sum_kernel, dim3((max_k * max_k + 255) / 256, blocks), dim3(256), 0, stream, table_dev, sb);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------------ product with the inverse factor in fp64
+// One 64 x 64 tile of X Rinv per workgroup, 32 x 32 per wave, over the rows of Rinv that are not zero there.  Four
+// columns of X per lane and load (a row's sixteen side by side), Rinv as it lies; k step q of a load is column 4 l + q
+// for the lanes of group l, of either operand.  Bound by the matrix cores' fp64 rate like the Gram matrices.
+// 168 matrices of together 467 000 rows, k = 528: 2.7 ms, 54 TFLOP/s (the Gram matrices of the same 3.3 ms); asking
+// for fewer than four workgroups per compute unit lets the accumulators move through both register files in every
+// step, 2.9 ms.  The refresh steps of the 60M, 130M and 1B models take 4.03, 5.53 and 85.5 ms with the two fp64
+// passes; 3.90, 5.40 and 80.3 ms with the products in two and three bf16 pieces, which lose weak directions (see
+// ORTH_SHIFT in api.hip), and 4.57, 6.42 and 88.4 ms with three passes of those.
+__global__ __launch_bounds__(256, 4) void apply64_kernel(const Apply64Block* table, const Apply64Block single, const int col_tiles) {
+    typedef double d4_t __attribute__((ext_vector_type(4)));
+    typedef float f4_t __attribute__((ext_vector_type(4)));
+    typedef f4_t f4u_t __attribute__((aligned(4)));
+    typedef const float __attribute__((address_space(1))) gfloat;
+    typedef const f4u_t __attribute__((address_space(1))) gf4u;
+    Apply64Block b = single;
+    if (table) b = table[blockIdx.y];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4, k = b.k;
+    const int i0 = (int)(blockIdx.x / col_tiles) * 64 + (wave >> 1) * 32;
+    const int j0 = (col_tiles - 1 - (int)(blockIdx.x % col_tiles)) * 64 + (wave & 1) * 32;      // (most work first)
+    if (i0 >= b.rows || j0 >= k) return;
+    const int end = min(k, j0 + 32), steps = min(end, k / 16 * 16) / 16;
+    gfloat* X = (gfloat*)b.X;
+    gfloat* R = (gfloat*)b.Rinv;
+    size_t row[2];
+    unsigned col[2];
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+        row[f] = (size_t)min(i0 + 16 * f + li, b.rows - 1) * k;
+        col[f] = min(j0 + 16 * f + li, k - 1);
+    }
+    d4_t acc[2][2] = {};
+    f4_t a[2][2];
+    float c[2][4][2];
+    auto fetch = [&](int s, int t) {
+        const int kk = 16 * min(t, steps - 1) + 4 * lk;
+#pragma unroll
+        for (int f = 0; f < 2; ++f) a[s][f] = *(gf4u*)(X + row[f] + kk);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int g = 0; g < 2; ++g) c[s][q][g] = R[(size_t)(kk + q) * k + col[g]];
+    };
+    auto multiply = [&](int s) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int f = 0; f < 2; ++f)
+#pragma unroll
+                for (int g = 0; g < 2; ++g)
+                    acc[f][g] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[s][f][q], (double)c[s][q][g], acc[f][g], 0, 0, 0);
+    };
+    if (steps > 0) {
+        fetch(0, 0);
+        for (int t = 0; t + 1 < steps; t += 2) {
+            fetch(1, t + 1);
+            multiply(0);
+            fetch(0, t + 2);
+            multiply(1);
+        }
+        if (steps & 1) multiply(0);
+    }
+    if (16 * steps < end) {                                    // the last columns of X, fewer than sixteen
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int kk = 16 * steps + 4 * lk + q, at = min(kk, k - 1);
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                a[0][f][q] = kk < k ? X[row[f] + at] : 0.0f;
+                c[0][q][f] = kk < k ? R[(size_t)at * k + col[f]] : 0.0f;
+            }
+        }
+        multiply(0);
+    }
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = i0 + 16 * f + 4 * v + lk, j = j0 + 16 * g + li;
+                if (i < b.rows && j < k) b.out[(size_t)i * k + j] = (float)acc[f][g][v];
+            }
+}
+
+hipError_t launch_apply64(const Apply64Block* table_dev, const Apply64Block* single, int blocks, int max_rows, int max_k,
+                          hipStream_t stream) {
+    if (blocks <= 0 || max_rows <= 0 || max_k <= 0) return hipSuccess;
+    Apply64Block sb{};
+    if (single) sb = *single;
+    const int ct = (max_k + 63) / 64;
+    hipLaunchKernelGGL(apply64_kernel, dim3((max_rows + 63) / 64 * ct, blocks), dim3(256), 0, stream, table_dev, sb, ct);
     return hipGetLastError();
 }
 

@@ -114,6 +114,53 @@ def test_refresh_tall_full_sketch(tsr, rows, k):
             assert float(torch.linalg.norm(X.T @ X - eye)) < 2.0 ** -20 * k
 
 
+def _refresh(tsr, how, G, r, p, q, key):
+    """Bases by the single call, or by a plan (a bf16 gradient then takes the other family of kernels)."""
+    m, n = G.shape
+    om = dev(si.omega(n, r + p, key))
+    U, V = torch.full((m, r), float("nan"), device="cuda"), torch.full((n, r), float("nan"), device="cuda")
+    if how == "call":
+        tsr.tsr_refresh_rsvd(dev(G), om, r, p, q, U, V)
+    else:
+        z = lambda *s: torch.zeros(*s, device="cuda")  # noqa: E731
+        plan = tsr.Plan([dict(G=dev(G), W=z(m, n), U=U, V=V, M=z(r, r), Vm=z(r, r), C=z(r, r), D=z(r, r))], with_refresh=True, p=p,
+                        precision=tsr.TSR_PREC_BF16 if G.dtype == torch.bfloat16 else tsr.TSR_PREC_SPLIT)
+        plan.tsr_refresh_batched([om], q)
+        torch.cuda.synchronize()
+        plan.close()
+    return U.cpu().double(), V.cpu().double()
+
+
+# what the fp64 passes of the final orthonormalisation are for: with one power iteration the sketch is singular to fp32
+# (the shifted normalisations in it leave small x (100 small)^2 of the small rows' directions)
+@pytest.mark.parametrize("how,g", [("plan", torch.bfloat16), ("call", torch.bfloat16), ("plan", torch.float32)])
+@pytest.mark.parametrize("small,q", [(1e-4, 0), (1e-4, 1), (3e-4, 1)])
+def test_refresh_rows_of_two_scales(tsr, how, g, small, q):
+    """Sixty rows that are not zero, two thirds of them `small` times the others (an embedding's gradient with rare
+    tokens): the sketch holds their span, and the small ones come back to what one fp32 rounding of the large ones is
+    to them, 2^-24 / small; the columns are orthonormal to what the last pass allows, 1e4 x 2^-24.  Medians of five
+    matrices: how far a sketch is from dependent columns differs from one to the other."""
+    m, n, r, p, lead = 2000, 512, 64, 8, 60
+    eye = torch.eye(lead, dtype=torch.float64)
+    found = []
+    for seed in range(5):
+        key = si.stream_key(706, seed)
+        at = torch.randperm(m, generator=torch.Generator().manual_seed(seed))[:lead]
+        G = torch.zeros(m, n)
+        G[at] = si.normal((lead, n), si.stream_key(key, 1))
+        G[at[20:]] *= small
+        G = G.to(g)
+        U, V = _refresh(tsr, how, G, r, p, q, si.stream_key(key, 2))
+        U, V, G64, weak = U[:, :lead], V[:, :lead], G.double(), at[20:]
+        rel = lambda E, rows: float(torch.linalg.norm(E[rows]) / torch.linalg.norm(G64[rows]))  # noqa: E731
+        found.append((rel(G64 - U @ (U.T @ G64), weak), rel(G64 - (G64 @ V) @ V.T, weak),
+                      *(float(torch.linalg.norm(X.T @ X - eye, ord=2)) for X in (U, V))))
+        assert rel(G64 - U @ (U.T @ G64 @ V) @ V.T, slice(None)) < 2e-5
+    median = [sorted(column)[2] for column in zip(*found)]
+    assert max(median[:2]) < 2.0 ** -24 / small, median
+    assert max(median[2:]) < 1e4 * 2.0 ** -24, median
+
+
 # the factorization takes four columns at a time, sixteen per tile: dropped columns from every place of a panel on,
 # from the first of a tile on, and tiles of nothing else
 @pytest.mark.parametrize("rank", [1, 2, 3, 4, 5, 15, 16, 17, 21, 32, 35])
