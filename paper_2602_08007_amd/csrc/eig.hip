@@ -1304,20 +1304,26 @@ __global__ __launch_bounds__(256) void eig_finish_kernel(const JacobiBlock* tabl
     cgdouble* sig = (cgdouble*)jb.scratch + eig_tridiag_at(k);
     const double sj = sig[j];
     int rank = 0;                                            // descending, ties by index
+    double top = 0.0;
     for (int i = lane; i < k; i += 64) {
         const double si = sig[i];
         rank += (si > sj || (si == sj && i < j)) ? 1 : 0;
+        top = fmax(top, si);
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) rank += __shfl_xor(rank, o, 64);
+    for (int o = 32; o > 0; o >>= 1) {
+        rank += __shfl_xor(rank, o, 64);
+        top = fmax(top, __shfl_xor(top, o, 64));
+    }
     if (lane == 0 && jb.sigma) jb.sigma[rank] = (float)sj;
     if (rank >= r) return;
-    const double inv = (sj > 0.0) ? 1.0 / sj : 0.0;
+    const bool null = sj <= SVD_NULL * top;                  // (not a NaN, which is passed on)
+    const double inv = null ? 0.0 : 1.0 / sj;
     gfloat* xr = (gfloat*)jb.XrT + (size_t)rank * k;
     gfloat* gr = (gfloat*)jb.GrT + (size_t)rank * k;
     for (int c = lane; c < k; c += 64) {
         xr[c] = (float)(ER[c] * inv);
-        gr[c] = (float)E[c];
+        gr[c] = null ? 0.0f : (float)E[c];
     }
 }
 

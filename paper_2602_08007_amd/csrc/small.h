@@ -85,7 +85,11 @@ hipError_t launch_apply64(const Apply64Block* table_dev, const Apply64Block* sin
 // Gacc R = diag(sigma) X^T (rows mutually orthogonal), from the symmetric eigenproblem of R R^T.
 // Outputs, for the r largest sigma in descending order: XrT (r x k fp32) rows x_j^T, GrT
 // (r x k fp32) rows of Gacc, and sigma (k fp32, optional, all k values descending).
+// A singular value <= SVD_NULL sigma_1 is rounding, and so is what its x_j holds: 2^-53 sigma_1 / sigma_j of the leading
+// ones.  Both its rows are zero (as columns of length one the x_j would count the leading directions again in the
+// projection: U U^T G V V^T of an exact rank 5 at r = 40 came out eight times G).
 // Work: Gacc k x k doubles, tmp 2 k x k + 64 doubles, scratch eig_scratch_doubles(k) (launch_eig_svd only).
+constexpr double SVD_NULL = 1e-11;
 struct JacobiBlock {
     double* R; double* Gacc; double* tmp;
     float* XrT; float* GrT; float* sigma;

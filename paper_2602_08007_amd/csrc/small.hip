@@ -1377,10 +1377,15 @@ __global__ __launch_bounds__(SMALL_THREADS) void jacobi_kernel(const JacobiBlock
         const int rank = s_rank[j];
         if (rank >= r) continue;
         const double sj = s_d[j];
-        const double inv = (sj > 0.0) ? 1.0 / sj : 0.0;
+        double top = 0.0;
+        for (int i = lane; i < k; i += 64) top = fmax(top, s_d[i]);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) top = fmax(top, __shfl_xor(top, o, 64));
+        const bool null = sj <= SVD_NULL * top;              // (not a NaN, which is passed on)
+        const double inv = null ? 0.0 : 1.0 / sj;
         for (int c = lane; c < k; c += 64) {
             blk->XrT[(size_t)rank * k + c] = (float)(T[(size_t)j * k + c] * inv);
-            blk->GrT[(size_t)rank * k + c] = (float)W[(size_t)j * k + c];
+            blk->GrT[(size_t)rank * k + c] = null ? 0.0f : (float)W[(size_t)j * k + c];
         }
     }
 }

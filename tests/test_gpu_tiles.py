@@ -186,6 +186,26 @@ def test_refresh_dropped_columns(tsr, rank):
     assert float(torch.linalg.norm(back - G.double()) / torch.linalg.norm(G.double())) < tol
 
 
+@pytest.mark.parametrize("how,g", [("plan", torch.bfloat16), ("call", torch.bfloat16), ("call", torch.float32)])
+@pytest.mark.parametrize("rank,r,q", [(1, 40, 1), (5, 40, 1), (16, 40, 0), (35, 40, 1), (100, 560, 1)])
+def test_refresh_beyond_the_rank(tsr, how, g, rank, r, q):
+    """Rows that are not zero, fewer than r of them: the leading columns are orthonormal, and all r columns, with
+    which a step projects, leave the gradient as it is (a column beyond the rank is zero, or orthogonal to the others).
+    The last rank of 560 takes the one-kernel small SVD.  Products and storage in fp32 over `rank` rows, four in a row."""
+    m, n, p = (120, 152, 8) if r == 40 else (700, 608, 8)
+    key = si.stream_key(707, rank)
+    G = torch.zeros(m, n)
+    G[torch.randperm(m, generator=torch.Generator().manual_seed(rank))[:rank]] = si.normal((rank, n), si.stream_key(key, 1))
+    U, V = _refresh(tsr, how, G.to(g), r, p, q, si.stream_key(key, 2))
+    G64 = G.to(g).double()
+    assert bool(torch.isfinite(U).all() and torch.isfinite(V).all())
+    eye = torch.eye(rank, dtype=torch.float64)
+    for X in (U[:, :rank], V[:, :rank]):
+        assert float(torch.linalg.norm(X.T @ X - eye)) < 4 * rank * 2.0 ** -22
+    back = U @ (U.T @ G64 @ V) @ V.T
+    assert float(torch.linalg.norm(back - G64) / torch.linalg.norm(G64)) < 4 * (rank + 4) * 2.0 ** -22
+
+
 # panels of 128 rows: 343 and 344 (three groups of workers), 1025 (one), 8 (every worker by itself)
 @pytest.mark.parametrize("m,n,r,workers,summed", [(43801, 136, 128, 8, True), (44000, 131, 128, 7, True),
                                                   (131077, 257, 256, 4, True), (1000, 136, 128, 8, False)])
