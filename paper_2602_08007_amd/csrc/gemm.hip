@@ -491,7 +491,7 @@ hipError_t launch_gemm(const GemmLaunch& L, const GemmVariant& v, hipStream_t st
 // A single call on a small matrix is bound by its launches, on the host (3-4 us each) as on the device (3-6 us each,
 // of which the trips to memory are the most).  So the two products of the projection are one launch here (and the
 // sum of its partial cores a second), and the two products of the lift one: seven launches of a step become four,
-// 38.1 -> 28.0 us for 512 x 1376 fp32 at r = 64, 38.5 -> 28.6 us for 1001 x 1365 bf16 at r = 96.  What is left is the
+// 38.1 -> 28.4 us for 512 x 1376 fp32 at r = 64, 38.5 -> 29.8 us for 1001 x 1365 bf16 at r = 96.  What is left is the
 // host's (four launches and the caller's program around them; the kernels take 18 and 29 us).
 // Both keep the arithmetic of the general kernel: the intermediate in fp32, cut into pieces for the second product.
 // Used for r <= 128, where the intermediate of 64 rows fits the registers and LDS of a workgroup, and matrices whose
@@ -589,14 +589,18 @@ template <int NS> __device__ inline void put4(float (&x)[4], unsigned short* d, 
     }
 }
 
-// One partial core per workgroup: U_s^T (G_sc V_c) for 64 rows s and a range c of columns.
+// One partial core per workgroup: U_s^T (G_sc V_c) for 64 rows s and a range c of columns.  What G_sc V_c loses on its
+// way into the second product stays where the ranges cancel each other (the general kernel cuts the finished sum into
+// pieces), so it goes there in three pieces, as good as fp32, whatever the precision.  In as many as the other operands
+// it cost up to 1 us less (1001 x 1365 bf16 r = 96 16.9 / 17.9), and an error of 0.6 where two halves of the columns cancel
+// to 2^-8 (bf16 operands; now as with the general kernel).
 template <bool G_BF16, int NSA, int NSB, int RP>
-__global__ __launch_bounds__(NTHREADS, 2) void project_one_kernel(const ProjectOne q) {
+__global__ __launch_bounds__(NTHREADS, RP * NSB > 128 ? 1 : 2) void project_one_kernel(const ProjectOne q) {     // (LDS)
     constexpr int TM = 64, FN = RP / 64;
     typedef Operand<false, G_BF16, TM, false> OpG;
     typedef Operand<true, false, RP, false> OpV;
-    constexpr int FIRST = 2 * (NSA * OpG::TILE + NSB * OpV::TILE), SECOND = 4 * NSB * OpV::TILE;
-    __shared__ __attribute__((aligned(16))) unsigned short lds[FIRST > SECOND ? FIRST : SECOND];
+    constexpr int NSP = 3, FIRST = 2 * (NSA * OpG::TILE + NSB * OpV::TILE), HALF = (NSB + NSP) * OpV::TILE;
+    __shared__ __attribute__((aligned(16))) unsigned short lds[FIRST > 2 * HALF ? FIRST : 2 * HALF];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
     const int slab = blockIdx.x / q.chunks, chunk = blockIdx.x % q.chunks;
     const int row0 = slab * TM, rows = min(q.m - row0, TM);
@@ -626,7 +630,6 @@ __global__ __launch_bounds__(NTHREADS, 2) void project_one_kernel(const ProjectO
     }
     __syncthreads();
     // U_s and P, both with the slab's rows as the contraction: [32 rows][operand][piece][column][row]
-    constexpr int HALF = 2 * NSB * OpV::TILE;
     u.template store<NSB>(su[0], lds, 0, vectors && rows < BK, edge_r && vectors);
     if (rows > BK) u.template store<NSB>(su[1], lds + HALF, 1, vectors && rows < 2 * BK, edge_r && vectors);
 #pragma unroll
@@ -634,14 +637,14 @@ __global__ __launch_bounds__(NTHREADS, 2) void project_one_kernel(const ProjectO
 #pragma unroll
         for (int e = 0; e < 16; e += 4) {
             float x[4] = {P[0][j][e], P[0][j][e + 1], P[0][j][e + 2], P[0][j][e + 3]};
-            put4<NSB>(x, lds + wm * HALF + NSB * OpV::TILE + lds_at<false>((wn * FN + j) * 32, lane & 31, (e >> 2) * 8 + (lane >> 5) * 4),
+            put4<NSP>(x, lds + wm * HALF + NSB * OpV::TILE + lds_at<false>((wn * FN + j) * 32, lane & 31, (e >> 2) * 8 + (lane >> 5) * 4),
                       OpV::TILE);
         }
     __syncthreads();
     f32x16 C[FN][FN];
     clear(C);
     for (int h = 0; h * BK < rows; ++h)
-        multiply_tiles<NSB, NSB, FN, FN, OpV, OpV>(C, lds + h * HALF, lds + h * HALF + NSB * OpV::TILE, wm * FN * 32, wn * FN * 32,
+        multiply_tiles<NSB, NSP, FN, FN, OpV, OpV>(C, lds + h * HALF, lds + h * HALF + NSB * OpV::TILE, wm * FN * 32, wn * FN * 32,
                                                    lds_pitch<false>(), OpV::TILE, lane);
     TSR_GLOBAL float* out = (TSR_GLOBAL float*)q.part + (long long)blockIdx.x * q.r * q.r;
 #pragma unroll

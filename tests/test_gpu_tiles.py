@@ -48,6 +48,24 @@ def test_project_sizes(tsr, m, n, r, dtype, prec):
     check_close(C, orc.project_core(G, U, V), TOL[prec] * max(1.0, (min(m, n) / r) ** 0.5), "core")
 
 
+@pytest.mark.parametrize("m,n,r", [(64, 700, 17), (200, 1000, 64), (1000, 650, 100), (700, 900, 200)])
+@pytest.mark.parametrize("dtype,prec", [(torch.bfloat16, "bf16"), (torch.bfloat16, "split"), (torch.float32, "bf16"), (torch.float32, "split")])
+def test_project_columns_that_cancel(tsr, m, n, r, dtype, prec):
+    """Two halves of the columns whose products cancel to 2^-8 of either (the one is the other with the opposite sign,
+    100 columns and more away, so that no range of a k split holds both alike): the precision counts against the sum."""
+    key, half = si.stream_key(708, m, n, r), n // 2 - 13
+    A = si.normal((m, half), si.stream_key(key, 1)).bfloat16().float()
+    G = torch.cat([A, -A, torch.zeros(m, n - 2 * half)], 1)
+    V1 = si.normal((half, r), si.stream_key(key, 2)) / half ** 0.5
+    V = torch.cat([V1, V1, si.normal((n - 2 * half, r), si.stream_key(key, 3)) / (n - 2 * half) ** 0.5], 0)
+    G[:, 2 * half:] = (2.0 ** -8 * si.normal((m, n - 2 * half), si.stream_key(key, 4))).bfloat16().float()
+    U = si.orthonormal(m, r, si.stream_key(key, 5)).float()
+    C = torch.full((r, r), float("nan"), device="cuda")
+    tsr.tsr_project_core(dev(G.to(dtype)), dev(U), dev(V), C, precision=getattr(tsr, "TSR_PREC_" + prec.upper()))
+    # and fp32 sums of n products with errors of random sign, 2^8 times the result
+    check_close(C, orc.project_core(G, U, V), TOL[prec] + 4 * n ** 0.5 * 2.0 ** -16, "core")
+
+
 # (the last two: beyond the kernel for one small matrix, with the intermediate on the side of the columns)
 @pytest.mark.parametrize("m,n,r", SIZES + [(4 * 259, 259, 150), (33000, 133, 40)])
 @pytest.mark.parametrize("prec", ["split", "bf16"])
