@@ -259,13 +259,21 @@ int build_project_one(ProjectProgram& pg, const std::vector<BlockView>& block, i
 
 // A matrix whose launches would have 64 x 64 tiles anyway (fewer than 256 units of work, see pick_shape) takes the
 // kernels made for one of r <= 128, two launches for the projection and one for the lift.  Measured on the device, us,
-// the four and two launches of the general kernels first: 512 x 1376 r = 64 projection 17.0 / 9.3, lift 9.2 / 6.1;
-// 200 x 333 r = 17 14.6 / 7.3 and 8.6 / 5.8; 4029 x 492 r = 56 21.2 / 13.5 and 11.7 / 9.2; with r between 96 and 128 the
-// kernels take about the same time, 768 x 2048 r = 96 20.0 / 18.0 and 11.4 / 11.0, 1024 x 2048 r = 128 21.8 / 20.9 and
-// 13.0 / 12.4, and the host's three launches less remain (some 11 us of a step).
+// the four and two launches of the general kernels first (the host's three launches less are some 11 us of a step):
+//   r <= 64: 512 x 1376 r = 64 projection 17.1 / 9.9, lift 9.4 / 6.4; 200 x 333 r = 17 15.1 / 7.9 and 9.0 / 6.0; 8000 x 512
+//     r = 64, 252 units, 28.2 / 22.6 and 15.2 / 13.3.  The lift of 3000 x 1024, 192 units, is the one that loses, 12.4 / 12.9.
+//   above that, with two 64-wide blocks of columns, up to 128 units: lift of 2000 x 1000 r = 128 13.9 / 13.5, at 192 units
+//     (3000 x 1024) 15.4 / 19.3; but the general lift's first product has the most to do where the matrix is wide
+//     (512 x 8000, 252 units, 19.9 / 17.8).  Projection of 1000 x 2000 r = 96 22.3 / 19.9, of 512 x 2048 17.3 / 18.6, of
+//     3000 x 1024 24.2 / 30.3.
+//   above r = 96 the partial cores count, r x r each: the projection of tall matrices only (4000 x 512 r = 128 25.6 / 24.6,
+//     512 x 4000 21.3 / 24.5), and of the smallest (512 x 512 15.3 / 15.1, 1024 x 1024, 64 units, 18.7 / 20.4).
 bool one_small_matrix(int m, int n, int r, bool project) {
     const long long units = (long long)ceil_div(m, 128) * (project ? std::max(1, n / 128) : ceil_div(n, 128));
-    return r <= ONE_MAX_R && units < 256;
+    if (r > ONE_MAX_R || units >= 256) return false;
+    if (r <= 64) return true;
+    if (project) return units <= 128 && (r <= 96 || m >= 2LL * n || units <= 32);
+    return units <= 128 || n >= 8LL * m;
 }
 
 // Projection of one matrix: about 128 workgroups (64 and 256 are slower from 512 x 1376 on), as many partial cores as

@@ -15,6 +15,7 @@ PROGRAM = r"""
 #include <cstdlib>
 #include <cstring>
 #include <vector>
+#include "gemm.h"
 #include "small.h"
 #include "tsr.h"
 static char *ws, *ws_end;
@@ -42,9 +43,18 @@ hipError_t launch_gram64(const Gram64Block* table, const Gram64Block* single, in
     }
     return hipSuccess;
 }
+hipError_t launch_project_one(const ProjectOne&, int, int, int, hipStream_t) { printf("project_one\n"); return hipSuccess; }
+hipError_t launch_lift_one(const LiftOne&, int, int, hipStream_t) { printf("lift_one\n"); return hipSuccess; }
 }
-// g_dtype r p, then m n per block
+static int call(int m, int n, int r) {                         // the projection and the lift of one matrix
+    float* a = (float*)0x10000;
+    const size_t bytes = tsr_project_workspace_bytes(m, n, r), lift = tsr_backproject_workspace_bytes(m, n, r);
+    if (tsr_project_core(a, 0, m, n, n, a, a, r, 1.0f, 0, a, 0, (void*)0x100000, bytes, nullptr) != TSR_OK) return 3;
+    return tsr_backproject_apply(a, m, n, n, a, a, a, r, 1.0f, 0.0f, 1.0f, 0, (void*)0x100000, lift, nullptr) == TSR_OK ? 0 : 4;
+}
+// "call" m n r; or the refresh of a plan: g_dtype r p, then m n per block
 int main(int argc, char** argv) {
+    if (!strcmp(argv[1], "call")) return call(atoi(argv[2]), atoi(argv[3]), atoi(argv[4]));
     const int g = atoi(argv[1]), r = atoi(argv[2]), p = atoi(argv[3]), count = (argc - 4) / 2;
     std::vector<tsr_matrix_desc> d(count);
     float* a = (float*)0x10000;
@@ -108,3 +118,15 @@ def test_gram_matrices_are_cut_into_row_pieces(program, g, r, dims):
             workgroups += splits * tiles * (tiles + 1) // 2
         if max(n for n, *_ in launch) >= 32000:
             assert workgroups >= 190, launch
+
+
+# (the sizes of the comment at the rule: with more than 128 units the general kernels are up to a quarter faster
+# there, as they are for the projection of square and wide matrices above r = 96)
+@pytest.mark.parametrize("m,n,r,project,lift", [
+    (512, 1376, 64, True, True), (8000, 512, 64, True, True), (2000, 1000, 128, True, True), (1000, 2000, 96, True, True),
+    (512, 512, 128, True, True), (4000, 512, 128, True, True), (512, 8000, 72, False, True), (3000, 1024, 72, False, False),
+    (3000, 1000, 128, False, False), (1024, 1024, 128, False, True), (512, 4000, 128, False, True), (4096, 4096, 64, False, False),
+    (300, 300, 129, False, False)])
+def test_kernels_of_one_small_matrix(program, m, n, r, project, lift):
+    taken = [ln[0] for ln in program("call", m, n, r)]
+    assert taken == ["project_one"] * project + ["lift_one"] * lift
