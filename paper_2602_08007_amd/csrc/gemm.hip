@@ -857,8 +857,11 @@ hipError_t launch_splitk_reduce(const ReduceProblem* probs_dev, const ReduceProb
     ReduceProblem s{};
     if (single) s = *single;
     // Threads that share the partials where there are many of them and too few outputs to fill the chip: cores of the
-    // 32000 x 2048 embedding and LM head (256 partials) 15 -> 8 us, the refresh of 512 x 1376 at r = 64 4.1 -> 3.5 us each.
-    if (max_splits >= 8 && (long long)bx * count < 256) {
+    // 32000 x 2048 embedding and LM head (256 partials) 15 -> 8 us, the refresh of 512 x 1376 at r = 64 4.1 -> 3.5 us each,
+    // 512 x 200 outputs of 16 partials 4.1 -> 3.9.  Eight or ten partials are one trip to memory for a thread that has them
+    // all, and their lines come in longer pieces: 1024 x 128 outputs 2.8 so and 4.4 shared, 2000 x 128 4.4 and 5.2.
+    const long long fill = (long long)bx * count;
+    if ((max_splits >= 16 && fill < 256) || (max_splits >= 8 && fill <= 64)) {
         hipLaunchKernelGGL(splitk_reduce_wide_kernel, dim3((max_elems + 63) / 64, count), dim3(256), 0, stream, probs_dev, s, alpha, beta);
         return hipGetLastError();
     }

@@ -11,6 +11,7 @@ PKG = os.path.join(ROOT, "paper_2602_08007_amd")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 PROGRAM = r"""
+#include <dlfcn.h>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -22,7 +23,16 @@ static char *ws, *ws_end;
 extern "C" {
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return hipSuccess; }
+hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* n, hipStream_t* s) {
+    *g = *b = dim3(1); *n = 0; *s = nullptr;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* kernel, dim3, dim3, void**, size_t, hipStream_t) {
+    Dl_info at{};
+    printf("launch %s\n", dladdr(kernel, &at) && at.dli_sname ? at.dli_sname : "?");
+    return hipSuccess;
+}
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
@@ -88,7 +98,7 @@ def program(tmp_path_factory):
     build = subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROCM, "include"),
                             "-I", os.path.join(PKG, "csrc"), "-I", os.path.join(ROOT, "include"), str(src), "-o", str(exe),
                             "-rdynamic", os.path.join(PKG, "libtsr.so"), "-Wl,-rpath," + PKG,
-                            "-L" + os.path.join(ROCM, "lib"), "-lamdhip64", "-Wl,-rpath," + os.path.join(ROCM, "lib")],
+                            "-L" + os.path.join(ROCM, "lib"), "-lamdhip64", "-ldl", "-Wl,-rpath," + os.path.join(ROCM, "lib")],
                            capture_output=True, text=True)
     assert build.returncode == 0, build.stderr
 
@@ -128,5 +138,13 @@ def test_gram_matrices_are_cut_into_row_pieces(program, g, r, dims):
     (3000, 1000, 128, False, False), (1024, 1024, 128, False, True), (512, 4000, 128, False, True), (4096, 4096, 64, False, False),
     (300, 300, 129, False, False)])
 def test_kernels_of_one_small_matrix(program, m, n, r, project, lift):
-    taken = [ln[0] for ln in program("call", m, n, r)]
+    taken = [ln[0] for ln in program("call", m, n, r) if ln[0] != "launch"]
     assert taken == ["project_one"] * project + ["lift_one"] * lift
+
+
+# G V of m x n: m x r outputs and their partials (k split 8, 10, 16, 25 and 62 ways), C = U^T P behind it
+@pytest.mark.parametrize("m,n,r,shared", [(1024, 1024, 130, False), (1500, 1500, 130, False), (512, 2048, 200, True),
+                                          (300, 6000, 150, True)])
+def test_reductions_that_share_the_partials(program, m, n, r, shared):
+    reductions = [ln[1] for ln in program("call", m, n, r) if ln[0] == "launch" and "splitk_reduce" in ln[1]]
+    assert len(reductions) == 2 and ("wide" in reductions[0]) == shared, reductions
