@@ -47,7 +47,6 @@ struct GemmStage {
     std::vector<ReduceProblem> reduces;
     int max_reduce_elems = 0, max_splits = 1;
     bool direct = true;
-    bool b_upper = false;                          // B is upper triangular
     int tiles_m = 0, tiles_n = 0, ksplit = 1;      // single-problem decode
     const GemmProblem* d_probs = nullptr;
     const GemmTile* d_tiles = nullptr;
@@ -167,7 +166,6 @@ int run_stage(const GemmStage& st, bool grouped, float alpha, float beta, Ctx& c
     hipStream_t stream = cx.s;
     GemmLaunch L{};
     L.n_tiles = (int)st.tiles.size();
-    L.b_upper = st.b_upper && st.direct;
     if (grouped) {
         L.probs = st.d_probs; L.tiles = st.d_tiles;
     } else {
@@ -548,7 +546,7 @@ void build_orth(OrthProgram& op, const std::vector<RefreshBlock>& blocks, bool o
     // the Cholesky kernels read the lower triangle of the Gram matrix only
     build_stage(op.gramA, variant(1, 1, 0, 2, 2), gA, ar, 512, true);
     build_stage(op.qA, variant(0, 1, 0, pieces_x, pieces_x), qA, ar, 1);
-    op.qA.b_upper = true;                                  // (one tile's k is never split at want_tiles = 1)
+    for (GemmProblem& p : op.qA.probs) p.kchunk = -p.kchunk;    // upper triangular (no split at want_tiles = 1)
     // The fp64 Gram matrices have their partials where the intermediate pass has its own, and beyond these as much as
     // the general kernel would take for fp32 ones of all blocks.  (gramA alone has none of the blocks on the NT
     // family: within its share those were computed by one workgroup a tile over all rows, refresh of two

@@ -18,7 +18,8 @@ struct GemmProblem {
     long long lda, ldb, ldc;
     long long c_split_stride;  // elements between the partial outputs of consecutive k-splits
     int M, N, K;
-    int kchunk;         // K range handled by one tile (multiple of 32); K if no split
+    int kchunk;         // K range handled by one tile (multiple of 32); K if no split; negative (no split): B is upper
+                        // triangular, element (j, k) zero for k > j
 };
 
 struct GemmTile {       // one workgroup's work
@@ -32,7 +33,6 @@ struct GemmLaunch {
     int tiles_m, tiles_n, ksplit;  // decode of blockIdx when tiles == nullptr
     int n_tiles;               // grid size
     float alpha, beta;         // epilogue scalars of the whole launch; beta == 0: C is not read
-    int b_upper;               // B is upper triangular (element (j, k) zero for k > j): only launches without split
 };
 
 // Operand layout / precision of one instantiation.
