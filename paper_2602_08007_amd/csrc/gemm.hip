@@ -857,12 +857,12 @@ hipError_t launch_splitk_reduce(const ReduceProblem* probs_dev, const ReduceProb
     if (bx > 1024) bx = 1024;
     ReduceProblem s{};
     if (single) s = *single;
-    // Threads that share the partials where there are many of them and too few outputs to fill the chip: cores of the
-    // 32000 x 2048 embedding and LM head (256 partials) 15 -> 8 us, the refresh of 512 x 1376 at r = 64 4.1 -> 3.5 us each,
-    // 512 x 200 outputs of 16 partials 4.1 -> 3.9.  Eight or ten partials are one trip to memory for a thread that has them
-    // all, and their lines come in longer pieces: 1024 x 128 outputs 2.8 so and 4.4 shared, 2000 x 128 4.4 and 5.2.
-    const long long fill = (long long)bx * count;
-    if ((max_splits >= 16 && fill < 256) || (max_splits >= 8 && fill <= 64)) {
+    // Threads that share the partials where there are many of them and too few outputs to fill the chip.  Device time behind
+    // a kernel that writes the partials, us, one thread to all partials / shared: 5184 outputs of 8 partials 1.9 / 2.3, of 16
+    // 2.3 / 2.3, of 28 3.8 / 2.7, of 128 8.3 / 3.4; 65536 of 16 3.5 / 4.0, of 28 5.8 / 5.4, of 128 8.5 / 7.9; 131072 of 16
+    // 5.5 / 6.1, of 128 10.8 / 12.4 (the lines come in longer pieces where one thread has all partials).  Cores of the
+    // 32000 x 2048 embedding and LM head, 256 partials, 15 -> 8.
+    if (max_splits > 16 && (long long)bx * count <= 64) {
         hipLaunchKernelGGL(splitk_reduce_wide_kernel, dim3((max_elems + 63) / 64, count), dim3(256), 0, stream, probs_dev, s, alpha, beta);
         return hipGetLastError();
     }
