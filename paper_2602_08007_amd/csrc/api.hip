@@ -312,17 +312,33 @@ int project_one_matrix(const std::vector<BlockView>& block, int prec, float alph
 
 struct LiftProgram {
     GemmStage ud;           // T = U D
-    GemmStage vd;           // T = V D^T, blocks with much longer columns than rows
+    GemmStage vd;           // T = V D^T, blocks with much longer columns than rows (see build_lift)
     GemmStage tvt;          // W = beta W + alpha T V^T, or U T^T
 };
 
-// The intermediate lies on the shorter side where the longer one has at least four times its rows (32000 x 2048 embedding
-// and LM head, r = 128: 20 -> 7 us); a launch of its own costs more than is saved below that.
-void build_lift(LiftProgram& lp, const std::vector<BlockView>& blocks, int prec, Arena& ar) {
+// The intermediate lies on the shorter side where the longer one has at least four times its rows.  Lift of one matrix,
+// us, on the side of the rows / of the columns: 4096 x 1024 r = 256 26.0 / 24.4, r = 128 18.2 / 17.5, 6000 x 512 r = 256
+// 23.3 / 19.1, 32000 x 2048 r = 128 144 / 132.  Beside other blocks it is a launch of its own, some 5 us, which the blocks
+// have to save: steps of plans whose last of seven matrices is h x 4 h transposed, 2 layers h = 256 r = 128 45.2 / 50.3,
+// 8 layers h = 512 r = 128 (1.6 million elements of the intermediate less) 197.9 / 198.3, r = 256 (3.1 million)
+// 303.8 / 301.2; of a 32000 x 512 embedding and LM head beside 28 smaller matrices at r = 128 (8.1 million) 326 / 315.
+// `idle`: memory that nothing reads any more when the lift begins.  Where the tall blocks of a plan stay with the others,
+// their intermediates lie there: the plan then fits any workspace that an earlier version asked for.
+void build_lift(LiftProgram& lp, const std::vector<BlockView>& blocks, int prec, Arena& ar, Arena* idle = nullptr) {
     std::vector<LogicalGemm> ud, vd, tvt;
+    auto tall = [](const BlockView& b) { return b.m >= 4 * (long long)b.n; };
+    long long less = 0;
+    bool all = true;
     for (const BlockView& b : blocks) {
-        float* T = ar.take<float>((size_t)b.m * b.r);
-        if (b.m >= 4 * (long long)b.n) {
+        if (tall(b)) less += (long long)(b.m - b.n) * b.r;
+        else all = false;
+    }
+    const bool columns = all || less >= 3000000;
+    for (const BlockView& b : blocks) {
+        const bool by_columns = columns && tall(b);
+        Arena& where = (idle && tall(b) && !by_columns) ? *idle : ar;
+        float* T = where.take<float>((size_t)(by_columns ? b.n : b.m) * b.r);
+        if (by_columns) {
             vd.push_back(LogicalGemm{b.V, b.D, b.r, b.r, b.n, b.r, b.r, T, b.r});
             tvt.push_back(LogicalGemm{b.U, T, b.r, b.r, b.m, b.n, b.r, b.W, b.ldw});
         } else {
@@ -1352,8 +1368,10 @@ static void build_plan(tsr_plan& pl, Arena& ar) {
     if (pl.use_fast) {
         build_fast_step(pl.fast, pl.blocks, pl.n_workers, ar);
     } else {
+        Arena projection = ar;
         build_project(pl.project, pl.blocks, pl.n_workers, pl.precision, ar);
-        build_lift(pl.lift, pl.blocks, pl.precision, ar);
+        build_lift(pl.lift, pl.blocks, pl.precision, ar, &projection);
+        ar.off = std::max(ar.off, projection.off);
     }
     pl.cores.clear();
     pl.max_core = 0;

@@ -132,6 +132,32 @@ def test_refresh_tall_full_sketch(tsr, rows, k):
             assert float(torch.linalg.norm(X.T @ X - eye)) < 2.0 ** -20 * k
 
 
+# blocks four times as high as wide beside others: the intermediate of the lift on the side of their rows, and (more than
+# three million elements less) on that of their columns, in a launch of its own
+@pytest.mark.parametrize("dims", [[(1100, 261, 64), (300, 501, 64), (77, 19, 7)], [(300, 501, 130), (24100, 301, 130), (130, 261, 130)]])
+@pytest.mark.parametrize("prec", ["split", "bf16"])
+def test_plan_with_tall_blocks(tsr, dims, prec):
+    blocks = []
+    for i, (m, n, r) in enumerate(dims):
+        key = si.stream_key(709, m, n)
+        U, V = _bases(m, n, r, key)
+        G = U @ torch.diag(torch.linspace(2.0, 1.0, r)) @ V.T + 0.01 * si.normal((m, n), si.stream_key(key, 3))
+        z = lambda *x: torch.zeros(*x, device="cuda")  # noqa: E731
+        blocks.append(dict(G=dev(G), W=z(m, n), U=dev(U), V=dev(V), M=z(r, r), Vm=z(r, r), C=z(r, r), D=z(r, r)))
+    plan = tsr.Plan(blocks, precision=getattr(tsr, "TSR_PREC_" + prec.upper()))
+    assert plan.tsr_plan_kernel_path() == 0                    # odd widths: the general kernels in either precision
+    for t in (1, 2):
+        for b in blocks:
+            b["W"].zero_(); b["M"].zero_(); b["Vm"].zero_()
+        plan.tsr_step_batched(1, lr=1.0, eps=1.0)
+    torch.cuda.synchronize()
+    for b in blocks:
+        G, U, V, C, D = (orc.f64(b[x]) for x in ("G", "U", "V", "C", "D"))
+        check_close(C, orc.project_core(G, U, V), TOL[prec] * max(1.0, (min(G.shape) / U.shape[1]) ** 0.5), "core")
+        check_close(orc.f64(b["W"]), -U @ D @ V.T, TOL[prec], "movement")
+    plan.close()
+
+
 def _refresh(tsr, how, G, r, p, q, key):
     """Bases by the single call, or by a plan (a bf16 gradient then takes the other family of kernels)."""
     m, n = G.shape

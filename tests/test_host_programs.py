@@ -62,9 +62,27 @@ static int call(int m, int n, int r) {                         // the projection
     if (tsr_project_core(a, 0, m, n, n, a, a, r, 1.0f, 0, a, 0, (void*)0x100000, bytes, nullptr) != TSR_OK) return 3;
     return tsr_backproject_apply(a, m, n, n, a, a, a, r, 1.0f, 0.0f, 1.0f, 0, (void*)0x100000, lift, nullptr) == TSR_OK ? 0 : 4;
 }
-// "call" m n r; or the refresh of a plan: g_dtype r p, then m n per block
+// a plan of fp32 blocks m n r, its workspace in bytes and the launches of a step
+static int step(int workers, int count, char** dims) {
+    std::vector<tsr_matrix_desc> d(count);
+    float* a = (float*)0x10000;
+    for (int i = 0; i < count; ++i) {
+        d[i] = tsr_matrix_desc{};
+        d[i].m = atoi(dims[3 * i]); d[i].n = atoi(dims[3 * i + 1]); d[i].r = atoi(dims[3 * i + 2]);
+        d[i].G = a; d[i].ldg = d[i].ldw = d[i].n; d[i].g_stride = (long long)d[i].m * d[i].n;
+        d[i].W = d[i].U = d[i].V = d[i].M = d[i].Vm = d[i].C = d[i].D = a;
+    }
+    const size_t bytes = tsr_plan_workspace_bytes(d.data(), count, workers, 0, 0, 0);
+    printf("bytes %zu\n", bytes);
+    tsr_plan* plan = nullptr;
+    if (tsr_plan_create(d.data(), count, workers, 0, 0, 0, aligned_alloc(256, bytes), bytes, nullptr, &plan) != TSR_OK) return 5;
+    const tsr_hyper h{1e-3f, 0.0f, 0.9f, 0.999f, 1e-8f, 1.0f};
+    return tsr_step_batched(plan, 1, &h, nullptr) == TSR_OK ? 0 : 6;
+}
+// "call" m n r; "step" workers, then m n r per block; or the refresh of a plan: g_dtype r p, then m n per block
 int main(int argc, char** argv) {
     if (!strcmp(argv[1], "call")) return call(atoi(argv[2]), atoi(argv[3]), atoi(argv[4]));
+    if (!strcmp(argv[1], "step")) return step(atoi(argv[2]), (argc - 3) / 3, argv + 3);
     const int g = atoi(argv[1]), r = atoi(argv[2]), p = atoi(argv[3]), count = (argc - 4) / 2;
     std::vector<tsr_matrix_desc> d(count);
     float* a = (float*)0x10000;
@@ -148,3 +166,19 @@ def test_kernels_of_one_small_matrix(program, m, n, r, project, lift):
 def test_reductions_that_share_the_partials(program, m, n, r, shared):
     reductions = [ln[1] for ln in program("call", m, n, r) if ln[0] == "launch" and "splitk_reduce" in ln[1]]
     assert ["wide" in x for x in reductions] == shared, reductions
+
+
+# plans of blocks at least four times as high as wide beside others: earlier sizes of their workspaces, which programs
+# may hold, and the products of their lift (one more where the tall blocks' intermediate lies on their columns' side)
+@pytest.mark.parametrize("dims,workers,earlier,products", [
+    ([(2172, 2975, 450), (1044, 854, 2), (610, 45, 24)], 2, 58298368, 2), ([(35, 214, 3), (1009, 90, 1)], 1, 18944, 2),
+    ([(209, 86, 1), (193, 30, 10)], 2, 32768, 2), ([(2048, 512, 64)] * 3, 1, 11032320, 2),
+    ([(32000, 512, 128)] * 2 + [(512, 512, 128)] * 4, 1, 80789760, 3)])
+def test_plans_with_tall_blocks(program, dims, workers, earlier, products):
+    out = program("step", workers, *[x for d in dims for x in d])
+    assert int(out[0][1]) <= earlier
+    # behind Adam: the lift
+    names = [ln[1] for ln in out if ln[0] == "launch"]
+    at = max(i for i, x in enumerate(names) if "adam" in x)
+    lift = [x for x in names[at + 1:] if "gemm" in x]
+    assert len(lift) == products, names
