@@ -283,7 +283,10 @@ int tsr_step_batched(tsr_plan* plan, int t, const tsr_hyper* h, void* stream);
  * 0 on `stream`, the others on the shared streams of the device's plans (default priority), which start after the
  * work already queued on `stream` and which `stream` waits for before the call returns its
  * place in the queue to the caller; for the caller the call is ordered on `stream` like every
- * other.  The call waits on the host for its small table uploads before it enqueues the kernels.
+ * other.  Refreshes of several plans of a device follow one another on the shared streams, whatever streams they were
+ * given: one also waits for the work queued before an earlier refresh on that one's stream, and a host thread waits while
+ * another one enqueues a refresh.  So nothing queued before a refresh may wait for the host to see a later refresh of
+ * another plan done.  The call waits on the host for its small table uploads before it enqueues the kernels.
  * While stage timing is on (tsr_plan_profile_begin) everything runs on `stream` alone. */
 int tsr_refresh_batched(tsr_plan* plan, const float* const* Omegas, int q, void* stream);
 

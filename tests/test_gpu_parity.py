@@ -908,6 +908,7 @@ def test_refresh_of_plans_that_share_streams(tsr):
             for b, (U, V) in zip(blocks_of[k], alone[k]):
                 assert torch.equal(b["U"], U) and torch.equal(b["V"], V)
                 b["U"].zero_(); b["V"].zero_()
+        torch.cuda.synchronize()              # before other streams write them
 
     for plan in plans:
         plan.tsr_refresh_batched(omegas, q)
@@ -923,10 +924,12 @@ def test_refresh_of_plans_that_share_streams(tsr):
     for t in threads:
         t.join()
     check(range(3))
-    plans[1].close()
     for k in (2, 0):
         plans[k].tsr_refresh_batched(omegas, q)
+    plans[1].close()                          # with the refreshes of the others on the shared streams
     check((0, 2))
+    plans[2].tsr_refresh_batched(omegas, q)
+    check((2,))
     for k in (0, 2):
         plans[k].close()
 
