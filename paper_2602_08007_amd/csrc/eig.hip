@@ -13,6 +13,7 @@
 // sweeps of the single-kernel variant (about k^2 dependent rotations per matrix).
 #include <hip/hip_runtime.h>
 
+#include "device_lds.h"
 #include "small.h"
 
 namespace tsr {
@@ -994,12 +995,8 @@ __global__ __launch_bounds__(64) void eig_invit_lds_kernel(const JacobiBlock* ta
 template <int V>
 hipError_t launch_invit_lds(const JacobiBlock* table_dev, const JacobiBlock& single, int blocks, int max_k, hipStream_t stream) {
     const int lds = 4 * max_k * V * (int)sizeof(double);
-    static thread_local bool configured = false;
-    if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void*)eig_invit_lds_kernel<V>, hipFuncAttributeMaxDynamicSharedMemorySize, EIG_INVIT_LDS);
-        if (e != hipSuccess) return e;
-        configured = true;
-    }
+    const hipError_t e = allow_lds((const void*)eig_invit_lds_kernel<V>, EIG_INVIT_LDS);
+    if (e != hipSuccess) return e;
     const EigGrid g{blocks, (max_k + V - 1) / V, 1};
     hipLaunchKernelGGL(eig_invit_lds_kernel<V>, eig_grid(g), dim3(64), lds, stream, table_dev, single, g, max_k);
     return hipGetLastError();
@@ -1258,12 +1255,8 @@ __global__ __launch_bounds__(256, 1) void eig_backtransform_kernel(const JacobiB
 template <int RT>
 hipError_t launch_backtransform(const JacobiBlock* table_dev, const JacobiBlock& single, int blocks, int max_k, hipStream_t stream) {
     constexpr int lds = 16 * ((16 * RT + 13) / 32 * 32 + 18) * 8;
-    static thread_local bool configured = false;
-    if (!configured && lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void*)eig_backtransform_kernel<RT>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
-    }
-    configured = true;
+    const hipError_t e = allow_lds((const void*)eig_backtransform_kernel<RT>, lds);
+    if (e != hipSuccess) return e;
     const EigGrid g{blocks, (max_k + 63) / 64, 0};
     hipLaunchKernelGGL(eig_backtransform_kernel<RT>, eig_grid(g), dim3(256), lds, stream, table_dev, single, g);
     return hipGetLastError();

@@ -17,6 +17,8 @@
 // cuts the traffic beyond W itself.
 #include "lift.h"
 
+#include "device_lds.h"
+
 namespace tsr {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -307,14 +309,8 @@ static hipError_t launch_lift_r(const LiftBlock* blocks_dev, const LiftTile* til
     fn_t fn = (mode == 0) ? (fn_t)lift_kernel<KSTEPS, 2, 1, 2>
               : (mode == 1) ? (fn_t)lift_kernel<KSTEPS, 1, 1, 1> : (fn_t)lift_kernel<KSTEPS, 1, 2, 1>;
     const int lds = (mode == 2 ? 2 : 1) * LIFT_TM * (KSTEPS * 16 + 8) * 2;
-    static thread_local const void* configured[16] = {nullptr};
-    bool done = false;
-    for (const void* c : configured) if (c == (const void*)fn) { done = true; break; }
-    if (!done) {
-        hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
-        for (const void*& c : configured) if (c == nullptr) { c = (const void*)fn; break; }
-    }
+    const hipError_t e = allow_lds((const void*)fn, lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(fn, dim3(n_wgs), dim3(LIFT_THREADS), lds, stream, blocks_dev, tiles_dev, ranges_dev, alpha, beta);
     return hipGetLastError();
 }

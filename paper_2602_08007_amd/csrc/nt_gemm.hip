@@ -9,6 +9,8 @@
 // operand preparation of the refresh products.
 #include "nt_gemm.h"
 
+#include "device_lds.h"
+
 namespace tsr {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -1133,12 +1135,8 @@ hipError_t launch_nt_gemm(const NtLaunch& L, const NtVariant& v, hipStream_t str
         if (!L.ranges || v.b_f32 || v.out_bf16 || v.fused_adam || v.b_pieces > 1) return hipErrorInvalidValue;
         const nt_fn fn = nt_rmw_ws_kernel<8, 4, 4, 4>;
         constexpr int threads = (4 + 4 + 4) * 64;
-        static thread_local bool configured_ws = false;
-        if (!configured_ws) {
-            hipError_t er = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, WS_LDS_BYTES);
-            if (er != hipSuccess) return er;
-            configured_ws = true;
-        }
+        const hipError_t er = allow_lds((const void*)fn, WS_LDS_BYTES);
+        if (er != hipSuccess) return er;
         hipLaunchKernelGGL(fn, dim3(L.n_tiles), dim3(threads), WS_LDS_BYTES, stream, L);
         return hipGetLastError();
     }
@@ -1147,15 +1145,8 @@ hipError_t launch_nt_gemm(const NtLaunch& L, const NtVariant& v, hipStream_t str
         if (e.shape == v.shape && e.b_f32 == v.b_f32 && e.out == out && e.pieces == (v.b_pieces > 1 ? v.b_pieces : 1)) {
             const nt_fn fn = L.ranges ? e.persistent : e.fn;
             if (fn == nullptr) return hipErrorInvalidValue;
-            static thread_local const void* configured[256] = {nullptr};
-            bool done = false;
-            for (const void* c : configured) if (c == (const void*)fn) { done = true; break; }
-            if (!done) {
-                hipError_t er = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                    e.lds_bytes);
-                if (er != hipSuccess) return er;
-                for (const void*& c : configured) if (c == nullptr) { c = (const void*)fn; break; }
-            }
+            const hipError_t er = allow_lds((const void*)fn, e.lds_bytes);
+            if (er != hipSuccess) return er;
             hipLaunchKernelGGL(fn, dim3(L.n_tiles), dim3(NT_THREADS), e.lds_bytes, stream, L);
             return hipGetLastError();
         }

@@ -2,6 +2,8 @@
 // subspace refresh (Cholesky + triangular inverse for the thin QR, one-sided Jacobi SVD).
 #include "small.h"
 
+#include "device_lds.h"
+
 namespace tsr {
 
 // ------------------------------------------------------------------ Adam on the core
@@ -982,12 +984,8 @@ template <int NT, int WAVES, int PART = 0>
 static hipError_t launch_chol_tiles(const CholBlock* table_dev, const CholBlock& single, int blocks, double tol, double shift_rel,
                                     hipStream_t stream) {
     constexpr int lds = (2 * NT + 4) * CT * CT_P * 8 + NT * CT * 8;
-    static thread_local bool configured = false;
-    if (!configured && lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void*)chol_tiles_kernel<NT, WAVES, PART>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
-    }
-    configured = true;
+    const hipError_t e = allow_lds((const void*)chol_tiles_kernel<NT, WAVES, PART>, lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((chol_tiles_kernel<NT, WAVES, PART>), dim3(blocks), dim3(64 * WAVES), lds, stream, table_dev, single, tol, shift_rel);
     return hipGetLastError();
 }

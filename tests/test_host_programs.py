@@ -20,6 +20,11 @@ PROGRAM = r"""
 #include "small.h"
 #include "tsr.h"
 static char *ws, *ws_end;
+static int device = 0;
+static const char* name_of(const void* symbol) {
+    Dl_info at{};
+    return dladdr(symbol, &at) && at.dli_sname ? at.dli_sname : "?";
+}
 extern "C" {
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
@@ -29,13 +34,15 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* n, hipStream_t* s
     return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* kernel, dim3, dim3, void**, size_t, hipStream_t) {
-    Dl_info at{};
-    printf("launch %s\n", dladdr(kernel, &at) && at.dli_sname ? at.dli_sname : "?");
+    printf("launch %s\n", name_of(kernel));
     return hipSuccess;
 }
 hipError_t hipGetLastError() { return hipSuccess; }
-hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
-hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void* kernel, hipFuncAttribute, int) {
+    printf("lds %p %d\n", kernel, device);
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) { *d = device; return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t)malloc(1); return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
@@ -79,9 +86,20 @@ static int step(int workers, int count, char** dims) {
     const tsr_hyper h{1e-3f, 0.0f, 0.9f, 0.999f, 1e-8f, 1.0f};
     return tsr_step_batched(plan, 1, &h, nullptr) == TSR_OK ? 0 : 6;
 }
-// "call" m n r; "step" workers, then m n r per block; or the refresh of a plan: g_dtype r p, then m n per block
+// refreshes of one matrix on two devices in turn
+static int devices(int m, int n, int r) {
+    float* a = (float*)0x10000;
+    const size_t bytes = tsr_refresh_workspace_bytes(m, n, r, 0);
+    for (int d : {0, 1, 0, 1}) {
+        device = d;
+        if (tsr_refresh_rsvd(a, 0, m, n, n, a, r, 0, 1, a, a, a, (void*)0x100000, bytes, nullptr) != TSR_OK) return 7;
+    }
+    return 0;
+}
+// "devices" m n r; "call" m n r; "step" workers, then m n r per block; or the refresh of a plan: g_dtype r p, then m n per block
 int main(int argc, char** argv) {
     if (!strcmp(argv[1], "call")) return call(atoi(argv[2]), atoi(argv[3]), atoi(argv[4]));
+    if (!strcmp(argv[1], "devices")) return devices(atoi(argv[2]), atoi(argv[3]), atoi(argv[4]));
     if (!strcmp(argv[1], "step")) return step(atoi(argv[2]), (argc - 3) / 3, argv + 3);
     const int g = atoi(argv[1]), r = atoi(argv[2]), p = atoi(argv[3]), count = (argc - 4) / 2;
     std::vector<tsr_matrix_desc> d(count);
@@ -182,3 +200,12 @@ def test_plans_with_tall_blocks(program, dims, workers, earlier, products):
     at = max(i for i, x in enumerate(names) if "adam" in x)
     lift = [x for x in names[at + 1:] if "gemm" in x]
     assert len(lift) == products, names
+
+
+@pytest.mark.parametrize("r,kernels", [(72, 1), (136, 1), (500, 3)])
+def test_large_lds_is_allowed_on_each_device(program, r, kernels):
+    """Kernels with more than 64 KB of dynamic LDS: the attribute is set once per kernel and device."""
+    lds = [tuple(ln[1:]) for ln in program("devices", 1000, 1000, r) if ln[0] == "lds"]
+    assert len(lds) == len(set(lds)), lds
+    assert {k for k, d in lds if d == "0"} == {k for k, d in lds if d == "1"}
+    assert len({k for k, _ in lds}) >= kernels
