@@ -453,10 +453,12 @@ struct RefreshProgram {
     GemmStage uout, vout;
 };
 
-// Tile of the wide kernel for products with r + p columns: 256 x 192 where that leaves fewer columns of padding and
-// there is more than one tile to a row (r + p = 528: refresh step of the 1B model 88.1 -> 86.6 ms; 392, no difference).
-// With a single tile the narrower one is faster (r + p = 136, 24 layers of the 130M model's shapes, 3.02 against 3.10 ms),
-// as it is where the columns are the same (r + p = 264: 5.72 against 5.97 ms).
+// Tile of the wide kernel for products with r + p columns: 256 x 192 where that leaves fewer columns of padding (513 to
+// 576 columns) and there is more than one tile to a row (refresh step of the 1B model at 528 88.1 -> 86.6 ms; the
+// products with G of 40 blocks 2048 x 2048 at 513, 528, 544 and 570 2.11 / 1.97, 2.15 / 2.02, 2.14 / 2.01, 2.21 / 2.08 ms).
+// Beyond, where fewer columns are padded again, it is the slower one (24 of 2048 x 2048 at 900 1.98 / 2.03, at 960
+// 1.99 / 2.04 ms), as with a single tile (136 columns, 24 layers of the 130M model's shapes, 3.02 against 3.10 ms) and
+// where the padding is the same (264: 5.72 against 5.97 ms).
 int nt_refresh_shape(const std::vector<RefreshBlock>& blocks) {
     long long at128 = 0, at192 = 0, tiles_m = 0, tiles_n = 0;
     int max_k = 0;
@@ -468,7 +470,7 @@ int nt_refresh_shape(const std::vector<RefreshBlock>& blocks) {
         max_k = std::max(max_k, b.k);
     }
     // (and only where the fewer tiles are still too many for a k split, whose partials would outgrow the workspace)
-    return (max_k > 192 && at192 < at128 && std::min(tiles_m, tiles_n) > 256) ? NT_256x192_K32 : NT_256x128_K32;
+    return (max_k > 192 && max_k <= 576 && at192 < at128 && std::min(tiles_m, tiles_n) > 256) ? NT_256x192_K32 : NT_256x128_K32;
 }
 
 void build_orth_nt(OrthNtPass& pass, const std::vector<RefreshBlock>& blocks, bool on_rows_m, Arena& ar) {

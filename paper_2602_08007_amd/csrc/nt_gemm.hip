@@ -349,6 +349,7 @@ __global__ __launch_bounds__(NT_THREADS, 1) void nt_wide_kernel(const NtLaunch L
     constexpr int CH = CHA + NP * CHB;                      // 16-byte chunks per thread and k-tile
     constexpr int NFRAG = FM + NP * FN;                     // fragment reads per k step
     constexpr int NMFMA = FM * FN * NP;                     // MFMAs per k step
+    // (fragment reads, LDS stores and loads go beside the groups, parts [g n / 4, (g + 1) n / 4) of them: any n will do)
     static_assert(NMFMA % 8 == 0, "the schedule issues the MFMAs of a k step in eight groups");
     constexpr int GRP = NMFMA / 8;
     extern __shared__ __attribute__((aligned(16))) unsigned short lds[];

@@ -10,7 +10,7 @@ import torch
 
 import synth_inputs as si
 from oracle import tsr_oracle as orc
-from gpu_util import check_close, dev, f32
+from gpu_util import check_close, dev, f32, padded
 
 pytestmark = pytest.mark.gpu
 
@@ -167,12 +167,65 @@ def _refresh(tsr, how, G, r, p, q, key):
         tsr.tsr_refresh_rsvd(dev(G), om, r, p, q, U, V)
     else:
         z = lambda *s: torch.zeros(*s, device="cuda")  # noqa: E731
-        plan = tsr.Plan([dict(G=dev(G), W=z(m, n), U=U, V=V, M=z(r, r), Vm=z(r, r), C=z(r, r), D=z(r, r))], with_refresh=True, p=p,
+        plan = tsr.Plan([dict(G=padded(G, (n + 7) // 8 * 8), W=z(m, n), U=U, V=V, M=z(r, r), Vm=z(r, r), C=z(r, r), D=z(r, r))], with_refresh=True, p=p,
                         precision=tsr.TSR_PREC_BF16 if G.dtype == torch.bfloat16 else tsr.TSR_PREC_SPLIT)
         plan.tsr_refresh_batched([om], q)
         torch.cuda.synchronize()
         plan.close()
     return U.cpu().double(), V.cpu().double()
+
+
+def _check_full_sketch(G, U, V, k):
+    """As test_refresh_full_sketch_sizes, with products in two bf16 pieces (bf16 gradients)."""
+    G64, r = G.double(), U.shape[1]
+    s = torch.linalg.svdvals(G64)
+    core, eye = U.T @ G64 @ V, torch.eye(r, dtype=torch.float64)
+    for X in (U, V):
+        assert float(torch.linalg.norm(X.T @ X - eye)) < 2.0 ** -20 * k
+    assert float((core.diagonal() - s[:r]).abs().max() / s[0]) < (k + 4) * 2.0 ** -22 + 3 * 2.0 ** -17
+    assert float(torch.linalg.norm(core - torch.diag(s[:r])) / torch.linalg.norm(s)) < 2e-5 + 3 * 2.0 ** -17
+
+
+# a plan's bf16 gradients with many rows on either side: the row pieces of the fp64 Gram matrices (see above) behind
+# the other family's products
+@pytest.mark.parametrize("rows,k", [(1025, 33), (4097, 64), (33000, 16), (2049, 97)])
+def test_refresh_tall_full_sketch_of_a_plan(tsr, rows, k):
+    for m, n in ((rows, k), (k, rows)):
+        key = si.stream_key(710, m, n)
+        G = si.normal((m, n), si.stream_key(key, 1)).bfloat16()
+        U, V = _refresh(tsr, "plan", G, k - 4, 4, 0, si.stream_key(key, 2))
+        _check_full_sketch(G, U, V, k)
+
+
+def test_refresh_wide_tiles_ragged(tsr, monkeypatch):
+    """The 256 x 192 tiles (513 to 576 columns, more than 256 tiles in one launch) at 531 columns, with a row remainder of
+    each kind, a tall and a wide block among the others."""
+    monkeypatch.setenv("TSR_TUNE_REFRESH_GROUPS", "1")
+    k, p = 531, 8
+    r = k - p
+    shapes = [(700, 536)] * 27 + [(4097, 531), (531, 700), (531, 4097)]
+    made, blocks, omegas = {}, [], []
+    for m, n in shapes:
+        if (m, n) not in made:
+            key = si.stream_key(711, m, n)
+            G = torch.zeros(m, (n + 7) // 8 * 8, dtype=torch.bfloat16, device="cuda")[:, :n]
+            G.copy_(si.normal((m, n), si.stream_key(key, 1)))
+            made[m, n] = G, dev(si.omega(n, k, si.stream_key(key, 2)))
+        G, om = made[m, n]
+        z = lambda *x: torch.zeros(*x, device="cuda")  # noqa: E731
+        blocks.append(dict(G=G, W=z(m, n), U=z(m, r), V=z(n, r), M=z(r, r), Vm=z(r, r), C=z(r, r), D=z(r, r)))
+        omegas.append(om)
+    plan = tsr.Plan(blocks, precision=tsr.TSR_PREC_BF16, with_refresh=True, p=p)
+    plan.tsr_refresh_batched(omegas, 0)
+    torch.cuda.synchronize()
+    for b in blocks[:26]:                                      # the same block: the same bits, wherever its tiles ran
+        assert torch.equal(b["U"], blocks[26]["U"]) and torch.equal(b["V"], blocks[26]["V"])
+    for b in blocks[27:]:
+        _check_full_sketch(b["G"].cpu(), b["U"].cpu().double(), b["V"].cpu().double(), k)
+    U, V = (blocks[0][x].cpu().double() for x in ("U", "V"))   # five columns short of everything
+    for X in (U, V):
+        assert float(torch.linalg.norm(X.T @ X - torch.eye(r, dtype=torch.float64))) < 2.0 ** -20 * k
+    plan.close()
 
 
 # what the fp64 passes of the final orthonormalisation are for: with one power iteration the sketch is singular to fp32
