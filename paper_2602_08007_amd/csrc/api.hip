@@ -507,7 +507,7 @@ void build_orth_nt(OrthNtPass& pass, const std::vector<RefreshBlock>& blocks, bo
 // fewer partial matrices.
 void build_gram64(OrthProgram& op, const std::vector<RefreshBlock>& blocks, bool on_rows_m, size_t bytes, Arena& ar) {
     long long base = 0;
-    for (const RefreshBlock& b : blocks) base += (long long)ceil_div(b.k, 64) * (ceil_div(b.k, 64) + 1) / 2;
+    for (const RefreshBlock& b : blocks) base += gram64_workgroups(b.k);
     std::vector<Gram64Block>& gram = op.first.gram;
     op.max_splits64 = 1;
     for (long long want = std::max(1LL, 512 / base); ; want = want * 3 / 4) {

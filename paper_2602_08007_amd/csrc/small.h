@@ -69,6 +69,7 @@ struct Gram64Block {
     const float* X; double* S; double* part;
     int rows, k, splits, chunk;
 };
+constexpr int gram64_workgroups(int k) { return (((k + 31) / 32) * ((k + 31) / 32 + 1) / 2 + 3) / 4; }   // of one piece
 hipError_t launch_gram64(const Gram64Block* table_dev, const Gram64Block* single, int blocks, int max_k, int max_splits,
                          hipStream_t stream);
 

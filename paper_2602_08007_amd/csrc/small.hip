@@ -197,25 +197,24 @@ hipError_t launch_stream(float* dst, const float* src, long long count, float sc
 }
 
 // ------------------------------------------------------------------ Gram matrix in fp64
-// One 64 x 64 tile on or below the diagonal per workgroup and range of rows, 32 x 32 per wave (2 x 2 fp64 MFMAs,
-// v_mfma_f64_16x16x4; the quadrant above the diagonal is left out).  Both operands come as they lie in memory: a
+// One 32 x 32 tile on or below the diagonal per wave and range of rows (2 x 2 fp64 MFMAs, v_mfma_f64_16x16x4), four
+// tiles in row order per workgroup.  Both operands come as they lie in memory: a
 // lane's element of a 4 x 16 operand is one float, four rows of 64 bytes per load, sixteen rows under way while the
 // last sixteen are multiplied (1024 cycles of MFMAs against sixteen loads), so neither LDS nor more bandwidth is asked
-// for: bound by the matrix cores' fp64 rate.
-__global__ __launch_bounds__(256) void gram64_kernel(const Gram64Block* table, const Gram64Block single, const int tiles) {
+// for: bound by the matrix cores' fp64 rate (168 matrices of together 467 000 rows, k = 528: 3.0 ms, 49 TFLOP/s; as four
+// quadrants of a 64 x 64 tile, of which those above the diagonal and beyond the matrix leave a SIMD idle, 3.3 ms).
+__global__ __launch_bounds__(256) void gram64_kernel(const Gram64Block* table, const Gram64Block single, const int workgroups) {
     typedef double d4_t __attribute__((ext_vector_type(4)));
     typedef const float __attribute__((address_space(1))) gfloat;
     Gram64Block b = single;
     if (table) b = table[blockIdx.y];
-    const int split = blockIdx.x / tiles, t = blockIdx.x % tiles;
-    int tm = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
-    while ((tm + 1) * (tm + 2) / 2 <= t) ++tm;
-    while (tm * (tm + 1) / 2 > t) --tm;
-    const int tn = t - tm * (tm + 1) / 2;
-    if (split >= b.splits || tm * 64 >= b.k) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
-    const int i0 = tm * 64 + (wave >> 1) * 32, j0 = tn * 64 + (wave & 1) * 32;
-    if (i0 >= b.k || j0 > i0) return;
+    const int split = blockIdx.x / workgroups, t = __builtin_amdgcn_readfirstlane(4 * (blockIdx.x % workgroups) + wave);
+    int qi = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+    while ((qi + 1) * (qi + 2) / 2 <= t) ++qi;
+    while (qi * (qi + 1) / 2 > t) --qi;
+    const int i0 = 32 * qi, j0 = 32 * (t - qi * (qi + 1) / 2);
+    if (split >= b.splits || i0 >= b.k) return;
     const int begin = split * b.chunk, end = min(b.rows, begin + b.chunk);
     gfloat* X = (gfloat*)b.X;
     unsigned ci[2], cj[2];
@@ -297,8 +296,8 @@ hipError_t launch_gram64(const Gram64Block* table_dev, const Gram64Block* single
     if (blocks <= 0 || max_k <= 0) return hipSuccess;
     Gram64Block sb{};
     if (single) sb = *single;
-    const int t = (max_k + 63) / 64, tiles = t * (t + 1) / 2;
-    hipLaunchKernelGGL(gram64_kernel, dim3(tiles * max_splits, blocks), dim3(256), 0, stream, table_dev, sb, tiles);
+    const int workgroups = gram64_workgroups(max_k);
+    hipLaunchKernelGGL(gram64_kernel, dim3(workgroups * max_splits, blocks), dim3(256), 0, stream, table_dev, sb, workgroups);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || max_splits <= 1) return e;
     hipLaunchKernelGGL(gram64_sum_kernel, dim3((max_k * max_k + 255) / 256, blocks), dim3(256), 0, stream, table_dev, sb);
@@ -309,11 +308,11 @@ hipError_t launch_gram64(const Gram64Block* table_dev, const Gram64Block* single
 // One 64 x 64 tile of X Rinv per workgroup, 32 x 32 per wave, over the rows of Rinv that are not zero there.  Four
 // columns of X per lane and load (a row's sixteen side by side), Rinv as it lies; k step q of a load is column 4 l + q
 // for the lanes of group l, of either operand.  Bound by the matrix cores' fp64 rate like the Gram matrices.
-// 168 matrices of together 467 000 rows, k = 528: 2.7 ms, 54 TFLOP/s (the Gram matrices of the same 3.3 ms); asking
+// 168 matrices of together 467 000 rows, k = 528: 2.7 ms, 54 TFLOP/s (the Gram matrices of the same 3.0 ms); asking
 // for fewer than four workgroups per compute unit lets the accumulators move through both register files in every
-// step, 2.9 ms.  The refresh steps of the 60M, 130M and 1B models take 4.03, 5.53 and 85.5 ms with the two fp64
-// passes; 3.90, 5.40 and 80.3 ms with the products in two and three bf16 pieces, which lose weak directions (see
-// ORTH_SHIFT in api.hip), and 4.57, 6.42 and 88.4 ms with three passes of those.
+// step, 2.9 ms.  The refreshes of the 60M, 130M and 1B models take 3.99, 5.53 and 84.8 ms with the two fp64
+// passes; 3.86, 5.30 and 79.3 ms with the products in two and three bf16 pieces, which lose weak directions (see
+// ORTH_SHIFT in api.hip), and 4.52, 6.35 and 87.6 ms with three passes of those.
 __global__ __launch_bounds__(256, 4) void apply64_kernel(const Apply64Block* table, const Apply64Block single, const int col_tiles) {
     typedef double d4_t __attribute__((ext_vector_type(4)));
     typedef float f4_t __attribute__((ext_vector_type(4)));

@@ -149,21 +149,21 @@ def program(tmp_path_factory):
 @pytest.mark.parametrize("r,dims", [(16, [(32000, 2048)] * 2), (128, [(32000, 2048)] * 2), (24, [(32000, 1024)]),
                                     (16, [(2048, 2048)] * 4 + [(2048, 5461)] * 2 + [(5461, 2048)])])
 def test_gram_matrices_are_cut_into_row_pieces(program, g, r, dims):
-    """The fp64 Gram matrices of a few tall blocks: about 200 workgroups a launch and more, no workgroup with more than
+    """The fp64 Gram matrices of a few tall blocks: about 200 waves a launch and more, no wave with more than
     2048 rows (some 60 us), the partial matrices inside the workspace.  Blocks with bf16 gradients as well, whose other
     Gram matrices are computed elsewhere."""
     rows = [tuple(map(int, ln[1:])) for ln in program(g, r, 8, *[x for d in dims for x in d]) if ln[0] == "gram64"]
     assert len(rows) % len(dims) == 0 and len(rows) >= 2 * len(dims)
     for at in range(0, len(rows), len(dims)):
         launch = rows[at:at + len(dims)]
-        workgroups = 0
+        waves = 0
         for n, k, splits, chunk, inside in launch:
             assert inside and k == r + 8 and splits * chunk >= n
             assert -(-n // splits) <= 2048, (n, k, splits)
-            tiles = -(-k // 64)
-            workgroups += splits * tiles * (tiles + 1) // 2
+            tiles = -(-k // 32)
+            waves += splits * tiles * (tiles + 1) // 2
         if max(n for n, *_ in launch) >= 32000:
-            assert workgroups >= 190, launch
+            assert waves >= 190, launch
 
 
 # (the sizes of the comment at the rule: with more than 128 units the general kernels are up to a quarter faster
