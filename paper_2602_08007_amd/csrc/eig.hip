@@ -259,7 +259,7 @@ __global__ __launch_bounds__(EIG_THREADS) void eig_tridiag_kernel(const JacobiBl
         const double xn = sqrt(xnorm2);
         double alpha = (x0 >= 0.0) ? -xn : xn;
         const double vnorm2 = xnorm2 - 2.0 * alpha * x0 + alpha * alpha;     // |x - alpha e1|^2
-        const bool skip = (xnorm2 - x0 * x0 <= 0.0) || vnorm2 <= 0.0;        // already tridiagonal here
+        const bool skip = (xnorm2 - x0 * x0 <= TRIDIAG_ZERO) || vnorm2 <= 0.0;        // already tridiagonal here
         if (skip) alpha = x0;
         const double beta = skip ? 0.0 : 2.0 / vnorm2;
         __syncthreads();
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void eig_tridiag_tiles_kernel(const 
         }
         const double x0 = x[t + 1];
         const double xnorm2 = eig_wave_sum_dpp(psum);
-        const bool skip = !(xnorm2 - x0 * x0 > 0.0);           // already tridiagonal here
+        const bool skip = !(xnorm2 - x0 * x0 > TRIDIAG_ZERO);  // already tridiagonal here
         // alpha = -sign(x0) |x|, beta = 2 / |x - alpha e1|^2 = 1 / (|x|^2 + |x0| |x|)
         double rs = __builtin_amdgcn_rsq(xnorm2);
         {

@@ -91,6 +91,10 @@ hipError_t launch_apply64(const Apply64Block* table_dev, const Apply64Block* sin
 // projection: U U^T G V V^T of an exact rank 5 at r = 40 came out eight times G).
 // Work: Gacc k x k doubles, tmp 2 k x k + 64 doubles, scratch eig_scratch_doubles(k) (launch_eig_svd only).
 constexpr double SVD_NULL = 1e-11;
+// Tridiagonalization: what a reflector would clear counts as zero where its square is this small.  (What is left of
+// a matrix of lower rank is rounding, of that again after the next columns, and so on down to squares that underflow,
+// and 2 / |v|^2 with them; the eigenproblem of the smallest fp32 gradients has entries of 1e-90, and resolves 1e-106.)
+constexpr double TRIDIAG_ZERO = 1e-280;
 struct JacobiBlock {
     double* R; double* Gacc; double* tmp;
     float* XrT; float* GrT; float* sigma;

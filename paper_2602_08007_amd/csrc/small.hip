@@ -1127,7 +1127,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void jacobi_kernel(const JacobiBlock
         const double xn = sqrt(xnorm2);
         double alpha = (x0 >= 0.0) ? -xn : xn;
         const double vnorm2 = xnorm2 - 2.0 * alpha * x0 + alpha * alpha;     // |x - alpha e1|^2
-        const bool skip = (xnorm2 - x0 * x0 <= 0.0) || vnorm2 <= 0.0;        // already tridiagonal here
+        const bool skip = (xnorm2 - x0 * x0 <= TRIDIAG_ZERO) || vnorm2 <= 0.0;        // already tridiagonal here
         if (skip) alpha = x0;
         __syncthreads();
         if (tid == 0) { s_d[j] = T[(size_t)j * k + j]; s_e[j] = alpha; if (!skip) s_v[0] = x0 - alpha; }

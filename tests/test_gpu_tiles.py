@@ -303,6 +303,31 @@ def test_refresh_beyond_the_rank(tsr, how, g, rank, r, q):
     assert float(torch.linalg.norm(back - G64) / torch.linalg.norm(G64)) < 4 * (rank + 4) * 2.0 ** -22
 
 
+# the tridiagonalizations (in registers; from memory down to 288 columns; the one kernel above 544) of what a spectrum
+# that ends in zeros leaves: after a few columns rounding of rounding, whose squares underflow
+@pytest.mark.parametrize("k", [72, 264, 400, 516, 560])
+@pytest.mark.parametrize("spectrum", ["steep 2", "steep 8", "rank 5"])
+def test_refresh_spectra_that_end_in_zeros(tsr, k, spectrum):
+    kind, by = spectrum.split()
+    m, n, r, p = k + 44, k + 24, k - 16, 16
+    for seed in range(2):
+        key = si.stream_key(712, k, seed, len(kind))
+        A, B = si.normal((m, n), si.stream_key(key, 1)), si.normal((n, n), si.stream_key(key, 3))
+        if kind == "steep":
+            G = torch.linalg.qr(A.double())[0] * 10.0 ** (-torch.arange(n, dtype=torch.float64) / float(by))
+        else:
+            G = A[:, :int(by)].double() @ B[:int(by)].double()
+        G = G.float()
+        U, V = torch.full((m, r), float("nan"), device="cuda"), torch.full((n, r), float("nan"), device="cuda")
+        sigma = torch.full((k,), float("nan"), device="cuda")
+        tsr.tsr_refresh_rsvd(dev(G), dev(si.omega(n, k, si.stream_key(key, 2))), r, p, seed, U, V, sigma)
+        assert bool(torch.isfinite(U).all() and torch.isfinite(V).all() and torch.isfinite(sigma).all())
+        s = torch.linalg.svdvals(G.double())
+        # (sketch and products in fp32 over k columns, four in a row, as above; what the sketch leaves out of a steep
+        # spectrum is its tail)
+        assert float((sigma.cpu().double() - s[:k]).abs().max() / s[0]) < (k + 4) * 2.0 ** -22
+
+
 # panels of 128 rows: 343 and 344 (three groups of workers), 1025 (one), 8 (every worker by itself)
 @pytest.mark.parametrize("m,n,r,workers,summed", [(43801, 136, 128, 8, True), (44000, 131, 128, 7, True),
                                                   (131077, 257, 256, 4, True), (1000, 136, 128, 8, False)])
