@@ -1049,30 +1049,49 @@ __global__ __launch_bounds__(EIG_THREADS) void eig_groups_kernel(const JacobiBlo
         }
         __syncthreads();
         double* coef = s_part;
-        for (int j = 1; j < k; ++j) {
-            const int cs = s_first[j];
-            if (cs == j) continue;                       // uniform
-            for (int pass = 0; pass < 2; ++pass) {
-                for (int i = cs + wave; i < j; i += nw) {
-                    double a = 0.0;
-                    for (int t = lane; t < k; t += 64) a += Z[(size_t)t * k + i] * Z[(size_t)t * k + j];
-                    a = eig_wave_sum(a);
-                    if (lane == 0) coef[i - cs] = a;
+        // Groups from the top down.  Where little of a vector is left (the null space of a matrix of much lower rank:
+        // inverse iteration finds few directions there), its rounding grows as it is brought back to length, with that
+        // its share of the vectors above the group: it is freed of these as well (singular values of 6e-2 sigma_1 came
+        // out beyond the rank, k = 516, rank 20).
+        for (int end = k; end > 0; end = s_first[end - 1]) {
+            const int cs = s_first[end - 1];
+            for (int j = cs + 1; j < end; ++j) {
+                auto remove = [&](int above) {           // from vector j what it has of the group's before it, and of those above
+                    const int before = j - cs, total = before + above;
+                    for (int q = wave; q < total; q += nw) {
+                        const int i = q < before ? cs + q : end + (q - before);
+                        double a = 0.0;
+                        for (int t = lane; t < k; t += 64) a += Z[(size_t)t * k + i] * Z[(size_t)t * k + j];
+                        a = eig_wave_sum(a);
+                        if (lane == 0) coef[q] = a;
+                    }
+                    __syncthreads();
+                    for (int t = tid; t < k; t += nt) {
+                        double a = 0.0;
+                        for (int q = 0; q < before; ++q) a += coef[q] * Z[(size_t)t * k + cs + q];
+                        for (int q = 0; q < above; ++q) a += coef[before + q] * Z[(size_t)t * k + end + q];
+                        Z[(size_t)t * k + j] -= a;
+                    }
+                    __syncthreads();
+                };
+                auto normalise = [&]() -> double {       // returns the square of the length
+                    double ss = 0.0;
+                    for (int t = tid; t < k; t += nt) { const double x = Z[(size_t)t * k + j]; ss += x * x; }
+                    ss = block_sum(ss);
+                    const double inv = (ss > 0.0) ? 1.0 / sqrt(ss) : 0.0;
+                    for (int t = tid; t < k; t += nt)
+                        Z[(size_t)t * k + j] = (ss > 0.0) ? Z[(size_t)t * k + j] * inv : eig_start_value((unsigned)t, (unsigned)(k + j));
+                    __syncthreads();
+                    return ss;
+                };
+                remove(0);
+                remove(0);
+                if (normalise() < 1e-2) {                // (uniform)
+                    remove(k - end);
+                    remove(k - end);
+                    normalise();
                 }
-                __syncthreads();
-                for (int t = tid; t < k; t += nt) {
-                    double a = 0.0;
-                    for (int i = cs; i < j; ++i) a += coef[i - cs] * Z[(size_t)t * k + i];
-                    Z[(size_t)t * k + j] -= a;
-                }
-                __syncthreads();
             }
-            double ss = 0.0;
-            for (int t = tid; t < k; t += nt) { const double x = Z[(size_t)t * k + j]; ss += x * x; }
-            ss = block_sum(ss);
-            const double inv = (ss > 0.0) ? 1.0 / sqrt(ss) : 0.0;
-            for (int t = tid; t < k; t += nt) Z[(size_t)t * k + j] *= inv;
-            __syncthreads();
         }
     }
 }

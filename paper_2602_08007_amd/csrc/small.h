@@ -86,11 +86,12 @@ hipError_t launch_apply64(const Apply64Block* table_dev, const Apply64Block* sin
 // Gacc R = diag(sigma) X^T (rows mutually orthogonal), from the symmetric eigenproblem of R R^T.
 // Outputs, for the r largest sigma in descending order: XrT (r x k fp32) rows x_j^T, GrT
 // (r x k fp32) rows of Gacc, and sigma (k fp32, optional, all k values descending).
-// A singular value <= SVD_NULL sigma_1 is rounding, and so is what its x_j holds: 2^-53 sigma_1 / sigma_j of the leading
-// ones.  Both its rows are zero (as columns of length one the x_j would count the leading directions again in the
-// projection: U U^T G V V^T of an exact rank 5 at r = 40 came out eight times G).
+// The eigenproblem holds squares: below 1e-8 sigma_1 a direction is rounding, and its x_j has 2^-53 sigma_1 / sigma_j and
+// more of the leading ones.  Up to SVD_NULL sigma_1 both its rows are zero (as columns of length one the x_j would
+// count the leading directions again in the projection: U U^T G V V^T of an exact rank 5 at r = 40 came out eight
+// times G).
 // Work: Gacc k x k doubles, tmp 2 k x k + 64 doubles, scratch eig_scratch_doubles(k) (launch_eig_svd only).
-constexpr double SVD_NULL = 1e-11;
+constexpr double SVD_NULL = 1e-9;
 // Tridiagonalization: what a reflector would clear counts as zero where its square is this small.  (What is left of
 // a matrix of lower rank is rounding, of that again after the next columns, and so on down to squares that underflow,
 // and 2 / |v|^2 with them; the eigenproblem of the smallest fp32 gradients has entries of 1e-90, and resolves 1e-106.)

@@ -306,7 +306,7 @@ def test_refresh_beyond_the_rank(tsr, how, g, rank, r, q):
 # the tridiagonalizations (in registers; from memory down to 288 columns; the one kernel above 544) of what a spectrum
 # that ends in zeros leaves: after a few columns rounding of rounding, whose squares underflow
 @pytest.mark.parametrize("k", [72, 264, 400, 516, 560])
-@pytest.mark.parametrize("spectrum", ["steep 2", "steep 8", "rank 5"])
+@pytest.mark.parametrize("spectrum", ["steep 2", "steep 8", "rank 5", "rank 20"])
 def test_refresh_spectra_that_end_in_zeros(tsr, k, spectrum):
     kind, by = spectrum.split()
     m, n, r, p = k + 44, k + 24, k - 16, 16
