@@ -87,8 +87,8 @@ def test_lift_sizes(tsr, m, n, r, prec):
                                303, 417, 528, 543, 544, 545])
 def test_refresh_full_sketch_sizes(tsr, k):
     """A sketch as wide as the matrix is high spans everything: the singular values and the leading
-    subspaces are those of the matrix, up to the orthonormality the last pass leaves (Gram matrix of three
-    bf16 pieces, 2^-24 per entry over k columns) and fp32 storage."""
+    subspaces are those of the matrix, up to the orthonormality the last pass leaves (fp64, stored in
+    fp32: below 2^-24 per entry over k columns)."""
     p = min(4, k - 1)
     r, m, n = k - p, k, k + 9
     key = si.stream_key(703, k)
@@ -100,7 +100,8 @@ def test_refresh_full_sketch_sizes(tsr, k):
     tsr.tsr_refresh_rsvd(dev(G), dev(si.omega(n, k, si.stream_key(key, 2))), r, p, 1, U, V, sigma)
     s = torch.linalg.svdvals(G.double())
     # an fp32 sum of k products is off by at most k x 2^-24 of the sum of their sizes; four such sums in a
-    # row lead from the matrix to the triangular factor (apply, Gram, apply, product with Q)
+    # row bound the way from the matrix to the triangular factor (the passes over Q and over the factor are fp64 and
+    # stored in fp32, the product with Q between them is one such sum)
     assert float((sigma.cpu().double() - s).abs().max() / s[0]) < (k + 4) * 2.0 ** -22
     U64, V64, eye = U.cpu().double(), V.cpu().double(), torch.eye(r, dtype=torch.float64)
     for X in (U64, V64):
@@ -109,8 +110,8 @@ def test_refresh_full_sketch_sizes(tsr, k):
     assert float(torch.linalg.norm(core - torch.diag(s[:r])) / torch.linalg.norm(s)) < 2e-5
 
 
-# the fp64 Gram matrices cut the rows into pieces (multiples of 16) and the columns into 64-wide tiles of 32-wide
-# quadrants: a remainder of one row, row counts around a piece's, one tile, one quadrant more, two tiles
+# the fp64 Gram matrices cut the rows into pieces (multiples of 16) and the columns into 32-wide tiles, one
+# per wave: a remainder of one row, row counts around a piece's, one tile, two, one column more, a fourth one
 @pytest.mark.parametrize("rows,k", [(1000, 20), (1025, 33), (4097, 64), (130, 65), (33000, 9), (2049, 97)])
 def test_refresh_tall_full_sketch(tsr, rows, k):
     """As above with many rows on either side (B^T is as tall as G^T): singular values and orthonormality."""

@@ -74,9 +74,9 @@ class Guarded:
         assert bool((self.buf[self.ws.numel():] == SENTINEL).all()), "bytes behind the workspace were written"
 
 
-# One product in two bf16 pieces (the second of the three orthonormalisation passes) enters Q R = X undiminished:
-# off by at most 3 x 2^-17 of |a||b| (second pieces up to 2^-17 of the first, their product dropped).  Long sums
-# average it out; here a sum has one to seventeen terms.
+# One product in two bf16 pieces, the coarsest that any path here has (B = Q^T G; the last orthonormalisation
+# passes are fp64), is off by at most 3 x 2^-17 of |a||b| (second pieces up to 2^-17 of the first, their product
+# dropped).  Long sums average it out; here a sum has one to seventeen terms.
 TWO_PIECES = 3 * 2.0 ** -17
 
 
@@ -198,7 +198,7 @@ def test_static_scratch_at_its_limit(tsr, m, n, r):
     C = torch.full((r, r), float("nan"), device="cuda")
     tsr.tsr_project_core_static(G.cuda(), U.cuda(), V.cuda(), C)
     ref = U.double().T @ (G.double() @ V.double())
-    # two products in two bf16 pieces; the core of a white gradient is sqrt(r / min(m, n)) of what the sums hold
+    # two products in two bf16 pieces or finer; the core of a white gradient is sqrt(r / min(m, n)) of what the sums hold
     assert float(torch.linalg.norm(C.cpu().double() - ref) / torch.linalg.norm(ref)) < 2 * TWO_PIECES * (min(m, n) / r) ** 0.5
 
 
